@@ -130,14 +130,14 @@ __host__ __device__ inline LdsLayout make_layout(int fmax, int smax, int ccap, i
     const int cr = lds_align4(ccap * CON_FLOATS) + (rw > mk ? rw : mk);
     o += cr > DYN_FLOATS ? cr : DYN_FLOATS;
   }
-  // level schedule: uint16 group offsets and robot row per level [ccap + 2]
-  // each, the groups by level (uint32) [ccap], each group's level [ccap] and
-  // first row [ccap + 1] (uint16)
-  L.lvl = o;   o += lds_align4((6 * ccap + 5 + 1) / 2);
+  // sweep schedule: each group's previous groups [ccap + 2] twice, its level
+  // [ccap] and first row [ccap + 1] (uint16)
+  L.lvl = o;   o += lds_align4((4 * ccap + 5 + 1) / 2);
   // two uint16 candidate lists; after the contact phase the level schedule's
-  // per-node row masks (64-bit, per node and 64-row chunk)
+  // per-node group masks (64-bit, per node and 64-group chunk) and the mask
+  // of the robot's nodes
   {
-    const int masks = (1 + AMAX + fmax) * ((ccap + WAVE - 1) / WAVE) * 2;
+    const int masks = (1 + AMAX + fmax) * ((ccap + WAVE - 1) / WAVE) * 2 + 2;
     L.cand = o;  o += lds_align4(L.ntmax > masks ? L.ntmax : masks);
   }
   L.frc = o;   o += force ? lds_align4(fmax * FRC_FLOATS) : 0;  // force-output accumulators

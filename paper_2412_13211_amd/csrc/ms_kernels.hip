@@ -27,6 +27,7 @@ __device__ __forceinline__ f3 mk3(float a, float b, float c) { return {a, b, c};
 __device__ __forceinline__ f3 operator+(f3 a, f3 b) { return {a.x + b.x, a.y + b.y, a.z + b.z}; }
 __device__ __forceinline__ f3 operator-(f3 a, f3 b) { return {a.x - b.x, a.y - b.y, a.z - b.z}; }
 __device__ __forceinline__ f3 operator*(f3 a, float s) { return {a.x * s, a.y * s, a.z * s}; }
+__device__ __forceinline__ f3 sel(bool c, f3 a, f3 b) { return {c ? a.x : b.x, c ? a.y : b.y, c ? a.z : b.z}; }
 __device__ __forceinline__ float dot(f3 a, f3 b) { return a.x * b.x + a.y * b.y + a.z * b.z; }
 __device__ __forceinline__ f3 cross(f3 a, f3 b) {
   return {a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x};
@@ -98,14 +99,26 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z) {
   z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
   return z ^ (z >> 31);
 }
-__device__ __forceinline__ int lane_id() { return threadIdx.x; }
 // the lane index, opaque to the optimizer: address arithmetic on it stays
-// where it is used instead of being hoisted out of the scene loop into
-// registers that live (or spill) across the whole step
-__device__ __forceinline__ int lane_fresh() {
-  int l = lane_id();
+// in the phase that asks for it instead of being hoisted out of the scene
+// and substep loops into registers that live (or spill) across the whole step
+__device__ __forceinline__ int lane_id() {
+  int l = threadIdx.x;
   asm volatile("" : "+v"(l));
   return l;
+}
+// the same for the kernel's arguments and the LDS block: a phase reads what it
+// needs itself (scalar loads, scalar adds) and keeps no scalar registers
+// occupied in the others
+__device__ __forceinline__ const KArgs& args_fresh() {
+  auto p = __builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const KArgs*)p;
+}
+__device__ __forceinline__ float* lds_fresh(float* L) {
+  int z = 0;
+  asm volatile("" : "+s"(z));
+  return L + z;
 }
 __device__ __forceinline__ int prefix_below(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
@@ -130,6 +143,8 @@ __device__ __forceinline__ float sum16(float v) {
 __device__ __forceinline__ float lane_val(float v, int src) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), src));
 }
+// a value equal in every lane, as a scalar
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ void wave_sync() { __syncthreads(); }
 // Ordering of LDS accesses between the lanes of the one wavefront of a
 // workgroup: the LDS executes a wavefront's instructions in issue order, so a
@@ -259,11 +274,12 @@ struct Scene {
   float gx0, gy0, gix, giy;  // furniture grid: origin and inverse cell sizes (xy)
 };
 
-__device__ __forceinline__ void load_scene(const KArgs& a, const Scene& S, float* L, const Robot& rb) {
+__device__ __forceinline__ void load_scene(const KArgs& a, const Scene& S, float* L) {
+  const Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
   const int lane = lane_id();
   const LdsLayout& Y = a.L;
   if (lane < ND) {
-    const int ln = lane_fresh();
+    const int ln = lane_id();
     rb.q[lane] = a.x_in[(size_t)S.s * ND + ln];
     rb.qd[lane] = a.x_in[(size_t)a.S * ND + (size_t)S.s * ND + ln];
     rb.u[lane] = a.u[(size_t)S.s * ND + ln];
@@ -310,7 +326,7 @@ __device__ __forceinline__ void load_scene(const KArgs& a, const Scene& S, float
   if (Y.smax > 0) {
     float* St = L + Y.stat;
     const float* src = a.statics + (size_t)S.s0 * 6;
-    for (int i = lane_fresh(); i < S.ns * 6; i += WAVE) St[i] = src[i];
+    for (int i = lane_id(); i < S.ns * 6; i += WAVE) St[i] = src[i];
   }
   float* Pl = L + Y.plane;
   if (lane < S.np) {
@@ -329,7 +345,8 @@ __device__ __forceinline__ void load_scene(const KArgs& a, const Scene& S, float
   wave_sync();
 }
 
-__device__ __forceinline__ void store_scene(const KArgs& a, const Scene& S, float* L, const Robot& rb, uint32_t& status) {
+__device__ __forceinline__ void store_scene(const KArgs& a, const Scene& S, float* L, uint32_t& status) {
+  const Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
   const int lane = lane_id();
   const LdsLayout& Y = a.L;
   bool bad = false;
@@ -337,7 +354,7 @@ __device__ __forceinline__ void store_scene(const KArgs& a, const Scene& S, floa
   if (lane < ND) {
     float q = rb.q[lane], qd = rb.qd[lane];
     bad |= !isfinite(q) || !isfinite(qd);
-    const int ln = lane_fresh();
+    const int ln = lane_id();
     a.x_out[(size_t)S.s * ND + ln] = q;
     a.x_out[(size_t)a.S * ND + (size_t)S.s * ND + ln] = qd;
   }
@@ -368,7 +385,8 @@ __device__ __forceinline__ void store_scene(const KArgs& a, const Scene& S, floa
 
 // ---------------------------------------------------------------- record for the adjoint
 // state at a substep boundary (q, qd, free bodies, door/drawer joints)
-__device__ __forceinline__ void rec_state(const KArgs& a, const Scene& S, const float* L, const Robot& rb, float* R) {
+__device__ __forceinline__ void rec_state(const KArgs& a, const Scene& S, float* L, float* R) {
+  const Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
   const int lane = lane_id();
   const LdsLayout& Y = a.L;
   if (lane < ND) {
@@ -417,7 +435,8 @@ __device__ __forceinline__ void rec_contacts(const KArgs& a, const float* L, int
 }
 
 // ---------------------------------------------------------------- phases
-__device__ __forceinline__ void phase_drive(const KArgs& a, const Scene& S, const Robot& rb) {
+__device__ __forceinline__ void phase_drive(const KArgs& a, const Scene& S, float* L) {
+  const Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
   const int j = lane_id();
   if (j < S.nb) {
     const DModel* M = S.M;
@@ -447,7 +466,8 @@ __device__ __forceinline__ void phase_drive(const KArgs& a, const Scene& S, cons
 }
 
 // world frames by pointer jumping over the tree; spheres; free and aux frames
-__device__ __forceinline__ void phase_kinematics(const KArgs& a, const Scene& S, float* L, const Robot& rb) {
+__device__ __forceinline__ void phase_kinematics(const KArgs& a, const Scene& S, float* L) {
+  const Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
   const int lane = lane_id();
   const DModel* M = S.M;
   const int nb = S.nb;
@@ -1000,8 +1020,9 @@ __device__ __forceinline__ void exact_grouped(const ConCtx& X, int rcap, int nbo
   }
 }
 
-__device__ __forceinline__ void phase_contacts(const KArgs& a, const Scene& S, float* L, const Robot& rb, int& NC, int& NR, int& NL,
-                               uint32_t& status, uint64_t& keysum) {
+__device__ __forceinline__ void phase_contacts(const KArgs& a, const Scene& S, float* L, int& NC, int& NR, int& NL, uint32_t& status,
+                                               uint64_t& keysum) {
+  const Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
   const int lane = lane_id();
   const LdsLayout& Y = a.L;
   ConCtx X;
@@ -1327,8 +1348,10 @@ __device__ __forceinline__ void phase_contacts(const KArgs& a, const Scene& S, f
   keysum = ks;
   if (__ballot(E.over)) status |= 2u;
   if (__ballot(E.rover)) status |= 8u;
-  NC = E.n;
-  NR = E.nr;
+  // the same in every lane: scalar registers, uniform loops over them
+  NC = uniform(E.n);
+  NR = uniform(E.nr);
+  NL = uniform(NL);
   wave_sync();
 }
 
@@ -1395,7 +1418,8 @@ __device__ __forceinline__ void ri_add(RI& I, float m, f3 d, const float* Jc) {
   I.J[5] += Jc[5] - m * d.y * d.z;
 }
 
-__device__ __forceinline__ void phase_dynamics(const KArgs& a, const Scene& S, float* L, const Robot& rb, float& vR) {
+__device__ __forceinline__ void phase_dynamics(const KArgs& a, const Scene& S, float* L, float& vR) {
+  const Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
   const int lane = lane_id();
   const DModel* M = S.M;
   const int nb = S.nb;
@@ -1410,7 +1434,7 @@ __device__ __forceinline__ void phase_dynamics(const KArgs& a, const Scene& S, f
   // are added by a 16-lane reduction, and lane 0 of the row leaves the sum in
   // LDS for body i's own lane.  (One lane per body looping over the other
   // bodies made each sum a chain of 16 dependent LDS rounds.)
-  const int lf = lane_fresh(), q = lf >> 4, kq = lf & 15;
+  const int lf = lane_id(), q = lf >> 4, kq = lf & 15;
   // pass 1 (lane per body): COM and world inertia about the COM (kept for the
   // subtree sums); (pair lanes) twist v_i = sum over k in anc-or-self(i) of
   // s_k qd_k at p_i; (lane per body) the velocity-product acceleration
@@ -1419,7 +1443,7 @@ __device__ __forceinline__ void phase_dynamics(const KArgs& a, const Scene& S, f
   float vp[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   f3 pi = mk3(0.f, 0.f, 0.f);
   if (lane < nb) {
-    const int i = lane_fresh();
+    const int i = lane_id();
     pi = body_p(rb, i);
     const float* R = rb.R + i * 9;
     const f3 d = mv(R, mk3(M->com[i][0], M->com[i][1], M->com[i][2]));
@@ -1644,6 +1668,17 @@ __device__ __forceinline__ f3 aux_col(const float* A, int x, f3 p) {
   return ax;
 }
 
+// the same, in the sweeps
+__device__ __forceinline__ f3 aux_col_f(const float* A, int x, f3 p) {
+#pragma clang fp contract(off)
+  const f3 ax = mk3(A[(A_AX + 0) * AMAX + x], A[(A_AX + 1) * AMAX + x], A[(A_AX + 2) * AMAX + x]);
+  if (A[A_TYPE * AMAX + x] == 0.f) {
+    const f3 r = p - mk3(A[(A_P + 0) * AMAX + x], A[(A_P + 1) * AMAX + x], A[(A_P + 2) * AMAX + x]);
+    return {fmaf(ax.y, r.z, -(ax.z * r.y)), fmaf(ax.z, r.x, -(ax.x * r.z)), fmaf(ax.x, r.y, -(ax.y * r.x))};
+  }
+  return ax;
+}
+
 // Entry j of the robot's Jacobian row for direction d at the point p of a
 // contact on body `body`: d . (a_j x (p - o_j)) for a revolute joint, d . a_j
 // for a prismatic one, 0 when joint j does not move the body
@@ -1657,8 +1692,53 @@ __device__ __forceinline__ float robot_J(const DModel* M, const Robot& rb, int n
   return J;
 }
 
-__device__ __forceinline__ void phase_rows(const KArgs& a, const Scene& S, float* L, const Robot& rb, int NC, int NR, int NL,
-                           uint32_t& status) {
+// The sweeps' arithmetic with its fused multiply-adds written out (and no
+// contraction beside them), so that every form of a row update -- a lone
+// body's, a level's, the robot's -- rounds alike whatever code surrounds it,
+// and a record holds exactly the values of the step.
+__device__ __forceinline__ float dot_f(f3 a, f3 b) { return fmaf(a.z, b.z, fmaf(a.x, b.x, a.y * b.y)); }
+__device__ __forceinline__ f3 cross_f(f3 a, f3 b) {
+  return {fmaf(a.y, b.z, -(a.z * b.y)), fmaf(a.z, b.x, -(a.x * b.z)), fmaf(a.x, b.y, -(a.y * b.x))};
+}
+// a + b s
+__device__ __forceinline__ f3 madd(f3 a, f3 b, float s) {
+  return {fmaf(b.x, s, a.x), fmaf(b.y, s, a.y), fmaf(b.z, s, a.z)};
+}
+// the tangents of onb_a
+__device__ __forceinline__ void onb_f(f3 n, float a, f3& t1, f3& t2) {
+#pragma clang fp contract(off)
+  const float sg = copysignf(1.f, n.z);
+  const float b = n.x * n.y * a;
+  t1 = {fmaf(n.x * (sg * n.x), a, 1.f), sg * b, -sg * n.x};
+  t2 = {b, fmaf(n.y * n.y, a, sg), -n.y};
+}
+// What the sweeps read of a robot row, laid out so that lane (d, j) of the
+// wave (d = lane >> 4: direction; j = lane & 15: joint) finds its own part
+// with a few wide loads: w = M~^-1 J^T [3][16], then per direction its vector,
+// inverse effective mass, coupling to the normal (0 for the normal), bias (0
+// for the tangents) and impulse, then the contact point.  The blocks lie in
+// LDS that is dead between the rows phase and the next substep: past the
+// contact list's end, past the robot's Jacobian rows, the robot's sphere
+// centres, the level schedule's links and the culling lists.
+constexpr int RB_DIR = 3 * ND, RB_P = RB_DIR + 24, RB_FLOATS = RB_P + 4;
+enum { RB_IW = 3, RB_WT = 4, RB_BIAS = 5, RB_LAM = 6 };
+// offset of robot row rr's block, -1 if there is no room for it
+__device__ __forceinline__ int rob_block(const LdsLayout& Y, int NC, int NR, int rr) {
+  const int base[5] = {Y.con + lds_align4(NC * CSTR), Y.rows + NR * ROW_FLOATS, Y.sph, Y.lvl, Y.cand};
+  const int end[5] = {Y.rows, Y.rows + Y.rcap * ROW_FLOATS, Y.fr, Y.lvl + ((Y.ccap + 2) & ~3), Y.frc};
+  int off = -1;
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    const int n = (end[i] - base[i]) / RB_FLOATS;
+    if (off < 0 && rr >= 0 && rr < n) off = base[i] + rr * RB_FLOATS;
+    rr -= n;
+  }
+  return off;
+}
+
+__device__ __forceinline__ void phase_rows(const KArgs& a, const Scene& S, float* L, int NC, int NR, int NL,
+                                           uint32_t& status) {
+  const Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
   const int lane = lane_id();
   const LdsLayout& Y = a.L;
   float* C = L + Y.con;
@@ -1724,6 +1804,8 @@ __device__ __forceinline__ void phase_rows(const KArgs& a, const Scene& S, float
     for (int t = 0; t < 3; ++t) C[(ci) * CSTR + C_LAM + t] = 0.f;
   }
   wave_sync();
+  // lane rr: where robot row rr's block lies
+  const int rblk = lane < NR ? rob_block(Y, NC, NR, lane) : -1;
   // robot rows: lane (d, j) builds J[d][j] = d . (dp/dq_j) and W = J M~^-1 J^T
   float* Rw = L + Y.rows;
   const int d = lane >> 4, j = lane & 15;
@@ -1746,6 +1828,8 @@ __device__ __forceinline__ void phase_rows(const KArgs& a, const Scene& S, float
 #pragma unroll
       for (int k = 0; k < ND; ++k) w += rb.Minv[j * ND + k] * row[d * ND + k];
     }
+    const int blk = rr < WAVE ? __builtin_amdgcn_readlane(rblk, rr) : -1;
+    if (blk >= 0 && d < 3) L[blk + lane] = w;
     const float wn = __shfl(w, j, WAVE);  // M~^-1 J_n^T
     if (d < 3) {
       // W_dd, and the couplings J_d M~^-1 J_n^T of the tangents (added to
@@ -1759,69 +1843,102 @@ __device__ __forceinline__ void phase_rows(const KArgs& a, const Scene& S, float
     }
     wave_sync();
   }
-  // inverse effective masses; rows below 1e-12 are skipped (inverse 0)
+  // inverse effective masses; rows below 1e-12 are skipped (inverse 0), a
+  // friction pair with either one below
   bool degen = false;
   for (int ci = lane; ci < NC; ci += WAVE) {
-    for (int dd = 0; dd < 3; ++dd) {
-      float W = C[(ci) * CSTR + C_IW + dd];
-      int info = __float_as_int(C[(ci) * CSTR + C_INFO]);
-      bool lim = side_kind(info & 0xffff) == K_LIMIT;
-      if (lim && dd > 0) continue;
-      if (W >= 1e-12f) C[(ci) * CSTR + C_IW + dd] = 1.f / W;
-      else {
-        C[(ci) * CSTR + C_IW + dd] = 0.f;
-        degen = true;
-      }
+    float* c = C + ci * CSTR;
+    const bool lim = side_kind(__float_as_int(c[C_INFO]) & 0xffff) == K_LIMIT;
+    const float W0 = c[C_IW], W1 = lim ? 1.f : c[C_IW + 1], W2 = lim ? 1.f : c[C_IW + 2];
+    const bool ok0 = W0 >= 1e-12f, ok1 = W1 >= 1e-12f && W2 >= 1e-12f;
+    c[C_IW] = ok0 ? 1.f / W0 : 0.f;
+    if (!lim) {
+      c[C_IW + 1] = ok1 ? 1.f / W1 : 0.f;
+      c[C_IW + 2] = ok1 ? 1.f / W2 : 0.f;
     }
+    degen = degen || !ok0 || !ok1;
   }
   if (__ballot(degen)) status |= 4u;
   wave_sync();
+  // the robot rows' blocks: lane (d, j) writes value j of direction d, the
+  // last 16 lanes the contact point
+  for (int rr = 0; rr < min(NR, WAVE); ++rr) {
+    const int blk = __builtin_amdgcn_readlane(rblk, rr);
+    if (blk < 0) break;
+    const float* c = C + (NL + rr) * CSTR;
+    const f3 n = mk3(c[C_N], c[C_N + 1], c[C_N + 2]);
+    f3 t1, t2;
+    onb_f(n, c[C_ONB], t1, t2);
+    const f3 D = d == 0 ? n : (d == 1 ? t1 : t2);
+    float v = j == 0 ? D.x : (j == 1 ? D.y : D.z);
+    const int dd = d < 3 ? d : 0;
+    if (j == RB_IW) v = c[C_IW + dd];
+    if (j == RB_WT) v = d == 0 ? 0.f : c[C_WTN + (dd > 0 ? dd - 1 : 0)];
+    if (j == RB_BIAS) v = d == 0 ? c[C_BIAS] : 0.f;
+    if (j >= RB_LAM) v = 0.f;
+    if (d < 3) {
+      if (j < 8) L[blk + RB_DIR + 8 * d + j] = v;
+    } else if (j < 3) {
+      L[blk + RB_P + j] = c[C_P + j];
+    }
+  }
+  wave_sync();
 }
 
-// Level schedule.  Rows are first merged into groups: a run of consecutive
-// rows (in canonical order) between one free body and static targets is one
-// group, run by one lane in order with the body's state in registers; every
-// other row is a group of its own.  level(g) = 1 + max level of earlier
-// groups sharing a node, so that executing the levels in order performs the
-// sequential row updates exactly.  Then an order list of the groups grouped
-// by level; each level's robot row is kept apart.
-// The nodes are the robot (0), the door / drawer joints (1 + x) and the free
-// bodies (1 + AMAX + f); static targets are no node.  For every node a bit
-// mask of the groups touching it (LDS atomics, one bit per group) gives each
-// group the previous group on each of its nodes, and the levels are the
-// longest-path depths of that DAG, relaxed over the lanes until no level
-// changes (as many rounds as the deepest chain).
+// Schedule of the sweeps.  In the canonical order the joint-limit rows come
+// first, then the robot's rows, then the free bodies' rows, so a sweep may run
+// the limit rows, then all robot rows, then the free bodies' rows (each row
+// after every earlier row it shares a node with), and that is the sequential
+// order's arithmetic bit for bit.  The free bodies' rows are merged into
+// groups: a run of consecutive rows between one free body and static targets
+// is one group, run by one lane in order with the body's state in registers;
+// every other row is a group of its own.
+//   - A group that holds every row of its body (no robot, door / drawer or
+//     other body touches it) is alone: its sweeps depend on nothing else.  It
+//     gets level 0.
+//   - The others get level(g) = 1 + max level of the earlier groups sharing a
+//     node; executing the levels in order performs the sequential updates.
+// The nodes are the door / drawer joints (1 + x) and the free bodies
+// (1 + AMAX + f); static targets are no node.  For every node a bit mask of
+// the groups touching it (LDS atomics, one bit per group) gives each group the
+// previous group on each of its nodes, and the levels are the longest-path
+// depths of that DAG, relaxed over the lanes until no level changes (as many
+// rounds as the deepest chain).
 __device__ __forceinline__ void row_nodes(int inf, int& na, int& nbn) {
   na = node_of(inf & 0xffff);
-  nbn = side_kind(inf & 0xffff) == K_LIMIT ? 63 : node_of((inf >> 16) & 0xffff);
+  nbn = node_of((inf >> 16) & 0xffff);
 }
 // a row between a free body and a static target (may join its predecessor's group)
 __device__ __forceinline__ bool row_single(int inf) {
   return side_kind(inf & 0xffff) == K_FREE && side_kind((inf >> 16) & 0xffff) == K_STATIC;
 }
-__device__ __forceinline__ int phase_levels(const KArgs& a, float* L, int NC, int NR, int NL) {
+struct Levels {
+  int ng, maxl;  // groups of free-body rows, levels
+};
+// per group its level and first row (and one entry past the last group)
+__device__ __forceinline__ uint16_t* level_of_groups(float* L, const LdsLayout& Y) {
+  return reinterpret_cast<uint16_t*>(L + Y.lvl) + 2 * (Y.ccap + 2);
+}
+__device__ __forceinline__ Levels phase_levels(const KArgs& a, float* L, int NC, int NR, int NL) {
   const int lane = lane_id();
   const LdsLayout& Y = a.L;
   const float* C = L + Y.con;
   const int cc = Y.ccap;
-  // per level the offset of its groups in `order` and its robot row (0xffff:
-  // none); the groups of each level (first row | rows << 16); each group's
-  // level and first row.  While the levels are found, loff and rob hold each
-  // group's previous group on its first and second node (0xffff: none).
-  uint16_t* loff = reinterpret_cast<uint16_t*>(L + Y.lvl);     // [cc + 2]
-  uint16_t* rob = loff + cc + 2;                               // [cc + 2]
-  uint32_t* order = reinterpret_cast<uint32_t*>(rob + cc + 2);  // [cc]
-  uint16_t* lvl = reinterpret_cast<uint16_t*>(order + cc);     // [cc]
-  uint16_t* gfirst = lvl + cc;                                 // [cc + 1]
+  const int r0 = NL + NR;
+  // each group's previous group on its first and second node (0xffff: none)
+  uint16_t* pvA = reinterpret_cast<uint16_t*>(L + Y.lvl);  // [cc + 2]
+  uint16_t* pvB = pvA + cc + 2;                            // [cc + 2]
+  uint16_t* lvl = level_of_groups(L, Y);                   // [cc]
+  uint16_t* gfirst = lvl + cc;                             // [cc + 1]
   // group starts and first rows
   int NG = 0;
-  for (int base = 0; base < NC; base += WAVE) {
+  for (int base = r0; base < NC; base += WAVE) {
     const int r = base + lane;
     bool st = false;
     if (r < NC) {
       const int inf = __float_as_int(C[r * CSTR + C_INFO]);
       st = true;
-      if (r > 0 && row_single(inf)) {
+      if (r > r0 && row_single(inf)) {
         const int pinf = __float_as_int(C[(r - 1) * CSTR + C_INFO]);
         st = !(row_single(pinf) && (pinf & 0xffff) == (inf & 0xffff));
       }
@@ -1833,9 +1950,13 @@ __device__ __forceinline__ int phase_levels(const KArgs& a, float* L, int NC, in
   if (lane == 0) gfirst[NG] = (uint16_t)NC;
   const int nch = (NG + WAVE - 1) / WAVE;
   const int nnode = 1 + AMAX + Y.fmax;
-  unsigned long long* nm = reinterpret_cast<unsigned long long*>(L + Y.cand);  // [nnode][nch]
-  for (int e = lane; e < nnode * nch; e += WAVE) nm[e] = 0ull;
+  unsigned long long* nm = reinterpret_cast<unsigned long long*>(L + Y.cand);  // [nnode][nch], then the robot's nodes
+  for (int e = lane; e <= nnode * nch; e += WAVE) nm[e] = 0ull;
   lds_order();
+  for (int rr = lane; rr < NR; rr += WAVE) {
+    const int n = node_of((__float_as_int(C[(NL + rr) * CSTR + C_INFO]) >> 16) & 0xffff);
+    atomicOr(nm + nnode * nch, 1ull << n);
+  }
   for (int ch = 0; ch < nch; ++ch) {
     const int g = ch * WAVE + lane;
     if (g < NG) {
@@ -1857,401 +1978,513 @@ __device__ __forceinline__ int phase_levels(const KArgs& a, float* L, int NC, in
     }
     return m ? w * WAVE + 63 - __clzll((long long)m) : -1;
   };
+  const unsigned long long robn = nm[nnode * nch];
   for (int ch = 0; ch < nch; ++ch) {
     const int g = ch * WAVE + lane;
     if (g < NG) {
       int na, nbn;
       row_nodes(__float_as_int(C[gfirst[g] * CSTR + C_INFO]), na, nbn);
       const int pa = prev(na, g), pb = nbn == 63 ? -1 : prev(nbn, g);
-      loff[g] = (uint16_t)(pa < 0 ? 0xffff : pa);
-      rob[g] = (uint16_t)(pb < 0 ? 0xffff : pb);
-      lvl[g] = 1;
+      bool alone = nbn == 63 && pa < 0 && !((robn >> na) & 1ull);
+      for (int w = g >> 6; w < nch; ++w) {
+        const unsigned long long m = nm[na * nch + w];
+        alone = alone && (w == (g >> 6) ? (m >> (g & 63)) == 1ull : m == 0ull);
+      }
+      pvA[g] = (uint16_t)(pa < 0 ? 0xffff : pa);
+      pvB[g] = (uint16_t)(pb < 0 ? 0xffff : pb);
+      lvl[g] = alone ? 0 : 1;
     }
   }
   lds_order();
   // relax: level(g) = 1 + max(level(prev on node A), level(prev on node B))
+  int maxl = 0;
   for (;;) {
     bool changed = false;
     for (int ch = 0; ch < nch; ++ch) {
       const int g = ch * WAVE + lane;
-      if (g < NG) {
-        const int pa = loff[g], pb = rob[g];
+      if (g < NG && lvl[g] != 0) {
+        const int pa = pvA[g], pb = pvB[g];
         const int la = pa == 0xffff ? 0 : lvl[pa], lb = pb == 0xffff ? 0 : lvl[pb];
         const int nl = 1 + max(la, lb);
         if (nl != lvl[g]) {
           lvl[g] = (uint16_t)nl;
           changed = true;
         }
+        maxl = max(maxl, nl);
       }
     }
     if (!__ballot(changed)) break;
     lds_order();
   }
-  int maxl = 0;
-  for (int g = lane; g < NG; g += WAVE) maxl = max(maxl, (int)lvl[g]);
   for (int off = 32; off > 0; off >>= 1) maxl = max(maxl, __shfl_xor(maxl, off, WAVE));
-  lds_order();
-  for (int e = lane; e <= maxl + 1; e += WAVE) rob[e] = 0xffff;
-  lds_order();
-  // robot rows are groups of their own: rob[level] = the row
-  for (int g = lane; g < NG; g += WAVE) {
-    const int r = gfirst[g];
-    if (r >= NL && r < NL + NR) rob[lvl[g]] = (uint16_t)r;
-  }
-  int pos = 0;
-  for (int lv = 1; lv <= maxl; ++lv) {
-    if (lane == 0) loff[lv - 1] = (uint16_t)pos;
-    for (int base = 0; base < NG; base += WAVE) {
-      const int g = base + lane;
-      bool m = false;
-      int r = 0;
-      if (g < NG) {
-        r = gfirst[g];
-        m = !(r >= NL && r < NL + NR) && lvl[g] == lv;
-      }
-      uint64_t mk = __ballot(m);
-      if (m) order[pos + prefix_below(mk)] = (uint32_t)r | ((uint32_t)(gfirst[g + 1] - r) << 16);
-      pos += __popcll(mk);
-    }
-  }
-  if (lane == 0) loff[maxl] = (uint16_t)pos;
   wave_sync();
-  return maxl;
+  return Levels{uniform(NG), uniform(maxl)};
 }
 
-// One dynamic side of a contact held in registers during a row update:
-// free body (x, v, w, 1/m, world inverse inertia) or door / drawer joint
-// (point-Jacobian column at the contact point, joint velocity, 1/M~).
-struct SideReg {
-  int kind, idx;
-  f3 x, v, w, col;
-  float im, qv;
-  // symmetric world inverse inertia (xx yy zz xy xz yz), named scalars so
-  // that the whole side stays in registers
-  float i0, i1, i2, i3, i4, i5;
+// Scale of a friction pair with squared length nn onto the disk of radius
+// lim (>= 0): a select, not a branch, so the lanes of a level do not split.
+// The floor keeps the reciprocal root finite at nn = 0, where it is not used,
+// and is below every pair of impulses above 1e-19 N s.
+__device__ __forceinline__ float disk_scale(float nn, float lim) {
+  float sc = lim * __builtin_amdgcn_rsqf(fmaxf(nn, 1.17549435e-38f));
+  asm volatile("" : "+v"(sc));
+  return nn > lim * lim ? sc : 1.f;
+}
+
+// the constants of a contact row that a sweep reads
+struct RowC {
+  f3 n, p;
+  float iw0, iw1, iw2, bias, ta, wt1, wt2;
 };
-__device__ __forceinline__ void side_load(const float* F, const float* A, int sv, f3 p, SideReg& S) {
-  S.kind = side_kind(sv);
-  S.idx = side_idx(sv);
-  S.x = S.v = S.w = S.col = mk3(0.f, 0.f, 0.f);
-  S.im = S.qv = 0.f;
-  S.i0 = S.i1 = S.i2 = S.i3 = S.i4 = S.i5 = 0.f;
-  if (S.kind == K_FREE) {
-    const float* f = F + S.idx * FSTR;
-    S.x = mk3(f[F_X], f[F_X + 1], f[F_X + 2]);
-    S.v = mk3(f[F_V], f[F_V + 1], f[F_V + 2]);
-    S.w = mk3(f[F_W], f[F_W + 1], f[F_W + 2]);
-    S.im = f[F_IM];
-    S.i0 = f[F_II + 0];
-    S.i1 = f[F_II + 1];
-    S.i2 = f[F_II + 2];
-    S.i3 = f[F_II + 3];
-    S.i4 = f[F_II + 4];
-    S.i5 = f[F_II + 5];
-  } else if (S.kind == K_AUX) {
-    S.col = aux_col(A, S.idx, p);
-    S.qv = A[A_V * AMAX + S.idx];
-    S.im = A[A_IM * AMAX + S.idx];
+__device__ __forceinline__ void row_load(const float* c, RowC& R) {
+  R.n = mk3(c[C_N], c[C_N + 1], c[C_N + 2]);
+  R.p = mk3(c[C_P], c[C_P + 1], c[C_P + 2]);
+  R.iw0 = c[C_IW];
+  R.iw1 = c[C_IW + 1];
+  R.iw2 = c[C_IW + 2];
+  R.bias = c[C_BIAS];
+  R.ta = c[C_ONB];
+  R.wt1 = c[C_WTN];
+  R.wt2 = c[C_WTN + 1];
+}
+// impulses of a row
+struct Lam {
+  float l0, l1, l2;
+};
+__device__ __forceinline__ Lam lam_load(const float* c) { return {c[C_LAM], c[C_LAM + 1], c[C_LAM + 2]}; }
+__device__ __forceinline__ void lam_store(float* c, const Lam& l) {
+  c[C_LAM] = l.l0;
+  c[C_LAM + 1] = l.l1;
+  c[C_LAM + 2] = l.l2;
+}
+// Update of a contact row whose sides approach with velocity u at the contact
+// point (relative, owner minus target): the normal, then the friction pair,
+// which sees the velocity after the normal update as t . u + dl (t . K n) with
+// the couplings t . K n of the two sides' inverse inertias from the rows
+// phase.  Returns the row's impulse change (applied to the bodies once).
+// tape: the row's record slots, or null.
+// (A row whose inverse effective mass is 0 leaves its impulse 0: the rows
+// phase zeroes both of a friction pair.)
+__device__ __forceinline__ f3 row_update(const RowC& R, f3 u, float mu, Lam& l, float* tape) {
+#pragma clang fp contract(off)
+  f3 t1, t2;
+  onb_f(R.n, R.ta, t1, t2);
+  const float y0 = fmaf(-R.iw0, R.bias + dot_f(R.n, u), l.l0);
+  const float nl = fmaxf(0.f, y0), dl = nl - l.l0;
+  const float y1 = fmaf(-R.iw1, fmaf(dl, R.wt1, dot_f(t1, u)), l.l1);
+  const float y2 = fmaf(-R.iw2, fmaf(dl, R.wt2, dot_f(t2, u)), l.l2);
+  const float sc = disk_scale(fmaf(y2, y2, y1 * y1), mu * nl);
+  const float d1 = fmaf(y1, sc, -l.l1), d2 = fmaf(y2, sc, -l.l2);
+  if (tape) {
+    tape[0] = y0;
+    tape[1] = y1;
+    tape[2] = y2;
   }
+  l.l0 = nl;
+  l.l1 = y1 * sc;
+  l.l2 = y2 * sc;
+  return madd(madd(R.n * dl, t1, d1), t2, d2);
 }
-// velocity of the contact point p of a side
-__device__ __forceinline__ f3 side_vel(const SideReg& S, f3 p) {
-  if (S.kind == K_FREE) return S.v + cross(S.w, p - S.x);
-  if (S.kind == K_AUX) return S.col * S.qv;
-  return mk3(0.f, 0.f, 0.f);
+// a free body in registers during the sweeps of its rows
+struct BodyReg {
+  f3 x, v, w;
+  float im, i0, i1, i2, i3, i4, i5;
+};
+__device__ __forceinline__ void body_consts(const float* f, BodyReg& B) {
+  B.x = mk3(f[F_X], f[F_X + 1], f[F_X + 2]);
+  B.im = f[F_IM];
+  B.i0 = f[F_II];
+  B.i1 = f[F_II + 1];
+  B.i2 = f[F_II + 2];
+  B.i3 = f[F_II + 3];
+  B.i4 = f[F_II + 4];
+  B.i5 = f[F_II + 5];
 }
-// apply the impulse P at p
-__device__ __forceinline__ void side_impulse(SideReg& S, f3 p, f3 P) {
-  if (S.kind == K_FREE) {
-    const f3 q = cross(p - S.x, P);
-    S.v = S.v + P * S.im;
-    S.w = S.w + mk3(S.i0 * q.x + S.i3 * q.y + S.i4 * q.z, S.i3 * q.x + S.i1 * q.y + S.i5 * q.z,
-                    S.i4 * q.x + S.i5 * q.y + S.i2 * q.z);
-  } else if (S.kind == K_AUX) {
-    S.qv += dot(S.col, P) * S.im;
-  }
+__device__ __forceinline__ void body_load(const float* f, BodyReg& B) {
+  body_consts(f, B);
+  B.v = mk3(f[F_V], f[F_V + 1], f[F_V + 2]);
+  B.w = mk3(f[F_W], f[F_W + 1], f[F_W + 2]);
 }
-__device__ __forceinline__ void side_store(float* F, float* A, const SideReg& S) {
-  if (S.kind == K_FREE) {
-    float* f = F + S.idx * FSTR;
-    f[F_V] = S.v.x; f[F_V + 1] = S.v.y; f[F_V + 2] = S.v.z;
-    f[F_W] = S.w.x; f[F_W + 1] = S.w.y; f[F_W + 2] = S.w.z;
-  } else if (S.kind == K_AUX) {
-    A[A_V * AMAX + S.idx] = S.qv;
-  }
+__device__ __forceinline__ void body_store(float* f, const BodyReg& B) {
+  f[F_V] = B.v.x; f[F_V + 1] = B.v.y; f[F_V + 2] = B.v.z;
+  f[F_W] = B.w.x; f[F_W + 1] = B.w.y; f[F_W + 2] = B.w.z;
 }
-// friction pair: Jacobi step on both tangent rows from the same velocity,
-// then projection onto the disk of radius mu * lambda_n
-__device__ __forceinline__ void friction_disk(float l1, float l2, float r1, float r2, float iw1, float iw2, float lim,
-                                              float& y1, float& y2) {
-  y1 = l1 - r1 * iw1;
-  y2 = l2 - r2 * iw2;
-  const float nn = y1 * y1 + y2 * y2;
-  // outside the disk: scaled onto it (onto 0 for a radius of 0); selects,
-  // not branches, so the lanes of a level do not split
-  const float sc = nn > lim * lim ? (lim > 0.f ? lim * rsqrtf(nn) : 0.f) : 1.f;
-  y1 *= sc;
-  y2 *= sc;
+// (world inverse inertia) q
+__device__ __forceinline__ f3 body_iinv(const BodyReg& B, f3 q) {
+  return {dot_f(mk3(B.i0, B.i3, B.i4), q), dot_f(mk3(B.i3, B.i1, B.i5), q), dot_f(mk3(B.i4, B.i5, B.i2), q)};
+}
+// a row of the body against a static target
+__device__ __forceinline__ void body_row(BodyReg& B, const RowC& R, float mu, Lam& l, float* tape) {
+#pragma clang fp contract(off)
+  const f3 ra = R.p - B.x;
+  const f3 u = B.v + cross_f(B.w, ra);
+  const f3 P = row_update(R, u, mu, l, tape);
+  B.v = madd(B.v, P, B.im);
+  B.w = B.w + body_iinv(B, cross_f(ra, P));
 }
 
-__device__ __forceinline__ void phase_pgs(const KArgs& a, const Scene& S, float* L, int NC, int NL, int maxl,
-                                          float& vR, float* tape) {
+// The sweeps of the bodies that only static targets touch: one lane per body
+// runs all its sweeps with the body in registers (nothing else reads or
+// writes it).  The next row's constants are loaded a row ahead, its impulses
+// right after the current row's are stored, so that a row's chain waits for
+// no LDS round trip.
+__device__ __forceinline__ void pgs_alone(const KArgs& a, float* L, int NG, float* tape) {
+  const LdsLayout& Y = a.L;
+  float* C = L + Y.con;
+  const uint16_t* lvl = level_of_groups(L, Y);
+  const uint16_t* gfirst = lvl + Y.ccap;
+  const float mu = a.mu;
+  const int K = a.K, tsw = a.RL.tsw;
+#pragma unroll 1
+  for (int g = lane_id(); g < NG; g += WAVE) {
+    if (lvl[g] != 0) continue;
+    const int c0 = gfirst[g], gn = gfirst[g + 1] - c0;
+    float* fa = L + Y.fr + side_idx(__float_as_int(C[c0 * CSTR + C_INFO]) & 0xffff) * FSTR;
+    BodyReg B;
+    body_load(fa, B);
+    float* cb = C + c0 * CSTR;
+    RowC R;
+    row_load(cb, R);
+    Lam l = lam_load(cb);
+    int k = 0;  // row within the group
+    float* tp = tape ? tape + c0 * 3 : nullptr;
+    const int n = K * gn;
+#pragma unroll 2
+    for (int i = 0; i < n; ++i) {
+      float* c = cb + k * CSTR;
+      float* tr = tp ? tp + k * 3 : nullptr;
+      k = k + 1 == gn ? 0 : k + 1;
+      if (tp && k == 0) tp += tsw;
+      float* cn = cb + k * CSTR;
+      RowC Rn;
+      row_load(cn, Rn);
+      body_row(B, R, mu, l, tr);
+      lam_store(c, l);
+      l = lam_load(cn);
+      R = Rn;
+    }
+    body_store(fa, B);
+  }
+}
+
+// The sweeps of everything else: per sweep the joint-limit rows, the robot's
+// rows in order, then the levels of the other groups (one lane per group,
+// groups owned by fixed lanes; the groups of a level share no node).
+// Robot rows: one serial chain, bound by its instruction count and the VALU's
+// dependent latency (a wavefront alone on its SIMD issues an instruction every
+// 5 cycles, dependent ones every 9).  So the wave's 16-lane rows work on
+// different directions: lane (d, j) holds direction d's vector, coupling,
+// impulse and entry j of J_d, and joint j's velocity; J_d . v of all three
+// directions is one 16-lane reduction, the rest of the three rows' arithmetic
+// one instruction stream, and the scalars that cross go through readlane.  A
+// row's data is loaded a row ahead, and a free body that consecutive rows
+// push stays in registers.  (With every lane forming all three directions and
+// each row looking up its level, side codes and data in turn, a row update
+// took 2.2 k cycles.)
+struct RobRow {
+  int sB;
+  float Jd, wn, w1, w2;
+  f3 D;
+  float iw, wt, bias, l;
+  f3 n, t1, t2, p;
+  BodyReg B;  // a free-body target's constants
+};
+// a lane's group of free-body rows
+struct Group {
+  int lv, c0, gn, fa, kB, xi, fb;
+  RowC R;
+  BodyReg A, B;
+};
+__device__ __forceinline__ void pgs_linked(const KArgs& a, float* L, int NC, int NL, int NR, Levels lv_, float& vR,
+                                           float* tape) {
+#pragma clang fp contract(off)
   const int lane = lane_id();
   const LdsLayout& Y = a.L;
   float* C = L + Y.con;
-  const int cc = Y.ccap;
   float* F = L + Y.fr;
   float* A = L + Y.aux;
   const float* Rw = L + Y.rows;
-  const uint16_t* loff = reinterpret_cast<const uint16_t*>(L + Y.lvl);
-  const uint16_t* rob = loff + cc + 2;
-  const uint32_t* order = reinterpret_cast<const uint32_t*>(rob + cc + 2);
+  const uint16_t* lvl = level_of_groups(L, Y);
+  const uint16_t* gfirst = lvl + Y.ccap;
   const float mu = a.mu;
-  const int j = lane & 15;
-  // w = M~^-1 J^T of the first robot rows, kept over the sweeps: in the
-  // robot's sphere centres and the culling lists (both dead until the next
-  // substep's kinematics and contacts)
-  float* wcA = L + Y.sph;
-  float* wcB = L + Y.cand;
-  const int wc1 = (Y.fr - Y.sph) / ROW_FLOATS, wc2 = (Y.frc - Y.cand) / ROW_FLOATS;
+  const int j = lane & 15, dr = lane >> 4;
   const float* Minv = robot_view(L + Y.robot, L + Y.dyn).Minv;
   // the zero record's velocities (kept zero by every update that uses it)
   if (lane < 6) F[Y.fmax * FSTR + F_V + lane] = 0.f;
-  wave_sync();
+  lds_order();
+  const int maxl = lv_.maxl, NG = lv_.ng;
+  // lane rr: the target side of robot row rr
+  const int rsB = lane < NR ? (__float_as_int(C[(NL + lane) * CSTR + C_INFO]) >> 16) & 0xffff : 0;
+  // the lane's group: level (0: alone, or none), first row, rows, body, the
+  // other side, and the first row's and the bodies' constants (a scene with
+  // more groups than lanes loads them again for each 64)
+  Group G;
+  auto grp_load = [&](int base) {
+    const int g = base + lane;
+    G.lv = g < NG ? (int)lvl[g] : 0;
+    if (G.lv == 0) return;
+    G.c0 = gfirst[g];
+    G.gn = (int)gfirst[g + 1] - G.c0;
+    const float* c = C + G.c0 * CSTR;
+    const int info = __float_as_int(c[C_INFO]);
+    const int sB = (info >> 16) & 0xffff;
+    G.fa = side_idx(info & 0xffff);
+    G.kB = side_kind(sB);
+    G.xi = side_idx(sB);
+    G.fb = G.kB == K_FREE ? G.xi : Y.fmax;
+    row_load(c, G.R);
+    body_consts(F + G.fa * FSTR, G.A);
+    body_consts(F + G.fb * FSTR, G.B);
+  };
+  grp_load(0);
+  const int rblk = lane < NR ? rob_block(Y, NC, NR, lane) : -1;
+  // robot rows with a block (a prefix of them: blocks are given out in order)
+  const int NB = __popcll(__ballot(rblk >= 0));
+  const int dd = dr < 3 ? dr : 2;  // this lane's direction (the last 16 lanes repeat the third)
+  // row rr (which has a block): every load unconditional, a target that is no
+  // free body reads the zero record
+  auto rob_load = [&](int rr, RobRow& Q) {
+    const float* b = L + __builtin_amdgcn_readlane(rblk, rr);
+    Q.sB = __builtin_amdgcn_readlane(rsB, rr);
+    const float4* q = reinterpret_cast<const float4*>(b + RB_DIR);
+    Q.Jd = Rw[rr * ROW_FLOATS + dd * ND + j];
+    const float4 q0 = q[2 * dd], q1 = q[2 * dd + 1];
+    Q.D = mk3(q0.x, q0.y, q0.z);
+    Q.iw = q0.w;
+    Q.wt = q1.x;
+    Q.bias = q1.y;
+    Q.l = q1.z;
+    Q.wn = b[j];
+    Q.w1 = b[ND + j];
+    Q.w2 = b[2 * ND + j];
+    const float4 a0 = q[0], a1 = q[2], a2 = q[4], ap = q[6];
+    Q.n = mk3(a0.x, a0.y, a0.z);
+    Q.t1 = mk3(a1.x, a1.y, a1.z);
+    Q.t2 = mk3(a2.x, a2.y, a2.z);
+    Q.p = mk3(ap.x, ap.y, ap.z);
+    body_consts(F + (side_kind(Q.sB) == K_FREE ? side_idx(Q.sB) : Y.fmax) * FSTR, Q.B);
+  };
+  // Row rr from the approach velocity sv of each lane's direction: the normal
+  // (first 16 lanes), then the friction pair, which sees the velocity after
+  // the normal update: t . u + dl (t . K n), the couplings of both sides from
+  // the rows phase.  (dl, dl1, dl2): the impulse changes.
+  auto rob_solve = [&](const RobRow& Q, float sv, float* tr, float& dl, float& dl1, float& dl2) -> float {
+#pragma clang fp contract(off)
+    const float y0 = fmaf(-Q.iw, Q.bias + sv, Q.l);
+    const float nl0 = fmaxf(0.f, y0), dl0 = nl0 - Q.l;
+    dl = lane_val(dl0, 0);
+    const float lim = mu * lane_val(nl0, 0);
+    const float y = fmaf(-Q.iw, fmaf(Q.wt, dl, sv), Q.l);
+    const float y1 = lane_val(y, ND), y2 = lane_val(y, 2 * ND);
+    const float sc = disk_scale(fmaf(y2, y2, y1 * y1), lim);
+    const float df = fmaf(y, sc, -Q.l);
+    dl1 = lane_val(df, ND);
+    dl2 = lane_val(df, 2 * ND);
+    vR = vR + fmaf(Q.w2, dl2, fmaf(Q.wn, dl, Q.w1 * dl1));
+    if (tr && j == 0 && dr < 3) tr[dr] = dr == 0 ? y0 : y;
+    return dr == 0 ? nl0 : y * sc;
+  };
+  // row rr from Q; the row after it is loaded into N
+  auto rob_step = [&](int rr, float* tsweep, RobRow& Q, RobRow& N) {
+#pragma clang fp contract(off)
+    float* lam = L + __builtin_amdgcn_readlane(rblk, rr) + RB_DIR + 8 * dd + RB_LAM;
+    float* tr = tsweep ? tsweep + (NL + rr) * 3 : nullptr;
+    const int kB = side_kind(Q.sB), xi = side_idx(Q.sB);
+    float* f = F + (kB == K_FREE ? xi : Y.fmax) * FSTR;
+    f3 bv = mk3(f[F_V], f[F_V + 1], f[F_V + 2]), bw = mk3(f[F_W], f[F_W + 1], f[F_W + 2]);
+    rob_load(rr + 1 < NB ? rr + 1 : 0, N);
+    float sv = sum16(Q.Jd * vR), ln, dl, dl1, dl2;
+    if (kB == K_STATIC) {
+      ln = rob_solve(Q, sv, tr, dl, dl1, dl2);
+    } else if (kB == K_FREE) {
+      const f3 rB = Q.p - Q.B.x;
+      sv = sv - dot_f(Q.D, bv + cross_f(bw, rB));
+      ln = rob_solve(Q, sv, tr, dl, dl1, dl2);
+      // the target receives -P (every lane stores the same values)
+      const f3 P = madd(madd(Q.t1 * dl1, Q.n, dl), Q.t2, dl2);
+      const f3 q = mk3(fmaf(rB.z, P.y, -(rB.y * P.z)), fmaf(rB.x, P.z, -(rB.z * P.x)), fmaf(rB.y, P.x, -(rB.x * P.y)));
+      bv = madd(bv, P, -Q.B.im);
+      bw = bw + body_iinv(Q.B, q);
+      f[F_V] = bv.x; f[F_V + 1] = bv.y; f[F_V + 2] = bv.z;
+      f[F_W] = bw.x; f[F_W + 1] = bw.y; f[F_W + 2] = bw.z;
+    } else {
+      const f3 col = aux_col_f(A, xi, Q.p);
+      const float qv = A[A_V * AMAX + xi], imx = A[A_IM * AMAX + xi];
+      sv = sv - dot_f(Q.D, col * qv);
+      ln = rob_solve(Q, sv, tr, dl, dl1, dl2);
+      const f3 P = madd(madd(Q.t1 * dl1, Q.n, dl), Q.t2, dl2);
+      A[A_V * AMAX + xi] = fmaf(imx, fmaf(-col.z, P.z, fmaf(col.y, -P.y, -(col.x * P.x))), qv);
+    }
+    *lam = ln;
+    N.l = NB == 1 ? ln : N.l;  // loaded above before this row's store
+    lds_order();
+  };
+  // a row without a block, from the contact record, w from M~^-1 (symmetric,
+  // so lane j reads its column: consecutive across the lanes)
+  auto rob_step_far = [&](int rr, float* tsweep) {
+#pragma clang fp contract(off)
+    float* c = C + (NL + rr) * CSTR;
+    const float* row = Rw + rr * ROW_FLOATS;
+    float* tr = tsweep ? tsweep + (NL + rr) * 3 : nullptr;
+    const int sB = uniform((__float_as_int(c[C_INFO]) >> 16) & 0xffff), kB = side_kind(sB), xi = side_idx(sB);
+    RobRow Q;
+    Q.n = mk3(c[C_N], c[C_N + 1], c[C_N + 2]);
+    Q.p = mk3(c[C_P], c[C_P + 1], c[C_P + 2]);
+    onb_f(Q.n, c[C_ONB], Q.t1, Q.t2);
+    Q.D = sel(dd == 0, Q.n, sel(dd == 1, Q.t1, Q.t2));
+    Q.iw = c[C_IW + dd];
+    Q.wt = dd == 0 ? 0.f : c[C_WTN + (dd == 2 ? 1 : 0)];
+    Q.bias = dd == 0 ? c[C_BIAS] : 0.f;
+    Q.l = c[C_LAM + dd];
+    Q.wn = Q.w1 = Q.w2 = 0.f;
+#pragma unroll 1
+    for (int k = 0; k < ND; k += 4) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float m = Minv[(k + e) * ND + j];
+        Q.wn = fmaf(m, row[k + e], Q.wn);
+        Q.w1 = fmaf(m, row[ND + k + e], Q.w1);
+        Q.w2 = fmaf(m, row[2 * ND + k + e], Q.w2);
+      }
+    }
+    float* f = F + (kB == K_FREE ? xi : Y.fmax) * FSTR;
+    body_load(f, Q.B);
+    const f3 rB = Q.p - Q.B.x;
+    float sv = sum16(row[dd * ND + j] * vR), dl, dl1, dl2;
+    f3 col = mk3(0.f, 0.f, 0.f);
+    float qv = 0.f;
+    if (kB == K_FREE) {
+      sv = sv - dot_f(Q.D, Q.B.v + cross_f(Q.B.w, rB));
+    } else if (kB == K_AUX) {
+      col = aux_col_f(A, xi, Q.p);
+      qv = A[A_V * AMAX + xi];
+      sv = sv - dot_f(Q.D, col * qv);
+    }
+    c[C_LAM + dd] = rob_solve(Q, sv, tr, dl, dl1, dl2);
+    const f3 P = madd(madd(Q.t1 * dl1, Q.n, dl), Q.t2, dl2);
+    if (kB == K_FREE) {
+      Q.B.v = madd(Q.B.v, P, -Q.B.im);
+      Q.B.w = Q.B.w + body_iinv(Q.B, mk3(fmaf(rB.z, P.y, -(rB.y * P.z)), fmaf(rB.x, P.z, -(rB.z * P.x)),
+                                         fmaf(rB.y, P.x, -(rB.x * P.y))));
+      body_store(f, Q.B);
+    } else if (kB == K_AUX) {
+      A[A_V * AMAX + xi] =
+          fmaf(A[A_IM * AMAX + xi], fmaf(-col.z, P.z, fmaf(col.y, -P.y, -(col.x * P.x))), qv);
+    }
+    lds_order();
+  };
+  RobRow Q0, Q1;
+  if (NB > 0) rob_load(0, Q0);
 #pragma unroll 1
   for (int it = 0; it < a.K; ++it) {
-    int o1 = 0;  // a level's rows start where the previous level's end
+    float* tsweep = tape ? tape + it * a.RL.tsw : nullptr;
+    // joint-limit rows: the first row of a joint runs its second one too
+    if (NL > 0) {
+      if (lane < NL) {
+        const int x0 = side_idx(__float_as_int(C[lane * CSTR + C_INFO]) & 0xffff);
+        const int xp = lane > 0 ? side_idx(__float_as_int(C[(lane - 1) * CSTR + C_INFO]) & 0xffff) : -1;
+        if (xp != x0) {
+          float v = A[A_V * AMAX + x0];
+          for (int ci = lane; ci < NL; ++ci) {
+            float* c = C + ci * CSTR;
+            const int info = __float_as_int(c[C_INFO]);
+            if (side_idx(info & 0xffff) != x0) break;
+            const float sg = ((info >> 16) & 1) ? -1.f : 1.f;
+            const float iwl = c[C_IW], l0 = c[C_LAM];  // iwl = 1 / W
+            const float y = fmaf(-iwl, fmaf(sg, v, c[C_BIAS]), l0);
+            const float nl = fmaxf(0.f, y);
+            if (tsweep) tsweep[ci * 3] = y;
+            v = fmaf(sg * A[A_IM * AMAX + x0], nl - l0, v);
+            c[C_LAM] = nl;
+          }
+          A[A_V * AMAX + x0] = v;
+        }
+      }
+      lds_order();
+    }
+    // the robot's rows, two at a time (the loaded rows change places without
+    // copies)
+#pragma unroll 1
+    for (int rr = 0; rr < NB; rr += 2) {
+      rob_step(rr, tsweep, Q0, Q1);
+      if (rr + 1 < NB) rob_step(rr + 1, tsweep, Q1, Q0);
+      else Q0 = Q1;
+    }
+#pragma unroll 1
+    for (int rr = NB; rr < NR; ++rr) rob_step_far(rr, tsweep);
+    // the other groups, level by level
 #pragma unroll 1
     for (int lv = 1; lv <= maxl; ++lv) {
-      const int rc = rob[lv] == 0xffff ? -1 : (int)rob[lv];
-      const int o0 = o1;
-      o1 = loff[lv];
-      if (rc >= 0) {
-        // the level's robot row: lane j of each 16-lane row holds joint
-        // velocity j; row d < 3 of the wave forms J_d . v in one reduction
-        const float* row = Rw + (rc - NL) * ROW_FLOATS;
-        const float* c = C + rc * CSTR;
-        int info = __float_as_int(c[C_INFO]);
-        f3 n = mk3(c[C_N], c[C_N + 1], c[C_N + 2]);
-        f3 p = mk3(c[C_P], c[C_P + 1], c[C_P + 2]);
-        float iw0 = c[C_IW], iw1 = c[C_IW + 1], iw2 = c[C_IW + 2];
-        float bias = c[C_BIAS];
-        float l0 = c[C_LAM], l1 = c[C_LAM + 1], l2 = c[C_LAM + 2];
-        const float wtn1 = c[C_WTN], wtn2 = c[C_WTN + 1];
-        const int dr = lane >> 4;
-        const float Jd = row[(dr < 3 ? dr : 2) * ND + j];
-        // lane j's entries of w = M~^-1 J^T: formed in the first sweep (M~^-1
-        // is symmetric, so lane j reads its column: consecutive across the
-        // lanes, no bank conflicts) and kept for the later ones where LDS
-        // that is dead during the sweeps has room
-        float wn = 0.f, w1 = 0.f, w2 = 0.f;
-        const int rr = rc - NL;
-        float* wc = rr < wc1 ? wcA + rr * ROW_FLOATS : (rr < wc1 + wc2 ? wcB + (rr - wc1) * ROW_FLOATS : nullptr);
-        if (it == 0 || wc == nullptr) {
-#pragma unroll 8
-          for (int k = 0; k < ND; ++k) {
-            const float m = Minv[k * ND + j];
-            wn += m * row[k];
-            w1 += m * row[ND + k];
-            w2 += m * row[2 * ND + k];
-          }
-          if (wc != nullptr && dr < 3) wc[lane] = dr == 0 ? wn : (dr == 1 ? w1 : w2);
-        } else {
-          wn = wc[j];
-          w1 = wc[ND + j];
-          w2 = wc[2 * ND + j];
-        }
-        f3 t1, t2;
-        onb_a(n, c[C_ONB], t1, t2);
-        SideReg B;
-        side_load(F, A, (info >> 16) & 0xffff, p, B);
-        const float dsum = sum16(dr < 3 ? Jd * vR : 0.f);
-        const float dn = lane_val(dsum, 0), d1 = lane_val(dsum, ND), d2 = lane_val(dsum, 2 * ND);
-        const f3 uB = side_vel(B, p);
-        float r = dn - dot(n, uB) + bias;
-        float nl = l0;
-        if (iw0 > 0.f) nl = fmaxf(0.f, l0 - r * iw0);
-        if (tape && lane == 0) tape[it * a.RL.tsw + rc * 3] = l0 - r * iw0;
-        const float dl = nl - l0;
-        float dl1 = 0.f, dl2 = 0.f;
-        if (iw1 > 0.f && iw2 > 0.f) {
-          // the friction pair sees the velocity after the normal update:
-          // t . u + dl (t . K n), the couplings of both sides from the rows
-          // phase; the impulses are then applied together
-          const float u1 = d1 - dot(t1, uB) + dl * wtn1, u2 = d2 - dot(t2, uB) + dl * wtn2;
-          float y1, y2;
-          friction_disk(l1, l2, u1, u2, iw1, iw2, mu * nl, y1, y2);
-          if (tape && lane == 0) {
-            tape[it * a.RL.tsw + rc * 3 + 1] = l1 - u1 * iw1;
-            tape[it * a.RL.tsw + rc * 3 + 2] = l2 - u2 * iw2;
-          }
-          dl1 = y1 - l1;
-          dl2 = y2 - l2;
-          l1 = y1;
-          l2 = y2;
-        }
-        vR += wn * dl + w1 * dl1 + w2 * dl2;
-        side_impulse(B, p, (n * dl + t1 * dl1 + t2 * dl2) * (-1.f));
-        if (lane == 0) {
-          side_store(F, A, B);
-          float* cw = C + rc * CSTR;
-          cw[C_LAM] = nl;
-          cw[C_LAM + 1] = l1;
-          cw[C_LAM + 2] = l2;
-        }
-        // the per-lane rows below touch other nodes; the fence also keeps the
-        // robot row's registers from living into them
-        lds_order();
-      }
-      // the level's other rows, one lane each (they share no node)
 #pragma unroll 1
-      for (int e = o0 + lane; e < o1; e += WAVE) {
-        const uint32_t ge = order[e];
-        const int gn = ge >> 16;
-        if (gn > 1) {
-          // a group: consecutive rows between one free body and static
-          // targets, in order, with the body's velocities in registers
-          const int c0 = ge & 0xffff;
-          float* fa = F + side_idx(__float_as_int(C[c0 * CSTR + C_INFO]) & 0xffff) * FSTR;
-          const f3 xa = mk3(fa[F_X], fa[F_X + 1], fa[F_X + 2]);
-          f3 va = mk3(fa[F_V], fa[F_V + 1], fa[F_V + 2]), wa = mk3(fa[F_W], fa[F_W + 1], fa[F_W + 2]);
-          const float ima = fa[F_IM];
-          const float i0 = fa[F_II], i1 = fa[F_II + 1], i2 = fa[F_II + 2], i3 = fa[F_II + 3], i4 = fa[F_II + 4],
-                      i5 = fa[F_II + 5];
-#pragma unroll 1
-          for (int ci = c0; ci < c0 + gn; ++ci) {
-            float* c = C + ci * CSTR;
-            const f3 n = mk3(c[C_N], c[C_N + 1], c[C_N + 2]);
-            const f3 p = mk3(c[C_P], c[C_P + 1], c[C_P + 2]);
-            const float iw0 = c[C_IW], iw1 = c[C_IW + 1], iw2 = c[C_IW + 2], bias = c[C_BIAS];
-            const float l0 = c[C_LAM];
-            float l1 = c[C_LAM + 1], l2 = c[C_LAM + 2];
-            const f3 ra = p - xa;
-            const f3 u = va + cross(wa, ra);
-            const float r = dot(n, u) + bias;
-            float nl = l0;
-            if (iw0 > 0.f) nl = fmaxf(0.f, l0 - r * iw0);
-            if (tape) tape[it * a.RL.tsw + ci * 3] = l0 - r * iw0;
-            const float dl = nl - l0;
-            f3 P = n * dl;
-            if (iw1 > 0.f && iw2 > 0.f) {
-              f3 t1, t2;
-              onb_a(n, c[C_ONB], t1, t2);
-              const float u1 = dot(t1, u) + dl * c[C_WTN], u2 = dot(t2, u) + dl * c[C_WTN + 1];
-              float y1, y2;
-              friction_disk(l1, l2, u1, u2, iw1, iw2, mu * nl, y1, y2);
-              if (tape) {
-                tape[it * a.RL.tsw + ci * 3 + 1] = l1 - u1 * iw1;
-                tape[it * a.RL.tsw + ci * 3 + 2] = l2 - u2 * iw2;
-              }
-              P = P + t1 * (y1 - l1) + t2 * (y2 - l2);
-              l1 = y1;
-              l2 = y2;
-            }
-            const f3 q = cross(ra, P);
-            va = va + P * ima;
-            wa = wa + mk3(i0 * q.x + i3 * q.y + i4 * q.z, i3 * q.x + i1 * q.y + i5 * q.z, i4 * q.x + i5 * q.y + i2 * q.z);
-            c[C_LAM] = nl;
-            c[C_LAM + 1] = l1;
-            c[C_LAM + 2] = l2;
-          }
-          fa[F_V] = va.x; fa[F_V + 1] = va.y; fa[F_V + 2] = va.z;
-          fa[F_W] = wa.x; fa[F_W + 1] = wa.y; fa[F_W + 2] = wa.z;
-          continue;
-        }
-        const int ci = ge & 0xffff;
-        float* c = C + ci * CSTR;
-        const int info = __float_as_int(c[C_INFO]);
-        const int sA = info & 0xffff, sB = (info >> 16) & 0xffff;
-        float bias = c[C_BIAS];
-        float l0 = c[C_LAM];
-        if (side_kind(sA) == K_LIMIT) {
-          int x = side_idx(sA);
-          float sg = ((info >> 16) & 1) ? -1.f : 1.f;
-          float iwl = c[C_IW];  // = 1 / W
-          float r = sg * A[A_V * AMAX + x] + bias;
-          float nl = fmaxf(0.f, l0 - r * iwl);
-          if (tape) tape[it * a.RL.tsw + ci * 3] = l0 - r * iwl;
-          A[A_V * AMAX + x] += sg * A[A_IM * AMAX + x] * (nl - l0);
-          c[C_LAM] = nl;
-          continue;
-        }
-        // side A is a free body (the owner); side B a free body, a door /
-        // drawer or static.  A static B reads and writes the zero record past
-        // the scene's free bodies (no mass, no velocity), so both sides run
-        // the same loads and arithmetic without branches; a door / drawer
-        // adds its joint's part in a branch of its own.
-        const f3 n = mk3(c[C_N], c[C_N + 1], c[C_N + 2]);
-        const f3 p = mk3(c[C_P], c[C_P + 1], c[C_P + 2]);
-        const float iw0 = c[C_IW], iw1 = c[C_IW + 1], iw2 = c[C_IW + 2];
-        float l1 = c[C_LAM + 1], l2 = c[C_LAM + 2];
-        const int kB = side_kind(sB), xi = side_idx(sB);
-        float* fa = F + side_idx(sA) * FSTR;
-        float* fb = F + (kB == K_FREE ? xi : Y.fmax) * FSTR;
-        const f3 xa = mk3(fa[F_X], fa[F_X + 1], fa[F_X + 2]), xb = mk3(fb[F_X], fb[F_X + 1], fb[F_X + 2]);
+      for (int base = 0; base < NG; base += WAVE) {
+        if (NG > WAVE) grp_load(base);
+        if (G.lv != lv) continue;
+        float* c = C + G.c0 * CSTR;
+        float* fa = F + G.fa * FSTR;
+        Lam l = lam_load(c);
+        float* tr = tsweep ? tsweep + G.c0 * 3 : nullptr;
         f3 va = mk3(fa[F_V], fa[F_V + 1], fa[F_V + 2]), wa = mk3(fa[F_W], fa[F_W + 1], fa[F_W + 2]);
+        if (G.kB == K_STATIC) {
+          // consecutive rows between one free body and static targets, the
+          // next row's constants loaded a row ahead
+          BodyReg B = G.A;
+          B.v = va;
+          B.w = wa;
+          RowC R = G.R;
+#pragma unroll 1
+          for (int k = 1;; ++k) {
+            RowC Rn;
+            float* cn = c + (k < G.gn ? CSTR : 0);
+            row_load(cn, Rn);
+            body_row(B, R, mu, l, tr);
+            lam_store(c, l);
+            if (k >= G.gn) break;
+            c = cn;
+            l = lam_load(c);
+            if (tr) tr += 3;
+            R = Rn;
+          }
+          body_store(fa, B);
+          continue;
+        }
+        // side A is a free body (the owner); side B a free body or a door /
+        // drawer, which reads and writes the zero record past the scene's
+        // free bodies (no mass, no velocity) and adds its joint's part
+        const RowC& R = G.R;
+        float* fb = F + G.fb * FSTR;
         f3 vb = mk3(fb[F_V], fb[F_V + 1], fb[F_V + 2]), wb = mk3(fb[F_W], fb[F_W + 1], fb[F_W + 2]);
-        const f3 ra = p - xa, rb = p - xb;
-        f3 u = (va + cross(wa, ra)) - (vb + cross(wb, rb));
+        const f3 ra = R.p - G.A.x, rb = R.p - G.B.x;
+        f3 u = (va + cross_f(wa, ra)) - (vb + cross_f(wb, rb));
         f3 col = mk3(0.f, 0.f, 0.f);
         float qv = 0.f, imx = 0.f;
-        if (kB == K_AUX) {
-          col = aux_col(A, xi, p);
-          qv = A[A_V * AMAX + xi];
-          imx = A[A_IM * AMAX + xi];
-          u = u - col * qv;
+        if (G.kB == K_AUX) {
+          col = aux_col_f(A, G.xi, R.p);
+          qv = A[A_V * AMAX + G.xi];
+          imx = A[A_IM * AMAX + G.xi];
+          u = madd(u, col, -qv);
         }
-        float r = dot(n, u) + bias;
-        float nl = l0;
-        if (iw0 > 0.f) nl = fmaxf(0.f, l0 - r * iw0);
-        if (tape) tape[it * a.RL.tsw + ci * 3] = l0 - r * iw0;
-        float dl = nl - l0;
-        f3 P = n * dl;
-        if (iw1 > 0.f && iw2 > 0.f) {
-          // the friction pair sees the velocity after the normal update: its
-          // tangential parts are t . u + dl (t . K n), with the couplings
-          // t . K n of the two sides' inverse inertias from the rows phase;
-          // the normal and friction impulses are then applied together
-          f3 t1, t2;
-          onb_a(n, c[C_ONB], t1, t2);
-          const float u1 = dot(t1, u) + dl * c[C_WTN], u2 = dot(t2, u) + dl * c[C_WTN + 1];
-          float y1, y2;
-          friction_disk(l1, l2, u1, u2, iw1, iw2, mu * nl, y1, y2);
-          if (tape) {
-            tape[it * a.RL.tsw + ci * 3 + 1] = l1 - u1 * iw1;
-            tape[it * a.RL.tsw + ci * 3 + 2] = l2 - u2 * iw2;
-          }
-          P = P + t1 * (y1 - l1) + t2 * (y2 - l2);
-          l1 = y1;
-          l2 = y2;
-        }
-        {
-          const float ima = fa[F_IM], imb = fb[F_IM];
-          const f3 qa = cross(ra, P), qb = cross(rb, P);
-          const float* ia = fa + F_II;
-          const float* ib = fb + F_II;
-          va = va + P * ima;
-          wa = wa + mk3(ia[0] * qa.x + ia[3] * qa.y + ia[4] * qa.z, ia[3] * qa.x + ia[1] * qa.y + ia[5] * qa.z,
-                        ia[4] * qa.x + ia[5] * qa.y + ia[2] * qa.z);
-          vb = vb - P * imb;
-          wb = wb - mk3(ib[0] * qb.x + ib[3] * qb.y + ib[4] * qb.z, ib[3] * qb.x + ib[1] * qb.y + ib[5] * qb.z,
-                        ib[4] * qb.x + ib[5] * qb.y + ib[2] * qb.z);
-          fa[F_V] = va.x; fa[F_V + 1] = va.y; fa[F_V + 2] = va.z;
-          fa[F_W] = wa.x; fa[F_W + 1] = wa.y; fa[F_W + 2] = wa.z;
-          fb[F_V] = vb.x; fb[F_V + 1] = vb.y; fb[F_V + 2] = vb.z;
-          fb[F_W] = wb.x; fb[F_W + 1] = wb.y; fb[F_W + 2] = wb.z;
-          if (kB == K_AUX) A[A_V * AMAX + xi] = qv - dot(col, P) * imx;
-        }
-        c[C_LAM] = nl;
-        c[C_LAM + 1] = l1;
-        c[C_LAM + 2] = l2;
+        const f3 P = row_update(R, u, mu, l, tr);
+        va = madd(va, P, G.A.im);
+        wa = wa + body_iinv(G.A, cross_f(ra, P));
+        vb = madd(vb, P, -G.B.im);
+        wb = wb - body_iinv(G.B, cross_f(rb, P));
+        fa[F_V] = va.x; fa[F_V + 1] = va.y; fa[F_V + 2] = va.z;
+        fa[F_W] = wa.x; fa[F_W + 1] = wa.y; fa[F_W + 2] = wa.z;
+        fb[F_V] = vb.x; fb[F_V + 1] = vb.y; fb[F_V + 2] = vb.z;
+        fb[F_W] = wb.x; fb[F_W + 1] = wb.y; fb[F_W + 2] = wb.z;
+        if (G.kB == K_AUX) A[A_V * AMAX + G.xi] = fmaf(-dot_f(col, P), imx, qv);
+        lam_store(c, l);
       }
       lds_order();
     }
   }
+  // the robot rows' impulses back to the contact list (the force outputs read them)
+  if (rblk >= 0)
+    for (int d = 0; d < 3; ++d) C[(NL + lane) * CSTR + C_LAM + d] = L[rblk + RB_DIR + 8 * d + RB_LAM];
 }
 
-__device__ __forceinline__ void phase_integrate(const KArgs& a, const Scene& S, float* L, const Robot& rb, float vR) {
+__device__ __forceinline__ void phase_integrate(const KArgs& a, const Scene& S, float* L, float vR) {
+  const Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
   const int lane = lane_id();
   if (lane < ND) {
     rb.qd[lane] = vR;
@@ -2364,7 +2597,9 @@ __device__ __forceinline__ void phase_forces(const KArgs& a, const Scene& S, flo
 // adjoint; 2: also the contact-force outputs.  Separate instantiations, so
 // the plain step keeps its register allocation.
 template <int MODE>
-__device__ __forceinline__ void run_scene(const KArgs& a, int s, float* L) {
+__device__ __forceinline__ void run_scene(int s, float* const L0) {
+  const KArgs& a = args_fresh();
+  float* const L = lds_fresh(L0);
   constexpr bool REC = MODE == 1;
   const int lane = lane_id();
   Scene S;
@@ -2383,7 +2618,6 @@ __device__ __forceinline__ void run_scene(const KArgs& a, int s, float* L) {
     S.gix = g[2];
     S.giy = g[3];
   }
-  Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
   const unsigned long long t_scene = a.cost ? clock64() : 0ull;
   const bool prof = a.phase_cycles != nullptr;
   unsigned long long cyc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -2394,7 +2628,7 @@ __device__ __forceinline__ void run_scene(const KArgs& a, int s, float* L) {
     cyc[k] += t2 - tc;                       \
     tc = t2;                                 \
   }
-  load_scene(a, S, L, rb);
+  load_scene(args_fresh(), S, lds_fresh(L0));
   MS_PHASE(7)
   uint32_t status = 0;
   float frc = 0.f;
@@ -2426,33 +2660,39 @@ __device__ __forceinline__ void run_scene(const KArgs& a, int s, float* L) {
     uint64_t keysum = 0;
     float vR;
     const int ks = a.sub0 + k;
-    if (rec) rec_state(a, S, L, rb, rec + ks * a.RL.ss);
-    phase_drive(a, S, rb);
-    phase_kinematics(a, S, L, rb);
+    if (rec) rec_state(args_fresh(), S, lds_fresh(L0), rec + ks * a.RL.ss);
+    phase_drive(args_fresh(), S, lds_fresh(L0));
+    phase_kinematics(args_fresh(), S, lds_fresh(L0));
     MS_PHASE(0)
     // unconstrained dynamics first: it needs only the frames, and its
     // articulated-body scratch is dead before the contact list is written
     // into the same LDS
-    phase_dynamics(a, S, L, rb, vR);
+    phase_dynamics(args_fresh(), S, lds_fresh(L0), vR);
     MS_PHASE(2)
-    phase_contacts(a, S, L, rb, NC, NR, NL, status, keysum);
+    phase_contacts(args_fresh(), S, lds_fresh(L0), NC, NR, NL, status, keysum);
     // a launch in a smaller layout gives up a scene at its first overflowing
     // contact list; everything written so far the retry writes again alike
     if (a.fit_mode == 1 && (status & 10u)) break;
-    if (rec) rec_contacts(a, L, NC, NL, NR, rec + a.RL.con + ks * a.RL.cstride);
+    if (rec) rec_contacts(args_fresh(), lds_fresh(L0), NC, NL, NR, rec + a.RL.con + ks * a.RL.cstride);
     max_nc = max(max_nc, NC - NL);
     max_nr = max(max_nr, NR);
     MS_PHASE(1)
-    phase_rows(a, S, L, rb, NC, NR, NL, status);
-    MS_PHASE(3)
-    int maxl = phase_levels(a, L, NC, NR, NL);
+    // the schedule before the rows: its masks lie where the rows phase
+    // leaves the robot rows' w
+    const Levels lv = phase_levels(args_fresh(), lds_fresh(L0), NC, NR, NL);
     MS_PHASE(4)
-    phase_pgs(a, S, L, NC, NL, maxl, vR, rec ? rec + a.RL.tape + (size_t)ks * a.K * a.RL.tsw : nullptr);
-    if (MODE == 2) phase_forces(a, S, L, NL, NR, frc, ks == a.n_sub_total - 1);
+    phase_rows(args_fresh(), S, lds_fresh(L0), NC, NR, NL, status);
+    MS_PHASE(3)
+    {
+      float* tape = rec ? rec + a.RL.tape + (size_t)ks * a.K * a.RL.tsw : nullptr;
+      pgs_alone(args_fresh(), lds_fresh(L0), lv.ng, tape);
+      pgs_linked(args_fresh(), lds_fresh(L0), NC, NL, NR, lv, vR, tape);
+    }
+    if (MODE == 2) phase_forces(args_fresh(), S, lds_fresh(L0), NL, NR, frc, ks == a.n_sub_total - 1);
     MS_PHASE(5)
-    phase_integrate(a, S, L, rb, vR);
+    phase_integrate(args_fresh(), S, lds_fresh(L0), vR);
     MS_PHASE(6)
-    if (rec && ks == a.n_sub_total - 1) rec_state(a, S, L, rb, rec + (ks + 1) * a.RL.ss);
+    if (rec && ks == a.n_sub_total - 1) rec_state(args_fresh(), S, lds_fresh(L0), rec + (ks + 1) * a.RL.ss);
     if (a.debug && lane == 0) {
       uint32_t* d = a.debug + ((size_t)s * a.n_sub_total + a.sub0 + k) * 4;
       d[0] = (uint32_t)(NC - NL);
@@ -2468,7 +2708,7 @@ __device__ __forceinline__ void run_scene(const KArgs& a, int s, float* L) {
     if (lane == 0) a.retry[1 + atomicAdd(a.retry, 1)] = s;
     return;
   }
-  store_scene(a, S, L, rb, status);
+  store_scene(args_fresh(), S, lds_fresh(L0), status);
   if (MODE == 2 && a.grip) {
     const float* FR = L + a.L.frc;
     const float* A = L + a.L.aux;
@@ -2530,10 +2770,10 @@ __device__ __forceinline__ void step_body(const KArgs& a, float* lds) {
     if (a.persistent) {
       int got = 0;
       if (threadIdx.x == 0) got = atomicAdd(a.queue + qi, 1);
-      pos = base + __shfl(got, 0, WAVE);
+      pos = base + uniform(got);
     }
     if (pos >= end) break;
-    run_scene<MODE>(a, a.fit_mode == 3 ? a.retry[1 + pos] : a.order[pos], lds);
+    run_scene<MODE>(uniform(a.fit_mode == 3 ? a.retry[1 + pos] : a.order[pos]), lds);
     if (!a.persistent) break;
     __syncthreads();
   }
@@ -2574,9 +2814,8 @@ __global__ __launch_bounds__(WAVE) void k_spawn_check(KArgs a, uint8_t* collide)
   S.f0 = ds.f0; S.s0 = ds.s0; S.p0 = ds.p0; S.a0 = ds.a0;
   S.hold = a.scenes[s].hold;
   float* L = lds;
-  Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
-  load_scene(a, S, L, rb);
-  phase_kinematics(a, S, L, rb);
+  load_scene(a, S, L);
+  phase_kinematics(a, S, L);
   const LdsLayout& Y = a.L;
   ConCtx X;
   X.M = S.M;

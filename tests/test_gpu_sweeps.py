@@ -1,0 +1,95 @@
+"""The Gauss-Seidel sweeps' special cases: robot rows with and without room
+for their data beside the contact list (and more of them than lanes), and more
+groups of free-body rows than lanes.
+
+The room for a robot row's data depends on the contact caps, the arithmetic
+does not, so a step under generous caps and one under caps that just fit the
+scenes' contacts agree bit for bit.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import scenegen as sg
+from _parity import errors, fp32_sensitivity, same_contacts
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _ms():
+    import paper_2412_13211_amd as ms
+    return ms
+
+
+def _crowded(depth, n=6, seed=3):
+    """Robots standing `depth` of the way into furniture, beside doors,
+    drawers and objects."""
+    b = sg.make(5, n, seed=seed)
+    st = sg.split_state(b.state0, n, b.n_free, b.n_aux)
+    for s in range(n):
+        box = b.static_box[b.static_off[s] + s]
+        st["q"][s, 0:2] += depth * (box[0:2] - st["q"][s, 0:2])
+        # an object against the robot's base
+        f = b.free_off[s]
+        st["free"][f, 0:2] = st["q"][s, 0:2] + 0.35
+    b.state0[:] = sg.join_state(st["q"], st["qd"], st["free"], st["aux"])
+    return b
+
+
+def _run(ms, b, ccap, rcap):
+    mb = ms.MsBatch(b, contact_cap=ccap, robot_contact_cap=rcap)
+    mb.enable_debug(True)
+    rf, bf = mb.enable_forces()
+    x = torch.as_tensor(b.state0).cuda()
+    u = torch.as_tensor(b.controls(0)).cuda()
+    out = mb.step(x, u)
+    torch.cuda.synchronize()
+    d = mb.debug_contacts()
+    return out.cpu().numpy(), rf.cpu().numpy(), bf.cpu().numpy(), d, mb.status()
+
+
+@pytest.mark.parametrize("depth", [0.0, 0.15, 0.25, 0.35])
+def test_robot_rows_independent_of_their_room(depth):
+    ms = _ms()
+    b = _crowded(depth)
+    wide = _run(ms, b, 640, 300)
+    nc, nr = int(wide[3][..., 0].max()), int(wide[3][..., 1].max())
+    print(f"[robot rows] depth {depth}: up to {nc} contacts, {nr} of the robot", flush=True)
+    assert not np.any(wide[4] & (ms.MS_ST_OVERFLOW | ms.MS_ST_ROBOT_OVERFLOW))
+    # joint-limit rows share the contact cap
+    tight = _run(ms, b, nc + 4, max(nr, 1))
+    assert not np.any(tight[4] & (ms.MS_ST_OVERFLOW | ms.MS_ST_ROBOT_OVERFLOW))
+    for a, c in zip(wide[:3], tight[:3]):
+        assert np.array_equal(a.view(np.uint32), c.view(np.uint32))
+
+
+def test_more_groups_than_lanes():
+    """58 spheres on the floor in touching rows: 58 floor groups and 54 pairs."""
+    ms = _ms()
+    rng = np.random.default_rng(5)
+    objs = []
+    for i in range(58):
+        r = 0.05
+        row, col = divmod(i, 15)
+        objs.append(sg.sphere_object(r, float(rng.uniform(0.1, 1.0)),
+                                     (col * (2 * r + 1e-3), row * 0.3, r + float(rng.uniform(-2e-4, 2e-4))),
+                                     vel=tuple(rng.normal(0, 0.05, 3)), angvel=tuple(rng.normal(0, 0.2, 3))))
+    b = sg.custom_batch([sg.empty_model()],
+                        [dict(free=objs, planes=[(0.0, 0.0, 1.0, 0.0)])], h=0.002, n_sub=4, pgs_iters=10,
+                        contact_cap=160)
+    o = oracle.Oracle(b)
+    x = b.state0.astype(np.float64)
+    u = np.zeros((1, 16))
+    mb = ms.MsBatch(b)
+    mb.enable_debug(True)
+    xg = mb.step(torch.as_tensor(b.state0).cuda(), torch.zeros((1, 16), device="cuda")).cpu().numpy()
+    xo, d = o.step(x, u, debug=True)
+    assert d["n_contacts"].min() > 64
+    assert same_contacts(d, mb.debug_contacts()).all()
+    pe, ve = errors(o, b, xo, xg.astype(np.float64))
+    ps, vs = fp32_sensitivity(o, b, x, u)
+    pf, vf = errors(o, b, xo, o.step_f32(x, u))
+    # the repository's one-step parity bars
+    assert pe.max() <= max(1e-5, 10 * ps.max(), 4 * pf.max()), pe
+    assert ve.max() <= max(1e-4, 10 * vs.max(), 4 * vf.max()), ve
