@@ -174,18 +174,19 @@ MSA_HD inline Ids unpack_ids(float f) {
   const int v = __builtin_bit_cast(int, f);
   return Ids{v & 3, (v >> 7) & 255, (v >> 2) & 7, (v >> 5) & 3, (v >> 15) & 0xffff};
 }
-// contact adjoint record: direction adjoints (n, t1, t2), contact point, W, bias
-enum { B_D = 0, B_P = 9, B_W = 12, B_BIAS = 15, CB = 16 };
+// contact adjoint record: direction adjoints (n, t1, t2), contact point, W,
+// bias.  (The wavefront kernel keeps nine lever adjoints from B_P on while it
+// reverses the sweeps of a free body's contacts.)
+enum { B_D = 0, B_P = 9, B_W = 18, B_BIAS = 21, CB = 22 };
 // free-body adjoint record
 enum { F_XB = 0, F_RB = 3, F_IIB = 12, F_IWB = 21, FB = 30 };
 // door / drawer adjoint record
 enum { X_RB = 0, X_BCB = 9, X_QB = 12, XB = 16 };
 
-// level schedule arrays (ints): level of row (then of group), groups by
-// level, level offsets, robot row of each level, first row of each group,
-// last level of each dynamic node, counters
+// sweep schedule arrays (ints): a row's nodes (then a group's level), first
+// row of each group, groups touching each dynamic node
 MSA_HD inline int lv_rows(int ccap) { return 2 * AMAX + ccap; }
-MSA_HD inline int lv_ints(int ccap) { return 5 * lv_rows(ccap) + 5 + 64 + 8; }
+MSA_HD inline int lv_ints(int ccap) { return 2 * lv_rows(ccap) + 1 + 64; }
 
 struct WS {
   int wave;  // the wavefront kernel's LDS layout
@@ -235,7 +236,7 @@ MSA_HD inline WS ws_layout(int fmax, int ntmax, int ccap, int rcap, int K, int n
   w.xR = take(AMAX * 9); w.xbc = take(AMAX * 3); w.xa = take(AMAX * 3); w.xo = take(AMAX * 3);
   w.xM = take(AMAX); w.xC = take(AMAX); w.xty = take(AMAX);
   w.tau = take(ND); w.arm = take(ND); w.L = take(ND * ND); w.z = take(ND);
-  w.rv = take(ND * 6); w.ra = take(ND * 6); w.rfl = take(ND * 6); w.rff = take(ND * 6);
+  w.rv = take(ND * 6); w.ra = take(ND * 6); w.rfl = take(wave ? 0 : ND * 6); w.rff = take(ND * 6);
   w.vR = take(ND); w.vA = take(AMAX); w.vF = take(fm * 6);
   // impulses: working storage of the lane kernel's forward sweeps (the
   // reverse sweeps read them from the tape)
@@ -265,7 +266,7 @@ MSA_HD inline WS ws_layout(int fmax, int ntmax, int ccap, int rcap, int K, int n
   w.Mb = take(ND * ND);
   w.bacc = take(ND * 9);
   w.lv = take(wave ? lv_ints(ccap) : 0);
-  w.Minv = take(wave ? ND * ND : 0);
+  w.Minv = w.L;  // the elimination runs in registers and replaces M~
   w.lz = take(wave ? ND : 0);
   w.total = o;
   return w;

@@ -33,7 +33,25 @@ void launch_step_bwd(const BwdArgs& a, hipStream_t st) {
 // ============================================================ wavefront per scene
 namespace {
 
-__device__ __forceinline__ int lane_id() { return threadIdx.x; }
+// the lane index, opaque to the optimizer: address arithmetic on it stays in
+// the phase that asks for it instead of being hoisted out of the substep loop
+// into registers that live across the whole step
+__device__ __forceinline__ int lane_id() {
+  int l = threadIdx.x;
+  asm volatile("" : "+v"(l));
+  return l;
+}
+// the same for the kernel's arguments and the LDS block
+__device__ __forceinline__ const BwdArgs& args_fresh() {
+  auto p = __builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const BwdArgs*)p;
+}
+__device__ __forceinline__ float* lds_fresh(float* L) {
+  int z = 0;
+  asm volatile("" : "+s"(z));
+  return L + z;
+}
 __device__ __forceinline__ void wsync() { __syncthreads(); }
 // Ordering of LDS accesses between the lanes of the workgroup's one
 // wavefront: the LDS executes a wavefront's instructions in issue order, so a
@@ -64,19 +82,15 @@ __device__ __forceinline__ float row_sum(float s16, int q) {
 
 // level-schedule views inside the LDS block
 struct Lv {
-  int *lvl, *order, *loff, *rob, *gfirst, *last, *cnt;
+  int *lvl, *gfirst, *last;
 };
 __device__ __forceinline__ Lv lv_view(float* L, const msa::WS& w) {
   Lv v;
   int* p = reinterpret_cast<int*>(L + w.lv);
   const int R = msa::lv_rows(w.ccap);
   v.lvl = p; p += R;
-  v.order = p; p += R;
-  v.loff = p; p += R + 2;
-  v.rob = p; p += R + 2;
   v.gfirst = p; p += R + 1;
-  v.last = p; p += 64;
-  v.cnt = p;  // [0] nc, [1] nrob, [2] nlim, [3] maxl, [4] status
+  v.last = p;
   return v;
 }
 
@@ -94,151 +108,648 @@ __device__ __forceinline__ void row_nodes(const msa::Eng& E, int r, int& na, int
   nbn = tk == 2 ? 1 + ti : (tk == 3 ? 1 + AMAX + ti : -1);
 }
 
-// Reverse of a robot contact's row updates in sweep it.  Lane j of each
-// 16-lane row carries the robot's joint j in registers (the four copies
-// equal); the target side (a free body or a door / drawer joint, none for
-// furniture and planes) is carried in registers by every lane alike, so the
-// sums over the joints are the only exchanges, and each 16-lane row forms
-// one of them: the friction part's four sums come from one reduction, the
-// normal part's two from another.  Lanes 0..15 write the joints back, lane 0
-// the target side and the contact's adjoints.
-__device__ void robot_contact_bar(msa::Eng& E, int it, int ci, float* L) {
+// ------------------------------------------------------------ Gauss-Seidel^T
+// A free body's side of a contact in registers: position, velocities, their
+// adjoints, c = I^-1 wbar kept beside wbar, inverse mass, world inverse inertia
+// (xx yy zz xy xz yz), and the adjoints of position and inverse inertia.
+struct BSide {
+  msa::V x, v, w, vb, wb, c;
+  float im, i0, i1, i2, i3, i4, i5;
+  msa::V xb;
+  float II[9];
+};
+__device__ __forceinline__ msa::V bs_iinv(const BSide& B, msa::V q) {
+  return {B.i0 * q.x + B.i3 * q.y + B.i4 * q.z, B.i3 * q.x + B.i1 * q.y + B.i5 * q.z,
+          B.i4 * q.x + B.i5 * q.y + B.i2 * q.z};
+}
+__device__ __forceinline__ void bs_consts(const msa::WS& w, const float* L, int f, BSide& B) {
+  B.x = msa::V{L[w.st + 32 + 16 * f], L[w.st + 32 + 16 * f + 1], L[w.st + 32 + 16 * f + 2]};
+  const float* I = L + w.fIi + f * 9;
+  B.i0 = I[0];
+  B.i1 = I[4];
+  B.i2 = I[8];
+  B.i3 = I[1];
+  B.i4 = I[2];
+  B.i5 = I[5];
+  B.im = L[w.fim + f];
+}
+__device__ __forceinline__ void bs_load(const msa::WS& w, const float* L, int f, BSide& B) {
+  bs_consts(w, L, f, B);
+  const float *v = L + w.vF + f * 6, *vb = L + w.vFb + f * 6;
+  B.v = msa::V{v[0], v[1], v[2]};
+  B.w = msa::V{v[3], v[4], v[5]};
+  B.vb = msa::V{vb[0], vb[1], vb[2]};
+  B.wb = msa::V{vb[3], vb[4], vb[5]};
+  B.c = bs_iinv(B, B.wb);
+  B.xb = msa::V{0.f, 0.f, 0.f};
+#pragma unroll
+  for (int t = 0; t < 9; ++t) B.II[t] = 0.f;
+}
+// velocities, their adjoints, and the accumulated position and inertia adjoints
+__device__ __forceinline__ void bs_store(const msa::WS& w, float* L, int f, const BSide& B) {
+  float *v = L + w.vF + f * 6, *vb = L + w.vFb + f * 6, *fb = L + w.fb + f * msa::FB;
+  v[0] = B.v.x; v[1] = B.v.y; v[2] = B.v.z;
+  v[3] = B.w.x; v[4] = B.w.y; v[5] = B.w.z;
+  vb[0] = B.vb.x; vb[1] = B.vb.y; vb[2] = B.vb.z;
+  vb[3] = B.wb.x; vb[4] = B.wb.y; vb[5] = B.wb.z;
+  fb[msa::F_XB] += B.xb.x;
+  fb[msa::F_XB + 1] += B.xb.y;
+  fb[msa::F_XB + 2] += B.xb.z;
+#pragma unroll
+  for (int t = 0; t < 9; ++t) fb[msa::F_IIB + t] += B.II[t];
+}
+// direction vector D, lever row ang = (p - x) x D and b = I^-1 ang of one
+// direction of a side (the target's are the negatives: see the uses)
+struct DirC {
+  msa::V D, ang, b;
+};
+__device__ __forceinline__ void dir_consts(const BSide& B, msa::V rr, msa::V D, DirC& C) {
+  C.D = D;
+  C.ang = cross(rr, D);
+  C.b = bs_iinv(B, C.ang);
+}
+__device__ __forceinline__ msa::V vmadd(msa::V a, msa::V b, float s) {
+  return {a.x + b.x * s, a.y + b.y * s, a.z + b.z * s};
+}
+__device__ __forceinline__ void outer_add(float* M, msa::V a, msa::V b) {
+  M[0] += a.x * b.x; M[1] += a.x * b.y; M[2] += a.x * b.z;
+  M[3] += a.y * b.x; M[4] += a.y * b.y; M[5] += a.y * b.z;
+  M[6] += a.z * b.x; M[7] += a.z * b.y; M[8] += a.z * b.z;
+}
+// the primitives of a side with row (sgn D, sgn ang): s folds the sign into
+// the scalar.  bs_apply: v += M^-1 J^T dl.  bs_apply_bar: its adjoint; returns
+// dlbar, adds to the direction's linear part Lb and its lever part G.
+// bs_rowvel: J . v.  bs_rowvel_bar: its adjoint for rbar.
+__device__ __forceinline__ void bs_apply(BSide& B, const DirC& C, float s) {
+  B.v = vmadd(B.v, C.D, B.im * s);
+  B.w = vmadd(B.w, C.b, s);
+}
+__device__ __forceinline__ float bs_dlb(const BSide& B, const DirC& C) {
+  return B.im * dot(C.D, B.vb) + dot(C.b, B.wb);
+}
+__device__ __forceinline__ float bs_rowvel(const BSide& B, const DirC& C) { return dot(C.D, B.v) + dot(C.ang, B.w); }
+
+// contact ci's update in one sweep as the tape has it: the impulse changes
+// (normal, tangents), the disk's scale and the quantities its adjoint needs
+struct TapeU {
+  float y0, y1, y2, d0, d1, d2, rn, sc, lim;
+  bool proj;
+};
+// y: the sweep's pre-projection values, q: the previous sweep's (0 in the first)
+__device__ __forceinline__ void tape_update(const float* y, const float* q, float mu, TapeU& T) {
+  T.y0 = y[0];
+  T.y1 = y[1];
+  T.y2 = y[2];
+  const float nl = fmaxf(y[0], 0.f), pl = fmaxf(q[0], 0.f);
+  T.lim = mu * nl;
+  const float nn = y[1] * y[1] + y[2] * y[2];
+  T.rn = __builtin_amdgcn_rsqf(fmaxf(nn, 1.17549435e-38f));
+  T.proj = nn > T.lim * T.lim;
+  T.sc = T.proj ? T.lim * T.rn : 1.f;
+  const float pm = mu * pl, pn = q[1] * q[1] + q[2] * q[2];
+  const float ps = pn > pm * pm ? pm * __builtin_amdgcn_rsqf(fmaxf(pn, 1.17549435e-38f)) : 1.f;
+  T.d0 = nl - pl;
+  T.d1 = y[1] * T.sc - q[1] * ps;
+  T.d2 = y[2] * T.sc - q[2] * ps;
+}
+// adjoint of the disk projection: (yb1, yb2) from the projected values'
+// adjoints to the unprojected ones'; returns the radius' adjoint
+__device__ __forceinline__ float disk_bar(const TapeU& T, float& yb1, float& yb2) {
+  const float u1 = T.y1 * T.rn, u2 = T.y2 * T.rn, g = u1 * yb1 + u2 * yb2;
+  const float p1 = T.sc * (yb1 - u1 * g), p2 = T.sc * (yb2 - u2 * g);
+  yb1 = T.proj ? p1 : yb1;
+  yb2 = T.proj ? p2 : yb2;
+  return T.proj && T.lim > 0.f ? g : 0.f;
+}
+
+// Reverse of one contact row's update (friction pair, then normal) between the
+// free body A and a static target or (PAIR) the free body B, everything in
+// registers but the contact's records.  The contact's adjoint record collects,
+// per direction, the linear part Lb of the direction's adjoint and the lever
+// part G (the adjoint of the lever row, owner minus target), from which
+// row_finish forms the direction and contact-point adjoints once: the levers
+// do not change over the sweeps, so an update adds 18 numbers instead of
+// forming cross products with each of its six row adjoints.
+template <bool PAIR>
+__device__ __forceinline__ void row_bar(const msa::WS& w, float* L, int ci, const float* y, const float* q, float mu,
+                                        BSide& A, BSide& B) {
   using namespace msa;
-  const int lane = lane_id(), j = lane & 15, q = lane >> 4;
-  const bool jv = j < E.nb;           // this lane holds joint j
-  const bool own = lane < 16 && jv;   // and writes it back
+  const float* e = L + w.con + ci * CR;
+  float* cb = L + w.conb + ci * CB;
+  float* lb = L + w.lamb + ci * 3;
+  const V p{e[C_P], e[C_P + 1], e[C_P + 2]};
+  const float iw0 = e[C_W], iw1 = e[C_W + 1], iw2 = e[C_W + 2], bias = e[C_BIAS];
+  float lb0 = lb[0];
+  const float lb1 = lb[1], lb2 = lb[2];
+  const V rA = p - A.x;
+  DirC N, T1, T2, NB, T1B, T2B;
+  dir_consts(A, rA, V{e[C_N], e[C_N + 1], e[C_N + 2]}, N);
+  dir_consts(A, rA, V{e[C_T1], e[C_T1 + 1], e[C_T1 + 2]}, T1);
+  dir_consts(A, rA, V{e[C_T2], e[C_T2 + 1], e[C_T2 + 2]}, T2);
+  V xAB{0.f, 0.f, 0.f};
+  if (PAIR) {
+    const V rB = p - B.x;
+    dir_consts(B, rB, N.D, NB);
+    dir_consts(B, rB, T1.D, T1B);
+    dir_consts(B, rB, T2.D, T2B);
+    xAB = A.x - B.x;
+  }
+  TapeU T;
+  tape_update(y, q, mu, T);
+  V Ld[3], G[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    Ld[d] = V{cb[3 * d], cb[3 * d + 1], cb[3 * d + 2]};
+    G[d] = V{cb[9 + 3 * d], cb[10 + 3 * d], cb[11 + 3 * d]};
+  }
+  // the target's share of a direction's adjoint from its lever adjoint gB:
+  // its lever differs from the owner's by xAB, and its position moves the
+  // contact's lever
+  auto target_bar = [&](int d, V D, V lin, V gB) {
+    Ld[d] = Ld[d] - lin - cross(gB, xAB);
+    G[d] = G[d] - gB;
+    const V xc = cross(D, gB);
+    B.xb = B.xb + xc;
+    A.xb = A.xb - xc;
+  };
+  // adjoint of the impulse application of one direction (dl its impulse change)
+  auto apply_bar = [&](int d, const DirC& C, const DirC& CB_, float dl) -> float {
+    float dlb = bs_dlb(A, C);
+    Ld[d] = vmadd(Ld[d], A.vb, A.im * dl);
+    G[d] = vmadd(G[d], A.c, dl);
+    outer_add(A.II, A.wb * dl, C.ang);
+    if (PAIR) {
+      dlb -= bs_dlb(B, CB_);
+      outer_add(B.II, B.wb * -dl, CB_.ang);
+      target_bar(d, C.D, B.vb * (B.im * dl), B.c * dl);
+    }
+    return dlb;
+  };
+  auto rowvel = [&](const DirC& C, const DirC& CB_) -> float {
+    float r = bs_rowvel(A, C);
+    if (PAIR) r -= bs_rowvel(B, CB_);
+    return r;
+  };
+  auto rowvel_bar = [&](int d, const DirC& C, const DirC& CB_, float rb) {
+    Ld[d] = vmadd(Ld[d], A.v, rb);
+    G[d] = vmadd(G[d], A.w, rb);
+    A.vb = vmadd(A.vb, C.D, rb);
+    A.wb = vmadd(A.wb, C.ang, rb);
+    A.c = vmadd(A.c, C.b, rb);
+    if (PAIR) {
+      target_bar(d, C.D, B.v * rb, B.w * rb);
+      B.vb = vmadd(B.vb, C.D, -rb);
+      B.wb = vmadd(B.wb, CB_.ang, -rb);
+      B.c = vmadd(B.c, CB_.b, -rb);
+    }
+  };
+  // friction pair
+  bs_apply(A, T2, -T.d2);
+  bs_apply(A, T1, -T.d1);
+  if (PAIR) {
+    bs_apply(B, T2B, T.d2);
+    bs_apply(B, T1B, T.d1);
+  }
+  const float d1b = apply_bar(1, T1, T1B, T.d1), d2b = apply_bar(2, T2, T2B, T.d2);
+  float yb1 = lb1 + d1b, yb2 = lb2 + d2b;
+  lb0 += mu * disk_bar(T, yb1, yb2);
+  const float r1 = rowvel(T1, T1B), r2 = rowvel(T2, T2B);
+  const float rb1 = -yb1 * iw1, rb2 = -yb2 * iw2;
+  rowvel_bar(1, T1, T1B, rb1);
+  rowvel_bar(2, T2, T2B, rb2);
+  // normal
+  bs_apply(A, N, -T.d0);
+  if (PAIR) bs_apply(B, NB, T.d0);
+  const float dlb = apply_bar(0, N, NB, T.d0);
+  const float yb = T.y0 > 0.f ? lb0 + dlb : 0.f;
+  const float r0 = rowvel(N, NB) + bias;
+  const float rb0 = -yb * iw0;
+  rowvel_bar(0, N, NB, rb0);
+  lb[0] = yb - dlb;
+  lb[1] = yb1 - d1b;
+  lb[2] = yb2 - d2b;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    cb[3 * d] = Ld[d].x; cb[3 * d + 1] = Ld[d].y; cb[3 * d + 2] = Ld[d].z;
+    cb[9 + 3 * d] = G[d].x; cb[10 + 3 * d] = G[d].y; cb[11 + 3 * d] = G[d].z;
+  }
+  // W's adjoint: yb r / W^2
+  cb[B_W] -= rb0 * r0 * iw0;
+  cb[B_W + 1] -= rb1 * r1 * iw1;
+  cb[B_W + 2] -= rb2 * r2 * iw2;
+  cb[B_BIAS] += rb0;
+}
+
+// add to a value that other lanes (SHARED) may add to in the same instruction
+template <bool SHARED>
+__device__ __forceinline__ void add_to(float* p, float v) {
+  if (SHARED) unsafeAtomicAdd(p, v);
+  else *p += v;
+}
+template <bool SHARED>
+__device__ __forceinline__ void add3_to(float* p, msa::V v) {
+  add_to<SHARED>(p, v.x);
+  add_to<SHARED>(p + 1, v.y);
+  add_to<SHARED>(p + 2, v.z);
+}
+// Rows^T and contacts^T of a contact: from its adjoint record to the adjoints
+// of its sides' geometry.  A free-body owner's are in registers (A.xb, A.II,
+// Rb); a moving target's are added to its record.  ROB: a robot contact (one
+// lane per contact, so lanes may share a target or a body; the joints' part
+// is robot_rows_bar_wave's).  The record holds row_bar's sums, or for a robot
+// contact or a door / drawer target the direction and point adjoints.
+template <bool ROB>
+__device__ __forceinline__ void row_finish(const msa::Eng& E, float* L, int ci, BSide& A, float* Rb) {
+  using namespace msa;
   const WS& w = E.w;
-  const long e = w.con + (long)ci * CR, cb = w.conb + (long)ci * CB, lb = w.lamb + ci * 3;
-  const long rr = (long)ci * 3 * ND + j;
-  const int row = E.nlim + ci;
+  const float* e = L + w.con + ci * CR;
+  const float* cb = L + w.conb + ci * CB;
+  const Ids id = unpack_ids(e[C_ID]);
+  const V p{e[C_P], e[C_P + 1], e[C_P + 2]}, n{e[C_N], e[C_N + 1], e[C_N + 2]};
+  const bool direct = ROB || id.tk == 2;
+  V db[3], pb{0.f, 0.f, 0.f};
+#pragma unroll
+  for (int d = 0; d < 3; ++d) db[d] = V{cb[3 * d], cb[3 * d + 1], cb[3 * d + 2]};
+  if (direct) pb = V{cb[B_P], cb[B_P + 1], cb[B_P + 2]};
+  auto dirv = [&](int d) -> V {
+    const int o = d == 0 ? C_N : (d == 1 ? C_T1 : C_T2);
+    return V{e[o], e[o + 1], e[o + 2]};
+  };
+  if (!ROB) {
+    const V rA = p - A.x;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      DirC C;
+      dir_consts(A, rA, dirv(d), C);
+      const float Wb = cb[B_W + d];
+      // W += D . D / m + ang . I^-1 ang
+      V G = C.b * (2.f * Wb);
+      if (!direct) G = G + V{cb[9 + 3 * d], cb[10 + 3 * d], cb[11 + 3 * d]};
+      db[d] = vmadd(db[d], C.D, 2.f * Wb * A.im) + cross(G, rA);
+      outer_add(A.II, C.ang * Wb, C.ang);
+      const V pc = cross(C.D, G);
+      pb = pb + pc;
+      A.xb = A.xb - pc;
+    }
+  }
+  BSide B;
+  V xbB{0.f, 0.f, 0.f};
+  if (id.tk == 3) {
+    bs_consts(w, L, id.ti, B);
+#pragma unroll
+    for (int t = 0; t < 9; ++t) B.II[t] = 0.f;
+    const V rB = p - B.x;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      DirC T;
+      dir_consts(B, rB, dirv(d), T);
+      const float Wb = cb[B_W + d];
+      const V g = T.b * (2.f * Wb);
+      outer_add(B.II, T.ang * Wb, T.ang);
+      db[d] = vmadd(db[d], T.D, 2.f * Wb * B.im) + cross(g, rB);
+      const V pt = cross(T.D, g);
+      pb = pb + pt;
+      xbB = xbB - pt;
+    }
+  } else if (id.tk == 2) {
+    const V a = E.v3(w.xa + id.ti * 3);
+    const V ev = p - E.v3(w.xo + id.ti * 3);
+    const bool rev = L[w.xty + id.ti] == 0.f;
+    const V col = rev ? cross(a, ev) : a;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const V D = dirv(d);
+      const float Jb = cb[B_W + d] * 2.f * dot(D, col) / L[w.xM + id.ti];  // -J's adjoint
+      db[d] = vmadd(db[d], col, Jb);
+      if (rev) pb = vmadd(pb, cross(D, a), Jb);
+    }
+  }
+  // contacts^T: p = c - r n, the basis, and the gap's geometry
+  const float r = e[C_R], phi = e[C_PHI];
+  const V c = p + n * r;
+  const float phib = cb[B_BIAS] * (phi >= 0.f ? 1.f / E.pr.h : E.pr.beta / E.pr.h);
+  float nbv[3] = {0.f, 0.f, 0.f};
+  onb_bar(n, db[1], db[2], nbv);
+  const V nb3 = db[0] + V{nbv[0], nbv[1], nbv[2]} - pb * r;
+  V cbar = pb;
+  if (id.tk == 0) {
+    const float4 pl = E.sc.Pl[id.ti];
+    cbar = cbar + V{pl.x, pl.y, pl.z} * phib;
+  } else if (id.tk == 1) {
+    const float* bx = E.sc.St + id.ti * 6;
+    V bcb{0.f, 0.f, 0.f};
+    box_phi_bar(c, V{bx[0], bx[1], bx[2]}, nullptr, V{bx[3], bx[4], bx[5]}, phib, nb3, cbar, bcb, nullptr);
+  } else if (id.tk == 2) {
+    float R[9], Tb[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    E.ld9(w.xR + id.ti * 9, R);
+    V bcb{0.f, 0.f, 0.f};
+    box_phi_bar(c, E.v3(w.xbc + id.ti * 3), R, ld3(E.sc.A[id.ti].bh), phib, nb3, cbar, bcb, Tb);
+    float* xb = L + w.xb + id.ti * XB;
+#pragma unroll
+    for (int t = 0; t < 9; ++t) add_to<ROB>(xb + X_RB + t, Tb[t]);
+    add3_to<ROB>(xb + X_BCB, bcb);
+  } else {
+    const DFree& Gf = E.sc.F[id.ti];
+    float* gb = L + w.fb + id.ti * FB;
+    if (Gf.type == 0) {
+      float R[9], Tb[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      E.ld9(w.fR + id.ti * 9, R);
+      box_phi_bar(c, B.x, R, ld3(Gf.half), phib, nb3, cbar, xbB, Tb);
+#pragma unroll
+      for (int t = 0; t < 9; ++t) add_to<ROB>(gb + F_RB + t, Tb[t]);
+    } else {
+      const V d = c - B.x;
+      const float dist = sqrtf(dot(d, d));
+      V dbv = d * 0.f;
+      if (!(dist < 1e-12f)) {
+        const V nn = d * (1.f / dist);
+        dbv = nn * phib + (nb3 - nn * dot(nn, nb3)) * (1.f / dist);
+      }
+      cbar = cbar + dbv;
+      xbB = xbB - dbv;
+    }
+    add3_to<ROB>(gb + F_XB, xbB);
+#pragma unroll
+    for (int t = 0; t < 9; ++t) add_to<ROB>(gb + F_IIB + t, B.II[t]);
+  }
+  if (ROB) {
+    // owner point: a sphere of a robot body
+    float* ac = L + w.bacc + E.sc.M->sph_body[id.oi] * 9;
+    add3_to<ROB>(ac, cbar);
+    add3_to<ROB>(ac + 3, cross(c, cbar));
+  } else {
+    // owner point: the body's centre, or a box's vertex
+    A.xb = A.xb + cbar;
+    if (id.ok == 1) {
+      const DFree& F = E.sc.F[id.oi];
+      const V loc{(id.ov & 1) ? F.half[0] : -F.half[0], (id.ov & 2) ? F.half[1] : -F.half[1],
+                  (id.ov & 4) ? F.half[2] : -F.half[2]};
+      outer_add(Rb, cbar, loc);
+    }
+  }
+}
+
+// owner body of a group of rows: A's accumulators start at zero
+__device__ __forceinline__ void finish_begin(const msa::WS& w, const float* L, int f, BSide& A, float* Rb) {
+  bs_consts(w, L, f, A);
+  A.xb = msa::V{0.f, 0.f, 0.f};
+#pragma unroll
+  for (int t = 0; t < 9; ++t) A.II[t] = Rb[t] = 0.f;
+}
+__device__ __forceinline__ void finish_end(const msa::WS& w, float* L, int f, const BSide& A, const float* Rb) {
+  float* fb = L + w.fb + f * msa::FB;
+  fb[msa::F_XB] += A.xb.x;
+  fb[msa::F_XB + 1] += A.xb.y;
+  fb[msa::F_XB + 2] += A.xb.z;
+#pragma unroll
+  for (int t = 0; t < 9; ++t) {
+    fb[msa::F_IIB + t] += A.II[t];
+    fb[msa::F_RB + t] += Rb[t];
+  }
+}
+
+// The reverse sweeps of the bodies that only static targets touch (groups of
+// level 0), then their rows^T and contacts^T: one lane per body, the body in
+// registers over all sweeps.  Every lane reads its rows' tape values straight
+// from the record, a row ahead.
+__device__ __forceinline__ void gs_alone_bar(const msa::Eng& E, float* L, const Lv& LV, int G, const float* tape,
+                                             int tsw) {
+  using namespace msa;
+  const WS& w = E.w;
+  const int K = E.pr.K;
   const float mu = E.pr.mu;
-  const Ids id = E.ids(e);
-  const bool tf = id.tk == 3, tx = id.tk == 2;
-  // robot side: joint j's velocity, its adjoint, the three rows' J and
-  // M~^-1 J entries and their adjoints
-  float vr = 0.f, vrb = 0.f, J[3] = {0.f, 0.f, 0.f}, Wr[3] = {0.f, 0.f, 0.f};
-  float Jb[3] = {0.f, 0.f, 0.f}, Wrb[3] = {0.f, 0.f, 0.f};
-  if (jv) {
-    vr = L[w.vR + j];
-    vrb = L[w.vRb + j];
+#pragma unroll 1
+  for (int g = lane_id(); g < G; g += 64) {
+    if (LV.lvl[g] != 0) continue;
+    const int r0 = LV.gfirst[g], gn = LV.gfirst[g + 1] - r0, c0 = r0 - E.nlim;
+    const int f = unpack_ids(L[w.con + c0 * CR + C_ID]).oi;
+    BSide A, B;
+    bs_load(w, L, f, A);
+    int k = gn - 1;
+    const float* ty = tape + (size_t)(K - 1) * tsw + 3 * (r0 + k);
+    float y[3], q[3];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      J[k] = L[w.rJ + rr + k * ND];
-      Wr[k] = L[w.rw + rr + k * ND];
+    for (int t = 0; t < 3; ++t) {
+      y[t] = ty[t];
+      q[t] = K > 1 ? ty[t - tsw] : 0.f;
+    }
+    const int n = K * gn;
+    int it = K - 1;
+#pragma unroll 1
+    for (int i = 0; i < n; ++i) {
+      const int ck = c0 + k;
+      // the next row: the one before it in this sweep, or the last of the sweep before
+      if (--k < 0) {
+        k = gn - 1;
+        --it;
+      }
+      float yn[3], qn[3];
+      const float* tn = tape + (size_t)(it > 0 ? it : 0) * tsw + 3 * (r0 + k);
+      const float* tq = tape + (size_t)(it > 0 ? it - 1 : 0) * tsw + 3 * (r0 + k);
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        yn[t] = tn[t];
+        qn[t] = tq[t];
+      }
+      row_bar<false>(w, L, ck, y, q, mu, A, B);
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        y[t] = yn[t];
+        q[t] = it > 0 ? qn[t] : 0.f;
+      }
+    }
+    bs_store(w, L, f, A);
+    float Rb[9];
+    finish_begin(w, L, f, A, Rb);
+#pragma unroll 1
+    for (int c = c0; c < c0 + gn; ++c) row_finish<false>(E, L, c, A, Rb);
+    finish_end(w, L, f, A, Rb);
+  }
+}
+
+// Reverse of the robot's rows of one sweep, last row first.  Lane j of each
+// 16-lane row carries the robot's joint j (velocity vr and its adjoint vrb,
+// kept in registers over all sweeps, the four copies equal), each 16-lane row
+// q forms one of the sums over the joints and keeps one of the accumulators:
+// friction part: w_1 . vbar, w_2 . vbar, J_1 . v, J_2 . v and the adjoints of
+// w_1, w_2, J_1, J_2; normal part: rows 0 and 1 for w_n and J_n.  The target
+// side (a free body or a door / drawer joint, none for furniture and planes)
+// is carried by every lane alike.
+struct RobB {
+  float J0, J1, J2, w0, w1, w2;  // this lane's joint
+  float iw0, iw1, iw2, bias, lb0, lb1, lb2;
+  float y[3], q[3];
+  msa::Ids id;
+};
+__device__ __forceinline__ void rob_bar_load(const msa::Eng& E, const float* L, int rr, const float* ty,
+                                             const float* tq, RobB& R) {
+  using namespace msa;
+  const WS& w = E.w;
+  const int j = lane_id() & 15;
+  const float* e = L + w.con + rr * CR;
+  const float* J = L + w.rJ + rr * 3 * ND + j;
+  const float* W = L + w.rw + rr * 3 * ND + j;
+  R.J0 = J[0]; R.J1 = J[ND]; R.J2 = J[2 * ND];
+  R.w0 = W[0]; R.w1 = W[ND]; R.w2 = W[2 * ND];
+  R.iw0 = e[C_W]; R.iw1 = e[C_W + 1]; R.iw2 = e[C_W + 2];
+  R.bias = e[C_BIAS];
+  const float* lb = L + w.lamb + rr * 3;
+  R.lb0 = lb[0]; R.lb1 = lb[1]; R.lb2 = lb[2];
+  const int o = 3 * (E.nlim + rr);
+#pragma unroll
+  for (int t = 0; t < 3; ++t) {
+    R.y[t] = ty[o + t];
+    R.q[t] = tq ? tq[o + t] : 0.f;
+  }
+  Ids id = unpack_ids(e[C_ID]);
+  id.tk = __builtin_amdgcn_readfirstlane(id.tk);
+  id.ti = __builtin_amdgcn_readfirstlane(id.ti);
+  R.id = id;
+}
+__device__ __forceinline__ void rob_bar(const msa::Eng& E, float* L, int rr, const RobB& R, float& vr, float& vrb) {
+  using namespace msa;
+  const WS& w = E.w;
+  const int lane = lane_id(), j = lane & 15, qq = lane >> 4;
+  const float mu = E.pr.mu;
+  TapeU T;
+  tape_update(R.y, R.q, mu, T);
+  const bool hi = (qq & 2) != 0, odd = (qq & 1) != 0;
+  // where this lane's accumulators are: rows 0..3 w_1, w_2, J_1, J_2
+  float* acc = L + (hi ? w.rJb : w.rwb) + (rr * 3 + 1 + (odd ? 1 : 0)) * ND + j;
+  float* acn = L + (odd ? w.rJb : w.rwb) + rr * 3 * ND + j;
+  const float a0 = *acc, an0 = *acn;
+  float* cb = L + w.conb + rr * CB;
+  const float Wb0 = cb[B_W], Wb1 = cb[B_W + 1], Wb2 = cb[B_W + 2], bb = cb[B_BIAS];
+  vr += -(R.w2 * T.d2) - R.w1 * T.d1;
+  const float sw = odd ? R.w2 : R.w1, sj = odd ? R.J2 : R.J1;
+  const float xf = hi ? vr : vrb;
+  const float s4 = sum16((hi ? sj : sw) * xf);
+  float d1b = row_sum(s4, 0), d2b = row_sum(s4, 1), r1 = row_sum(s4, 2), r2 = row_sum(s4, 3), dlb, r0;
+  float rb0, rb1, rb2, yb1, yb2, yb, lb0 = R.lb0;
+  // the scalars between the friction part's sums and its updates
+  auto friction = [&]() {
+    yb1 = R.lb1 + d1b;
+    yb2 = R.lb2 + d2b;
+    lb0 += mu * disk_bar(T, yb1, yb2);
+    rb1 = -yb1 * R.iw1;
+    rb2 = -yb2 * R.iw2;
+  };
+  auto joints = [&]() {
+    *acc = a0 + (hi ? (odd ? rb2 : rb1) : (odd ? T.d2 : T.d1)) * xf;
+    vrb += rb1 * R.J1 + rb2 * R.J2;
+    vr -= R.w0 * T.d0;
+    const float xn = odd ? vr : vrb;
+    const float s2 = sum16((odd ? R.J0 : R.w0) * xn);
+    dlb = row_sum(s2, 0);
+    r0 = row_sum(s2, 1);
+  };
+  auto normal = [&]() {
+    yb = T.y0 > 0.f ? lb0 + dlb : 0.f;
+    r0 += R.bias;
+    rb0 = -yb * R.iw0;
+    if (!hi) *acn = an0 + (odd ? rb0 : T.d0) * (odd ? vr : vrb);
+    vrb += rb0 * R.J0;
+  };
+  if (R.id.tk < 2) {
+    friction();
+    joints();
+    normal();
+  } else {
+    const float* e = L + w.con + rr * CR;
+    const V p{e[C_P], e[C_P + 1], e[C_P + 2]}, D0{e[C_N], e[C_N + 1], e[C_N + 2]},
+        D1{e[C_T1], e[C_T1 + 1], e[C_T1 + 2]}, D2{e[C_T2], e[C_T2 + 1], e[C_T2 + 2]};
+    if (R.id.tk == 3) {
+      // the target's rows are -(D, (p - x) x D); its share of the direction
+      // and contact-point adjoints as in row_bar, with the levers applied here
+      BSide B;
+      bs_load(w, L, R.id.ti, B);
+      const V rB = p - B.x;
+      DirC N, T1, T2;
+      dir_consts(B, rB, D0, N);
+      dir_consts(B, rB, D1, T1);
+      dir_consts(B, rB, D2, T2);
+      V Ld0{0.f, 0.f, 0.f}, Ld1 = Ld0, Ld2 = Ld0, G0 = Ld0, G1 = Ld0, G2 = Ld0;
+      bs_apply(B, T2, T.d2);
+      bs_apply(B, T1, T.d1);
+      d1b -= bs_dlb(B, T1);
+      d2b -= bs_dlb(B, T2);
+      Ld1 = vmadd(Ld1, B.vb, B.im * T.d1);
+      Ld2 = vmadd(Ld2, B.vb, B.im * T.d2);
+      G1 = vmadd(G1, B.c, T.d1);
+      G2 = vmadd(G2, B.c, T.d2);
+      outer_add(B.II, B.wb * -T.d1, T1.ang);
+      outer_add(B.II, B.wb * -T.d2, T2.ang);
+      r1 -= bs_rowvel(B, T1);
+      r2 -= bs_rowvel(B, T2);
+      friction();
+      Ld1 = vmadd(Ld1, B.v, rb1);
+      Ld2 = vmadd(Ld2, B.v, rb2);
+      G1 = vmadd(G1, B.w, rb1);
+      G2 = vmadd(G2, B.w, rb2);
+      B.vb = vmadd(vmadd(B.vb, D1, -rb1), D2, -rb2);
+      B.wb = vmadd(vmadd(B.wb, T1.ang, -rb1), T2.ang, -rb2);
+      B.c = vmadd(vmadd(B.c, T1.b, -rb1), T2.b, -rb2);
+      joints();
+      bs_apply(B, N, T.d0);
+      dlb -= bs_dlb(B, N);
+      Ld0 = vmadd(Ld0, B.vb, B.im * T.d0);
+      G0 = vmadd(G0, B.c, T.d0);
+      outer_add(B.II, B.wb * -T.d0, N.ang);
+      r0 -= bs_rowvel(B, N);
+      normal();
+      Ld0 = vmadd(Ld0, B.v, rb0);
+      G0 = vmadd(G0, B.w, rb0);
+      B.vb = vmadd(B.vb, D0, -rb0);
+      B.wb = vmadd(B.wb, N.ang, -rb0);
+      const V pb = cross(D0, G0) + cross(D1, G1) + cross(D2, G2);
+      B.xb = B.xb + pb;
+      const V e0 = Ld0 + cross(G0, rB), e1 = Ld1 + cross(G1, rB), e2 = Ld2 + cross(G2, rB);
+      if (lane == 0) {
+        bs_store(w, L, R.id.ti, B);
+        cb[0] -= e0.x; cb[1] -= e0.y; cb[2] -= e0.z;
+        cb[3] -= e1.x; cb[4] -= e1.y; cb[5] -= e1.z;
+        cb[6] -= e2.x; cb[7] -= e2.y; cb[8] -= e2.z;
+        cb[B_P] -= pb.x; cb[B_P + 1] -= pb.y; cb[B_P + 2] -= pb.z;
+      }
+    } else {
+      // a door / drawer joint: J = -(d . col), col = a x (p - o) or a
+      Eng::XSide X;
+      Eng::RowAcc Q;
+      E.xs_load(X, R.id.ti);
+      Q.p = p;
+      Q.d[0] = D0; Q.d[1] = D1; Q.d[2] = D2;
+      Q.db[0] = Q.db[1] = Q.db[2] = Q.pb = V{0.f, 0.f, 0.f};
+      Eng::xs_apply(X, Q, 2, -T.d2);
+      Eng::xs_apply(X, Q, 1, -T.d1);
+      d1b += Eng::xs_apply_bar(X, Q, 1, T.d1);
+      d2b += Eng::xs_apply_bar(X, Q, 2, T.d2);
+      r1 += Eng::xs_rowvel(X, Q, 1);
+      r2 += Eng::xs_rowvel(X, Q, 2);
+      friction();
+      Eng::xs_rowvel_bar(X, Q, 1, rb1);
+      Eng::xs_rowvel_bar(X, Q, 2, rb2);
+      joints();
+      Eng::xs_apply(X, Q, 0, -T.d0);
+      dlb += Eng::xs_apply_bar(X, Q, 0, T.d0);
+      r0 += Eng::xs_rowvel(X, Q, 0);
+      normal();
+      Eng::xs_rowvel_bar(X, Q, 0, rb0);
+      if (lane == 0) {
+        E.xs_store(X);
+        for (int k = 0; k < 3; ++k) E.a3(w.conb + rr * CB + B_D + k * 3, Q.db[k]);
+        E.a3(w.conb + rr * CB + B_P, Q.pb);
+      }
     }
   }
-  Eng::FSide B;
-  Eng::XSide X;
-  if (tf) E.fs_load(B, id.ti, -1.f);
-  if (tx) E.xs_load(X, id.ti);
-  Eng::RowAcc R;
-  R.p = E.v3(e + C_P);
-  R.d[0] = E.v3(e + C_N);
-  R.d[1] = E.v3(e + C_T1);
-  R.d[2] = E.v3(e + C_T2);
-  for (int k = 0; k < 3; ++k) R.db[k] = V{0.f, 0.f, 0.f};
-  R.pb = V{0.f, 0.f, 0.f};
-  auto t_apply = [&](int di, float dl) {
-    if (tf) Eng::fs_apply(B, R, di, dl);
-    else if (tx) Eng::xs_apply(X, R, di, dl);
-  };
-  auto t_apply_bar = [&](int di, float dl) -> float {
-    if (tf) return Eng::fs_apply_bar(B, R, di, dl);
-    if (tx) return Eng::xs_apply_bar(X, R, di, dl);
-    return 0.f;
-  };
-  auto t_rowvel = [&](int di) -> float {
-    if (tf) return Eng::fs_rowvel(B, R, di);
-    if (tx) return Eng::xs_rowvel(X, R, di);
-    return 0.f;
-  };
-  auto t_rowvel_bar = [&](int di, float rb) {
-    if (tf) Eng::fs_rowvel_bar(B, R, di, rb);
-    else if (tx) Eng::xs_rowvel_bar(X, R, di, rb);
-  };
-  const float W0 = L[e + C_W], W1 = L[e + C_W + 1], W2 = L[e + C_W + 2];
-  float lb0 = L[lb], lb1 = L[lb + 1], lb2 = L[lb + 2];
-  float Wb0 = 0.f, Wb1 = 0.f, Wb2 = 0.f, biasb = 0.f;
-  if (W1 >= 1e-12f && W2 >= 1e-12f) {
-    const float y1 = E.tape_at(it, row, 1), y2 = E.tape_at(it, row, 2);
-    const float lim = mu * E.normal_after(it, ci);
-    float o1, o2, p1, p2;
-    const bool proj = disk_proj(y1, y2, lim, o1, o2);
-    E.prev_fric(it, ci, p1, p2);
-    const float d1 = o1 - p1, d2 = o2 - p2;
-    vr += Wr[2] * (-d2);
-    vr += Wr[1] * (-d1);
-    t_apply(2, -d2);
-    t_apply(1, -d1);
-    // rows 0..3: w_1 . vbar, w_2 . vbar, J_1 . v, J_2 . v
-    const float part = !jv ? 0.f : (q == 0 ? Wr[1] * vrb : (q == 1 ? Wr[2] * vrb : (q == 2 ? J[1] * vr : J[2] * vr)));
-    const float s4 = sum16(part);
-    Wrb[1] += vrb * d1;
-    Wrb[2] += vrb * d2;
-    const float b1 = t_apply_bar(1, d1);
-    const float b2 = t_apply_bar(2, d2);
-    const float d1b = row_sum(s4, 0) + b1, d2b = row_sum(s4, 1) + b2;
-    float yb1, yb2, limb;
-    Eng::fric_bar(y1, y2, lim, proj, lb1 + d1b, lb2 + d2b, yb1, yb2, limb);
-    const float l1 = -d1b + yb1, l2 = -d2b + yb2;
-    const float r1 = row_sum(s4, 2) + t_rowvel(1);
-    const float r2 = row_sum(s4, 3) + t_rowvel(2);
-    const float rb1 = -yb1 / W1, rb2 = -yb2 / W2;
-    lb0 += mu * limb;
-    Wb1 += yb1 * r1 / (W1 * W1);
-    Wb2 += yb2 * r2 / (W2 * W2);
-    t_rowvel_bar(1, rb1);
-    t_rowvel_bar(2, rb2);
-    lb1 = l1;
-    lb2 = l2;
-    Jb[1] += rb1 * vr;
-    Jb[2] += rb2 * vr;
-    vrb += rb1 * J[1];
-    vrb += rb2 * J[2];
-  }
-  if (W0 >= 1e-12f) {
-    const float y = E.tape_at(it, row, 0);
-    const float nl = y > 0.f ? y : 0.f;
-    const float dl = nl - E.prev_normal(it, ci);
-    vr += Wr[0] * (-dl);
-    t_apply(0, -dl);
-    // rows 0..1: w_n . vbar, J_n . v
-    const float s2 = sum16(!jv ? 0.f : (q == 0 ? Wr[0] * vrb : J[0] * vr));
-    Wrb[0] += vrb * dl;
-    const float dlb = row_sum(s2, 0) + t_apply_bar(0, dl);
-    float lold, yb;
-    Eng::normal_bar(y, lb0 + dlb, dlb, lold, yb);
-    const float r = row_sum(s2, 1) + t_rowvel(0) + L[e + C_BIAS];
-    const float rb = -yb / W0;
-    Wb0 += yb * r / (W0 * W0);
-    biasb += rb;
-    t_rowvel_bar(0, rb);
-    Jb[0] += rb * vr;
-    vrb += rb * J[0];
-    lb0 = lold;
-  }
-  if (own) {
-    L[w.vR + j] = vr;
-    L[w.vRb + j] = vrb;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      L[w.rJb + rr + k * ND] += Jb[k];
-      L[w.rwb + rr + k * ND] += Wrb[k];
-    }
-  }
-  if (lane == 0) {
-    L[lb] = lb0;
-    L[lb + 1] = lb1;
-    L[lb + 2] = lb2;
-    for (int k = 0; k < 3; ++k) E.a3(cb + B_D + k * 3, R.db[k]);
-    E.a3(cb + B_P, R.pb);
-    L[cb + B_W] += Wb0;
-    L[cb + B_W + 1] += Wb1;
-    L[cb + B_W + 2] += Wb2;
-    L[cb + B_BIAS] += biasb;
-    if (tf) E.fs_store(B);
-    if (tx) E.xs_store(X);
-  }
+  // uniform values: every lane stores the same
+  float* lb = L + w.lamb + rr * 3;
+  lb[0] = yb - dlb;
+  lb[1] = yb1 - d1b;
+  lb[2] = yb2 - d2b;
+  cb[B_W] = Wb0 - rb0 * r0 * R.iw0;
+  cb[B_W + 1] = Wb1 - rb1 * r1 * R.iw1;
+  cb[B_W + 2] = Wb2 - rb2 * r2 * R.iw2;
+  cb[B_BIAS] = bb + rb0;
 }
 
 __device__ __forceinline__ void zero_lds(float* L, long off, int n) {
@@ -307,9 +818,20 @@ __device__ __forceinline__ void rows_wave(msa::Eng& E, float* L) {
     }
   }
   wsync();
+  // the sweeps read inverse effective masses (a row below 1e-12, or a friction
+  // pair with either one below, is skipped: inverse 0), except where a free
+  // body's target is a door / drawer (the engine's form)
   bool bad = false;
-  for (int ci = lane; ci < E.nc; ci += 64)
-    for (int di = 0; di < 3; ++di) bad |= !(L[w.con + (long)ci * CR + C_W + di] >= 1e-12f);
+  for (int ci = lane; ci < E.nc; ci += 64) {
+    float* e = L + w.con + ci * CR;
+    const bool ok0 = e[C_W] >= 1e-12f, ok1 = e[C_W + 1] >= 1e-12f, ok2 = e[C_W + 2] >= 1e-12f;
+    bad |= !(ok0 && ok1 && ok2);
+    const Ids id = unpack_ids(e[C_ID]);
+    if (id.ok != 0 && id.tk == 2) continue;
+    e[C_W] = ok0 ? 1.f / e[C_W] : 0.f;
+    e[C_W + 1] = ok1 && ok2 ? 1.f / e[C_W + 1] : 0.f;
+    e[C_W + 2] = ok1 && ok2 ? 1.f / e[C_W + 2] : 0.f;
+  }
   if (__ballot(bad)) E.status |= Eng::MS_DEGENERATE_BIT;
 }
 
@@ -542,7 +1064,7 @@ __device__ __forceinline__ void recompute_wave(msa::Eng& E, float* L, const floa
     }
   }
   wsync();
-  // body forces f_i = I_i a_i + v_i x* (I_i v_i) into rfl and rff
+  // body forces f_i = I_i a_i + v_i x* (I_i v_i)
   if (lane < nb) {
     const int i = lane;
     float v[6], acc[6], fl[6], hv[6], t6[6];
@@ -552,7 +1074,6 @@ __device__ __forceinline__ void recompute_wave(msa::Eng& E, float* L, const floa
     E.mul6(w.kI + i * 36, v, hv);
     Eng::crf6(v, hv, t6);
     for (int t = 0; t < 6; ++t) fl[t] += t6[t];
-    E.st6(w.rfl + i * 6, fl);
     E.st6(w.rff + i * 6, fl);
   }
   wsync();
@@ -564,8 +1085,7 @@ __device__ __forceinline__ void recompute_wave(msa::Eng& E, float* L, const floa
     }
   }
   wsync();
-  // bias torques C_i = s_i . f_i; M~ = M + diag(armature), copied to the
-  // M~^-1 buffer for the elimination
+  // bias torques C_i = s_i . f_i; M~ = M + diag(armature)
   if (lane < nb) {
     const int i = lane;
     float c = 0.f;
@@ -800,30 +1320,365 @@ __device__ __forceinline__ void kin_bar_wave(const msa::Eng& E, float* L) {
   }
 }
 
-__device__ void bwd_scene(const BwdArgs& a, int s, float* L) {
+// the adjoint engine of scene s over the LDS block, from arguments read anew
+__device__ __forceinline__ void eng_fresh(msa::Eng& E, int s, float* L0, int nc = 0, int nrob = 0, int nlim = 0) {
   using namespace msa;
-  const int lane = lane_id();
+  const BwdArgs& a = args_fresh();
   const DScene& D = a.scenes[s];
-  Eng E;
   E.sc = SceneRef{a.models + D.model, a.free + D.f0, a.statics + 6 * (size_t)D.s0, a.planes + D.p0, a.aux + D.a0,
                   D.hold, D.nf, D.ns, D.np, D.na};
   E.pr = a.pr;
   E.w = a.w;
-  E.b = Buf{L, 1};
+  E.b = Buf{lds_fresh(L0), 1};
   E.nb = E.sc.M->nb;
   E.nsph = E.sc.M->nsph;
   E.status = 0;
-  E.nc = E.nrob = E.nlim = 0;
-  E.cur_s = a.w.st;
-  const WS& w = a.w;
-  const RecLayout& RL = a.RL;
+  E.nc = nc;
+  E.nrob = nrob;
+  E.nlim = nlim;
+  E.cur_s = E.w.st;
+}
+
+// A substep's start state, end velocities and contact list from the record;
+// the contact counts
+__device__ __forceinline__ void load_substep(msa::Eng& E, float* L, const float* st0, const float* st1,
+                                             const float* cr, int& nc, int& nrob, int& nlim) {
+  using namespace msa;
+  const int lane = lane_id();
+  const WS& w = E.w;
+  const int fm = w.fmax, nf = E.sc.nf;
+  for (int i = lane; i < w.ss; i += 64) L[w.st + i] = st0[i];
+  if (lane < ND) L[w.vR + lane] = st1[ND + lane];
+  if (lane < E.sc.na) L[w.vA + lane] = st1[32 + 16 * fm + 4 * lane + 1];
+  for (int f = lane; f < nf; f += 64) {
+    const float* x = st1 + 32 + 16 * f;
+    L[w.vF + f * 6 + 0] = x[8]; L[w.vF + f * 6 + 1] = x[9]; L[w.vF + f * 6 + 2] = x[10];
+    L[w.vF + f * 6 + 3] = x[12]; L[w.vF + f * 6 + 4] = x[13]; L[w.vF + f * 6 + 5] = x[14];
+  }
+  // the substep's contacts as the forward kernel emitted them
+  const int NCf = __builtin_amdgcn_readfirstlane(__float_as_int(cr[0]));
+  const int NL = __builtin_amdgcn_readfirstlane(__float_as_int(cr[1]));
+  nrob = __builtin_amdgcn_readfirstlane(__float_as_int(cr[2]));
+  nc = NCf - NL;
+  nlim = NL;
+  for (int ci = lane; ci < nc; ci += 64) {
+    const float* c = cr + 4 + (size_t)(NL + ci) * CSTR;
+    const int info = __float_as_int(c[0]);
+    const int key = __float_as_int(c[16]);
+    const int aside = info & 0xffff;
+    const int akind = (aside >> 8) & 0xff, aidx = aside & 0xff;
+    const int osub = key & 0xff, tk = (key >> 8) & 3, ti = key >> 10;
+    int ok, oi, ov = 0;
+    float r;
+    if (akind == 1) {  // robot sphere
+      ok = 0;
+      oi = osub;
+      r = E.sc.M->sph[osub].w;
+    } else {  // free body
+      oi = aidx;
+      if (E.sc.F[aidx].type == 0) {
+        ok = 1;
+        ov = osub;
+        r = 0.f;
+      } else {
+        ok = 2;
+        r = E.sc.F[aidx].half[0];
+      }
+    }
+    const long eo = w.con + (long)ci * CR;
+    V n{c[1], c[2], c[3]}, p{c[4], c[5], c[6]};
+    L[eo + C_ID] = pack_ids(ok, oi, ov, tk, ti);
+    L[eo + C_R] = r;
+    L[eo + C_PHI] = c[14];
+    bs3(E.b, eo + C_N, n);
+    bs3(E.b, eo + C_P, p);
+  }
+  wsync();
+}
+
+// Schedule of the reverse sweeps.  As in the forward sweeps (limit rows, the
+// robot's rows, then the free bodies' rows in groups; every group with all of
+// its body's rows alone: level 0; the others by levels over the nodes they
+// share), run backwards.  Each row's nodes packed per lane; the groups' first
+// rows; how many groups touch each node (LDS atomics); one pass over the
+// groups that are not alone with the last level of node j in lane j's register
+// (read with readlane).
+struct Sched {
+  int ng, maxl;
+};
+__device__ __forceinline__ Sched build_schedule(const msa::Eng& E, float* L) {
+  using namespace msa;
+  const int lane = lane_id();
+  const Lv LV = lv_view(L, E.w);
+  const int R = E.nlim + E.nc, r0 = E.nlim + E.nrob;
+  LV.last[lane] = 0;
+  for (int r = r0 + lane; r < R; r += 64) {
+    int n1, n2;
+    row_nodes(E, r, n1, n2);
+    const Ids id = E.ids(E.w.con + (long)(r - E.nlim) * CR);
+    LV.lvl[r] = n1 | ((n2 + 1) << 8) | (id.tk < 2 ? 1 << 17 : 0);
+  }
+  lds_order();
+  int G = 0;
+  for (int base = r0; base < R; base += 64) {
+    const int r = base + lane;
+    bool st = false;
+    if (r < R) {
+      const int pk = LV.lvl[r];
+      st = true;
+      if (r > r0 && (pk >> 17) & 1) {
+        const int pp = LV.lvl[r - 1];
+        st = !(((pp >> 17) & 1) && (pp & 0xff) == (pk & 0xff));
+      }
+    }
+    const uint64_t mk = __ballot(st);
+    if (st) LV.gfirst[G + __popcll(mk & ((1ull << lane) - 1ull))] = r;
+    G += __popcll(mk);
+  }
+  if (lane == 0) LV.gfirst[G] = R;
+  lds_order();
+  // groups per node; a robot contact's target counts as touched by another
+  for (int g = lane; g < G; g += 64) {
+    const int pk = LV.lvl[LV.gfirst[g]], n2 = ((pk >> 8) & 0xff) - 1;
+    atomicAdd(&LV.last[pk & 0xff], 1);
+    if (n2 >= 0) atomicAdd(&LV.last[n2], 1);
+  }
+  for (int rr = lane; rr < E.nrob; rr += 64) {
+    const Ids id = E.ids(E.w.con + (long)rr * CR);
+    const int n2 = id.tk == 2 ? 1 + id.ti : (id.tk == 3 ? 1 + AMAX + id.ti : -1);
+    if (n2 >= 0) atomicAdd(&LV.last[n2], 2);
+  }
+  lds_order();
+  int last = 0, maxl = 0;
+  for (int base = 0; base < G; base += 64) {
+    const bool in = base + lane < G;
+    const int pkv = in ? LV.lvl[LV.gfirst[base + lane]] : 0;
+    const bool alone = in && ((pkv >> 17) & 1) && LV.last[pkv & 0xff] == 1;
+    int mine = 0;
+    uint64_t todo = __ballot(in && !alone);
+    while (todo) {
+      const int k = __ffsll((long long)todo) - 1;
+      todo &= todo - 1ull;
+      const int pk = __builtin_amdgcn_readlane(pkv, k);
+      const int n1 = pk & 0xff, n2 = ((pk >> 8) & 0xff) - 1;
+      int lv = __builtin_amdgcn_readlane(last, n1);
+      if (n2 >= 0) {
+        const int l2 = __builtin_amdgcn_readlane(last, n2);
+        lv = l2 > lv ? l2 : lv;
+      }
+      ++lv;
+      if (lane == n1 || lane == n2) last = lv;
+      if (lane == k) mine = lv;
+      maxl = lv > maxl ? lv : maxl;
+    }
+    lds_order();
+    // group g's first row is at index >= g, so the packs still to be read
+    // (groups past this chunk) are not overwritten
+    if (in) LV.lvl[base + lane] = mine;
+    lds_order();
+  }
+  return Sched{G, maxl};
+}
+
+// adjoint accumulators of a substep; integrate^T: lane per DoF, door / drawer
+// joint and free body
+__device__ __forceinline__ void integrate_wave(const msa::Eng& E, float* L) {
+  const int lane = lane_id();
+  const msa::WS& w = E.w;
+  const int fm = w.fmax;
+  zero_lds(L, w.gB, w.ss);
+  zero_lds(L, w.vRb, ND);
+  zero_lds(L, w.vAb, AMAX);
+  zero_lds(L, w.vFb, fm * 6);
+  zero_lds(L, w.limb, 2 * AMAX);
+  zero_lds(L, w.llamb, 2 * AMAX);
+  zero_lds(L, w.lamb, 3 * E.nc);
+  zero_lds(L, w.conb, E.nc * msa::CB);
+  zero_lds(L, w.rJb, E.nrob * 3 * ND);
+  zero_lds(L, w.rwb, E.nrob * 3 * ND);
+  zero_lds(L, w.fb, fm * msa::FB);
+  zero_lds(L, w.xb, AMAX * msa::XB);
+  zero_lds(L, w.bacc, ND * 9);
+  zero_lds(L, w.Mb, ND * ND);
+  wsync();
+  if (lane < ND) E.integrate_bar_dof(lane);
+  if (lane >= ND && lane < ND + AMAX) E.integrate_bar_aux(lane - ND);
+  for (int f = lane; f < E.sc.nf; f += 64) E.integrate_bar_free(w.st, f);
+  wsync();
+}
+
+// The reverse sweeps of everything that is not alone: per sweep the levels
+// last to first (one lane per group), the robot's rows last to first, the
+// joint-limit rows; the tape two sweeps at a time in an LDS ring.
+__device__ __forceinline__ void gs_linked_bar(msa::Eng& E, float* L, Sched sc, const float* tape_g, int tsw) {
+  using namespace msa;
+  const int lane = lane_id();
+  const WS& w = E.w;
+  const Lv LV = lv_view(L, w);
+  const int K = E.pr.K, NR = E.nrob, NL = E.nlim;
+  if (sc.maxl == 0 && NR == 0 && NL == 0) return;
+  E.tb = Buf{L + w.tring, 1};
+  E.tsw = w.trs;
+  E.tmask = 1;
+  const int R3 = 3 * (NL + E.nc);
+  // the tape of this substep's sweeps (sweep it in slot it & 1); the reverse
+  // sweep it reads sweeps it and it - 1
+  auto stage = [&](int it) {
+    float* dst = L + w.tring + (it & 1) * w.trs;
+    const float* src = tape_g + (size_t)it * tsw;
+    for (int i = lane; i < R3; i += 64) dst[i] = src[i];
+  };
+  // the sweep two back is loaded into registers a sweep ahead and written to
+  // its slot once that slot is free, so that no sweep waits for the record
+  constexpr int TPF = 8;  // tape floats per lane carried in registers (the rest staged directly)
+  float pf[TPF];
+  auto fetch = [&](int it) {
+    const float* src = tape_g + (size_t)it * tsw;
+#pragma unroll
+    for (int k = 0; k < TPF; ++k) {
+      const int i = lane + 64 * k;
+      pf[k] = i < R3 ? src[i] : 0.f;
+    }
+  };
+  auto put = [&](int it) {
+    float* dst = L + w.tring + (it & 1) * w.trs;
+#pragma unroll
+    for (int k = 0; k < TPF; ++k) {
+      const int i = lane + 64 * k;
+      if (i < R3) dst[i] = pf[k];
+    }
+    const float* src = tape_g + (size_t)it * tsw;
+    for (int i = lane + 64 * TPF; i < R3; i += 64) dst[i] = src[i];
+  };
+  if (K > 0) stage(K - 1);
+  if (K > 1) stage(K - 2);
+  if (K > 2) fetch(K - 3);
+  // the lane's group (of the first 64): level, first row, rows
+  const int glv = lane < sc.ng ? LV.lvl[lane] : 0;
+  const int gr0 = lane < sc.ng ? LV.gfirst[lane] : 0, ggn = lane < sc.ng ? LV.gfirst[lane + 1] - gr0 : 0;
+  float vr = L[w.vR + (lane & 15)], vrb = L[w.vRb + (lane & 15)];
+  lds_order();
+  const float mu = E.pr.mu;
+#pragma unroll 1
+  for (int it = K - 1; it >= 0; --it) {
+    if (it >= 1 && it <= K - 2) {
+      put(it - 1);
+      if (it >= 2) fetch(it - 2);
+    }
+    lds_order();
+    const float* ty = L + w.tring + (it & 1) * w.trs;
+    const float* tq = it > 0 ? L + w.tring + ((it - 1) & 1) * w.trs : nullptr;
+#pragma unroll 1
+    for (int lv = sc.maxl; lv >= 1; --lv) {
+#pragma unroll 1
+      for (int g = lane; g < sc.ng; g += 64) {
+        const bool first = g == lane;
+        if ((first ? glv : LV.lvl[g]) != lv) continue;
+        const int r0 = first ? gr0 : LV.gfirst[g], gn = first ? ggn : LV.gfirst[g + 1] - r0;
+        const Ids id = unpack_ids(L[w.con + (r0 - NL) * CR + C_ID]);
+        if (id.tk == 2) {
+          E.contact_bar(it, r0 - NL);
+          continue;
+        }
+        BSide A, B;
+        bs_load(w, L, id.oi, A);
+        auto row = [&](int r, float* y, float* q) {
+#pragma unroll
+          for (int t = 0; t < 3; ++t) {
+            y[t] = ty[3 * r + t];
+            q[t] = tq ? tq[3 * r + t] : 0.f;
+          }
+        };
+        float y[3], q[3];
+        if (id.tk == 3) {
+          bs_load(w, L, id.ti, B);
+          row(r0, y, q);
+          row_bar<true>(w, L, r0 - NL, y, q, mu, A, B);
+          bs_store(w, L, id.ti, B);
+        } else {
+#pragma unroll 1
+          for (int r = r0 + gn - 1; r >= r0; --r) {
+            row(r, y, q);
+            row_bar<false>(w, L, r - NL, y, q, mu, A, B);
+          }
+        }
+        bs_store(w, L, id.oi, A);
+      }
+      lds_order();
+    }
+    if (NR > 0) {
+      // two rows at a time, the next one's data loaded a row ahead
+      RobB R0, R1;
+      rob_bar_load(E, L, NR - 1, ty, tq, R0);
+#pragma unroll 1
+      for (int rr = NR - 1; rr >= 0; rr -= 2) {
+        rob_bar_load(E, L, rr > 0 ? rr - 1 : 0, ty, tq, R1);
+        rob_bar(E, L, rr, R0, vr, vrb);
+        lds_order();
+        if (rr == 0) break;
+        rob_bar_load(E, L, rr > 1 ? rr - 2 : 0, ty, tq, R0);
+        rob_bar(E, L, rr - 1, R1, vr, vrb);
+        lds_order();
+      }
+    }
+    // limit rows: the first row of a joint runs its second one first
+    if (lane < NL) {
+      const float x = L[w.lim + lane * 4];
+      if (lane == 0 || L[w.lim + (lane - 1) * 4] != x) {
+        int n = 1;
+        while (lane + n < NL && L[w.lim + (lane + n) * 4] == x) ++n;
+        for (int li = lane + n - 1; li >= lane; --li) E.limit_bar(it, li);
+      }
+    }
+    lds_order();
+  }
+  if (lane < ND) {
+    L[w.vR + lane] = vr;
+    L[w.vRb + lane] = vrb;
+  }
+  lds_order();
+}
+
+// rows^T and contacts^T of everything that is not alone: robot rows over the
+// lanes, then level by level (rows of a level touch disjoint bodies) the other
+// groups, one lane each
+__device__ __forceinline__ void finish_linked(msa::Eng& E, float* L, Sched sc) {
+  using namespace msa;
+  const int lane = lane_id();
+  const WS& w = E.w;
+  const Lv LV = lv_view(L, w);
+  robot_rows_bar_wave(E, L);
+  for (int rr = lane; rr < E.nrob; rr += 64) {
+    BSide A;
+    row_finish<true>(E, L, rr, A, nullptr);
+  }
+  lds_order();
+#pragma unroll 1
+  for (int lv = 1; lv <= sc.maxl; ++lv) {
+#pragma unroll 1
+    for (int g = lane; g < sc.ng; g += 64) {
+      if (LV.lvl[g] != lv) continue;
+      const int c0 = LV.gfirst[g] - E.nlim, c1 = LV.gfirst[g + 1] - E.nlim;
+      const int f = unpack_ids(L[w.con + c0 * CR + C_ID]).oi;
+      BSide A;
+      float Rb[9];
+      finish_begin(w, L, f, A, Rb);
+#pragma unroll 1
+      for (int c = c0; c < c1; ++c) row_finish<false>(E, L, c, A, Rb);
+      finish_end(w, L, f, A, Rb);
+    }
+    lds_order();
+  }
+  if (lane == 0)
+    for (int li = 0; li < E.nlim; ++li) E.rows_bar_limit(li);
+  wsync();
+}
+
+__device__ void bwd_scene(int s, float* const L0) {
+  using namespace msa;
+  const BwdArgs& a = args_fresh();
+  const RecLayout RL = a.RL;
   const float* rec = a.rec + (size_t)s * RL.total;
-  const int nf = D.nf, na = D.na, fm = w.fmax;
-  const size_t S = (size_t)a.S;
-  const size_t oq = 16 * (size_t)s, oqd = 16 * S + 16 * (size_t)s;
-  const size_t ofr = 32 * S + 16 * (size_t)D.f0, oax = 32 * S + 16 * (size_t)a.NF + 4 * (size_t)D.a0;
-  const float* u = a.u + 16 * (size_t)s;
-  Lv LV = lv_view(L, w);
   const bool prof = a.cycles != nullptr;
   unsigned long long cyc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   unsigned long long tc = prof ? clock64() : 0;
@@ -834,338 +1689,143 @@ __device__ void bwd_scene(const BwdArgs& a, int s, float* L) {
       tc = t2;
     }
   };
-
+  uint32_t status = 0;
   // adjoint of the end state
-  zero_lds(L, w.gA, w.ss);
-  zero_lds(L, w.ub, ND);
-  wsync();
-  if (lane < ND) {
-    L[w.gA + lane] = a.gxo[oq + lane];
-    L[w.gA + ND + lane] = a.gxo[oqd + lane];
-  }
-  for (int i = lane; i < nf * 16; i += 64) L[w.gA + 32 + i] = a.gxo[ofr + i];
-  if (lane < na * 4) L[w.gA + 32 + 16 * fm + lane] = a.gxo[oax + lane];
-  wsync();
-
-  for (int si = a.pr.nsub - 1; si >= 0; --si) {
-    const float* st0 = rec + (size_t)si * RL.ss;
-    const float* st1 = rec + (size_t)(si + 1) * RL.ss;
-    const float* cr = rec + RL.con + (size_t)si * RL.cstride;
-    // state at the substep start; velocities at its end (after Gauss-Seidel)
-    for (int i = lane; i < w.ss; i += 64) L[w.st + i] = st0[i];
-    if (lane < ND) L[w.vR + lane] = st1[ND + lane];
-    if (lane < na) L[w.vA + lane] = st1[32 + 16 * fm + 4 * lane + 1];
-    for (int f = lane; f < nf; f += 64) {
-      const float* x = st1 + 32 + 16 * f;
-      L[w.vF + f * 6 + 0] = x[8]; L[w.vF + f * 6 + 1] = x[9]; L[w.vF + f * 6 + 2] = x[10];
-      L[w.vF + f * 6 + 3] = x[12]; L[w.vF + f * 6 + 4] = x[13]; L[w.vF + f * 6 + 5] = x[14];
-    }
-    // the substep's contacts as the forward kernel emitted them
-    const int NCf = __float_as_int(cr[0]), NL = __float_as_int(cr[1]), NR = __float_as_int(cr[2]);
-    const int nc = NCf - NL;
-    for (int ci = lane; ci < nc; ci += 64) {
-      const float* c = cr + 4 + (size_t)(NL + ci) * CSTR;
-      const int info = __float_as_int(c[0]);
-      const int key = __float_as_int(c[16]);
-      const int aside = info & 0xffff;
-      const int akind = (aside >> 8) & 0xff, aidx = aside & 0xff;
-      const int osub = key & 0xff, tk = (key >> 8) & 3, ti = key >> 10;
-      int ok, oi, ov = 0;
-      float r;
-      if (akind == 1) {  // robot sphere
-        ok = 0;
-        oi = osub;
-        r = E.sc.M->sph[osub].w;
-      } else {  // free body
-        oi = aidx;
-        if (E.sc.F[aidx].type == 0) {
-          ok = 1;
-          ov = osub;
-          r = 0.f;
-        } else {
-          ok = 2;
-          r = E.sc.F[aidx].half[0];
-        }
-      }
-      const long eo = w.con + (long)ci * CR;
-      V n{c[1], c[2], c[3]}, p{c[4], c[5], c[6]};
-      L[eo + C_ID] = pack_ids(ok, oi, ov, tk, ti);
-      L[eo + C_R] = r;
-      L[eo + C_PHI] = c[14];
-      bs3(E.b, eo + C_N, n);
-      bs3(E.b, eo + C_P, p);
-    }
+  {
+    Eng E;
+    eng_fresh(E, s, L0);
+    float* L = E.b.p;
+    const BwdArgs& a = args_fresh();
+    const DScene& D = a.scenes[s];
+    const int lane = lane_id();
+    const WS& w = E.w;
+    const size_t S = (size_t)a.S;
+    zero_lds(L, w.gA, w.ss);
+    zero_lds(L, w.ub, ND);
     wsync();
+    if (lane < ND) {
+      L[w.gA + lane] = a.gxo[16 * (size_t)s + lane];
+      L[w.gA + ND + lane] = a.gxo[16 * S + 16 * (size_t)s + lane];
+    }
+    const float* gf = a.gxo + 32 * S + 16 * (size_t)D.f0;
+    for (int i = lane; i < D.nf * 16; i += 64) L[w.gA + 32 + i] = gf[i];
+    if (lane < D.na * 4)
+      L[w.gA + 32 + 16 * w.fmax + lane] = a.gxo[32 * S + 16 * (size_t)a.NF + 4 * (size_t)D.a0 + lane];
+    wsync();
+  }
+  const int nsub = a.pr.nsub;
+#pragma unroll 1
+  for (int si = nsub - 1; si >= 0; --si) {
+    int nc, nrob, nlim;
+    {
+      Eng E;
+      eng_fresh(E, s, L0);
+      load_substep(E, E.b.p, rec + (size_t)si * RL.ss, rec + (size_t)(si + 1) * RL.ss,
+                   rec + RL.con + (size_t)si * RL.cstride, nc, nrob, nlim);
+    }
     phase(0);
     // recompute: drive, kinematics, frames and dynamics (without the
-    // unconstrained velocities) on one lane; M~^-1 and the contact rows over
-    // the lanes; the limit rows and the level schedule on one lane
-    E.nc = nc;
-    E.nrob = NR;
-    recompute_wave(E, L, u);
+    // unconstrained velocities); M~^-1 and the contact rows over the lanes; the
+    // limit rows on one lane
+    {
+      Eng E;
+      eng_fresh(E, s, L0, nc, nrob, nlim);
+      recompute_wave(E, E.b.p, args_fresh().u + 16 * (size_t)s);
+      status |= E.status;
+    }
     phase(1);
     wsync();
-    solve_z_wave(E, L);
-    rows_wave(E, L);
-    if (lane == 0) {
-      E.build_lims();
-      if (E.nlim != NL) E.status |= MS_ST_RECORD;
-      LV.cnt[2] = E.nlim;
-      LV.cnt[4] = (int)E.status;
-    }
-    wsync();
-    // level schedule.  Rows are merged into groups first: a run of
-    // consecutive rows between one free body and static targets is one group
-    // (reversed by one lane, last row first, with the body in registers);
-    // every other row is a group of its own.  level(g) = 1 + the largest
-    // level of the earlier groups sharing a dynamic node.  Each row's nodes
-    // packed per lane; the groups' first rows; one pass over the groups with
-    // the last level of node j in lane j's register (read with readlane);
-    // then per-level counts, offsets and the order (entries: first row |
-    // rows << 16)
-    E.nlim = LV.cnt[2];
     {
-      const int R = E.nlim + E.nc;
-      for (int r = lane; r < R; r += 64) {
-        int n1, n2;
-        row_nodes(E, r, n1, n2);
-        bool robot = false, single = false;
-        if (r >= E.nlim) {
-          const Ids id = E.ids(w.con + (long)(r - E.nlim) * CR);
-          robot = id.ok == 0;
-          single = id.ok != 0 && (id.tk == 0 || id.tk == 1);
-        }
-        LV.lvl[r] = n1 | ((n2 + 1) << 8) | (robot ? 1 << 16 : 0) | (single ? 1 << 17 : 0);
+      Eng E;
+      eng_fresh(E, s, L0, nc, nrob, nlim);
+      solve_z_wave(E, E.b.p);
+      rows_wave(E, E.b.p);
+      if (lane_id() == 0) {
+        E.build_lims();
+        if (E.nlim != nlim) E.status |= MS_ST_RECORD;
       }
+      status |= E.status;
       wsync();
-      int G = 0;
-      for (int base = 0; base < R; base += 64) {
-        const int r = base + lane;
-        bool st = false;
-        if (r < R) {
-          const int pk = LV.lvl[r];
-          st = true;
-          if (r > 0 && (pk >> 17) & 1) {
-            const int pp = LV.lvl[r - 1];
-            st = !(((pp >> 17) & 1) && (pp & 0xff) == (pk & 0xff));
-          }
-        }
-        const uint64_t mk = __ballot(st);
-        if (st) LV.gfirst[G + __popcll(mk & ((1ull << lane) - 1ull))] = r;
-        G += __popcll(mk);
-      }
-      if (lane == 0) LV.gfirst[G] = R;
-      wsync();
-      int last = 0, maxl = 0;
-      for (int base = 0; base < G; base += 64) {
-        const int pkv = base + lane < G ? LV.lvl[LV.gfirst[base + lane]] : 0;
-        int mine = 0;
-        const int n = G - base < 64 ? G - base : 64;
-        for (int k = 0; k < n; ++k) {
-          const int pk = __builtin_amdgcn_readlane(pkv, k);
-          const int n1 = pk & 0xff, n2 = ((pk >> 8) & 0xff) - 1;
-          int lv = __builtin_amdgcn_readlane(last, n1);
-          if (n2 >= 0) {
-            const int l2 = __builtin_amdgcn_readlane(last, n2);
-            lv = l2 > lv ? l2 : lv;
-          }
-          ++lv;
-          if (lane == n1 || lane == n2) last = lv;
-          if (lane == k) mine = lv | (pk & (1 << 16));
-          maxl = lv > maxl ? lv : maxl;
-        }
-        wsync();
-        // group g's first row is at index >= g, so the packs still to be
-        // read (groups past this chunk) are not overwritten
-        if (base + lane < G) LV.lvl[base + lane] = mine;
-      }
-      for (int l = lane; l <= maxl + 1; l += 64) {
-        LV.loff[l] = 0;
-        LV.rob[l] = -1;
-      }
-      wsync();
-      for (int g = lane; g < G; g += 64) {
-        const int v = LV.lvl[g], lv = v & 0xffff;
-        if (v >> 16) LV.rob[lv] = LV.gfirst[g];
-        else atomicAdd(&LV.loff[lv], 1);
-      }
-      wsync();
-      if (lane == 0) {
-        int acc = 0;
-        for (int l = 1; l <= maxl; ++l) {
-          const int c = LV.loff[l];
-          LV.loff[l - 1] = acc;
-          acc += c;
-        }
-        LV.loff[maxl] = acc;
-      }
-      wsync();
-      // fill (groups of one level touch disjoint bodies, so their order
-      // within the level does not change any result): loff[l - 1] is the
-      // running write position of level l
-      for (int g = lane; g < G; g += 64) {
-        const int v = LV.lvl[g];
-        if (!(v >> 16)) {
-          const int r0 = LV.gfirst[g];
-          LV.order[atomicAdd(&LV.loff[(v & 0xffff) - 1], 1)] = r0 | ((LV.gfirst[g + 1] - r0) << 16);
-        }
-      }
-      wsync();
-      if (lane == 0) {
-        // restore the offsets
-        int acc = 0;
-        for (int l = 1; l <= maxl; ++l) {
-          const int end = LV.loff[l - 1];
-          LV.loff[l - 1] = acc;
-          acc = end;
-        }
-        LV.loff[maxl] = acc;
-        LV.cnt[0] = E.nc;
-        LV.cnt[1] = E.nrob;
-        LV.cnt[3] = maxl;
-      }
     }
-    wsync();
+    Sched sc;
+    {
+      Eng E;
+      eng_fresh(E, s, L0, nc, nrob, nlim);
+      sc = build_schedule(E, E.b.p);
+      sc.ng = __builtin_amdgcn_readfirstlane(sc.ng);
+      sc.maxl = __builtin_amdgcn_readfirstlane(sc.maxl);
+    }
     phase(2);
-    E.nc = LV.cnt[0];
-    E.nrob = LV.cnt[1];
-    E.nlim = LV.cnt[2];
-    E.status = (uint32_t)LV.cnt[4];
-    const int maxl = LV.cnt[3];
-    // the tape of this substep's sweeps: two sweeps at a time staged in an
-    // LDS ring (sweep it in slot it & 1); the reverse sweep it reads sweeps
-    // it and it - 1
-    const float* tape_g = rec + RL.tape + (size_t)si * a.pr.K * RL.tsw;
-    E.tb = Buf{L + w.tring, 1};
-    E.tsw = w.trs;
-    E.tmask = 1;
-    const int R3 = 3 * (E.nlim + E.nc);
-    auto stage = [&](int it) {
-      float* dst = L + w.tring + (it & 1) * w.trs;
-      const float* src = tape_g + (size_t)it * RL.tsw;
-      for (int i = lane; i < R3; i += 64) dst[i] = src[i];
-    };
-    // a reverse sweep reads its own tape slot and the previous sweep's; the
-    // sweep two back is loaded into registers a sweep ahead and written to
-    // its slot once that slot is free, so that no sweep waits for the record
-    constexpr int TPF = 8;  // tape floats per lane carried in registers (the rest staged directly)
-    float pf[TPF];
-    auto fetch = [&](int it) {
-      const float* src = tape_g + (size_t)it * RL.tsw;
-#pragma unroll
-      for (int k = 0; k < TPF; ++k) {
-        const int i = lane + 64 * k;
-        pf[k] = i < R3 ? src[i] : 0.f;
-      }
-    };
-    auto put = [&](int it) {
-      float* dst = L + w.tring + (it & 1) * w.trs;
-#pragma unroll
-      for (int k = 0; k < TPF; ++k) {
-        const int i = lane + 64 * k;
-        if (i < R3) dst[i] = pf[k];
-      }
-      const float* src = tape_g + (size_t)it * RL.tsw;
-      for (int i = lane + 64 * TPF; i < R3; i += 64) dst[i] = src[i];
-    };
-    if (a.pr.K > 0) stage(a.pr.K - 1);
-    if (a.pr.K > 1) stage(a.pr.K - 2);
-    if (a.pr.K > 2) fetch(a.pr.K - 3);
-    // adjoint accumulators of this substep
-    zero_lds(L, w.gB, w.ss);
-    zero_lds(L, w.vRb, ND);
-    zero_lds(L, w.vAb, AMAX);
-    zero_lds(L, w.vFb, fm * 6);
-    zero_lds(L, w.limb, 2 * AMAX);
-    zero_lds(L, w.llamb, 2 * AMAX);
-    zero_lds(L, w.lamb, 3 * E.nc);
-    zero_lds(L, w.conb, E.nc * CB);
-    zero_lds(L, w.rJb, E.nrob * 3 * ND);
-    zero_lds(L, w.rwb, E.nrob * 3 * ND);
-    zero_lds(L, w.fb, fm * FB);
-    zero_lds(L, w.xb, AMAX * XB);
-    zero_lds(L, w.bacc, ND * 9);
-    zero_lds(L, w.Mb, ND * ND);
-    wsync();
-    // integrate^T: lane per DoF, door / drawer joint and free body
-    if (lane < ND) E.integrate_bar_dof(lane);
-    if (lane >= ND && lane < ND + AMAX) E.integrate_bar_aux(lane - ND);
-    for (int f = lane; f < nf; f += 64) E.integrate_bar_free(w.st, f);
-    wsync();
+    {
+      Eng E;
+      eng_fresh(E, s, L0, nc, nrob, nlim);
+      integrate_wave(E, E.b.p);
+    }
     phase(3);
-    // Gauss-Seidel sweeps in reverse, levels in reverse
-    for (int it = a.pr.K - 1; it >= 0; --it) {
-      if (it >= 1 && it <= a.pr.K - 2) {
-        put(it - 1);
-        if (it >= 2) fetch(it - 2);
-      }
-      lds_order();
-      for (int lv = maxl; lv >= 1; --lv) {
-        const int rr = LV.rob[lv];
-        if (rr >= 0) robot_contact_bar(E, it, rr - E.nlim, L);
-        const int o0 = LV.loff[lv - 1], o1 = LV.loff[lv];
-        for (int k = o0 + lane; k < o1; k += 64) {
-          const int ge = LV.order[k], r = ge & 0xffff, gn = ge >> 16;
-          if (gn > 1) E.contact_group_bar(it, r - E.nlim, gn);
-          else if (r < E.nlim) E.limit_bar(it, r);
-          else E.contact_bar(it, r - E.nlim);
-        }
-        lds_order();
-      }
+    // Gauss-Seidel sweeps in reverse
+    const float* tape_g = rec + RL.tape + (size_t)si * a.pr.K * RL.tsw;
+    {
+      Eng E;
+      eng_fresh(E, s, L0, nc, nrob, nlim);
+      gs_alone_bar(E, E.b.p, lv_view(E.b.p, E.w), sc.ng, tape_g, RL.tsw);
+    }
+    {
+      Eng E;
+      eng_fresh(E, s, L0, nc, nrob, nlim);
+      gs_linked_bar(E, E.b.p, sc, tape_g, RL.tsw);
     }
     phase(4);
-    // rows^T: robot rows over the lanes; then level by level (rows of a
-    // level touch disjoint bodies) the other rows, the robot rows' target
-    // sides and the limit rows, one lane each
-    robot_rows_bar_wave(E, L);
-    for (int lv = 1; lv <= maxl; ++lv) {
-      const int rr = LV.rob[lv];
-      if (rr >= 0 && lane == 0) E.rows_bar_one(rr - E.nlim, false);
-      const int o0 = LV.loff[lv - 1], o1 = LV.loff[lv];
-      for (int k = o0 + lane; k < o1; k += 64) {
-        const int ge = LV.order[k], r0 = ge & 0xffff, gn = ge >> 16;
-        for (int r = r0; r < r0 + gn; ++r) {
-          if (r < E.nlim) E.rows_bar_limit(r);
-          else E.rows_bar_one(r - E.nlim, false);
-        }
-      }
-      wsync();
+    {
+      Eng E;
+      eng_fresh(E, s, L0, nc, nrob, nlim);
+      finish_linked(E, E.b.p, sc);
     }
     phase(5);
-    dynamics_bar_wave(E, L);
+    {
+      Eng E;
+      eng_fresh(E, s, L0, nc, nrob, nlim);
+      dynamics_bar_wave(E, E.b.p);
+    }
     phase(6);
-    // contacts^T level by level (rows of a level touch disjoint bodies);
     // frames^T per free body / joint; kinematics^T per joint
-    for (int lv = 1; lv <= maxl; ++lv) {
-      const int rr = LV.rob[lv];
-      if (rr >= 0 && lane == 0) E.contact_geom_bar(rr - E.nlim);
-      const int o0 = LV.loff[lv - 1], o1 = LV.loff[lv];
-      for (int k = o0 + lane; k < o1; k += 64) {
-        const int ge = LV.order[k], r0 = ge & 0xffff, gn = ge >> 16;
-        for (int r = r0; r < r0 + gn; ++r)
-          if (r >= E.nlim) E.contact_geom_bar(r - E.nlim);
-      }
+    {
+      Eng E;
+      eng_fresh(E, s, L0, nc, nrob, nlim);
+      float* L = E.b.p;
+      const WS& w = E.w;
+      const int lane = lane_id();
+      for (int f = lane; f < E.sc.nf; f += 64) E.free_frame_bar(w.st, f);
+      if (lane >= ND && lane < ND + E.sc.na) E.aux_frame_bar(lane - ND);
+      kin_bar_wave(E, L);
+      wsync();
+      for (int i = lane; i < w.ss; i += 64) L[w.gA + i] = L[w.gB + i];
       wsync();
     }
-    if (lane == 0) LV.cnt[4] = (int)E.status;
-    for (int f = lane; f < E.sc.nf; f += 64) E.free_frame_bar(w.st, f);
-    if (lane >= ND && lane < ND + E.sc.na) E.aux_frame_bar(lane - ND);
-    kin_bar_wave(E, L);
-    wsync();
-    for (int i = lane; i < w.ss; i += 64) L[w.gA + i] = L[w.gB + i];
-    wsync();
     phase(7);
   }
-  if (lane < ND) {
-    a.gxi[oq + lane] = L[w.gA + lane];
-    a.gxi[oqd + lane] = L[w.gA + ND + lane];
-    a.gu[16 * (size_t)s + lane] = L[w.ub + lane];
+  {
+    Eng E;
+    eng_fresh(E, s, L0);
+    const float* L = E.b.p;
+    const BwdArgs& a = args_fresh();
+    const DScene& D = a.scenes[s];
+    const int lane = lane_id();
+    const WS& w = E.w;
+    const size_t S = (size_t)a.S;
+    if (lane < ND) {
+      a.gxi[16 * (size_t)s + lane] = L[w.gA + lane];
+      a.gxi[16 * S + 16 * (size_t)s + lane] = L[w.gA + ND + lane];
+      a.gu[16 * (size_t)s + lane] = L[w.ub + lane];
+    }
+    float* gf = a.gxi + 32 * S + 16 * (size_t)D.f0;
+    for (int i = lane; i < D.nf * 16; i += 64) gf[i] = L[w.gA + 32 + i];
+    if (lane < D.na * 4)
+      a.gxi[32 * S + 16 * (size_t)a.NF + 4 * (size_t)D.a0 + lane] = L[w.gA + 32 + 16 * w.fmax + lane];
+    // the status bits lane 0 met
+    if (lane == 0 && status) a.status[s] |= status;
+    if (prof && lane == 0)
+      for (int k = 0; k < 8; ++k) a.cycles[(size_t)s * 8 + k] = cyc[k];
   }
-  for (int i = lane; i < nf * 16; i += 64) a.gxi[ofr + i] = L[w.gA + 32 + i];
-  if (lane < na * 4) a.gxi[oax + lane] = L[w.gA + 32 + 16 * fm + lane];
-  if (lane == 0 && LV.cnt[4]) a.status[s] |= (uint32_t)LV.cnt[4];
-  if (prof && lane == 0)
-    for (int k = 0; k < 8; ++k) a.cycles[(size_t)s * 8 + k] = cyc[k];
 }
 
 // does every substep's contact list of scene s hold at most cc contacts and
@@ -1204,7 +1864,7 @@ __device__ void bwd_checked(const BwdArgs& a, int s, float* lds) {
     if (lane_id() == 0) a.status[s] |= MS_ST_RECORD;
     return;
   }
-  bwd_scene(a, s, lds);
+  bwd_scene(s, lds);
 }
 
 __global__ __launch_bounds__(64) void k_step_bwd_wave(BwdArgs a) {
@@ -1215,7 +1875,7 @@ __global__ __launch_bounds__(64) void k_step_bwd_wave(BwdArgs a) {
   const int end = loop ? *a.n_over : a.S;
   const int step = loop ? (int)gridDim.x : a.S;
   for (int pos = (a.fit_mode == 1 ? *a.n_over : 0) + (int)blockIdx.x; pos < end; pos += step) {
-    bwd_checked(a, a.order[pos], lds);
+    bwd_checked(a, __builtin_amdgcn_readfirstlane(a.order[pos]), lds);
     wsync();
   }
 }

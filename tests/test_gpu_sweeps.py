@@ -11,6 +11,7 @@ import pytest
 
 import oracle
 import scenegen as sg
+from _grad import GRAD_TOL, compare, oracle_vjp_smooth, scene_vectors
 from _parity import errors, fp32_sensitivity, same_contacts
 
 torch = pytest.importorskip("torch")
@@ -64,9 +65,8 @@ def test_robot_rows_independent_of_their_room(depth):
         assert np.array_equal(a.view(np.uint32), c.view(np.uint32))
 
 
-def test_more_groups_than_lanes():
+def _sphere_floor(pgs_iters=10, n_sub=4):
     """58 spheres on the floor in touching rows: 58 floor groups and 54 pairs."""
-    ms = _ms()
     rng = np.random.default_rng(5)
     objs = []
     for i in range(58):
@@ -75,9 +75,13 @@ def test_more_groups_than_lanes():
         objs.append(sg.sphere_object(r, float(rng.uniform(0.1, 1.0)),
                                      (col * (2 * r + 1e-3), row * 0.3, r + float(rng.uniform(-2e-4, 2e-4))),
                                      vel=tuple(rng.normal(0, 0.05, 3)), angvel=tuple(rng.normal(0, 0.2, 3))))
-    b = sg.custom_batch([sg.empty_model()],
-                        [dict(free=objs, planes=[(0.0, 0.0, 1.0, 0.0)])], h=0.002, n_sub=4, pgs_iters=10,
-                        contact_cap=160)
+    return sg.custom_batch([sg.empty_model()], [dict(free=objs, planes=[(0.0, 0.0, 1.0, 0.0)])], h=0.002,
+                           n_sub=n_sub, pgs_iters=pgs_iters, contact_cap=160)
+
+
+def test_more_groups_than_lanes():
+    ms = _ms()
+    b = _sphere_floor()
     o = oracle.Oracle(b)
     x = b.state0.astype(np.float64)
     u = np.zeros((1, 16))
@@ -93,3 +97,49 @@ def test_more_groups_than_lanes():
     # the repository's one-step parity bars
     assert pe.max() <= max(1e-5, 10 * ps.max(), 4 * pf.max()), pe
     assert ve.max() <= max(1e-4, 10 * vs.max(), 4 * vf.max()), ve
+
+
+def _vjp(mb, b, g):
+    x = torch.as_tensor(b.state0).cuda()
+    u = torch.as_tensor(np.ascontiguousarray(b.controls(0))).cuda()
+    gx, gu = mb.step_backward(x, u, torch.as_tensor(g.astype(np.float32)).cuda())
+    torch.cuda.synchronize()
+    return gx.cpu().numpy().astype(np.float64), gu.cpu().numpy().astype(np.float64)
+
+
+def _check_gradient(ms, b, **caps):
+    """The wavefront adjoint against the oracle's, on its smooth components
+    (the repository's gradient bar), and twice the same bit for bit."""
+    o = oracle.Oracle(b)
+    x = b.state0.astype(np.float64)
+    u = np.asarray(b.controls(0), np.float64)
+    g = np.random.default_rng(2).normal(size=x.size)
+    ref, mask, scale = oracle_vjp_smooth(o, b, x, u, g)
+    mb = ms.MsBatch(b, backward=True, **caps)
+    first = _vjp(mb, b, g)
+    second = _vjp(mb, b, g)
+    assert all(np.array_equal(p, q) for p, q in zip(first, second))
+    err = compare(ref, mask, scale, scene_vectors(b, *first))
+    print(f"[gradient] {b.name}: rel err {np.array2string(err, precision=2)}, smooth "
+          f"{np.mean([m.mean() for m in mask]):.2f}", flush=True)
+    assert np.all(err <= GRAD_TOL), err
+
+
+@pytest.mark.parametrize("iters", [1, 2, 10])
+def test_gradient_more_groups_than_lanes(iters):
+    _check_gradient(_ms(), _sphere_floor(pgs_iters=iters, n_sub=2))
+
+
+@pytest.mark.parametrize("depth", [0.0, 0.1])
+def test_gradient_robot_rows(depth):
+    """Robot contacts with furniture, doors, drawers and objects."""
+    b = _crowded(depth)
+    st = sg.split_state(b.state0, b.n_scenes, b.n_free, b.n_aux)
+    rng = np.random.default_rng(4)
+    st["qd"][:, :15] = rng.normal(0.0, 0.1, st["qd"][:, :15].shape)
+    st["free"][:, 2] -= rng.uniform(0.0, 2e-4, b.n_free)
+    st["free"][:, 8:11] = rng.normal(0.0, 0.02, (b.n_free, 3))
+    st["free"][:, 12:15] = rng.normal(0.0, 0.05, (b.n_free, 3))
+    st["aux"][:, 0] += rng.uniform(1e-4, 1e-3, b.n_aux)
+    b.state0[:] = sg.join_state(st["q"], st["qd"], st["free"], st["aux"])
+    _check_gradient(_ms(), b)
