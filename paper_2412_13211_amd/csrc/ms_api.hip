@@ -143,7 +143,7 @@ size_t lds_bytes_of(const KArgs& a) { return (size_t)a.L.total * sizeof(float); 
 int persistent_grid(const ms_batch* b, size_t lds) {
   if (b->sched.grid > 0) return b->sched.grid;
   int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, step_kernel_ptr(), WAVE, lds) != hipSuccess || per_cu <= 0)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, step_kernel_ptr(), STEP_THREADS, lds) != hipSuccess || per_cu <= 0)
     per_cu = 1;
   return std::min(b->cnt.S, per_cu * b->n_cu);
 }
@@ -189,7 +189,7 @@ void set_step_order(ms_batch* b, KArgs& a, hipStream_t st, int fit_c) {
 // query, capped by the measured LDS rule of bwd_per_cu)
 int fwd_per_cu(size_t lds) {
   int n = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, step_kernel_ptr(), WAVE, lds) != hipSuccess) n = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, step_kernel_ptr(), STEP_THREADS, lds) != hipSuccess) n = 0;
   return std::min(n, (int)(size_t{163840} / (lds + 1024)));
 }
 

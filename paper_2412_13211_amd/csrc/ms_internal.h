@@ -16,6 +16,8 @@ namespace msk {
 constexpr int ND = 16;        // padded robot DoFs (one DoF per body)
 constexpr int SPH = 128;      // max robot collision spheres
 constexpr int WAVE = 64;
+constexpr int CTL_WORDS = 12;  // words the wavefronts of the forward step exchange in LDS
+constexpr int STEP_THREADS = 2 * WAVE;  // the forward step's workgroup: two wavefronts per scene
 constexpr int AMAX = 4;       // max door / drawer joints per scene
 constexpr int PMAX = 8;       // max planes per scene
 constexpr int FMAXL = 58;     // max free bodies per scene (node ids 1 + AMAX + f < 63)
@@ -74,7 +76,7 @@ struct DAux {
 // Offsets (in floats) of the regions of one scene's LDS block.
 struct LdsLayout {
   int fmax, smax, ccap, rcap, owners, ntmax;
-  int robot, sph, fr, aux, stat, plane, own, con, rows, dyn, cmask, nch, lvl, cand, frc, total;
+  int ctl, robot, sph, fr, aux, stat, plane, own, con, rows, dyn, cmask, fmask, nch, lvl, cand, frc, total;
 };
 
 __host__ __device__ inline int lds_align4(int x) { return (x + 3) & ~3; }
@@ -82,14 +84,13 @@ __host__ __device__ inline int lds_align4(int x) { return (x + 3) & ~3; }
 // Robot block (persistent over a substep): q qd tau arm u [5*16]; R[16*9]
 // p[16*3] s[16*6]; Minv[16*16].
 constexpr int ROBOT_FLOATS = 5 * ND + ND * 9 + ND * 3 + ND * 6 + ND * ND;
-// Dynamics scratch (only inside the dynamics phase, which runs before the
-// contacts are generated, so it shares the space of the contact list and the
-// robot contact rows): per body COM, mass and world inertia about the COM
+// Dynamics scratch (only inside the dynamics phase, beside which the contacts
+// are generated): per body COM, mass and world inertia about the COM
 // [16*BI_FLOATS], velocity-product accelerations and body forces [2*16*6],
-// M~ [16*16], tau - C [16].
+// tau - C [16], the per-body sums.  (M~ takes the place of its inverse.)
 constexpr int BI_FLOATS = 11;       // odd stride
 constexpr int DSUM_FLOATS = 17;     // odd stride: a_i (6), composite inertia (10) / subtree force (6), G_i (6)
-constexpr int DYN_FLOATS = ND * BI_FLOATS + 2 * ND * 6 + ND * ND + ND + ND * DSUM_FLOATS;
+constexpr int DYN_FLOATS = ND * BI_FLOATS + 2 * ND * 6 + ND + ND * DSUM_FLOATS;
 constexpr int FREE_FLOATS = 37;     // per free body (odd stride: conflict-free LDS banks)
 constexpr int FSTR = FREE_FLOATS;
 constexpr int AUX_FLOATS = 32;      // per aux joint
@@ -108,6 +109,8 @@ __host__ __device__ inline LdsLayout make_layout(int fmax, int smax, int ccap, i
   L.owners = fmax * 8;
   L.ntmax = PMAX + smax + AMAX + fmax;
   int o = 0;
+  // words the two wavefronts exchange: CTL_*
+  L.ctl = o;   o += CTL_WORDS;
   L.robot = o; o += lds_align4(ROBOT_FLOATS);
   L.sph = o;   o += nsph * 4;   // world sphere centres and radii of the robot
   L.fr = o;    o += lds_align4((fmax + 1) * FREE_FLOATS);  // + a zero record (static side)
@@ -115,24 +118,28 @@ __host__ __device__ inline LdsLayout make_layout(int fmax, int smax, int ccap, i
   L.stat = o;  o += lds_align4(L.smax * 6);
   L.plane = o; o += PMAX * 4;
   L.own = o;   o += lds_align4((L.owners + 1) / 2);        // uint16 owner table
-  L.con = o;
-  L.dyn = o;
-  L.rows = o + lds_align4(ccap * CON_FLOATS);
-  // the culling masks (per robot or free body and 64-target chunk, 64 bits)
-  // live in the robot rows' space: the contact phase fills them before the
-  // rows phase builds the rows
+  L.con = o;   o += lds_align4(ccap * CON_FLOATS);
+  // robot contact rows.  Before the rows phase builds them, the culling masks
+  // (per robot or free body and 64-target chunk, 64 bits) with the bodies'
+  // bounding spheres (4 floats each) lie there, the robot's then the free
+  // bodies', and after them, reaching into the sweep schedule, the dynamics
+  // scratch.
+  L.rows = o;
   L.nch = (L.ntmax + WAVE - 1) / WAVE;
-  L.cmask = L.rows;
-  {
-    // masks, then the robot's or the free bodies' bounding spheres (4 floats each)
-    const int rw = lds_align4(rcap * ROW_FLOATS),
-              mk = lds_align4((fmax > ND ? fmax : ND) * L.nch * 2) + (fmax > ND ? fmax : ND) * 4;
-    const int cr = lds_align4(ccap * CON_FLOATS) + (rw > mk ? rw : mk);
-    o += cr > DYN_FLOATS ? cr : DYN_FLOATS;
-  }
+  L.cmask = o;
+  L.fmask = o + lds_align4(ND * L.nch * 2) + ND * 4;
+  L.dyn = L.fmask + lds_align4(fmax * L.nch * 2) + fmax * 4;
   // sweep schedule: each group's previous groups [ccap + 2] twice, its level
   // [ccap] and first row [ccap + 1] (uint16)
-  L.lvl = o;   o += lds_align4((4 * ccap + 5 + 1) / 2);
+  const int sched = lds_align4((4 * ccap + 5 + 1) / 2);
+  {
+    int rw = lds_align4(rcap * ROW_FLOATS);
+    const int mk = L.dyn - L.rows, need = mk + DYN_FLOATS - sched;
+    rw = rw > mk ? rw : mk;
+    rw = rw > need ? rw : lds_align4(need);
+    o += rw;
+  }
+  L.lvl = o;   o += sched;
   // two uint16 candidate lists; after the contact phase the level schedule's
   // per-node group masks (64-bit, per node and 64-group chunk) and the mask
   // of the robot's nodes

@@ -1,18 +1,24 @@
 // ms_kernels.hip -- fused control-step kernel of the batched rigid-body step (gfx950).
 //
-// One 64-lane wavefront (one workgroup) advances one scene through all
-// substeps of a control step with the scene resident in LDS.  Per substep:
-//   drive -> forward kinematics (pointer jumping over the tree, lane per body)
-//   -> contact generation (lanes over (owner sphere, target) pairs in the
-//      canonical order, compacted with ballots so the list stays ordered)
-//   -> articulated-body algorithm in world coordinates (outward pass lane per
-//      body, inward pass serial, outward pass and the 16 columns of the
-//      inverse mass matrix as parallel triangular solves, one lane each)
-//   -> contact rows (lane per contact; robot rows lane per DoF and direction)
-//   -> level schedule of the canonical row order (lane per dynamic node)
-//   -> projected Gauss-Seidel: levels in order, the level's robot row with a
-//      16-lane shuffle reduction, the level's other rows one lane each
-//   -> semi-implicit Euler.
+// One workgroup of two wavefronts advances one scene through all substeps of a
+// control step with the scene resident in LDS.  The step is a few serial
+// chains that do not need each other, so wavefront 0 runs the robot's and
+// wavefront 1 the free bodies'; they meet at five barriers per substep:
+//   0: drive, robot and joint frames          1: free-body frames
+//   -- barrier --
+//   0: robot bodies against targets (bounds)  1: free bodies against targets (bounds)
+//   -- barrier --
+//   0: robot dynamics, inverse mass matrix    1: exact tests, contact list, free-body velocities
+//   -- barrier --
+//   0: contact rows                           1: sweep schedule
+//   -- barrier --
+//   0: sweeps of everything linked            1: sweeps of the bodies only static targets touch
+//   -- barrier --
+//   0: integrate robot and joints             1: integrate free bodies
+// One wavefront doing all in turn was bound by the latency of each chain, the
+// SIMDs idle two thirds of the time; LDS, not wavefront slots, limits the
+// scenes per CU, so the second wavefront is free.  A control step of 16, 1024
+// and 4096 uneven scenes: 183 -> 125, 539 -> 408 and 1019 -> 774 us.
 // The mathematics follows the textbook definitions cited in the C header; no
 // code is shared with the CPU oracle.
 #include "ms_internal.h"
@@ -103,7 +109,7 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z) {
 // in the phase that asks for it instead of being hoisted out of the scene
 // and substep loops into registers that live (or spill) across the whole step
 __device__ __forceinline__ int lane_id() {
-  int l = threadIdx.x;
+  int l = threadIdx.x & (WAVE - 1);
   asm volatile("" : "+v"(l));
   return l;
 }
@@ -145,11 +151,12 @@ __device__ __forceinline__ float lane_val(float v, int src) {
 }
 // a value equal in every lane, as a scalar
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ void wave_sync() { __syncthreads(); }
-// Ordering of LDS accesses between the lanes of the one wavefront of a
-// workgroup: the LDS executes a wavefront's instructions in issue order, so a
-// read issued after a write sees it; only the compiler must not move memory
-// accesses across (no wait for outstanding accesses, unlike the barrier).
+// both wavefronts of the workgroup
+__device__ __forceinline__ void both_sync() { __syncthreads(); }
+// Ordering of LDS accesses between the lanes of one wavefront: the LDS
+// executes a wavefront's instructions in issue order, so a read issued after a
+// write sees it; only the compiler must not move memory accesses across (no
+// wait for outstanding accesses, unlike the barrier).
 __device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
 
 // spatial 6-vectors [angular; linear] in world coordinates
@@ -172,12 +179,11 @@ struct Robot {
   float *q, *qd, *tau, *arm, *u;        // [16] each
   float *R, *p, *s;                     // [16][9], [16][3], [16][6]
   float *Minv;                          // [16][16]
-  // dynamics scratch, valid only inside the dynamics phase (it shares the
-  // LDS of the contact list and the robot contact rows, built afterwards):
-  // per body COM, mass and world inertia about the COM [16][BI_FLOATS],
-  // velocity-product accelerations and body forces [16][6] each, M~ [16][16],
-  // tau - C [16], the per-body sums of the pair-lane reductions
-  // [16][DSUM_FLOATS]
+  // dynamics scratch, valid only inside the dynamics phase: per body COM,
+  // mass and world inertia about the COM [16][BI_FLOATS], velocity-product
+  // accelerations and body forces [16][6] each, tau - C [16], the per-body
+  // sums of the pair-lane reductions [16][DSUM_FLOATS]; M~ [16][16] in the
+  // place of its inverse
   float *bI, *cc, *fo, *Mt, *rhs, *dsum;
 };
 __device__ __forceinline__ Robot robot_view(float* base, float* dyn) {
@@ -192,11 +198,11 @@ __device__ __forceinline__ Robot robot_view(float* base, float* dyn) {
   r.p = o; o += ND * 3;
   r.s = o; o += ND * 6;
   r.Minv = o; o += ND * ND;
+  r.Mt = r.Minv;
   o = dyn;
   r.bI = o; o += ND * BI_FLOATS;
   r.cc = o; o += ND * 6;
   r.fo = o; o += ND * 6;
-  r.Mt = o; o += ND * ND;
   r.rhs = o; o += ND;
   r.dsum = o; o += ND * DSUM_FLOATS;
   return r;
@@ -274,38 +280,19 @@ struct Scene {
   float gx0, gy0, gix, giy;  // furniture grid: origin and inverse cell sizes (xy)
 };
 
-__device__ __forceinline__ void load_scene(const KArgs& a, const Scene& S, float* L) {
+// robot, door / drawer joints, planes
+__device__ __forceinline__ void load_robot(const KArgs& a, const Scene& S, float* L) {
   const Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
   const int lane = lane_id();
   const LdsLayout& Y = a.L;
   if (lane < ND) {
-    const int ln = lane_id();
-    rb.q[lane] = a.x_in[(size_t)S.s * ND + ln];
-    rb.qd[lane] = a.x_in[(size_t)a.S * ND + (size_t)S.s * ND + ln];
-    rb.u[lane] = a.u[(size_t)S.s * ND + ln];
-  }
-  float* F = L + Y.fr;
-  const int fm = Y.fmax;
-  for (int f = lane; f < S.nf; f += WAVE) {
-    const float* xs = a.x_in + (size_t)a.S * 2 * ND + (size_t)(S.f0 + f) * 16;
-    float4 x0 = *reinterpret_cast<const float4*>(xs);
-    float4 x1 = *reinterpret_cast<const float4*>(xs + 4);
-    float4 x2 = *reinterpret_cast<const float4*>(xs + 8);
-    float4 x3 = *reinterpret_cast<const float4*>(xs + 12);
-    F[(f) * FSTR + F_X + 0] = x0.x; F[(f) * FSTR + F_X + 1] = x0.y; F[(f) * FSTR + F_X + 2] = x0.z;
-    F[(f) * FSTR + F_Q + 0] = x1.x; F[(f) * FSTR + F_Q + 1] = x1.y; F[(f) * FSTR + F_Q + 2] = x1.z;
-    F[(f) * FSTR + F_Q + 3] = x1.w;
-    F[(f) * FSTR + F_V + 0] = x2.x; F[(f) * FSTR + F_V + 1] = x2.y; F[(f) * FSTR + F_V + 2] = x2.z;
-    F[(f) * FSTR + F_W + 0] = x3.x; F[(f) * FSTR + F_W + 1] = x3.y; F[(f) * FSTR + F_W + 2] = x3.z;
-    DFree d = a.free[S.f0 + f];
-    F[(f) * FSTR + F_IM] = 1.f / d.mass;
-    F[(f) * FSTR + F_TYPE] = (float)d.type;
-    F[(f) * FSTR + F_H + 0] = d.half[0]; F[(f) * FSTR + F_H + 1] = d.half[1]; F[(f) * FSTR + F_H + 2] = d.half[2];
-    F[(f) * FSTR + F_IB + 0] = d.Ib[0]; F[(f) * FSTR + F_IB + 1] = d.Ib[1]; F[(f) * FSTR + F_IB + 2] = d.Ib[2];
+    rb.q[lane] = a.x_in[(size_t)S.s * ND + lane];
+    rb.qd[lane] = a.x_in[(size_t)a.S * ND + (size_t)S.s * ND + lane];
+    rb.u[lane] = a.u[(size_t)S.s * ND + lane];
   }
   // the zero record past the free bodies: the static side of a contact row
   // in the sweeps (no mass, no velocity)
-  if (lane < FREE_FLOATS) F[fm * FSTR + lane] = 0.f;
+  if (lane < FREE_FLOATS) L[Y.fr + Y.fmax * FSTR + lane] = 0.f;
   float* A = L + Y.aux;
   if (lane < S.na) {
     const float* xs = a.x_in + (size_t)a.S * 2 * ND + (size_t)a.NF * 16 + (size_t)(S.a0 + lane) * 4;
@@ -323,43 +310,81 @@ __device__ __forceinline__ void load_scene(const KArgs& a, const Scene& S, float
     A[A_TYPE * AMAX + lane] = (float)d.type;
     A[A_LIM * AMAX + lane] = (float)d.has_limit;
   }
-  if (Y.smax > 0) {
-    float* St = L + Y.stat;
-    const float* src = a.statics + (size_t)S.s0 * 6;
-    for (int i = lane_id(); i < S.ns * 6; i += WAVE) St[i] = src[i];
-  }
   float* Pl = L + Y.plane;
   if (lane < S.np) {
     float4 pl = a.planes[S.p0 + lane];
     Pl[lane * 4 + 0] = pl.x; Pl[lane * 4 + 1] = pl.y; Pl[lane * 4 + 2] = pl.z; Pl[lane * 4 + 3] = pl.w;
   }
-  // owner table of free bodies: boxes own 8 vertices, spheres 1
-  uint16_t* own = reinterpret_cast<uint16_t*>(L + Y.own);
-  if (lane == 0) {
-    int o = 0;
-    for (int f = 0; f < S.nf; ++f) {
-      int cnt = a.free[S.f0 + f].type == 0 ? 8 : 1;
-      for (int k = 0; k < cnt; ++k) own[o++] = (uint16_t)((f << 3) | k);
-    }
-  }
-  wave_sync();
+  lds_order();
 }
-
-__device__ __forceinline__ void store_scene(const KArgs& a, const Scene& S, float* L, uint32_t& status) {
-  const Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
+// free bodies with the table of their owners (boxes own 8 vertices, spheres
+// 1), furniture if staged
+__device__ __forceinline__ void load_free(const KArgs& a, const Scene& S, float* L) {
   const int lane = lane_id();
   const LdsLayout& Y = a.L;
+  float* F = L + Y.fr;
+  int cnt = 0;
+  for (int f = lane; f < S.nf; f += WAVE) {
+    const float* xs = a.x_in + (size_t)a.S * 2 * ND + (size_t)(S.f0 + f) * 16;
+    float4 x0 = *reinterpret_cast<const float4*>(xs);
+    float4 x1 = *reinterpret_cast<const float4*>(xs + 4);
+    float4 x2 = *reinterpret_cast<const float4*>(xs + 8);
+    float4 x3 = *reinterpret_cast<const float4*>(xs + 12);
+    DFree d = a.free[S.f0 + f];
+    F[(f) * FSTR + F_X + 0] = x0.x; F[(f) * FSTR + F_X + 1] = x0.y; F[(f) * FSTR + F_X + 2] = x0.z;
+    F[(f) * FSTR + F_Q + 0] = x1.x; F[(f) * FSTR + F_Q + 1] = x1.y; F[(f) * FSTR + F_Q + 2] = x1.z;
+    F[(f) * FSTR + F_Q + 3] = x1.w;
+    F[(f) * FSTR + F_V + 0] = x2.x; F[(f) * FSTR + F_V + 1] = x2.y; F[(f) * FSTR + F_V + 2] = x2.z;
+    F[(f) * FSTR + F_W + 0] = x3.x; F[(f) * FSTR + F_W + 1] = x3.y; F[(f) * FSTR + F_W + 2] = x3.z;
+    F[(f) * FSTR + F_IM] = 1.f / d.mass;
+    F[(f) * FSTR + F_TYPE] = (float)d.type;
+    F[(f) * FSTR + F_H + 0] = d.half[0]; F[(f) * FSTR + F_H + 1] = d.half[1]; F[(f) * FSTR + F_H + 2] = d.half[2];
+    F[(f) * FSTR + F_IB + 0] = d.Ib[0]; F[(f) * FSTR + F_IB + 1] = d.Ib[1]; F[(f) * FSTR + F_IB + 2] = d.Ib[2];
+    cnt = d.type == 0 ? 8 : 1;  // at most FMAXL < 64 bodies: one per lane
+  }
+  int at = cnt;
+  for (int off = 1; off < WAVE; off <<= 1) {
+    const int v = __shfl_up(at, off, WAVE);
+    if (lane >= off) at += v;
+  }
+  at -= cnt;
+  uint16_t* own = reinterpret_cast<uint16_t*>(L + Y.own);
+  for (int k = 0; k < cnt; ++k) own[at + k] = (uint16_t)((lane << 3) | k);
+  if (Y.smax > 0) {
+    float* St = L + Y.stat;
+    const float* src = a.statics + (size_t)S.s0 * 6;
+    for (int i = lane; i < S.ns * 6; i += WAVE) St[i] = src[i];
+  }
+  lds_order();
+}
+
+// the state out (none in record mode without an output buffer); true when a
+// value is not finite
+__device__ __forceinline__ bool store_robot(const KArgs& a, const Scene& S, float* L) {
+  if (!a.x_out) return false;
+  const Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
+  const int lane = lane_id();
   bool bad = false;
-  if (!a.x_out) return;  // record mode: the state goes to the record only
   if (lane < ND) {
     float q = rb.q[lane], qd = rb.qd[lane];
     bad |= !isfinite(q) || !isfinite(qd);
-    const int ln = lane_id();
-    a.x_out[(size_t)S.s * ND + ln] = q;
-    a.x_out[(size_t)a.S * ND + (size_t)S.s * ND + ln] = qd;
+    a.x_out[(size_t)S.s * ND + lane] = q;
+    a.x_out[(size_t)a.S * ND + (size_t)S.s * ND + lane] = qd;
   }
-  const float* F = L + Y.fr;
-  const int fm = Y.fmax;
+  const float* A = L + a.L.aux;
+  if (lane < S.na) {
+    float* xs = a.x_out + (size_t)a.S * 2 * ND + (size_t)a.NF * 16 + (size_t)(S.a0 + lane) * 4;
+    float q = A[A_Q * AMAX + lane], qd = A[A_QD * AMAX + lane];
+    bad |= !isfinite(q) || !isfinite(qd);
+    *reinterpret_cast<float4*>(xs) = make_float4(q, qd, 0.f, 0.f);
+  }
+  return __ballot(bad) != 0ull;
+}
+__device__ __forceinline__ bool store_free(const KArgs& a, const Scene& S, float* L) {
+  if (!a.x_out) return false;
+  const int lane = lane_id();
+  bool bad = false;
+  const float* F = L + a.L.fr;
   for (int f = lane; f < S.nf; f += WAVE) {
     float* xs = a.x_out + (size_t)a.S * 2 * ND + (size_t)(S.f0 + f) * 16;
     float4 x0 = make_float4(F[(f) * FSTR + F_X + 0], F[(f) * FSTR + F_X + 1], F[(f) * FSTR + F_X + 2], 0.f);
@@ -373,28 +398,32 @@ __device__ __forceinline__ void store_scene(const KArgs& a, const Scene& S, floa
     *reinterpret_cast<float4*>(xs + 8) = x2;
     *reinterpret_cast<float4*>(xs + 12) = x3;
   }
-  const float* A = L + Y.aux;
-  if (lane < S.na) {
-    float* xs = a.x_out + (size_t)a.S * 2 * ND + (size_t)a.NF * 16 + (size_t)(S.a0 + lane) * 4;
-    float q = A[A_Q * AMAX + lane], qd = A[A_QD * AMAX + lane];
-    bad |= !isfinite(q) || !isfinite(qd);
-    *reinterpret_cast<float4*>(xs) = make_float4(q, qd, 0.f, 0.f);
-  }
-  if (__ballot(bad)) status |= 1u;
+  return __ballot(bad) != 0ull;
 }
 
 // ---------------------------------------------------------------- record for the adjoint
-// state at a substep boundary (q, qd, free bodies, door/drawer joints)
-__device__ __forceinline__ void rec_state(const KArgs& a, const Scene& S, float* L, float* R) {
+// state at a substep boundary: q, qd and the door / drawer joints
+__device__ __forceinline__ void rec_robot(const KArgs& a, const Scene& S, float* L, float* R) {
   const Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
   const int lane = lane_id();
-  const LdsLayout& Y = a.L;
   if (lane < ND) {
     R[lane] = rb.q[lane];
     R[ND + lane] = rb.qd[lane];
   }
-  const float* F = L + Y.fr;
-  const int fm = Y.fmax;
+  const float* A = L + a.L.aux;
+  if (lane < AMAX) {
+    float* x = R + 32 + 16 * a.L.fmax + 4 * lane;
+    bool on = lane < S.na;
+    x[0] = on ? A[A_Q * AMAX + lane] : 0.f;
+    x[1] = on ? A[A_QD * AMAX + lane] : 0.f;
+    x[2] = 0.f;
+    x[3] = 0.f;
+  }
+}
+// and the free bodies
+__device__ __forceinline__ void rec_free(const KArgs& a, const Scene& S, float* L, float* R) {
+  const int lane = lane_id();
+  const float* F = L + a.L.fr;
   for (int f = lane; f < S.nf; f += WAVE) {
     float* x = R + 32 + 16 * f;
     x[0] = F[(f) * FSTR + F_X + 0]; x[1] = F[(f) * FSTR + F_X + 1]; x[2] = F[(f) * FSTR + F_X + 2]; x[3] = 0.f;
@@ -402,15 +431,6 @@ __device__ __forceinline__ void rec_state(const KArgs& a, const Scene& S, float*
     x[7] = F[(f) * FSTR + F_Q + 3];
     x[8] = F[(f) * FSTR + F_V + 0]; x[9] = F[(f) * FSTR + F_V + 1]; x[10] = F[(f) * FSTR + F_V + 2]; x[11] = 0.f;
     x[12] = F[(f) * FSTR + F_W + 0]; x[13] = F[(f) * FSTR + F_W + 1]; x[14] = F[(f) * FSTR + F_W + 2]; x[15] = 0.f;
-  }
-  const float* A = L + Y.aux;
-  if (lane < AMAX) {
-    float* x = R + 32 + 16 * fm + 4 * lane;
-    bool on = lane < S.na;
-    x[0] = on ? A[A_Q * AMAX + lane] : 0.f;
-    x[1] = on ? A[A_QD * AMAX + lane] : 0.f;
-    x[2] = 0.f;
-    x[3] = 0.f;
   }
 }
 // the substep's contact list as emitted (before the rows overwrite it)
@@ -465,8 +485,8 @@ __device__ __forceinline__ void phase_drive(const KArgs& a, const Scene& S, floa
   }
 }
 
-// world frames by pointer jumping over the tree; spheres; free and aux frames
-__device__ __forceinline__ void phase_kinematics(const KArgs& a, const Scene& S, float* L) {
+// world frames of the robot's bodies, its spheres, and the door / drawer frames
+__device__ __forceinline__ void kin_robot(const KArgs& a, const Scene& S, float* L) {
   const Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
   const int lane = lane_id();
   const DModel* M = S.M;
@@ -528,7 +548,7 @@ __device__ __forceinline__ void phase_kinematics(const KArgs& a, const Scene& S,
       s[0] = 0.f; s[1] = 0.f; s[2] = 0.f; s[3] = ax.x; s[4] = ax.y; s[5] = ax.z;
     }
   }
-  wave_sync();
+  lds_order();
   // sphere centres
   float* SW = L + a.L.sph;
   for (int k = lane; k < S.nsph; k += WAVE) {
@@ -536,23 +556,6 @@ __device__ __forceinline__ void phase_kinematics(const KArgs& a, const Scene& S,
     float4 sp = M->sph[k];
     f3 c = mv(rb.R + b * 9, mk3(sp.x, sp.y, sp.z)) + mk3(rb.p[b * 3], rb.p[b * 3 + 1], rb.p[b * 3 + 2]);
     SW[k * 4 + 0] = c.x; SW[k * 4 + 1] = c.y; SW[k * 4 + 2] = c.z; SW[k * 4 + 3] = sp.w;
-  }
-  // free bodies: rotation and world inverse inertia
-  float* F = L + a.L.fr;
-  const int fm = a.L.fmax;
-  for (int f = lane; f < S.nf; f += WAVE) {
-    float R[9];
-    quat_to_R(F[(f) * FSTR + F_Q + 0], F[(f) * FSTR + F_Q + 1], F[(f) * FSTR + F_Q + 2], F[(f) * FSTR + F_Q + 3], R);
-    float ib[3] = {1.f / F[(f) * FSTR + F_IB + 0], 1.f / F[(f) * FSTR + F_IB + 1], 1.f / F[(f) * FSTR + F_IB + 2]};
-    for (int t = 0; t < 9; ++t) F[(f) * FSTR + F_R + t] = R[t];
-    // world inverse inertia R diag(1/Ib) R^T, symmetric: xx yy zz xy xz yz
-    const int ii_r[6] = {0, 1, 2, 0, 0, 1}, ii_c[6] = {0, 1, 2, 1, 2, 2};
-#pragma unroll
-    for (int e = 0; e < 6; ++e) {
-      int i = ii_r[e], j = ii_c[e];
-      F[(f) * FSTR + F_II + e] = R[i * 3] * ib[0] * R[j * 3] + R[i * 3 + 1] * ib[1] * R[j * 3 + 1] +
-                                 R[i * 3 + 2] * ib[2] * R[j * 3 + 2];
-    }
   }
   // aux joints: moving frame and world box centre
   float* A = L + a.L.aux;
@@ -588,7 +591,28 @@ __device__ __forceinline__ void phase_kinematics(const KArgs& a, const Scene& S,
     A[A_M * AMAX + lane] = Mq;
     A[A_IM * AMAX + lane] = 1.f / Mq;
   }
-  wave_sync();
+  lds_order();
+}
+
+// free bodies: rotation and world inverse inertia
+__device__ __forceinline__ void kin_free(const KArgs& a, const Scene& S, float* L) {
+  const int lane = lane_id();
+  float* F = L + a.L.fr;
+  for (int f = lane; f < S.nf; f += WAVE) {
+    float R[9];
+    quat_to_R(F[(f) * FSTR + F_Q + 0], F[(f) * FSTR + F_Q + 1], F[(f) * FSTR + F_Q + 2], F[(f) * FSTR + F_Q + 3], R);
+    float ib[3] = {1.f / F[(f) * FSTR + F_IB + 0], 1.f / F[(f) * FSTR + F_IB + 1], 1.f / F[(f) * FSTR + F_IB + 2]};
+    for (int t = 0; t < 9; ++t) F[(f) * FSTR + F_R + t] = R[t];
+    // world inverse inertia R diag(1/Ib) R^T, symmetric: xx yy zz xy xz yz
+    const int ii_r[6] = {0, 1, 2, 0, 0, 1}, ii_c[6] = {0, 1, 2, 1, 2, 2};
+#pragma unroll
+    for (int e = 0; e < 6; ++e) {
+      int i = ii_r[e], j = ii_c[e];
+      F[(f) * FSTR + F_II + e] = R[i * 3] * ib[0] * R[j * 3] + R[i * 3 + 1] * ib[1] * R[j * 3 + 1] +
+                                 R[i * 3 + 2] * ib[2] * R[j * 3 + 2];
+    }
+  }
+  lds_order();
 }
 
 // ---------------------------------------------------------------- contacts
@@ -786,58 +810,9 @@ __device__ __forceinline__ void divmod(int i, int n, float inv, int& q, int& r) 
   if (r >= n) { ++q; r -= n; }
 }
 
-// wave-collective ordered compaction: out[] = item(i) for the i in [0, N)
-// with pred(item(i)), in increasing i
-template <class I, class P>
-__device__ __forceinline__ int compact(int N, uint16_t* out, I item, P pred) {
-  int cnt = 0;
-  for (int base = 0; base < N; base += WAVE) {
-    int i = base + lane_id();
-    int v = i < N ? item(i) : 0;
-    bool m = i < N && pred(v);
-    uint64_t mk = __ballot(m);
-    if (m) out[cnt + prefix_below(mk)] = (uint16_t)v;
-    cnt += __popcll(mk);
-  }
-  return cnt;
-}
-
 __device__ __forceinline__ float dist_point_box(f3 y, f3 e) {
   f3 d = mk3(fmaxf(fabsf(y.x) - e.x, 0.f), fmaxf(fabsf(y.y) - e.y, 0.f), fmaxf(fabsf(y.z) - e.z, 0.f));
   return sqrtf(dot(d, d));
-}
-
-// conservative test of a bounding sphere (c, R) against target t
-__device__ __forceinline__ bool sphere_near_target(const ConCtx& X, f3 c, float R, int t, float slack) {
-  const float* F = X.F;
-  const int fm = X.fm;
-  const float* A = X.A;
-  if (t < X.np) {
-    f3 pn = mk3(X.Pl[t * 4], X.Pl[t * 4 + 1], X.Pl[t * 4 + 2]);
-    return dot(pn, c) - X.Pl[t * 4 + 3] - R < slack;
-  }
-  if (t < X.np + X.ns) {
-    const float* bx = X.St + (t - X.np) * 6;
-    return dist_point_box(c - mk3(bx[0], bx[1], bx[2]), mk3(bx[3], bx[4], bx[5])) - R < slack;
-  }
-  if (t < X.np + X.ns + X.na) {
-    int x = t - X.np - X.ns;
-    float Rx[9];
-    for (int k = 0; k < 9; ++k) Rx[k] = A[(A_R + k) * AMAX + x];
-    f3 y = mtv(Rx, c - mk3(A[(A_BC + 0) * AMAX + x], A[(A_BC + 1) * AMAX + x], A[(A_BC + 2) * AMAX + x]));
-    return dist_point_box(y, mk3(A[(A_BH + 0) * AMAX + x], A[(A_BH + 1) * AMAX + x], A[(A_BH + 2) * AMAX + x])) - R <
-           slack;
-  }
-  int g = t - X.np - X.ns - X.na;
-  f3 xg = mk3(F[(g) * FSTR + F_X + 0], F[(g) * FSTR + F_X + 1], F[(g) * FSTR + F_X + 2]);
-  if (F[(g) * FSTR + F_TYPE] == 0.f) {
-    float Rg[9];
-    for (int k = 0; k < 9; ++k) Rg[k] = F[(g) * FSTR + F_R + k];
-    return dist_point_box(mtv(Rg, c - xg), mk3(F[(g) * FSTR + F_H + 0], F[(g) * FSTR + F_H + 1], F[(g) * FSTR + F_H + 2])) -
-               R < slack;
-  }
-  f3 d = c - xg;
-  return sqrtf(dot(d, d)) - R - F[(g) * FSTR + F_H + 0] < slack;
 }
 
 // conservative test of an axis-aligned box (centre bc, half extents he) against target t
@@ -1020,12 +995,8 @@ __device__ __forceinline__ void exact_grouped(const ConCtx& X, int rcap, int nbo
   }
 }
 
-__device__ __forceinline__ void phase_contacts(const KArgs& a, const Scene& S, float* L, int& NC, int& NR, int& NL, uint32_t& status,
-                                               uint64_t& keysum) {
-  const Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
-  const int lane = lane_id();
+__device__ __forceinline__ void con_ctx(const KArgs& a, const Scene& S, float* L, ConCtx& X) {
   const LdsLayout& Y = a.L;
-  ConCtx X;
   X.M = S.M;
   X.C = L + Y.con;
   X.cc = Y.ccap;
@@ -1040,10 +1011,298 @@ __device__ __forceinline__ void phase_contacts(const KArgs& a, const Scene& S, f
   X.NT = S.np + S.ns + S.na + S.nf;
   X.margin = a.margin;
   X.hash = a.debug != nullptr;
+}
+// Bounding volumes first; the exact test runs on the surviving pairs only.
+// The slack covers single-precision rounding of the bounding tests.
+//
+// The robot's part: the targets near the robot into listA, per robot body the
+// mask of those near its bounding sphere.  Returns the number of 64-target
+// chunks of listA.
+__device__ __forceinline__ int cull_robot(const KArgs& a, const Scene& S, float* L, float margin) {
+  const int lane = lane_id();
+  const LdsLayout& Y = a.L;
+  const Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
+  ConCtx X;
+  con_ctx(a, S, L, X);
+  const int NT = X.NT;
+  const float slack = margin + 1e-3f;
+  uint16_t* listA = reinterpret_cast<uint16_t*>(L + Y.cand);
+  const DModel* M = S.M;
+  // axis-aligned box around the robot's body bounding spheres
+  f3 lo = mk3(1e30f, 1e30f, 1e30f), hi = mk3(-1e30f, -1e30f, -1e30f);
+  if (lane < S.nb && M->sph_count[lane] > 0) {
+    float4 bs = M->bsph[lane];
+    f3 c = mv(rb.R + lane * 9, mk3(bs.x, bs.y, bs.z)) + body_p(rb, lane);
+    lo = mk3(c.x - bs.w, c.y - bs.w, c.z - bs.w);
+    hi = mk3(c.x + bs.w, c.y + bs.w, c.z + bs.w);
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    lo.x = fminf(lo.x, __shfl_xor(lo.x, off, WAVE)); lo.y = fminf(lo.y, __shfl_xor(lo.y, off, WAVE));
+    lo.z = fminf(lo.z, __shfl_xor(lo.z, off, WAVE)); hi.x = fmaxf(hi.x, __shfl_xor(hi.x, off, WAVE));
+    hi.y = fmaxf(hi.y, __shfl_xor(hi.y, off, WAVE)); hi.z = fmaxf(hi.z, __shfl_xor(hi.z, off, WAVE));
+  }
+  f3 bc = (lo + hi) * 0.5f, he = (hi - lo) * 0.5f;
+  // the robot's candidate targets in increasing order; the furniture
+  // boxes of four chunks are loaded together
+  int nra = 0;
+  for (int base = 0; base < NT; base += 4 * WAVE) {
+    float bx[4][6];
+    if (S.ns > 0) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int si = max(0, min(S.ns - 1, base + u * WAVE + lane - S.np));
+#pragma unroll
+        for (int e = 0; e < 6; ++e) bx[u][e] = X.St[si * 6 + e];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int t = base + u * WAVE + lane;
+      bool m = false;
+      if (t < NT) {
+        if (t >= S.np && t < S.np + S.ns)
+          m = fabsf(bc.x - bx[u][0]) < he.x + bx[u][3] + slack && fabsf(bc.y - bx[u][1]) < he.y + bx[u][4] + slack &&
+              fabsf(bc.z - bx[u][2]) < he.z + bx[u][5] + slack;
+        else
+          m = box_near_target(X, bc, he, t, slack);
+      }
+      const uint64_t mk = __ballot(m);
+      if (m) listA[nra + prefix_below(mk)] = (uint16_t)t;
+      nra += __popcll(mk);
+    }
+  }
+  // the robot bodies' bounding spheres against the robot's candidates,
+  // transposed as for the free bodies below: lanes over a chunk of the
+  // candidates, a loop over the bodies, one ballot per (body, chunk)
+  uint32_t* msk = reinterpret_cast<uint32_t*>(L + Y.cmask);
+  const int ncA = (nra + WAVE - 1) / WAVE;
+  // the bodies' bounding spheres (centre, radius; a body without spheres
+  // radius -1) where every lane reads them with one broadcast load
+  float4* rbd = reinterpret_cast<float4*>(L + Y.cmask + lds_align4(ND * Y.nch * 2));
+  if (lane < S.nb) {
+    float4 bs = M->bsph[lane];
+    const f3 c = mv(rb.R + lane * 9, mk3(bs.x, bs.y, bs.z)) + body_p(rb, lane);
+    rbd[lane] = make_float4(c.x, c.y, c.z, M->sph_count[lane] > 0 ? bs.w : -1.f);
+  }
+  lds_order();
+  for (int ch = 0; ch < ncA; ++ch) {
+    const int i = ch * WAVE + lane;
+    TBound B;
+    target_bound(X, i < nra ? (int)listA[i] : -1, B);
+#pragma unroll 4
+    for (int b = 0; b < S.nb; ++b) {
+      const float4 bd = rbd[b];
+      const bool m = bd.w >= 0.f && B.valid && bound_near(B, mk3(bd.x, bd.y, bd.z), bd.w, slack);
+      const uint64_t mk = __ballot(m);
+      if (lane == 0) {
+        msk[(b * ncA + ch) * 2] = (uint32_t)mk;
+        msk[(b * ncA + ch) * 2 + 1] = (uint32_t)(mk >> 32);
+      }
+    }
+  }
+  lds_order();
+  return ncA;
+}
+// Free bodies.  Bounding-sphere culling in two parts.  Furniture: each
+// body's lane looks up the cells of the scene's furniture grid its sphere
+// overlaps and tests only the boxes registered there.  Planes, door /
+// drawer boxes and free bodies, transposed: the lanes hold a chunk of
+// those targets' bounds, the loop runs over the bodies (their spheres by
+// broadcast loads from LDS), one ballot per body and chunk.  Both set the
+// bodies' bits in the mask table with LDS atomics; then the exact tests,
+// grouped.  The grid only skips boxes the bounding test would reject, so
+// the candidates are those of a test against every target.
+//
+// Lane f keeps body f's owner count (fmem) and first owner index (fob).
+__device__ __forceinline__ void cull_free(const KArgs& a, const Scene& S, float* L, int& fmem, int& fob) {
+  const int lane = lane_id();
+  const LdsLayout& Y = a.L;
+  ConCtx X;
+  con_ctx(a, S, L, X);
+  const int NT = X.NT;
+  const float slack = a.margin + 1e-3f;
+  const float* F = X.F;
+  uint32_t* msk = reinterpret_cast<uint32_t*>(L + Y.fmask);
+  unsigned long long* msk64 = reinterpret_cast<unsigned long long*>(msk);
+  const int nch = (NT + WAVE - 1) / WAVE;
+  // lane f: body f's bounding sphere, kind and first owner index
+  f3 fc = mk3(0.f, 0.f, 0.f);
+  float fR = 0.f;
+  int fb = 0;
+  fmem = 0;
+  if (lane < S.nf) {
+    fc = mk3(F[(lane) * FSTR + F_X + 0], F[(lane) * FSTR + F_X + 1], F[(lane) * FSTR + F_X + 2]);
+    f3 h = mk3(F[(lane) * FSTR + F_H + 0], F[(lane) * FSTR + F_H + 1], F[(lane) * FSTR + F_H + 2]);
+    fb = F[(lane) * FSTR + F_TYPE] == 0.f ? 1 : 0;
+    fR = fb ? sqrtf(dot(h, h)) : h.x;
+    fmem = fb ? 8 : 1;
+  }
+  fob = fmem;  // inclusive scan of the owners per body
+  for (int off = 1; off < WAVE; off <<= 1) {
+    const int v = __shfl_up(fob, off, WAVE);
+    if (lane >= off) fob += v;
+  }
+  fob += S.nsph - fmem;
+  // the bodies' spheres (centre, radius; the radius negative for a free
+  // sphere) where every lane reads them with one broadcast load
+  float4* fbd = reinterpret_cast<float4*>(L + Y.fmask + lds_align4(Y.fmax * Y.nch * 2));
+  if (lane < S.nf) fbd[lane] = make_float4(fc.x, fc.y, fc.z, fb ? fR : -fR);
+  for (int e = lane; e < S.nf * nch; e += WAVE) msk64[e] = 0ull;
+  lds_order();
+  // furniture, by the grid (lane per body): the words of every cell the
+  // sphere overlaps are loaded together, then the candidates' boxes four
+  // at a time
+  if (lane < S.nf && S.ns > 0) {
+    const int nw = a.sg_nw, nws = (S.ns + WAVE - 1) / WAVE;
+    const unsigned long long* cells =
+        reinterpret_cast<const unsigned long long*>(a.sgrid + (size_t)sgrid_floats(nw) * S.s + 4);
+    const float reach = fR + slack + 2e-3f;
+    const int x0 = max(0, min(SGRID - 1, (int)floorf((fc.x - reach - S.gx0) * S.gix)));
+    const int x1 = max(0, min(SGRID - 1, (int)floorf((fc.x + reach - S.gx0) * S.gix)));
+    const int y0 = max(0, min(SGRID - 1, (int)floorf((fc.y - reach - S.gy0) * S.giy)));
+    const int y1 = max(0, min(SGRID - 1, (int)floorf((fc.y + reach - S.gy0) * S.giy)));
+    const int ncell = (x1 - x0 + 1) * (y1 - y0 + 1);
+    for (int wg = 0; wg < nws; wg += 4) {
+      unsigned long long cw[4] = {0ull, 0ull, 0ull, 0ull};
+      int cx = x0, cy = y0;
+      for (int k0 = 0; k0 < ncell; k0 += 4) {
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+          const bool kv = k0 + kk < ncell;
+          const unsigned long long* c = cells + (min(cy, y1) * SGRID + cx) * nw;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const unsigned long long v = c[min(wg + u, nw - 1)];
+            cw[u] |= (kv && wg + u < nws) ? v : 0ull;
+          }
+          if (++cx > x1) {
+            cx = x0;
+            ++cy;
+          }
+        }
+      }
+      // the candidates in increasing order, taken from the words in turn
+      unsigned long long cur = cw[0], n1 = cw[1], n2 = cw[2], n3 = cw[3];
+      int wb = wg * 64;
+      auto refill = [&]() {
+        while (cur == 0ull && (n1 | n2 | n3) != 0ull) {
+          cur = n1;
+          n1 = n2;
+          n2 = n3;
+          n3 = 0ull;
+          wb += 64;
+        }
+      };
+      refill();
+      while (cur) {
+        int bi[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          refill();
+          bi[u] = cur ? wb + __ffsll((long long)cur) - 1 : -1;
+          cur &= cur - 1ull;
+        }
+        float bx[4][6];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const float* src = X.St + (bi[u] >= 0 ? bi[u] : bi[0]) * 6;
+#pragma unroll
+          for (int e = 0; e < 6; ++e) bx[u][e] = src[e];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          TBound B;
+          B.valid = true;
+          B.isplane = false;
+          B.ctr = mk3(bx[u][0], bx[u][1], bx[u][2]);
+          B.half = mk3(bx[u][3], bx[u][4], bx[u][5]);
+          B.rt = 0.f;
+          B.pd = 0.f;
+          B.g = -1;
+          B.gbox = 0;
+          if (bi[u] >= 0 && bound_near(B, fc, fR, slack)) {
+            const int t = S.np + bi[u];
+            atomicOr(msk64 + lane * nch + (t >> 6), 1ull << (t & 63));
+          }
+        }
+        refill();
+      }
+    }
+  }
+  // planes, door / drawer boxes and free bodies (transposed).  With at
+  // most 32 such targets both halves of the wave hold them, and each
+  // ballot serves two bodies (the lower half's and the upper half's).
+  const int NO = S.np + S.na + S.nf;
+  if (NO <= WAVE / 2) {
+    const int hh = lane >> 5, l = lane & 31;
+    const int t = l < S.np ? l : S.ns + l;  // the target index of other-target l
+    TBound B;
+    target_bound(X, l < NO ? t : -1, B);
+    uint64_t mym = 0;  // lane f: body f's bits over the other targets
+#pragma unroll 2
+    for (int f0 = 0; f0 < S.nf; f0 += 2) {
+      const int f = f0 + hh;
+      const float4 bd = fbd[f < S.nf ? f : S.nf - 1];
+      const bool fbox = bd.w >= 0.f;
+      bool m = f < S.nf && B.valid && bound_near(B, mk3(bd.x, bd.y, bd.z), fabsf(bd.w), slack);
+      if (B.g >= 0 && (B.g == f || (!B.gbox && (fbox || B.g <= f)))) m = false;
+      const uint64_t mk = __ballot(m);
+      mym = lane == f0 ? (mk & 0xffffffffull) : (lane == f0 + 1 ? (mk >> 32) : mym);
+    }
+    if (lane < S.nf)
+      while (mym) {
+        const int bit = __ffsll((long long)mym) - 1;
+        mym &= mym - 1ull;
+        const int tt = bit < S.np ? bit : S.ns + bit;
+        atomicOr(msk64 + lane * nch + (tt >> 6), 1ull << (tt & 63));
+      }
+  }
+  for (int base = 0; NO > WAVE / 2 && base < NO; base += WAVE) {
+    const int l = base + lane;
+    const int t = l < S.np ? l : S.ns + l;  // the target index of other-target l
+    TBound B;
+    target_bound(X, l < NO ? t : -1, B);
+    uint64_t mym = 0;  // lane f: body f's bits over this chunk of other targets
+#pragma unroll 2
+    for (int f = 0; f < S.nf; ++f) {
+      const float4 bd = fbd[f];
+      const bool fbox = bd.w >= 0.f;
+      bool m = B.valid && bound_near(B, mk3(bd.x, bd.y, bd.z), fabsf(bd.w), slack);
+      // pair rules of free-body targets: not itself; box vertices skip
+      // free spheres; sphere pairs once
+      if (B.g >= 0 && (B.g == f || (!B.gbox && (fbox || B.g <= f)))) m = false;
+      const uint64_t mk = __ballot(m);
+      mym = lane == f ? mk : mym;
+    }
+    if (lane < S.nf)
+      while (mym) {
+        const int bit = __ffsll((long long)mym) - 1;
+        mym &= mym - 1ull;
+        const int lo = base + bit;
+        const int tt = lo < S.np ? lo : S.ns + lo;
+        atomicOr(msk64 + lane * nch + (tt >> 6), 1ull << (tt & 63));
+      }
+  }
+  lds_order();
+}
+
+struct Contacts {
+  int nc, nr, nl;
+  uint32_t status;
+  uint64_t keysum;
+};
+// The contact list: joint-limit rows, then the exact tests of the robot's and
+// the free bodies' candidates in canonical order (ncA: chunks of the robot's
+// candidate list).
+__device__ __forceinline__ void emit_contacts(const KArgs& a, const Scene& S, float* L, int ncA, int fmem, int fob,
+                                              Contacts& out) {
+  const int lane = lane_id();
+  const LdsLayout& Y = a.L;
+  ConCtx X;
+  con_ctx(a, S, L, X);
   float* C = X.C;
   const int cc = X.cc;
   const float* Ax = X.A;
-
   int n = 0;
   // joint-limit rows of door / drawer joints come first in the canonical order
   if (lane == 0) {
@@ -1061,7 +1320,7 @@ __device__ __forceinline__ void phase_contacts(const KArgs& a, const Scene& S, f
     }
   }
   n = bcasti(n, 0);
-  NL = n;
+  out.nl = uniform(n);
   EmitState E{n, 0, false, false, 0ull};
   const int NT = X.NT;
   if (!a.cull) {
@@ -1081,278 +1340,27 @@ __device__ __forceinline__ void phase_contacts(const KArgs& a, const Scene& S, f
       emit(X, a.rcap, hit, isrob, po, E);
     }
   } else {
-    // bounding volumes first; the exact test runs on the surviving pairs only.
-    // The slack covers single-precision rounding of the bounding tests.
-    const float slack = a.margin + 1e-3f;
-    uint16_t* listA = reinterpret_cast<uint16_t*>(L + Y.cand);
-    uint16_t* listB = listA + Y.ntmax;
+    const uint16_t* listA = reinterpret_cast<const uint16_t*>(L + Y.cand);
     const DModel* M = S.M;
-    if (S.nsph > 0) {
-      // axis-aligned box around the robot's body bounding spheres
-      f3 lo = mk3(1e30f, 1e30f, 1e30f), hi = mk3(-1e30f, -1e30f, -1e30f);
-      if (lane < S.nb && M->sph_count[lane] > 0) {
-        float4 bs = M->bsph[lane];
-        f3 c = mv(rb.R + lane * 9, mk3(bs.x, bs.y, bs.z)) + body_p(rb, lane);
-        lo = mk3(c.x - bs.w, c.y - bs.w, c.z - bs.w);
-        hi = mk3(c.x + bs.w, c.y + bs.w, c.z + bs.w);
-      }
-      for (int off = 32; off > 0; off >>= 1) {
-        lo.x = fminf(lo.x, __shfl_xor(lo.x, off, WAVE)); lo.y = fminf(lo.y, __shfl_xor(lo.y, off, WAVE));
-        lo.z = fminf(lo.z, __shfl_xor(lo.z, off, WAVE)); hi.x = fmaxf(hi.x, __shfl_xor(hi.x, off, WAVE));
-        hi.y = fmaxf(hi.y, __shfl_xor(hi.y, off, WAVE)); hi.z = fmaxf(hi.z, __shfl_xor(hi.z, off, WAVE));
-      }
-      f3 bc = (lo + hi) * 0.5f, he = (hi - lo) * 0.5f;
-      // the robot's candidate targets in increasing order; the furniture
-      // boxes of four chunks are loaded together
-      int nra = 0;
-      for (int base = 0; base < NT; base += 4 * WAVE) {
-        float bx[4][6];
-        if (S.ns > 0) {
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const int si = max(0, min(S.ns - 1, base + u * WAVE + lane - S.np));
-#pragma unroll
-            for (int e = 0; e < 6; ++e) bx[u][e] = X.St[si * 6 + e];
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int t = base + u * WAVE + lane;
-          bool m = false;
-          if (t < NT) {
-            if (t >= S.np && t < S.np + S.ns)
-              m = fabsf(bc.x - bx[u][0]) < he.x + bx[u][3] + slack && fabsf(bc.y - bx[u][1]) < he.y + bx[u][4] + slack &&
-                  fabsf(bc.z - bx[u][2]) < he.z + bx[u][5] + slack;
-            else
-              m = box_near_target(X, bc, he, t, slack);
-          }
-          const uint64_t mk = __ballot(m);
-          if (m) listA[nra + prefix_below(mk)] = (uint16_t)t;
-          nra += __popcll(mk);
-        }
-      }
-      // the robot bodies' bounding spheres against the robot's candidates,
-      // transposed as for the free bodies below: lanes over a chunk of the
-      // candidates, a loop over the bodies, one ballot per (body, chunk)
-      uint32_t* msk = reinterpret_cast<uint32_t*>(L + Y.cmask);
-      const int ncA = (nra + WAVE - 1) / WAVE;
-      // the bodies' bounding spheres (centre, radius; a body without spheres
-      // radius -1) where every lane reads them with one broadcast load
-      float4* rbd = reinterpret_cast<float4*>(L + Y.cmask + lds_align4((Y.fmax > ND ? Y.fmax : ND) * Y.nch * 2));
-      if (lane < S.nb) {
-        float4 bs = M->bsph[lane];
-        const f3 c = mv(rb.R + lane * 9, mk3(bs.x, bs.y, bs.z)) + body_p(rb, lane);
-        rbd[lane] = make_float4(c.x, c.y, c.z, M->sph_count[lane] > 0 ? bs.w : -1.f);
-      }
-      lds_order();
-      for (int ch = 0; ch < ncA; ++ch) {
-        const int i = ch * WAVE + lane;
-        TBound B;
-        target_bound(X, i < nra ? (int)listA[i] : -1, B);
-#pragma unroll 4
-        for (int b = 0; b < S.nb; ++b) {
-          const float4 bd = rbd[b];
-          const bool m = bd.w >= 0.f && B.valid && bound_near(B, mk3(bd.x, bd.y, bd.z), bd.w, slack);
-          const uint64_t mk = __ballot(m);
-          if (lane == 0) {
-            msk[(b * ncA + ch) * 2] = (uint32_t)mk;
-            msk[(b * ncA + ch) * 2 + 1] = (uint32_t)(mk >> 32);
-          }
-        }
-      }
-      wave_sync();
+    if (S.nsph > 0)
       exact_grouped(
-          X, a.rcap, S.nb, msk, ncA, [&](int b) { return M->sph_count[b]; }, [&](int b) { return M->sph_first[b]; },
-          [&](int ch, int j) { return (int)listA[ch * WAVE + j]; }, E);
-    }
-    // free bodies.  Bounding-sphere culling in two parts.  Furniture: each
-    // body's lane looks up the cells of the scene's furniture grid its sphere
-    // overlaps and tests only the boxes registered there.  Planes, door /
-    // drawer boxes and free bodies, transposed: the lanes hold a chunk of
-    // those targets' bounds, the loop runs over the bodies (their spheres by
-    // broadcast loads from LDS), one ballot per body and chunk.  Both set the
-    // bodies' bits in the mask table with LDS atomics; then the exact tests,
-    // grouped.  The grid only skips boxes the bounding test would reject, so
-    // the candidates are those of a test against every target.
-    {
-      const float* F = X.F;
-      const int fm = X.fm;
-      uint32_t* msk = reinterpret_cast<uint32_t*>(L + Y.cmask);
-      unsigned long long* msk64 = reinterpret_cast<unsigned long long*>(msk);
-      const int nch = (NT + WAVE - 1) / WAVE;
-      // lane f: body f's bounding sphere, kind and first owner index
-      f3 fc = mk3(0.f, 0.f, 0.f);
-      float fR = 0.f;
-      int fb = 0, fmem = 0;
-      if (lane < S.nf) {
-        fc = mk3(F[(lane) * FSTR + F_X + 0], F[(lane) * FSTR + F_X + 1], F[(lane) * FSTR + F_X + 2]);
-        f3 h = mk3(F[(lane) * FSTR + F_H + 0], F[(lane) * FSTR + F_H + 1], F[(lane) * FSTR + F_H + 2]);
-        fb = F[(lane) * FSTR + F_TYPE] == 0.f ? 1 : 0;
-        fR = fb ? sqrtf(dot(h, h)) : h.x;
-        fmem = fb ? 8 : 1;
-      }
-      int fob = fmem;  // inclusive scan of the owners per body
-      for (int off = 1; off < WAVE; off <<= 1) {
-        const int v = __shfl_up(fob, off, WAVE);
-        if (lane >= off) fob += v;
-      }
-      fob += S.nsph - fmem;
-      // the bodies' spheres (centre, radius; the radius negative for a free
-      // sphere) where every lane reads them with one broadcast load
-      float4* fbd = reinterpret_cast<float4*>(L + Y.cmask + lds_align4((Y.fmax > ND ? Y.fmax : ND) * Y.nch * 2));
-      if (lane < S.nf) fbd[lane] = make_float4(fc.x, fc.y, fc.z, fb ? fR : -fR);
-      for (int e = lane; e < S.nf * nch; e += WAVE) msk64[e] = 0ull;
-      lds_order();
-      // furniture, by the grid (lane per body): the words of every cell the
-      // sphere overlaps are loaded together, then the candidates' boxes four
-      // at a time
-      if (lane < S.nf && S.ns > 0) {
-        const int nw = a.sg_nw, nws = (S.ns + WAVE - 1) / WAVE;
-        const unsigned long long* cells =
-            reinterpret_cast<const unsigned long long*>(a.sgrid + (size_t)sgrid_floats(nw) * S.s + 4);
-        const float reach = fR + slack + 2e-3f;
-        const int x0 = max(0, min(SGRID - 1, (int)floorf((fc.x - reach - S.gx0) * S.gix)));
-        const int x1 = max(0, min(SGRID - 1, (int)floorf((fc.x + reach - S.gx0) * S.gix)));
-        const int y0 = max(0, min(SGRID - 1, (int)floorf((fc.y - reach - S.gy0) * S.giy)));
-        const int y1 = max(0, min(SGRID - 1, (int)floorf((fc.y + reach - S.gy0) * S.giy)));
-        const int ncell = (x1 - x0 + 1) * (y1 - y0 + 1);
-        for (int wg = 0; wg < nws; wg += 4) {
-          unsigned long long cw[4] = {0ull, 0ull, 0ull, 0ull};
-          int cx = x0, cy = y0;
-          for (int k0 = 0; k0 < ncell; k0 += 4) {
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-              const bool kv = k0 + kk < ncell;
-              const unsigned long long* c = cells + (min(cy, y1) * SGRID + cx) * nw;
-#pragma unroll
-              for (int u = 0; u < 4; ++u) {
-                const unsigned long long v = c[min(wg + u, nw - 1)];
-                cw[u] |= (kv && wg + u < nws) ? v : 0ull;
-              }
-              if (++cx > x1) {
-                cx = x0;
-                ++cy;
-              }
-            }
-          }
-          // the candidates in increasing order, taken from the words in turn
-          unsigned long long cur = cw[0], n1 = cw[1], n2 = cw[2], n3 = cw[3];
-          int wb = wg * 64;
-          auto refill = [&]() {
-            while (cur == 0ull && (n1 | n2 | n3) != 0ull) {
-              cur = n1;
-              n1 = n2;
-              n2 = n3;
-              n3 = 0ull;
-              wb += 64;
-            }
-          };
-          refill();
-          while (cur) {
-            int bi[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              refill();
-              bi[u] = cur ? wb + __ffsll((long long)cur) - 1 : -1;
-              cur &= cur - 1ull;
-            }
-            float bx[4][6];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              const float* src = X.St + (bi[u] >= 0 ? bi[u] : bi[0]) * 6;
-#pragma unroll
-              for (int e = 0; e < 6; ++e) bx[u][e] = src[e];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              TBound B;
-              B.valid = true;
-              B.isplane = false;
-              B.ctr = mk3(bx[u][0], bx[u][1], bx[u][2]);
-              B.half = mk3(bx[u][3], bx[u][4], bx[u][5]);
-              B.rt = 0.f;
-              B.pd = 0.f;
-              B.g = -1;
-              B.gbox = 0;
-              if (bi[u] >= 0 && bound_near(B, fc, fR, slack)) {
-                const int t = S.np + bi[u];
-                atomicOr(msk64 + lane * nch + (t >> 6), 1ull << (t & 63));
-              }
-            }
-            refill();
-          }
-        }
-      }
-      // planes, door / drawer boxes and free bodies (transposed).  With at
-      // most 32 such targets both halves of the wave hold them, and each
-      // ballot serves two bodies (the lower half's and the upper half's).
-      const int NO = S.np + S.na + S.nf;
-      if (NO <= WAVE / 2) {
-        const int hh = lane >> 5, l = lane & 31;
-        const int t = l < S.np ? l : S.ns + l;  // the target index of other-target l
-        TBound B;
-        target_bound(X, l < NO ? t : -1, B);
-        uint64_t mym = 0;  // lane f: body f's bits over the other targets
-#pragma unroll 2
-        for (int f0 = 0; f0 < S.nf; f0 += 2) {
-          const int f = f0 + hh;
-          const float4 bd = fbd[f < S.nf ? f : S.nf - 1];
-          const bool fbox = bd.w >= 0.f;
-          bool m = f < S.nf && B.valid && bound_near(B, mk3(bd.x, bd.y, bd.z), fabsf(bd.w), slack);
-          if (B.g >= 0 && (B.g == f || (!B.gbox && (fbox || B.g <= f)))) m = false;
-          const uint64_t mk = __ballot(m);
-          mym = lane == f0 ? (mk & 0xffffffffull) : (lane == f0 + 1 ? (mk >> 32) : mym);
-        }
-        if (lane < S.nf)
-          while (mym) {
-            const int bit = __ffsll((long long)mym) - 1;
-            mym &= mym - 1ull;
-            const int tt = bit < S.np ? bit : S.ns + bit;
-            atomicOr(msk64 + lane * nch + (tt >> 6), 1ull << (tt & 63));
-          }
-      }
-      for (int base = 0; NO > WAVE / 2 && base < NO; base += WAVE) {
-        const int l = base + lane;
-        const int t = l < S.np ? l : S.ns + l;  // the target index of other-target l
-        TBound B;
-        target_bound(X, l < NO ? t : -1, B);
-        uint64_t mym = 0;  // lane f: body f's bits over this chunk of other targets
-#pragma unroll 2
-        for (int f = 0; f < S.nf; ++f) {
-          const float4 bd = fbd[f];
-          const bool fbox = bd.w >= 0.f;
-          bool m = B.valid && bound_near(B, mk3(bd.x, bd.y, bd.z), fabsf(bd.w), slack);
-          // pair rules of free-body targets: not itself; box vertices skip
-          // free spheres; sphere pairs once
-          if (B.g >= 0 && (B.g == f || (!B.gbox && (fbox || B.g <= f)))) m = false;
-          const uint64_t mk = __ballot(m);
-          mym = lane == f ? mk : mym;
-        }
-        if (lane < S.nf)
-          while (mym) {
-            const int bit = __ffsll((long long)mym) - 1;
-            mym &= mym - 1ull;
-            const int lo = base + bit;
-            const int tt = lo < S.np ? lo : S.ns + lo;
-            atomicOr(msk64 + lane * nch + (tt >> 6), 1ull << (tt & 63));
-          }
-      }
-      wave_sync();
-      exact_grouped(
-          X, a.rcap, S.nf, msk, nch, [&](int f) { return __builtin_amdgcn_readlane(fmem, f); },
-          [&](int f) { return __builtin_amdgcn_readlane(fob, f); }, [&](int ch, int j) { return ch * WAVE + j; }, E);
-    }
+          X, a.rcap, S.nb, reinterpret_cast<const uint32_t*>(L + Y.cmask), ncA, [&](int b) { return M->sph_count[b]; },
+          [&](int b) { return M->sph_first[b]; }, [&](int ch, int j) { return (int)listA[ch * WAVE + j]; }, E);
+    exact_grouped(
+        X, a.rcap, S.nf, reinterpret_cast<const uint32_t*>(L + Y.fmask), (NT + WAVE - 1) / WAVE,
+        [&](int f) { return __builtin_amdgcn_readlane(fmem, f); },
+        [&](int f) { return __builtin_amdgcn_readlane(fob, f); }, [&](int ch, int j) { return ch * WAVE + j; }, E);
   }
   uint64_t ks = E.ks;
   for (int off = 32; off > 0; off >>= 1) ks += __shfl_xor(ks, off, WAVE);
-  keysum = ks;
-  if (__ballot(E.over)) status |= 2u;
-  if (__ballot(E.rover)) status |= 8u;
+  out.keysum = ks;
+  out.status = 0;
+  if (__ballot(E.over)) out.status |= 2u;
+  if (__ballot(E.rover)) out.status |= 8u;
   // the same in every lane: scalar registers, uniform loops over them
-  NC = uniform(E.n);
-  NR = uniform(E.nr);
-  NL = uniform(NL);
-  wave_sync();
+  out.nc = uniform(E.n);
+  out.nr = uniform(E.nr);
+  lds_order();
 }
 
 // Joint-space dynamics of the robot: M~ = M + diag(arm) by the composite-
@@ -1418,7 +1426,7 @@ __device__ __forceinline__ void ri_add(RI& I, float m, f3 d, const float* Jc) {
   I.J[5] += Jc[5] - m * d.y * d.z;
 }
 
-__device__ __forceinline__ void phase_dynamics(const KArgs& a, const Scene& S, float* L, float& vR) {
+__device__ __forceinline__ void dyn_robot(const KArgs& a, const Scene& S, float* L, float& vR) {
   const Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
   const int lane = lane_id();
   const DModel* M = S.M;
@@ -1489,7 +1497,7 @@ __device__ __forceinline__ void phase_dynamics(const KArgs& a, const Scene& S, f
     ri_apply(Ib, v, Iv);
     crf(v, Iv, vp);
   }
-  wave_sync();
+  lds_order();
   // pass 2 (pair lanes): bias acceleration (qdd = 0, gravity as the base's
   // acceleration -g) a_i = -g + sum over anc-or-self of c_k, taken to p_i;
   // the subtree's composite inertia about p_i; then (lane per body) the body
@@ -1531,7 +1539,7 @@ __device__ __forceinline__ void phase_dynamics(const KArgs& a, const Scene& S, f
     ri_apply(Ib, acc6, fi);
     for (int t = 0; t < 6; ++t) rb.fo[i * 6 + t] = fi[t] + vp[t];
   }
-  wave_sync();
+  lds_order();
   // pass 3: (pair lanes) the subtree's body forces at p_i; (lane per body)
   // C_i = s_i . that sum, the right-hand side tau - C, G_i = I^c_i s_i and
   // M_ii; (pair lanes) M_ij = s_j . G_i for j a strict ancestor of i, all at
@@ -1571,7 +1579,7 @@ __device__ __forceinline__ void phase_dynamics(const KArgs& a, const Scene& S, f
       rb.Mt[j * ND + i] = v;
     }
   }
-  wave_sync();
+  lds_order();
   // M~^-1 by Gauss-Jordan elimination without pivoting (M~ is symmetric
   // positive definite) in registers: lane r < 16 holds row r, the pivot row
   // is read from its lane with readlane (the loops are unrolled, so every
@@ -1597,7 +1605,7 @@ __device__ __forceinline__ void phase_dynamics(const KArgs& a, const Scene& S, f
 #pragma unroll
     for (int k = 0; k < ND; ++k) rb.Minv[lane * ND + k] = lane < nb && k < nb ? e[k] : 0.f;
   }
-  wave_sync();
+  lds_order();
   // M~^-1 is symmetric, but the elimination rounds its two triangles
   // differently.  The rows read it row-wise for W = J M~^-1 J^T and the sweeps
   // column-wise for w = M~^-1 J^T; with the two triangles averaged both see
@@ -1613,7 +1621,7 @@ __device__ __forceinline__ void phase_dynamics(const KArgs& a, const Scene& S, f
       rb.Minv[k * ND + i] = m;
     }
   }
-  wave_sync();
+  lds_order();
   // unconstrained robot velocity qd + h M~^-1 (tau - C): joint j in lane j
   // of each 16-lane row (the four copies are equal)
   {
@@ -1623,9 +1631,26 @@ __device__ __forceinline__ void phase_dynamics(const KArgs& a, const Scene& S, f
       for (int k = 0; k < nb; ++k) qdd += rb.Minv[j * ND + k] * rb.rhs[k];
     vR = rb.qd[j] + a.h * qdd;
   }
-  // free bodies: v* = v + h g ; w* = w - h Iw^-1 (w x Iw w)
+  // aux joints: passive single-DoF bodies; the gravity torque about the axis
+  float* Ax = L + a.L.aux;
+  if (lane < S.na) {
+    DAux d = a.aux[S.a0 + lane];
+    f3 ax = mk3(Ax[(A_AX + 0) * AMAX + lane], Ax[(A_AX + 1) * AMAX + lane], Ax[(A_AX + 2) * AMAX + lane]);
+    f3 bc = mk3(Ax[(A_BC + 0) * AMAX + lane], Ax[(A_BC + 1) * AMAX + lane], Ax[(A_BC + 2) * AMAX + lane]);
+    f3 gvec = mk3(a.g[0], a.g[1], a.g[2]);
+    float gen;  // generalized gravity force
+    if (d.type == 0) gen = dot(ax, cross(bc - mk3(d.p0[0], d.p0[1], d.p0[2]), gvec * d.mass));
+    else gen = d.mass * dot(ax, gvec);
+    float qd = Ax[A_QD * AMAX + lane];
+    Ax[A_V * AMAX + lane] = qd + a.h * gen * Ax[A_IM * AMAX + lane];
+  }
+  lds_order();
+}
+
+// free bodies: v* = v + h g ; w* = w - h Iw^-1 (w x Iw w)
+__device__ __forceinline__ void dyn_free(const KArgs& a, const Scene& S, float* L) {
+  const int lane = lane_id();
   float* F = L + a.L.fr;
-  const int fm = a.L.fmax;
   for (int f = lane; f < S.nf; f += WAVE) {
     float R[9];
     for (int t = 0; t < 9; ++t) R[t] = F[(f) * FSTR + F_R + t];
@@ -1642,20 +1667,7 @@ __device__ __forceinline__ void phase_dynamics(const KArgs& a, const Scene& S, f
     F[(f) * FSTR + F_W + 2] = w.z - a.h * dw.z;
     for (int t = 0; t < 3; ++t) F[(f) * FSTR + F_V + t] += a.h * a.g[t];
   }
-  // aux joints: passive single-DoF bodies; the gravity torque about the axis
-  float* Ax = L + a.L.aux;
-  if (lane < S.na) {
-    DAux d = a.aux[S.a0 + lane];
-    f3 ax = mk3(Ax[(A_AX + 0) * AMAX + lane], Ax[(A_AX + 1) * AMAX + lane], Ax[(A_AX + 2) * AMAX + lane]);
-    f3 bc = mk3(Ax[(A_BC + 0) * AMAX + lane], Ax[(A_BC + 1) * AMAX + lane], Ax[(A_BC + 2) * AMAX + lane]);
-    f3 gvec = mk3(a.g[0], a.g[1], a.g[2]);
-    float gen;  // generalized gravity force
-    if (d.type == 0) gen = dot(ax, cross(bc - mk3(d.p0[0], d.p0[1], d.p0[2]), gvec * d.mass));
-    else gen = d.mass * dot(ax, gvec);
-    float qd = Ax[A_QD * AMAX + lane];
-    Ax[A_V * AMAX + lane] = qd + a.h * gen * Ax[A_IM * AMAX + lane];
-  }
-  wave_sync();
+  lds_order();
 }
 
 // Point-Jacobian column of aux joint x at world point p
@@ -1718,17 +1730,17 @@ __device__ __forceinline__ void onb_f(f3 n, float a, f3& t1, f3& t2) {
 // inverse effective mass, coupling to the normal (0 for the normal), bias (0
 // for the tangents) and impulse, then the contact point.  The blocks lie in
 // LDS that is dead between the rows phase and the next substep: past the
-// contact list's end, past the robot's Jacobian rows, the robot's sphere
-// centres, the level schedule's links and the culling lists.
+// contact list's end, past the robot's Jacobian rows, and the robot's sphere
+// centres.
 constexpr int RB_DIR = 3 * ND, RB_P = RB_DIR + 24, RB_FLOATS = RB_P + 4;
 enum { RB_IW = 3, RB_WT = 4, RB_BIAS = 5, RB_LAM = 6 };
 // offset of robot row rr's block, -1 if there is no room for it
 __device__ __forceinline__ int rob_block(const LdsLayout& Y, int NC, int NR, int rr) {
-  const int base[5] = {Y.con + lds_align4(NC * CSTR), Y.rows + NR * ROW_FLOATS, Y.sph, Y.lvl, Y.cand};
-  const int end[5] = {Y.rows, Y.rows + Y.rcap * ROW_FLOATS, Y.fr, Y.lvl + ((Y.ccap + 2) & ~3), Y.frc};
+  const int base[3] = {Y.con + lds_align4(NC * CSTR), Y.rows + NR * ROW_FLOATS, Y.sph};
+  const int end[3] = {Y.rows, Y.lvl, Y.fr};
   int off = -1;
 #pragma unroll
-  for (int i = 0; i < 5; ++i) {
+  for (int i = 0; i < 3; ++i) {
     const int n = (end[i] - base[i]) / RB_FLOATS;
     if (off < 0 && rr >= 0 && rr < n) off = base[i] + rr * RB_FLOATS;
     rr -= n;
@@ -1803,7 +1815,7 @@ __device__ __forceinline__ void phase_rows(const KArgs& a, const Scene& S, float
     C[(ci) * CSTR + C_WTN + 1] = W2n;
     for (int t = 0; t < 3; ++t) C[(ci) * CSTR + C_LAM + t] = 0.f;
   }
-  wave_sync();
+  lds_order();
   // lane rr: where robot row rr's block lies
   const int rblk = lane < NR ? rob_block(Y, NC, NR, lane) : -1;
   // robot rows: lane (d, j) builds J[d][j] = d . (dp/dq_j) and W = J M~^-1 J^T
@@ -1822,7 +1834,7 @@ __device__ __forceinline__ void phase_rows(const KArgs& a, const Scene& S, float
       f3 dir = d == 0 ? n : (d == 1 ? t1 : t2);
       row[d * ND + j] = robot_J(M, rb, S.nb, body, j, dir, p);
     }
-    wave_sync();
+    lds_order();
     float w = 0.f;
     if (d < 3) {
 #pragma unroll
@@ -1841,7 +1853,7 @@ __device__ __forceinline__ void phase_rows(const KArgs& a, const Scene& S, float
         if (d > 0) C[(ci) * CSTR + C_WTN + d - 1] += Wc;
       }
     }
-    wave_sync();
+    lds_order();
   }
   // inverse effective masses; rows below 1e-12 are skipped (inverse 0), a
   // friction pair with either one below
@@ -1859,7 +1871,7 @@ __device__ __forceinline__ void phase_rows(const KArgs& a, const Scene& S, float
     degen = degen || !ok0 || !ok1;
   }
   if (__ballot(degen)) status |= 4u;
-  wave_sync();
+  lds_order();
   // the robot rows' blocks: lane (d, j) writes value j of direction d, the
   // last 16 lanes the contact point
   for (int rr = 0; rr < min(NR, WAVE); ++rr) {
@@ -1882,7 +1894,7 @@ __device__ __forceinline__ void phase_rows(const KArgs& a, const Scene& S, float
       L[blk + RB_P + j] = c[C_P + j];
     }
   }
-  wave_sync();
+  lds_order();
 }
 
 // Schedule of the sweeps.  In the canonical order the joint-limit rows come
@@ -2017,7 +2029,7 @@ __device__ __forceinline__ Levels phase_levels(const KArgs& a, float* L, int NC,
     lds_order();
   }
   for (int off = 32; off > 0; off >>= 1) maxl = max(maxl, __shfl_xor(maxl, off, WAVE));
-  wave_sync();
+  lds_order();
   return Levels{uniform(NG), uniform(maxl)};
 }
 
@@ -2483,15 +2495,9 @@ __device__ __forceinline__ void pgs_linked(const KArgs& a, float* L, int NC, int
     for (int d = 0; d < 3; ++d) C[(NL + lane) * CSTR + C_LAM + d] = L[rblk + RB_DIR + 8 * d + RB_LAM];
 }
 
-__device__ __forceinline__ void phase_integrate(const KArgs& a, const Scene& S, float* L, float vR) {
-  const Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
+__device__ __forceinline__ void integrate_free(const KArgs& a, const Scene& S, float* L) {
   const int lane = lane_id();
-  if (lane < ND) {
-    rb.qd[lane] = vR;
-    if (lane < S.nb) rb.q[lane] += a.h * vR;
-  }
   float* F = L + a.L.fr;
-  const int fm = a.L.fmax;
   for (int f = lane; f < S.nf; f += WAVE) {
     f3 v = mk3(F[(f) * FSTR + F_V + 0], F[(f) * FSTR + F_V + 1], F[(f) * FSTR + F_V + 2]);
     f3 w = mk3(F[(f) * FSTR + F_W + 0], F[(f) * FSTR + F_W + 1], F[(f) * FSTR + F_W + 2]);
@@ -2522,13 +2528,23 @@ __device__ __forceinline__ void phase_integrate(const KArgs& a, const Scene& S, 
     F[(f) * FSTR + F_Q + 2] = r2 * inv;
     F[(f) * FSTR + F_Q + 3] = r3 * inv;
   }
+  lds_order();
+}
+
+__device__ __forceinline__ void integrate_robot(const KArgs& a, const Scene& S, float* L, float vR) {
+  const Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
+  const int lane = lane_id();
+  if (lane < ND) {
+    rb.qd[lane] = vR;
+    if (lane < S.nb) rb.q[lane] += a.h * vR;
+  }
   float* A = L + a.L.aux;
   if (lane < S.na) {
     float v = A[A_V * AMAX + lane];
     A[A_QD * AMAX + lane] = v;
     A[A_Q * AMAX + lane] += a.h * v;
   }
-  wave_sync();
+  lds_order();
 }
 
 // Contact-force outputs of a substep: the sum of the robot's normal impulses
@@ -2569,7 +2585,7 @@ __device__ __forceinline__ void phase_forces(const KArgs& a, const Scene& S, flo
     }
   }
   if (!a.frc_robot) {
-    wave_sync();
+    lds_order();
     return;
   }
   float part = 0.f;
@@ -2590,19 +2606,17 @@ __device__ __forceinline__ void phase_forces(const KArgs& a, const Scene& S, flo
       FR[(g) * FRC_FLOATS + R_FRC + 2] -= P.z / a.h;
     }
   }
-  wave_sync();
+  lds_order();
 }
 
-// MODE 0: the plain step; 1: also the record of the control step for the
-// adjoint; 2: also the contact-force outputs.  Separate instantiations, so
-// the plain step keeps its register allocation.
-template <int MODE>
-__device__ __forceinline__ void run_scene(int s, float* const L0) {
-  const KArgs& a = args_fresh();
-  float* const L = lds_fresh(L0);
-  constexpr bool REC = MODE == 1;
-  const int lane = lane_id();
-  Scene S;
+// Words the wavefronts of a workgroup exchange (LDS): the substep's contact
+// counts, status and schedule from wavefront 1, the chunks of the robot's candidate
+// list from wavefront 0; at a scene's end wavefront 1's check of the state and
+// the next queue position.
+enum { CTL_NC = 0, CTL_NR, CTL_NL, CTL_STATUS, CTL_NG, CTL_MAXL, CTL_NCA, CTL_BAD, CTL_POS };
+static_assert(CTL_POS < CTL_WORDS, "control words");
+
+__device__ __forceinline__ void scene_view(const KArgs& a, int s, Scene& S) {
   const DScene ds = a.scenes[s];
   S.s = s;
   S.M = a.models + ds.model;
@@ -2611,14 +2625,31 @@ __device__ __forceinline__ void run_scene(int s, float* const L0) {
   S.nf = ds.nf; S.ns = ds.ns; S.np = ds.np; S.na = ds.na; S.nfo = ds.nown;
   S.f0 = ds.f0; S.s0 = ds.s0; S.p0 = ds.p0; S.a0 = ds.a0;
   S.hold = a.scenes[s].hold;
-  {
-    const float* g = a.sgrid + (size_t)sgrid_floats(a.sg_nw) * s;
-    S.gx0 = g[0];
-    S.gy0 = g[1];
-    S.gix = g[2];
-    S.giy = g[3];
-  }
+  const float* g = a.sgrid + (size_t)sgrid_floats(a.sg_nw) * s;
+  S.gx0 = g[0];
+  S.gy0 = g[1];
+  S.gix = g[2];
+  S.giy = g[3];
+}
+
+// MODE 0: the plain step; 1: also the record of the control step for the
+// adjoint; 2: also the contact-force outputs.  Separate instantiations, so
+// the plain step keeps its register allocation.
+//
+// wv: the wavefront (0: the robot's part, 1: the free bodies').  Every barrier
+// is outside the branches on wv, and the substep loop ends alike in both
+// wavefronts (the counts and the status they test come from LDS words read
+// after a barrier).  Returns the next queue position.
+template <int MODE>
+__device__ __forceinline__ int run_scene(int s, int wv, float* const L0) {
+  const KArgs& a = args_fresh();
+  float* const L = lds_fresh(L0);
+  constexpr bool REC = MODE == 1;
+  const int lane = lane_id();
+  Scene S;
+  scene_view(a, s, S);
   const unsigned long long t_scene = a.cost ? clock64() : 0ull;
+  // the phases' time as wavefront 0 sees it, with its waits for wavefront 1
   const bool prof = a.phase_cycles != nullptr;
   unsigned long long cyc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   unsigned long long tc = prof ? clock64() : 0;
@@ -2628,87 +2659,152 @@ __device__ __forceinline__ void run_scene(int s, float* const L0) {
     cyc[k] += t2 - tc;                       \
     tc = t2;                                 \
   }
-  load_scene(args_fresh(), S, lds_fresh(L0));
-  MS_PHASE(7)
   uint32_t status = 0;
   float frc = 0.f;
-  if (MODE == 2) {
-    // the force sums of the control step: a launch that resumes the step
-    // (a.sub0 > 0) continues the sums so far, so that they add up in the
-    // order of one launch over the whole step
-    float* FR = L + a.L.frc;
-    float* A = L + a.L.aux;
-    const bool resume = a.sub0 > 0;
-    for (int f = lane; f < S.nf; f += WAVE) {
-      for (int t = 0; t < FRC_FLOATS; ++t) FR[(f) * FRC_FLOATS + t] = 0.f;
-      if (resume && a.frc_body)
-        for (int t = 0; t < 3; ++t) FR[(f) * FRC_FLOATS + R_FRC + t] = a.frc_body[(size_t)(S.f0 + f) * 4 + t];
-      if (resume && a.grip) FR[(f) * FRC_FLOATS + R_EE] = a.grip[2 * (size_t)(S.f0 + f)];
+  if (wv == 0) {
+    load_robot(args_fresh(), S, lds_fresh(L0));
+    if (MODE == 2) {
+      // the force sums of the control step: a launch that resumes the step
+      // (a.sub0 > 0) continues the sums so far, so that they add up in the
+      // order of one launch over the whole step
+      float* FR = L + a.L.frc;
+      float* A = L + a.L.aux;
+      const bool resume = a.sub0 > 0;
+      for (int f = lane; f < S.nf; f += WAVE) {
+        for (int t = 0; t < FRC_FLOATS; ++t) FR[(f) * FRC_FLOATS + t] = 0.f;
+        if (resume && a.frc_body)
+          for (int t = 0; t < 3; ++t) FR[(f) * FRC_FLOATS + R_FRC + t] = a.frc_body[(size_t)(S.f0 + f) * 4 + t];
+        if (resume && a.grip) FR[(f) * FRC_FLOATS + R_EE] = a.grip[2 * (size_t)(S.f0 + f)];
+      }
+      if (lane < S.na) {
+        A[A_EE * AMAX + lane] = resume && a.grip ? a.grip[2 * ((size_t)a.NF + S.a0 + lane)] : 0.f;
+        A[A_FMIN * AMAX + lane] = 0.f;
+      }
+      if (resume && a.frc_robot) frc = a.frc_robot[s];
+      lds_order();
     }
-    if (lane < S.na) {
-      A[A_EE * AMAX + lane] = resume && a.grip ? a.grip[2 * ((size_t)a.NF + S.a0 + lane)] : 0.f;
-      A[A_FMIN * AMAX + lane] = 0.f;
-    }
-    if (resume && a.frc_robot) frc = a.frc_robot[s];
-    wave_sync();
+  } else {
+    load_free(args_fresh(), S, lds_fresh(L0));
   }
+  MS_PHASE(7)
   float* rec = REC ? a.rec + (size_t)s * a.RL.total : nullptr;
   // the largest contact lists of the step, for the next step's routing
   int max_nc = 0, max_nr = 0;
   for (int k = 0; k < a.n_sub; ++k) {
-    int NC, NR, NL;
-    uint64_t keysum = 0;
-    float vR;
     const int ks = a.sub0 + k;
-    if (rec) rec_state(args_fresh(), S, lds_fresh(L0), rec + ks * a.RL.ss);
-    phase_drive(args_fresh(), S, lds_fresh(L0));
-    phase_kinematics(args_fresh(), S, lds_fresh(L0));
+    int* const ctl = reinterpret_cast<int*>(lds_fresh(L0) + args_fresh().L.ctl);
+    const bool cull = a.cull != 0;
+    float vR = 0.f;
+    int fmem = 0, fob = 0;  // wavefront 1: owners of the lane's body
+    uint64_t keysum = 0;
+    if (wv == 0) {
+      if (rec) rec_robot(args_fresh(), S, lds_fresh(L0), rec + ks * a.RL.ss);
+      phase_drive(args_fresh(), S, lds_fresh(L0));
+      kin_robot(args_fresh(), S, lds_fresh(L0));
+    } else {
+      if (rec) rec_free(args_fresh(), S, lds_fresh(L0), rec + ks * a.RL.ss);
+      kin_free(args_fresh(), S, lds_fresh(L0));
+    }
+    both_sync();
     MS_PHASE(0)
-    // unconstrained dynamics first: it needs only the frames, and its
-    // articulated-body scratch is dead before the contact list is written
-    // into the same LDS
-    phase_dynamics(args_fresh(), S, lds_fresh(L0), vR);
+    if (wv == 0) {
+      if (cull && S.nsph > 0) {
+        const int ncA = cull_robot(args_fresh(), S, lds_fresh(L0), args_fresh().margin);
+        if (lane_id() == 0) ctl[CTL_NCA] = ncA;
+      }
+    } else if (cull) {
+      cull_free(args_fresh(), S, lds_fresh(L0), fmem, fob);
+    }
+    both_sync();
+    MS_PHASE(1)
+    if (wv == 0) {
+      dyn_robot(args_fresh(), S, lds_fresh(L0), vR);
+    } else {
+      Contacts cn;
+      emit_contacts(args_fresh(), S, lds_fresh(L0), cull ? uniform(ctl[CTL_NCA]) : 0, fmem, fob, cn);
+      if (lane_id() == 0) {
+        ctl[CTL_NC] = cn.nc;
+        ctl[CTL_NR] = cn.nr;
+        ctl[CTL_NL] = cn.nl;
+        ctl[CTL_STATUS] = (int)cn.status;
+      }
+      keysum = cn.keysum;
+      if (rec && !(a.fit_mode == 1 && cn.status))
+        rec_contacts(args_fresh(), lds_fresh(L0), cn.nc, cn.nl, cn.nr, rec + a.RL.con + ks * a.RL.cstride);
+      dyn_free(args_fresh(), S, lds_fresh(L0));
+    }
+    both_sync();
     MS_PHASE(2)
-    phase_contacts(args_fresh(), S, lds_fresh(L0), NC, NR, NL, status, keysum);
+    const int NC = uniform(ctl[CTL_NC]), NR = uniform(ctl[CTL_NR]), NL = uniform(ctl[CTL_NL]);
+    status |= (uint32_t)uniform(ctl[CTL_STATUS]);
     // a launch in a smaller layout gives up a scene at its first overflowing
     // contact list; everything written so far the retry writes again alike
     if (a.fit_mode == 1 && (status & 10u)) break;
-    if (rec) rec_contacts(args_fresh(), lds_fresh(L0), NC, NL, NR, rec + a.RL.con + ks * a.RL.cstride);
     max_nc = max(max_nc, NC - NL);
     max_nr = max(max_nr, NR);
-    MS_PHASE(1)
-    // the schedule before the rows: its masks lie where the rows phase
-    // leaves the robot rows' w
-    const Levels lv = phase_levels(args_fresh(), lds_fresh(L0), NC, NR, NL);
+    Levels lv{0, 0};
+    if (wv == 0) {
+      phase_rows(args_fresh(), S, lds_fresh(L0), NC, NR, NL, status);
+      MS_PHASE(3)
+    } else {
+      lv = phase_levels(args_fresh(), lds_fresh(L0), NC, NR, NL);
+      if (lane_id() == 0) {
+        ctl[CTL_NG] = lv.ng;
+        ctl[CTL_MAXL] = lv.maxl;
+      }
+    }
+    both_sync();
     MS_PHASE(4)
-    phase_rows(args_fresh(), S, lds_fresh(L0), NC, NR, NL, status);
-    MS_PHASE(3)
     {
       float* tape = rec ? rec + a.RL.tape + (size_t)ks * a.K * a.RL.tsw : nullptr;
-      pgs_alone(args_fresh(), lds_fresh(L0), lv.ng, tape);
-      pgs_linked(args_fresh(), lds_fresh(L0), NC, NL, NR, lv, vR, tape);
+      if (wv == 0) {
+        lv = Levels{uniform(ctl[CTL_NG]), uniform(ctl[CTL_MAXL])};
+        pgs_linked(args_fresh(), lds_fresh(L0), NC, NL, NR, lv, vR, tape);
+        if (MODE == 2) phase_forces(args_fresh(), S, lds_fresh(L0), NL, NR, frc, ks == a.n_sub_total - 1);
+      } else {
+        pgs_alone(args_fresh(), lds_fresh(L0), lv.ng, tape);
+      }
     }
-    if (MODE == 2) phase_forces(args_fresh(), S, lds_fresh(L0), NL, NR, frc, ks == a.n_sub_total - 1);
+    both_sync();
     MS_PHASE(5)
-    phase_integrate(args_fresh(), S, lds_fresh(L0), vR);
-    MS_PHASE(6)
-    if (rec && ks == a.n_sub_total - 1) rec_state(args_fresh(), S, lds_fresh(L0), rec + (ks + 1) * a.RL.ss);
-    if (a.debug && lane == 0) {
-      uint32_t* d = a.debug + ((size_t)s * a.n_sub_total + a.sub0 + k) * 4;
-      d[0] = (uint32_t)(NC - NL);
-      d[1] = (uint32_t)NR;
-      d[2] = (uint32_t)keysum;
-      d[3] = (uint32_t)(keysum >> 32);
+    if (wv == 0) {
+      integrate_robot(args_fresh(), S, lds_fresh(L0), vR);
+      if (rec && ks == a.n_sub_total - 1) rec_robot(args_fresh(), S, lds_fresh(L0), rec + (ks + 1) * a.RL.ss);
+    } else {
+      integrate_free(args_fresh(), S, lds_fresh(L0));
+      if (rec && ks == a.n_sub_total - 1) rec_free(args_fresh(), S, lds_fresh(L0), rec + (ks + 1) * a.RL.ss);
+      if (a.debug && lane_id() == 0) {
+        uint32_t* d = a.debug + ((size_t)s * a.n_sub_total + a.sub0 + k) * 4;
+        d[0] = (uint32_t)(NC - NL);
+        d[1] = (uint32_t)NR;
+        d[2] = (uint32_t)keysum;
+        d[3] = (uint32_t)(keysum >> 32);
+      }
     }
+    MS_PHASE(6)
   }
   // a launch in a smaller layout stores nothing of a scene whose lists
   // overflowed it: the retry launch steps it again in the full layout, from
   // the unchanged input state
-  if (a.fit_mode == 1 && (status & 10u)) {
-    if (lane == 0) a.retry[1 + atomicAdd(a.retry, 1)] = s;
-    return;
+  const bool give_up = a.fit_mode == 1 && (status & 10u);
+  int* const ctl = reinterpret_cast<int*>(lds_fresh(L0) + args_fresh().L.ctl);
+  if (wv == 0) {
+    if (!give_up) {
+      if (store_robot(args_fresh(), S, lds_fresh(L0))) status |= 1u;
+    }
+    if (a.persistent && lane == 0) ctl[CTL_POS] = atomicAdd(a.queue + (a.fit_mode == 2 ? 1 : (a.fit_mode == 3 ? 2 : 0)), 1);
+  } else if (!give_up) {
+    const bool bad = store_free(args_fresh(), S, lds_fresh(L0));
+    if (lane_id() == 0) ctl[CTL_BAD] = bad ? 1 : 0;
   }
-  store_scene(args_fresh(), S, lds_fresh(L0), status);
+  both_sync();
+  const int next = a.persistent ? uniform(ctl[CTL_POS]) : 0;
+  if (wv != 0) return next;
+  if (give_up) {
+    if (lane == 0) a.retry[1 + atomicAdd(a.retry, 1)] = s;
+    return next;
+  }
+  status |= (uint32_t)uniform(ctl[CTL_BAD]);
   if (MODE == 2 && a.grip) {
     const float* FR = L + a.L.frc;
     const float* A = L + a.L.aux;
@@ -2756,38 +2852,38 @@ __device__ __forceinline__ void run_scene(int s, float* const L0) {
       }
     }
   }
+  return next;
 }
 
 template <int MODE>
 __device__ __forceinline__ void step_body(const KArgs& a, float* lds) {
-  // one call site: the persistent form pulls positions from its work
-  // counter, the plain form takes its block index once
-  const int qi = a.fit_mode == 2 ? 1 : (a.fit_mode == 3 ? 2 : 0);
+  // one call site: the persistent form pulls positions from its work counter
+  // (wavefront 0, for both), the plain form takes its block index once
+  const int wv = uniform((int)threadIdx.x >> 6);
   const int base = a.fit_mode == 1 ? *a.n_over : 0;
   const int end = a.fit_mode == 2 ? *a.n_over : (a.fit_mode == 3 ? a.retry[0] : a.S);
-  int pos = a.persistent ? 0 : base + (int)blockIdx.x;
-  for (;;) {
-    if (a.persistent) {
-      int got = 0;
-      if (threadIdx.x == 0) got = atomicAdd(a.queue + qi, 1);
-      pos = base + uniform(got);
-    }
-    if (pos >= end) break;
-    run_scene<MODE>(uniform(a.fit_mode == 3 ? a.retry[1 + pos] : a.order[pos]), lds);
+  int pos = base + (int)blockIdx.x;
+  if (a.persistent) {
+    int* const ctl = reinterpret_cast<int*>(lds + a.L.ctl);
+    if (threadIdx.x == 0) ctl[CTL_POS] = atomicAdd(a.queue + (a.fit_mode == 2 ? 1 : (a.fit_mode == 3 ? 2 : 0)), 1);
+    both_sync();
+    pos = base + uniform(ctl[CTL_POS]);
+  }
+  while (pos < end) {
+    pos = base + run_scene<MODE>(uniform(a.fit_mode == 3 ? a.retry[1 + pos] : a.order[pos]), wv, lds);
     if (!a.persistent) break;
-    __syncthreads();
   }
 }
 
-__global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_step(KArgs a) {
+__global__ __launch_bounds__(STEP_THREADS) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_step(KArgs a) {
   extern __shared__ float lds[];
   step_body<0>(a, lds);
 }
-__global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_step_rec(KArgs a) {
+__global__ __launch_bounds__(STEP_THREADS) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_step_rec(KArgs a) {
   extern __shared__ float lds[];
   step_body<1>(a, lds);
 }
-__global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_step_frc(KArgs a) {
+__global__ __launch_bounds__(STEP_THREADS) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_step_frc(KArgs a) {
   extern __shared__ float lds[];
   step_body<2>(a, lds);
 }
@@ -2805,36 +2901,19 @@ __global__ __launch_bounds__(WAVE) void k_spawn_check(KArgs a, uint8_t* collide)
   if (s >= a.S) return;
   const int lane = lane_id();
   Scene S;
-  const DScene ds = a.scenes[s];
-  S.s = s;
-  S.M = a.models + ds.model;
-  S.nb = S.M->nb;
-  S.nsph = S.M->nsph;
-  S.nf = ds.nf; S.ns = ds.ns; S.np = ds.np; S.na = ds.na; S.nfo = ds.nown;
-  S.f0 = ds.f0; S.s0 = ds.s0; S.p0 = ds.p0; S.a0 = ds.a0;
-  S.hold = a.scenes[s].hold;
+  scene_view(a, s, S);
   float* L = lds;
-  load_scene(a, S, L);
-  phase_kinematics(a, S, L);
-  const LdsLayout& Y = a.L;
+  load_robot(a, S, L);
+  load_free(a, S, L);
+  kin_robot(a, S, L);
+  kin_free(a, S, L);
   ConCtx X;
-  X.M = S.M;
-  X.C = L + Y.con;
-  X.cc = Y.ccap;
-  X.SW = L + Y.sph;
-  X.F = L + Y.fr;
-  X.fm = Y.fmax;
-  X.A = L + Y.aux;
-  X.Pl = L + Y.plane;
-  X.own = reinterpret_cast<const uint16_t*>(L + Y.own);
-  X.St = Y.smax > 0 ? (L + Y.stat) : (a.statics + (size_t)S.s0 * 6);
-  X.nsph = S.nsph; X.np = S.np; X.ns = S.ns; X.na = S.na; X.nf = S.nf;
-  X.NT = S.np + S.ns + S.na + S.nf;
+  con_ctx(a, S, L, X);
   X.margin = 0.f;
   X.hash = false;
+  bool hit = false;
   const int NT = X.NT, total = S.nsph * NT;
   const float invNT = NT > 0 ? 1.f / (float)NT : 0.f;
-  bool hit = false;
   for (int base = 0; base < total; base += WAVE) {
     int pair = base + lane;
     if (pair < total) {
@@ -2957,9 +3036,9 @@ __global__ void k_masked_copy(float* dst, const float* src, const uint8_t* mask,
 }
 
 void launch_step(const KArgs& a, int grid, size_t lds_bytes, hipStream_t st) {
-  if (a.rec) hipLaunchKernelGGL(k_step_rec, dim3(grid), dim3(WAVE), lds_bytes, st, a);
-  else if (a.frc_robot || a.grip) hipLaunchKernelGGL(k_step_frc, dim3(grid), dim3(WAVE), lds_bytes, st, a);
-  else hipLaunchKernelGGL(k_step, dim3(grid), dim3(WAVE), lds_bytes, st, a);
+  if (a.rec) hipLaunchKernelGGL(k_step_rec, dim3(grid), dim3(STEP_THREADS), lds_bytes, st, a);
+  else if (a.frc_robot || a.grip) hipLaunchKernelGGL(k_step_frc, dim3(grid), dim3(STEP_THREADS), lds_bytes, st, a);
+  else hipLaunchKernelGGL(k_step, dim3(grid), dim3(STEP_THREADS), lds_bytes, st, a);
 }
 void launch_reset_queue(int* q, hipStream_t st) { hipLaunchKernelGGL(k_reset_queue, dim3(1), dim3(64), 0, st, q); }
 
