@@ -2893,8 +2893,10 @@ __global__ void k_reset_queue(int* q) {
 }
 
 // Spawn check of a reset: collide[s] = 1 where a robot sphere penetrates
-// (phi < 0) another body; every (robot sphere, target) pair is tested with
-// the contact phase's pair function and a zero margin.
+// (phi < 0) another body: the step's culling and pair test of the robot with a
+// zero margin, one wavefront per scene.  Without culling every (robot sphere,
+// target) pair is tested: 4 to 11 thousand pairs in a furnished room where
+// the culling leaves a few hundred (4096 scenes: 174 -> 49 us).
 __global__ __launch_bounds__(WAVE) void k_spawn_check(KArgs a, uint8_t* collide) {
   extern __shared__ float lds[];
   const int s = blockIdx.x;
@@ -2912,16 +2914,27 @@ __global__ __launch_bounds__(WAVE) void k_spawn_check(KArgs a, uint8_t* collide)
   X.margin = 0.f;
   X.hash = false;
   bool hit = false;
-  const int NT = X.NT, total = S.nsph * NT;
-  const float invNT = NT > 0 ? 1.f / (float)NT : 0.f;
-  for (int base = 0; base < total; base += WAVE) {
-    int pair = base + lane;
-    if (pair < total) {
-      int o, t;
-      divmod(pair, NT, invNT, o, t);
-      PairOut po;
-      bool isrob;
-      hit |= eval_pair(X, o, t, po, isrob);
+  if (a.cull && S.nsph > 0) {
+    const int ncA = cull_robot(a, S, L, 0.f);
+    const uint16_t* listA = reinterpret_cast<const uint16_t*>(L + a.L.cand);
+    const DModel* M = S.M;
+    EmitState E{0, 0, false, false, 0ull};
+    exact_grouped(
+        X, a.rcap, S.nb, reinterpret_cast<const uint32_t*>(L + a.L.cmask), ncA, [&](int b) { return M->sph_count[b]; },
+        [&](int b) { return M->sph_first[b]; }, [&](int ch, int j) { return (int)listA[ch * WAVE + j]; }, E);
+    hit = E.n > 0 || E.over || E.rover;
+  } else {
+    const int NT = X.NT, total = S.nsph * NT;
+    const float invNT = NT > 0 ? 1.f / (float)NT : 0.f;
+    for (int base = 0; base < total; base += WAVE) {
+      int pair = base + lane;
+      if (pair < total) {
+        int o, t;
+        divmod(pair, NT, invNT, o, t);
+        PairOut po;
+        bool isrob;
+        hit |= eval_pair(X, o, t, po, isrob);
+      }
     }
   }
   uint64_t any = __ballot(hit);
