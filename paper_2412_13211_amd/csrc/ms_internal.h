@@ -122,24 +122,19 @@ __host__ __device__ inline LdsLayout make_layout(int fmax, int smax, int ccap, i
   // robot contact rows.  Before the rows phase builds them, the culling masks
   // (per robot or free body and 64-target chunk, 64 bits) with the bodies'
   // bounding spheres (4 floats each) lie there, the robot's then the free
-  // bodies', and after them, reaching into the sweep schedule, the dynamics
-  // scratch.
+  // bodies', and after them the dynamics scratch.
   L.rows = o;
   L.nch = (L.ntmax + WAVE - 1) / WAVE;
   L.cmask = o;
   L.fmask = o + lds_align4(ND * L.nch * 2) + ND * 4;
   L.dyn = L.fmask + lds_align4(fmax * L.nch * 2) + fmax * 4;
+  {
+    const int rw = lds_align4(rcap * ROW_FLOATS), mk = lds_align4(L.dyn - o + DYN_FLOATS);
+    o += rw > mk ? rw : mk;
+  }
   // sweep schedule: each group's previous groups [ccap + 2] twice, its level
   // [ccap] and first row [ccap + 1] (uint16)
-  const int sched = lds_align4((4 * ccap + 5 + 1) / 2);
-  {
-    int rw = lds_align4(rcap * ROW_FLOATS);
-    const int mk = L.dyn - L.rows, need = mk + DYN_FLOATS - sched;
-    rw = rw > mk ? rw : mk;
-    rw = rw > need ? rw : lds_align4(need);
-    o += rw;
-  }
-  L.lvl = o;   o += sched;
+  L.lvl = o;   o += lds_align4((4 * ccap + 5 + 1) / 2);
   // two uint16 candidate lists; after the contact phase the level schedule's
   // per-node group masks (64-bit, per node and 64-group chunk) and the mask
   // of the robot's nodes

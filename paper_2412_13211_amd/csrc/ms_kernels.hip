@@ -3,22 +3,21 @@
 // One workgroup of two wavefronts advances one scene through all substeps of a
 // control step with the scene resident in LDS.  The step is a few serial
 // chains that do not need each other, so wavefront 0 runs the robot's and
-// wavefront 1 the free bodies'; they meet at five barriers per substep:
-//   0: drive, robot and joint frames          1: free-body frames
+// wavefront 1 the free bodies'; they meet at three barriers per substep:
+//   0: drive, frames, robot bodies against   1: free-body frames, free bodies against
+//      targets (bounds)                         targets (bounds)
 //   -- barrier --
-//   0: robot bodies against targets (bounds)  1: free bodies against targets (bounds)
+//   0: robot dynamics, inverse mass matrix   1: exact tests, contact list, free-body
+//                                               velocities, free-body rows, schedule
 //   -- barrier --
-//   0: robot dynamics, inverse mass matrix    1: exact tests, contact list, free-body velocities
+//   0: robot rows, sweeps of everything      1: sweeps of the bodies only static
+//      linked, integration of the robot,        targets touch, integration of the
+//      the joints and those bodies              other bodies
 //   -- barrier --
-//   0: contact rows                           1: sweep schedule
-//   -- barrier --
-//   0: sweeps of everything linked            1: sweeps of the bodies only static targets touch
-//   -- barrier --
-//   0: integrate robot and joints             1: integrate free bodies
 // One wavefront doing all in turn was bound by the latency of each chain, the
 // SIMDs idle two thirds of the time; LDS, not wavefront slots, limits the
 // scenes per CU, so the second wavefront is free.  A control step of 16, 1024
-// and 4096 uneven scenes: 183 -> 125, 539 -> 408 and 1019 -> 774 us.
+// and 4096 uneven scenes: 183 -> 130, 539 -> 386 and 1019 -> 746 us.
 // The mathematics follows the textbook definitions cited in the C header; no
 // code is shared with the CPU oracle.
 #include "ms_internal.h"
@@ -151,6 +150,9 @@ __device__ __forceinline__ float lane_val(float v, int src) {
 }
 // a value equal in every lane, as a scalar
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ unsigned long long uniform64(unsigned long long v) {
+  return (unsigned long long)(uint32_t)uniform((int)(v >> 32)) << 32 | (uint32_t)uniform((int)v);
+}
 // both wavefronts of the workgroup
 __device__ __forceinline__ void both_sync() { __syncthreads(); }
 // Ordering of LDS accesses between the lanes of one wavefront: the LDS
@@ -485,7 +487,7 @@ __device__ __forceinline__ void phase_drive(const KArgs& a, const Scene& S, floa
   }
 }
 
-// world frames of the robot's bodies, its spheres, and the door / drawer frames
+// world frames of the robot's bodies and its spheres
 __device__ __forceinline__ void kin_robot(const KArgs& a, const Scene& S, float* L) {
   const Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
   const int lane = lane_id();
@@ -557,7 +559,12 @@ __device__ __forceinline__ void kin_robot(const KArgs& a, const Scene& S, float*
     f3 c = mv(rb.R + b * 9, mk3(sp.x, sp.y, sp.z)) + mk3(rb.p[b * 3], rb.p[b * 3 + 1], rb.p[b * 3 + 2]);
     SW[k * 4 + 0] = c.x; SW[k * 4 + 1] = c.y; SW[k * 4 + 2] = c.z; SW[k * 4 + 3] = sp.w;
   }
-  // aux joints: moving frame and world box centre
+  lds_order();
+}
+
+// door / drawer joints: moving frame, world box centre, inertia about the axis
+__device__ __forceinline__ void kin_aux(const KArgs& a, const Scene& S, float* L) {
+  const int lane = lane_id();
   float* A = L + a.L.aux;
   if (lane < S.na) {
     DAux d = a.aux[S.a0 + lane];
@@ -1691,19 +1698,6 @@ __device__ __forceinline__ f3 aux_col_f(const float* A, int x, f3 p) {
   return ax;
 }
 
-// Entry j of the robot's Jacobian row for direction d at the point p of a
-// contact on body `body`: d . (a_j x (p - o_j)) for a revolute joint, d . a_j
-// for a prismatic one, 0 when joint j does not move the body
-__device__ __forceinline__ float robot_J(const DModel* M, const Robot& rb, int nb, int body, int j, f3 d, f3 p) {
-  float J = 0.f;
-  if (j < nb && ((M->anc[body] >> j) & 1)) {
-    const float* s = rb.s + j * 6;
-    if (M->jtype[j] == 0) J = dot(d, cross(mk3(s[0], s[1], s[2]), p - mk3(rb.p[j * 3], rb.p[j * 3 + 1], rb.p[j * 3 + 2])));
-    else J = dot(d, mk3(s[3], s[4], s[5]));
-  }
-  return J;
-}
-
 // The sweeps' arithmetic with its fused multiply-adds written out (and no
 // contraction beside them), so that every form of a row update -- a lone
 // body's, a level's, the robot's -- rounds alike whatever code surrounds it,
@@ -1748,17 +1742,25 @@ __device__ __forceinline__ int rob_block(const LdsLayout& Y, int NC, int NR, int
   return off;
 }
 
-__device__ __forceinline__ void phase_rows(const KArgs& a, const Scene& S, float* L, int NC, int NR, int NL,
-                                           uint32_t& status) {
-  const Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
+// Inverse effective masses: rows below 1e-12 are skipped (inverse 0), a
+// friction pair with either one below
+__device__ __forceinline__ void inv_masses(float& W0, float& W1, float& W2, bool& degen) {
+  const bool ok0 = W0 >= 1e-12f, ok1 = W1 >= 1e-12f && W2 >= 1e-12f;
+  W0 = ok0 ? 1.f / W0 : 0.f;
+  W1 = ok1 ? 1.f / W1 : 0.f;
+  W2 = ok1 ? 1.f / W2 : 0.f;
+  degen = degen || !ok0 || !ok1;
+}
+// What the rows need of the free bodies and the joints, a lane per contact:
+// biases, tangents, inverse effective masses; of a robot row the effective
+// masses of its other side.  True when a row is degenerate.
+__device__ __forceinline__ bool rows_free(const KArgs& a, float* L, int NC) {
   const int lane = lane_id();
   const LdsLayout& Y = a.L;
   float* C = L + Y.con;
-  const int cc = Y.ccap;
   const float* F = L + Y.fr;
-  const int fm = Y.fmax;
   const float* A = L + Y.aux;
-  const DModel* M = S.M;
+  bool degen = false;
   // lane per contact: tangents, free / aux effective-mass parts, bias
   for (int ci = lane; ci < NC; ci += WAVE) {
     int info = __float_as_int(C[(ci) * CSTR + C_INFO]);
@@ -1767,7 +1769,9 @@ __device__ __forceinline__ void phase_rows(const KArgs& a, const Scene& S, float
     float bias = phi >= 0.f ? phi / a.h : a.beta * phi / a.h;
     if (side_kind(sA) == K_LIMIT) {
       int x = side_idx(sA);
-      C[(ci) * CSTR + C_IW + 0] = A[A_IM * AMAX + x];  // W = 1 / M~ for J = +-1
+      const float W = A[A_IM * AMAX + x];  // W = 1 / M~ for J = +-1
+      C[(ci) * CSTR + C_IW + 0] = W >= 1e-12f ? 1.f / W : 0.f;
+      degen = degen || !(W >= 1e-12f);
       C[(ci) * CSTR + C_BIAS] = bias;
       for (int t = 0; t < 3; ++t) C[(ci) * CSTR + C_LAM + t] = 0.f;
       continue;
@@ -1806,6 +1810,7 @@ __device__ __forceinline__ void phase_rows(const KArgs& a, const Scene& S, float
         W2n += J2 * J0 * im;
       }
     }
+    if (side_kind(sA) != K_ROBOT) inv_masses(W0, W1, W2, degen);
     C[(ci) * CSTR + C_IW + 0] = W0;
     C[(ci) * CSTR + C_IW + 1] = W1;
     C[(ci) * CSTR + C_IW + 2] = W2;
@@ -1816,85 +1821,94 @@ __device__ __forceinline__ void phase_rows(const KArgs& a, const Scene& S, float
     for (int t = 0; t < 3; ++t) C[(ci) * CSTR + C_LAM + t] = 0.f;
   }
   lds_order();
+  return __ballot(degen) != 0ull;
+}
+// The robot's rows, one after the other: lane (d, j) = (lane >> 4, lane & 15)
+// holds joint j of direction d.  J[d][j] = d . (dp/dq_j), w = M~^-1 J^T by
+// broadcasts within the 16-lane row (DPP, no LDS), W_dd = J_d w_d and the
+// couplings J_d M~^-1 J_n^T of the tangents by 16-lane sums, added to the
+// other side's parts.  What does not change from row to row (the lane's joint,
+// its row of M~^-1) stays in registers and the next contact is loaded ahead.
+// True when a row is degenerate.
+// (With J through LDS, the joint read anew for every row and the inverse
+// masses and the sweeps' blocks in passes of their own a row took 2.3 k
+// cycles.)
+template <int K>
+__device__ __forceinline__ float row_bcast(float v) {  // lane K of the lane's row of 16
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + K, 0xf, 0xf, false));
+}
+template <int K>
+__device__ __forceinline__ float minv_dot(const float* Mi, float J, float acc) {
+  acc = fmaf(Mi[K], row_bcast<K>(J), acc);
+  if constexpr (K + 1 < ND) return minv_dot<K + 1>(Mi, J, acc);
+  else return acc;
+}
+__device__ __forceinline__ bool rows_robot(const KArgs& a, const Scene& S, float* L, int NC, int NR, int NL) {
+  const Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
+  const int lane = lane_id();
+  const LdsLayout& Y = a.L;
+  float* C = L + Y.con;
+  const DModel* M = S.M;
   // lane rr: where robot row rr's block lies
   const int rblk = lane < NR ? rob_block(Y, NC, NR, lane) : -1;
-  // robot rows: lane (d, j) builds J[d][j] = d . (dp/dq_j) and W = J M~^-1 J^T
-  float* Rw = L + Y.rows;
   const int d = lane >> 4, j = lane & 15;
-  for (int rr = 0; rr < NR; ++rr) {
-    const int ci = NL + rr;
-    float* row = Rw + rr * ROW_FLOATS;
-    int info = __float_as_int(C[(ci) * CSTR + C_INFO]);
-    int body = side_idx(info & 0xffff);
-    if (d < 3) {
-      f3 n = mk3(C[(ci) * CSTR + C_N + 0], C[(ci) * CSTR + C_N + 1], C[(ci) * CSTR + C_N + 2]);
-      f3 p = mk3(C[(ci) * CSTR + C_P + 0], C[(ci) * CSTR + C_P + 1], C[(ci) * CSTR + C_P + 2]);
-      f3 t1, t2;
-      onb_a(n, C[(ci) * CSTR + C_ONB], t1, t2);
-      f3 dir = d == 0 ? n : (d == 1 ? t1 : t2);
-      row[d * ND + j] = robot_J(M, rb, S.nb, body, j, dir, p);
-    }
-    lds_order();
-    float w = 0.f;
-    if (d < 3) {
+  const int anc = lane < ND ? (int)M->anc[lane] : 0;
+  const bool rev = M->jtype[j] == 0;
+  const float* sj = rb.s + j * 6 + (rev ? 0 : 3);
+  const f3 ax = mk3(sj[0], sj[1], sj[2]), oj = mk3(rb.p[j * 3], rb.p[j * 3 + 1], rb.p[j * 3 + 2]);
+  float Mi[ND];
 #pragma unroll
-      for (int k = 0; k < ND; ++k) w += rb.Minv[j * ND + k] * row[d * ND + k];
-    }
-    const int blk = rr < WAVE ? __builtin_amdgcn_readlane(rblk, rr) : -1;
-    if (blk >= 0 && d < 3) L[blk + lane] = w;
+  for (int k = 0; k < ND; ++k) Mi[k] = rb.Minv[j * ND + k];
+  float* Rw = L + Y.rows;
+  bool degen = false;
+  for (int rr = 0; rr < NR; ++rr) {
+    float* c = C + (NL + rr) * CSTR;
+    const int body = side_idx(uniform(__float_as_int(c[C_INFO])) & 0xffff);
+    const f3 n = mk3(c[C_N], c[C_N + 1], c[C_N + 2]), p = mk3(c[C_P], c[C_P + 1], c[C_P + 2]);
+    const float ta = c[C_ONB], bias = c[C_BIAS];
+    const float Wo = c[C_IW + (d < 3 ? d : 0)], Wt = c[C_WTN + (d > 1 ? 1 : 0)];
+    f3 t1, t2;
+    onb_a(n, ta, t1, t2);
+    const f3 dir = d == 0 ? n : (d == 1 ? t1 : t2);
+    const bool moves = j < S.nb && ((__builtin_amdgcn_readlane(anc, body) >> j) & 1);
+    const float J = moves ? (rev ? dot(dir, cross(ax, p - oj)) : dot(dir, ax)) : 0.f;
+    const float w = minv_dot<0>(Mi, J, 0.f);
     const float wn = __shfl(w, j, WAVE);  // M~^-1 J_n^T
+    const float W = Wo + sum16(J * w);
+    // (lane 0 of the row speaks for it: the sum's first product may be fused
+    // with an addition, so that the lanes' sums differ in the last bit)
+    const float Wc = row_bcast<0>(Wt + sum16(J * wn));
+    // the three effective masses, of which each lane needs its own inverse
+    float W0 = lane_val(W, 0), W1 = lane_val(W, 16), W2 = lane_val(W, 32);
+    inv_masses(W0, W1, W2, degen);
+    const float iw = d == 0 ? W0 : (d == 1 ? W1 : W2);
     if (d < 3) {
-      // W_dd, and the couplings J_d M~^-1 J_n^T of the tangents (added to
-      // the other side's part of C_WTN)
-      const float Wr = sum16(row[d * ND + j] * w);
-      const float Wc = sum16(row[d * ND + j] * wn);
+      Rw[rr * ROW_FLOATS + lane] = J;
       if (j == 0) {
-        C[(ci) * CSTR + C_IW + d] += Wr;
-        if (d > 0) C[(ci) * CSTR + C_WTN + d - 1] += Wc;
+        c[C_IW + d] = iw;
+        if (d > 0) c[C_WTN + d - 1] = Wc;
       }
     }
-    lds_order();
-  }
-  // inverse effective masses; rows below 1e-12 are skipped (inverse 0), a
-  // friction pair with either one below
-  bool degen = false;
-  for (int ci = lane; ci < NC; ci += WAVE) {
-    float* c = C + ci * CSTR;
-    const bool lim = side_kind(__float_as_int(c[C_INFO]) & 0xffff) == K_LIMIT;
-    const float W0 = c[C_IW], W1 = lim ? 1.f : c[C_IW + 1], W2 = lim ? 1.f : c[C_IW + 2];
-    const bool ok0 = W0 >= 1e-12f, ok1 = W1 >= 1e-12f && W2 >= 1e-12f;
-    c[C_IW] = ok0 ? 1.f / W0 : 0.f;
-    if (!lim) {
-      c[C_IW + 1] = ok1 ? 1.f / W1 : 0.f;
-      c[C_IW + 2] = ok1 ? 1.f / W2 : 0.f;
-    }
-    degen = degen || !ok0 || !ok1;
-  }
-  if (__ballot(degen)) status |= 4u;
-  lds_order();
-  // the robot rows' blocks: lane (d, j) writes value j of direction d, the
-  // last 16 lanes the contact point
-  for (int rr = 0; rr < min(NR, WAVE); ++rr) {
-    const int blk = __builtin_amdgcn_readlane(rblk, rr);
-    if (blk < 0) break;
-    const float* c = C + (NL + rr) * CSTR;
-    const f3 n = mk3(c[C_N], c[C_N + 1], c[C_N + 2]);
-    f3 t1, t2;
-    onb_f(n, c[C_ONB], t1, t2);
+    const int blk = rr < WAVE ? __builtin_amdgcn_readlane(rblk, rr) : -1;
+    if (blk < 0) continue;
+    // the row's block: lane (d, j) writes value j of direction d, the last 16
+    // lanes the contact point
+    onb_f(n, ta, t1, t2);
     const f3 D = d == 0 ? n : (d == 1 ? t1 : t2);
     float v = j == 0 ? D.x : (j == 1 ? D.y : D.z);
-    const int dd = d < 3 ? d : 0;
-    if (j == RB_IW) v = c[C_IW + dd];
-    if (j == RB_WT) v = d == 0 ? 0.f : c[C_WTN + (dd > 0 ? dd - 1 : 0)];
-    if (j == RB_BIAS) v = d == 0 ? c[C_BIAS] : 0.f;
+    if (j == RB_IW) v = iw;
+    if (j == RB_WT) v = d == 0 ? 0.f : Wc;
+    if (j == RB_BIAS) v = d == 0 ? bias : 0.f;
     if (j >= RB_LAM) v = 0.f;
     if (d < 3) {
+      L[blk + lane] = w;
       if (j < 8) L[blk + RB_DIR + 8 * d + j] = v;
     } else if (j < 3) {
-      L[blk + RB_P + j] = c[C_P + j];
+      L[blk + RB_P + j] = j == 0 ? p.x : (j == 1 ? p.y : p.z);
     }
   }
   lds_order();
+  return degen;
 }
 
 // Schedule of the sweeps.  In the canonical order the joint-limit rows come
@@ -1925,7 +1939,8 @@ __device__ __forceinline__ bool row_single(int inf) {
   return side_kind(inf & 0xffff) == K_FREE && side_kind((inf >> 16) & 0xffff) == K_STATIC;
 }
 struct Levels {
-  int ng, maxl;  // groups of free-body rows, levels
+  int ng, maxl;              // groups of free-body rows, levels
+  unsigned long long linked;  // the free bodies some linked row touches (bit f)
 };
 // per group its level and first row (and one entry past the last group)
 __device__ __forceinline__ uint16_t* level_of_groups(float* L, const LdsLayout& Y) {
@@ -2008,6 +2023,17 @@ __device__ __forceinline__ Levels phase_levels(const KArgs& a, float* L, int NC,
     }
   }
   lds_order();
+  // the nodes of the robot's rows and of every group that is not alone
+  for (int ch = 0; ch < nch; ++ch) {
+    const int g = ch * WAVE + lane;
+    if (g < NG && lvl[g] != 0) {
+      int na, nbn;
+      row_nodes(__float_as_int(C[gfirst[g] * CSTR + C_INFO]), na, nbn);
+      atomicOr(nm + nnode * nch, (1ull << na) | (nbn == 63 ? 0ull : 1ull << nbn));
+    }
+  }
+  lds_order();
+  const unsigned long long linked = nm[nnode * nch] >> (1 + AMAX);
   // relax: level(g) = 1 + max(level(prev on node A), level(prev on node B))
   int maxl = 0;
   for (;;) {
@@ -2030,7 +2056,7 @@ __device__ __forceinline__ Levels phase_levels(const KArgs& a, float* L, int NC,
   }
   for (int off = 32; off > 0; off >>= 1) maxl = max(maxl, __shfl_xor(maxl, off, WAVE));
   lds_order();
-  return Levels{uniform(NG), uniform(maxl)};
+  return Levels{uniform(NG), uniform(maxl), uniform64(linked)};
 }
 
 // Scale of a friction pair with squared length nn onto the disk of radius
@@ -2495,10 +2521,12 @@ __device__ __forceinline__ void pgs_linked(const KArgs& a, float* L, int NC, int
     for (int d = 0; d < 3; ++d) C[(NL + lane) * CSTR + C_LAM + d] = L[rblk + RB_DIR + 8 * d + RB_LAM];
 }
 
-__device__ __forceinline__ void integrate_free(const KArgs& a, const Scene& S, float* L) {
+// the free bodies of a mask (lane f: body f)
+__device__ __forceinline__ void integrate_free(const KArgs& a, const Scene& S, float* L, unsigned long long mask) {
   const int lane = lane_id();
   float* F = L + a.L.fr;
-  for (int f = lane; f < S.nf; f += WAVE) {
+  const int f = lane;
+  if (f < S.nf && ((mask >> f) & 1ull)) {
     f3 v = mk3(F[(f) * FSTR + F_V + 0], F[(f) * FSTR + F_V + 1], F[(f) * FSTR + F_V + 2]);
     f3 w = mk3(F[(f) * FSTR + F_W + 0], F[(f) * FSTR + F_W + 1], F[(f) * FSTR + F_W + 2]);
     F[(f) * FSTR + F_X + 0] += a.h * v.x;
@@ -2613,7 +2641,7 @@ __device__ __forceinline__ void phase_forces(const KArgs& a, const Scene& S, flo
 // counts, status and schedule from wavefront 1, the chunks of the robot's candidate
 // list from wavefront 0; at a scene's end wavefront 1's check of the state and
 // the next queue position.
-enum { CTL_NC = 0, CTL_NR, CTL_NL, CTL_STATUS, CTL_NG, CTL_MAXL, CTL_NCA, CTL_BAD, CTL_POS };
+enum { CTL_NC = 0, CTL_NR, CTL_NL, CTL_STATUS, CTL_NG, CTL_MAXL, CTL_LINKED, CTL_NCA = CTL_LINKED + 2, CTL_BAD, CTL_POS };
 static_assert(CTL_POS < CTL_WORDS, "control words");
 
 __device__ __forceinline__ void scene_view(const KArgs& a, int s, Scene& S) {
@@ -2663,6 +2691,7 @@ __device__ __forceinline__ int run_scene(int s, int wv, float* const L0) {
   float frc = 0.f;
   if (wv == 0) {
     load_robot(args_fresh(), S, lds_fresh(L0));
+    kin_aux(args_fresh(), S, lds_fresh(L0));
     if (MODE == 2) {
       // the force sums of the control step: a launch that resumes the step
       // (a.sub0 > 0) continues the sums so far, so that they add up in the
@@ -2686,6 +2715,7 @@ __device__ __forceinline__ int run_scene(int s, int wv, float* const L0) {
   } else {
     load_free(args_fresh(), S, lds_fresh(L0));
   }
+  both_sync();
   MS_PHASE(7)
   float* rec = REC ? a.rec + (size_t)s * a.RL.total : nullptr;
   // the largest contact lists of the step, for the next step's routing
@@ -2697,44 +2727,53 @@ __device__ __forceinline__ int run_scene(int s, int wv, float* const L0) {
     float vR = 0.f;
     int fmem = 0, fob = 0;  // wavefront 1: owners of the lane's body
     uint64_t keysum = 0;
+    // frames and bounds
     if (wv == 0) {
       if (rec) rec_robot(args_fresh(), S, lds_fresh(L0), rec + ks * a.RL.ss);
       phase_drive(args_fresh(), S, lds_fresh(L0));
       kin_robot(args_fresh(), S, lds_fresh(L0));
-    } else {
-      if (rec) rec_free(args_fresh(), S, lds_fresh(L0), rec + ks * a.RL.ss);
-      kin_free(args_fresh(), S, lds_fresh(L0));
-    }
-    both_sync();
-    MS_PHASE(0)
-    if (wv == 0) {
+      MS_PHASE(0)
       if (cull && S.nsph > 0) {
         const int ncA = cull_robot(args_fresh(), S, lds_fresh(L0), args_fresh().margin);
         if (lane_id() == 0) ctl[CTL_NCA] = ncA;
       }
-    } else if (cull) {
-      cull_free(args_fresh(), S, lds_fresh(L0), fmem, fob);
+    } else {
+      if (rec) rec_free(args_fresh(), S, lds_fresh(L0), rec + ks * a.RL.ss);
+      kin_free(args_fresh(), S, lds_fresh(L0));
+      if (cull) cull_free(args_fresh(), S, lds_fresh(L0), fmem, fob);
     }
     both_sync();
     MS_PHASE(1)
+    // the robot's dynamics; the contact list, its schedule and rows
+    Levels lv{0, 0, 0ull};
     if (wv == 0) {
       dyn_robot(args_fresh(), S, lds_fresh(L0), vR);
+      MS_PHASE(2)
     } else {
       Contacts cn;
       emit_contacts(args_fresh(), S, lds_fresh(L0), cull ? uniform(ctl[CTL_NCA]) : 0, fmem, fob, cn);
+      keysum = cn.keysum;
+      const bool over = a.fit_mode == 1 && cn.status;
+      if (!over) {
+        if (rec)
+          rec_contacts(args_fresh(), lds_fresh(L0), cn.nc, cn.nl, cn.nr, rec + a.RL.con + ks * a.RL.cstride);
+        dyn_free(args_fresh(), S, lds_fresh(L0));
+        if (rows_free(args_fresh(), lds_fresh(L0), cn.nc)) cn.status |= 4u;
+        lv = phase_levels(args_fresh(), lds_fresh(L0), cn.nc, cn.nr, cn.nl);
+      }
       if (lane_id() == 0) {
         ctl[CTL_NC] = cn.nc;
         ctl[CTL_NR] = cn.nr;
         ctl[CTL_NL] = cn.nl;
         ctl[CTL_STATUS] = (int)cn.status;
+        ctl[CTL_NG] = lv.ng;
+        ctl[CTL_MAXL] = lv.maxl;
+        ctl[CTL_LINKED] = (int)lv.linked;
+        ctl[CTL_LINKED + 1] = (int)(lv.linked >> 32);
       }
-      keysum = cn.keysum;
-      if (rec && !(a.fit_mode == 1 && cn.status))
-        rec_contacts(args_fresh(), lds_fresh(L0), cn.nc, cn.nl, cn.nr, rec + a.RL.con + ks * a.RL.cstride);
-      dyn_free(args_fresh(), S, lds_fresh(L0));
     }
     both_sync();
-    MS_PHASE(2)
+    MS_PHASE(4)
     const int NC = uniform(ctl[CTL_NC]), NR = uniform(ctl[CTL_NR]), NL = uniform(ctl[CTL_NL]);
     status |= (uint32_t)uniform(ctl[CTL_STATUS]);
     // a launch in a smaller layout gives up a scene at its first overflowing
@@ -2742,46 +2781,39 @@ __device__ __forceinline__ int run_scene(int s, int wv, float* const L0) {
     if (a.fit_mode == 1 && (status & 10u)) break;
     max_nc = max(max_nc, NC - NL);
     max_nr = max(max_nr, NR);
-    Levels lv{0, 0};
-    if (wv == 0) {
-      phase_rows(args_fresh(), S, lds_fresh(L0), NC, NR, NL, status);
-      MS_PHASE(3)
-    } else {
-      lv = phase_levels(args_fresh(), lds_fresh(L0), NC, NR, NL);
-      if (lane_id() == 0) {
-        ctl[CTL_NG] = lv.ng;
-        ctl[CTL_MAXL] = lv.maxl;
-      }
-    }
-    both_sync();
-    MS_PHASE(4)
+    // sweeps and integration, each wavefront of its own bodies
     {
       float* tape = rec ? rec + a.RL.tape + (size_t)ks * a.K * a.RL.tsw : nullptr;
       if (wv == 0) {
-        lv = Levels{uniform(ctl[CTL_NG]), uniform(ctl[CTL_MAXL])};
+        if (rows_robot(args_fresh(), S, lds_fresh(L0), NC, NR, NL)) status |= 4u;
+        MS_PHASE(3)
+        lv.ng = uniform(ctl[CTL_NG]);
+        lv.maxl = uniform(ctl[CTL_MAXL]);
         pgs_linked(args_fresh(), lds_fresh(L0), NC, NL, NR, lv, vR, tape);
         if (MODE == 2) phase_forces(args_fresh(), S, lds_fresh(L0), NL, NR, frc, ks == a.n_sub_total - 1);
+        integrate_robot(args_fresh(), S, lds_fresh(L0), vR);
+        kin_aux(args_fresh(), S, lds_fresh(L0));
+        integrate_free(args_fresh(), S, lds_fresh(L0),
+                       (unsigned long long)(uint32_t)uniform(ctl[CTL_LINKED + 1]) << 32 |
+                           (uint32_t)uniform(ctl[CTL_LINKED]));
+        if (rec && ks == a.n_sub_total - 1) rec_robot(args_fresh(), S, lds_fresh(L0), rec + (ks + 1) * a.RL.ss);
       } else {
         pgs_alone(args_fresh(), lds_fresh(L0), lv.ng, tape);
+        integrate_free(args_fresh(), S, lds_fresh(L0), ~lv.linked);
+        if (a.debug && lane_id() == 0) {
+          uint32_t* d = a.debug + ((size_t)s * a.n_sub_total + a.sub0 + k) * 4;
+          d[0] = (uint32_t)(NC - NL);
+          d[1] = (uint32_t)NR;
+          d[2] = (uint32_t)keysum;
+          d[3] = (uint32_t)(keysum >> 32);
+        }
       }
     }
-    both_sync();
     MS_PHASE(5)
-    if (wv == 0) {
-      integrate_robot(args_fresh(), S, lds_fresh(L0), vR);
-      if (rec && ks == a.n_sub_total - 1) rec_robot(args_fresh(), S, lds_fresh(L0), rec + (ks + 1) * a.RL.ss);
-    } else {
-      integrate_free(args_fresh(), S, lds_fresh(L0));
-      if (rec && ks == a.n_sub_total - 1) rec_free(args_fresh(), S, lds_fresh(L0), rec + (ks + 1) * a.RL.ss);
-      if (a.debug && lane_id() == 0) {
-        uint32_t* d = a.debug + ((size_t)s * a.n_sub_total + a.sub0 + k) * 4;
-        d[0] = (uint32_t)(NC - NL);
-        d[1] = (uint32_t)NR;
-        d[2] = (uint32_t)keysum;
-        d[3] = (uint32_t)(keysum >> 32);
-      }
-    }
+    both_sync();
     MS_PHASE(6)
+    if (REC && wv != 0 && ks == a.n_sub_total - 1)
+      rec_free(args_fresh(), S, lds_fresh(L0), rec + (ks + 1) * a.RL.ss);
   }
   // a launch in a smaller layout stores nothing of a scene whose lists
   // overflowed it: the retry launch steps it again in the full layout, from
@@ -2908,6 +2940,7 @@ __global__ __launch_bounds__(WAVE) void k_spawn_check(KArgs a, uint8_t* collide)
   load_robot(a, S, L);
   load_free(a, S, L);
   kin_robot(a, S, L);
+  kin_aux(a, S, L);
   kin_free(a, S, L);
   ConCtx X;
   con_ctx(a, S, L, X);
