@@ -12,8 +12,8 @@
 // disappear only between evaluations (the contact set is held fixed).
 //
 // Two users:
-//   - the product path, k_step_bwd_wave (ms_backward.hip): one 64-lane
-//     wavefront per scene with its workspace (ws_layout(..., wave = true)) in
+//   - the product path, k_step_bwd_wave (ms_backward.hip): two 64-lane
+//     wavefronts per scene with its workspace (ws_layout(..., wave = true)) in
 //     LDS.  It reads the record the forward kernel wrote (substep states,
 //     contact lists, Gauss-Seidel tape) and recomputes kinematics, dynamics,
 //     M~^-1 and the rows across the lanes; the per-scene engine Eng below
@@ -199,6 +199,7 @@ struct WS {
   int vR, vA, vF, lam, llam, con, lim, rJ, rw;
   int vRb, vAb, vFb, lamb, llamb, limb, conb, rJb, rwb, fb, xb;
   int Mb, sb, Ib, Icb, fbar, abar, vbar, bacc;
+  int ctl;   // the schedule's group and level counts, from one wavefront to the other (wavefront kernel only)
   int lv;    // level schedule (wavefront kernel only)
   int tring;  // two sweeps of the tape staged from the record (wavefront kernel only)
   int trs;    // floats per staged sweep
@@ -265,6 +266,7 @@ MSA_HD inline WS ws_layout(int fmax, int ntmax, int ccap, int rcap, int K, int n
   w.fb = take(fm * FB); w.xb = take(AMAX * XB);
   w.Mb = take(ND * ND);
   w.bacc = take(ND * 9);
+  w.ctl = take(wave ? 2 : 0);
   w.lv = take(wave ? lv_ints(ccap) : 0);
   w.Minv = w.L;  // the elimination runs in registers and replaces M~
   w.lz = take(wave ? ND : 0);

@@ -322,7 +322,7 @@ msa::WS bwd_ws_wave(const ms_batch_desc* d, const Counts& c, int cc = -1, int rc
 // within the CU's 160 KiB, which stays below every measured threshold.
 int bwd_per_cu(size_t lds) {
   int n = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, step_bwd_wave_ptr(), 64, lds) != hipSuccess) n = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, step_bwd_wave_ptr(), BWD_THREADS, lds) != hipSuccess) n = 0;
   const int by_size = (int)(size_t{163840} / (lds + 1024));
   return std::min(n, by_size);
 }

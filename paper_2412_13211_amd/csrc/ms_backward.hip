@@ -37,7 +37,7 @@ namespace {
 // the phase that asks for it instead of being hoisted out of the substep loop
 // into registers that live across the whole step
 __device__ __forceinline__ int lane_id() {
-  int l = threadIdx.x;
+  int l = threadIdx.x & 63;
   asm volatile("" : "+v"(l));
   return l;
 }
@@ -52,11 +52,12 @@ __device__ __forceinline__ float* lds_fresh(float* L) {
   asm volatile("" : "+s"(z));
   return L + z;
 }
-__device__ __forceinline__ void wsync() { __syncthreads(); }
-// Ordering of LDS accesses between the lanes of the workgroup's one
-// wavefront: the LDS executes a wavefront's instructions in issue order, so a
-// read issued after a write sees it; only the compiler must not move memory
-// accesses across (no wait for outstanding accesses, unlike the barrier).
+// both wavefronts of the workgroup
+__device__ __forceinline__ void both_sync() { __syncthreads(); }
+// Ordering of LDS accesses between the lanes of one wavefront: the LDS
+// executes a wavefront's instructions in issue order, so a read issued after a
+// write sees it; only the compiler must not move memory accesses across (no
+// wait for outstanding accesses, unlike the barrier).
 __device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
 __device__ __forceinline__ float bcast0(float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0)); }
 // value of the lane N places along within its row of 16 lanes (DPP row
@@ -756,16 +757,29 @@ __device__ __forceinline__ void zero_lds(float* L, long off, int n) {
   for (int i = lane_id(); i < n; i += 64) L[off + i] = 0.f;
 }
 
-// contact rows (the same quantities as the engine's rows(), limit rows
-// excepted): one lane per contact for the tangents, bias and the free-body
-// and door/drawer shares of W; then one lane per robot row (contact,
-// direction) for J, w = M~^-1 J^T and the robot share of W
-__device__ __forceinline__ void rows_wave(msa::Eng& E, float* L) {
+// Contact rows (the same quantities as the engine's rows(), limit rows
+// excepted).  The sweeps read inverse effective masses (a row below 1e-12, or a
+// friction pair with either one below, is skipped: inverse 0), except where a
+// free body's target is a door / drawer (the engine's form).
+__device__ __forceinline__ bool row_inverse(float* e) {
+  using namespace msa;
+  const bool ok0 = e[C_W] >= 1e-12f, ok1 = e[C_W + 1] >= 1e-12f, ok2 = e[C_W + 2] >= 1e-12f;
+  const Ids id = unpack_ids(e[C_ID]);
+  if (id.ok == 0 || id.tk != 2) {
+    e[C_W] = ok0 ? 1.f / e[C_W] : 0.f;
+    e[C_W + 1] = ok1 && ok2 ? 1.f / e[C_W + 1] : 0.f;
+    e[C_W + 2] = ok1 && ok2 ? 1.f / e[C_W + 2] : 0.f;
+  }
+  return ok0 && ok1 && ok2;
+}
+// One lane per contact: the tangents, bias and the free-body and door/drawer
+// shares of W (of a robot row its target's share only)
+__device__ __forceinline__ void rows_free(msa::Eng& E, float* L) {
   using namespace msa;
   const int lane = lane_id();
   const WS& w = E.w;
-  const DModel& M = *E.sc.M;
   const float h = E.pr.h;
+  bool bad = false;
   for (int ci = lane; ci < E.nc; ci += 64) {
     const long e = w.con + (long)ci * CR;
     V n = E.v3(e + C_N), t1, t2;
@@ -788,8 +802,18 @@ __device__ __forceinline__ void rows_wave(msa::Eng& E, float* L) {
     }
     const float phi = L[e + C_PHI];
     L[e + C_BIAS] = phi >= 0.f ? phi / h : E.pr.beta * phi / h;
+    if (ok != 0) bad |= !row_inverse(L + e);
   }
-  wsync();
+  if (__ballot(bad)) E.status |= Eng::MS_DEGENERATE_BIT;
+  lds_order();
+}
+// robot rows, one lane per (contact, direction, joint): J, w = M~^-1 J^T and the
+// robot's share of W
+__device__ __forceinline__ void rows_robot(msa::Eng& E, float* L) {
+  using namespace msa;
+  const int lane = lane_id();
+  const WS& w = E.w;
+  const DModel& M = *E.sc.M;
   // robot rows, four at a time: lane j of a 16-lane group owns joint j
   const int g = lane >> 4, j = lane & 15, nr = 3 * E.nrob;
   for (int r0 = 0; r0 < nr; r0 += 4) {
@@ -806,7 +830,7 @@ __device__ __forceinline__ void rows_wave(msa::Eng& E, float* L) {
       }
       L[w.rJ + (long)r * ND + j] = Jj;
     }
-    wsync();
+    lds_order();
     // w_j = sum_k (M~^-1)_jk J_k; Minv row k holds M~^-1 e_k
     float s = 0.f;
     if (act)
@@ -817,22 +841,11 @@ __device__ __forceinline__ void rows_wave(msa::Eng& E, float* L) {
       if (j == 0) L[e + C_W + di] += W;
     }
   }
-  wsync();
-  // the sweeps read inverse effective masses (a row below 1e-12, or a friction
-  // pair with either one below, is skipped: inverse 0), except where a free
-  // body's target is a door / drawer (the engine's form)
+  lds_order();
   bool bad = false;
-  for (int ci = lane; ci < E.nc; ci += 64) {
-    float* e = L + w.con + ci * CR;
-    const bool ok0 = e[C_W] >= 1e-12f, ok1 = e[C_W + 1] >= 1e-12f, ok2 = e[C_W + 2] >= 1e-12f;
-    bad |= !(ok0 && ok1 && ok2);
-    const Ids id = unpack_ids(e[C_ID]);
-    if (id.ok != 0 && id.tk == 2) continue;
-    e[C_W] = ok0 ? 1.f / e[C_W] : 0.f;
-    e[C_W + 1] = ok1 && ok2 ? 1.f / e[C_W + 1] : 0.f;
-    e[C_W + 2] = ok1 && ok2 ? 1.f / e[C_W + 2] : 0.f;
-  }
+  for (int ci = lane; ci < E.nrob; ci += 64) bad |= !row_inverse(L + w.con + ci * CR);
   if (__ballot(bad)) E.status |= Eng::MS_DEGENERATE_BIT;
+  lds_order();
 }
 
 // adjoint of the robot rows (the robot owners' share; the engine's
@@ -858,17 +871,17 @@ __device__ __forceinline__ void robot_rows_bar_wave(msa::Eng& E, float* L) {
       Wb = L[w.conb + (long)ci * CB + B_W + di];
       L[w.rwb + rb] += Wb * L[w.rJ + rb];
     }
-    wsync();
+    lds_order();
     float s = 0.f;
     if (act)
       for (int k = 0; k < ND; ++k) s += L[w.Minv + k * ND + jj] * L[w.rwb + (long)r * ND + k];
-    wsync();
+    lds_order();
     if (act) {
       L[w.rJb + rb] += Wb * L[w.rw + rb] + s;
       L[w.rwb + rb] = s;
     }
   }
-  wsync();
+  lds_order();
   // M~bar: lane owns entries lane, lane + 64, ...
   for (int idx = lane; idx < ND * ND; idx += 64) {
     const int rr = idx / ND, cc = idx - ND * (idx / ND);
@@ -920,12 +933,11 @@ __device__ __forceinline__ void robot_rows_bar_wave(msa::Eng& E, float* L) {
       }
     }
   }
-  wsync();
+  lds_order();
 }
 
 // Recompute of a substep's articulated quantities over the lanes: drive
-// (lane per DoF), door/drawer and free-body frames (lane per joint / body),
-// body poses by pointer jumping (lane per body, four doubling rounds),
+// (lane per DoF), body poses by pointer jumping (lane per body, four doubling rounds),
 // per-body quantities (lane per body); CRBA and RNEA with the tree
 // recursions run down or up the tree by one lane per matrix or vector
 // component, the per-body terms one lane per body; M~^-1 by Gauss-Jordan
@@ -938,8 +950,6 @@ __device__ __forceinline__ void recompute_wave(msa::Eng& E, float* L, const floa
   const int nb = E.nb;
   const long s = w.st;
   if (lane < ND) E.drive_one(s, u, lane);
-  if (lane >= ND && lane < ND + E.sc.na) E.aux_frame(s, lane - ND);
-  for (int f = lane; f < E.sc.nf; f += 64) E.free_frame(s, f);
   // body poses: each body's joint transform relative to its parent, then
   // X_i <- X_a X_i with a the current ancestor, a <- a's ancestor, until the
   // root (the ancestor index lives in w.z, free until z is solved)
@@ -962,7 +972,7 @@ __device__ __forceinline__ void recompute_wave(msa::Eng& E, float* L, const floa
     anc = M.parent[i];
     L[w.z + i] = __int_as_float(anc);
   }
-  wsync();
+  lds_order();
   for (int round = 0; round < 4; ++round) {
     float Ra[9], R[9], Rn[9];
     V pa{0.f, 0.f, 0.f}, p{0.f, 0.f, 0.f};
@@ -977,7 +987,7 @@ __device__ __forceinline__ void recompute_wave(msa::Eng& E, float* L, const floa
       p = E.v3(w.kp + lane * 3);
       anc2 = __float_as_int(L[w.z + anc]);
     }
-    wsync();
+    lds_order();
     if (act) {
       mm3(Ra, R, Rn);
       for (int t = 0; t < 9; ++t) L[w.kR + lane * 9 + t] = Rn[t];
@@ -985,7 +995,7 @@ __device__ __forceinline__ void recompute_wave(msa::Eng& E, float* L, const floa
       anc = anc2;
       L[w.z + lane] = __int_as_float(anc);
     }
-    wsync();
+    lds_order();
   }
   // joint axis and origin from the parent's world pose
   if (lane < nb) {
@@ -1004,9 +1014,9 @@ __device__ __forceinline__ void recompute_wave(msa::Eng& E, float* L, const floa
     E.s3(w.ka + i * 3, rmv(Rj, ld3(M.axis[i])));
     E.s3(w.ko + i * 3, o);
   }
-  wsync();
+  lds_order();
   if (lane < nb) E.kin_body(lane);
-  wsync();
+  lds_order();
   // composite inertias (one lane per entry, up the tree) and velocities
   // v_i = v_par + s_i qd_i (one lane per component, down the tree)
   for (int idx = lane; idx < nb * 36; idx += 64) L[w.kIc + idx] = L[w.kI + idx];
@@ -1015,7 +1025,7 @@ __device__ __forceinline__ void recompute_wave(msa::Eng& E, float* L, const floa
     const int r = e >> 4, c = e & 15;
     L[w.L + e] = (r >= nb || c >= nb) && r == c ? 1.f : 0.f;
   }
-  wsync();
+  lds_order();
   if (lane < 36) {
     for (int i = nb - 1; i > 0; --i) {
       const int par = M.parent[i];
@@ -1028,7 +1038,7 @@ __device__ __forceinline__ void recompute_wave(msa::Eng& E, float* L, const floa
       L[w.rv + i * 6 + t] = (par >= 0 ? L[w.rv + par * 6 + t] : 0.f) + L[w.ks + i * 6 + t] * L[s + ND + i];
     }
   }
-  wsync();
+  lds_order();
   // mass matrix row / column i: M_ij = s_j . (Ic_i s_i), j an ancestor of i;
   // the terms v_i x (s_i qd_i) (into ra, summed down the tree below)
   if (lane < nb) {
@@ -1049,7 +1059,7 @@ __device__ __forceinline__ void recompute_wave(msa::Eng& E, float* L, const floa
     Eng::crm6(v, vJ, t6);
     E.st6(w.ra + i * 6, t6);
   }
-  wsync();
+  lds_order();
   // accelerations a_i = a_par + v_i x (s_i qd_i), a_root's parent = -g
   if (lane < 6) {
     const int t = lane;
@@ -1063,7 +1073,7 @@ __device__ __forceinline__ void recompute_wave(msa::Eng& E, float* L, const floa
       L[w.ra + i * 6 + t] += par >= 0 ? L[w.ra + par * 6 + t] : base;
     }
   }
-  wsync();
+  lds_order();
   // body forces f_i = I_i a_i + v_i x* (I_i v_i)
   if (lane < nb) {
     const int i = lane;
@@ -1076,7 +1086,7 @@ __device__ __forceinline__ void recompute_wave(msa::Eng& E, float* L, const floa
     for (int t = 0; t < 6; ++t) fl[t] += t6[t];
     E.st6(w.rff + i * 6, fl);
   }
-  wsync();
+  lds_order();
   // subtree force sums (one lane per component, up the tree)
   if (lane < 6) {
     for (int i = nb - 1; i > 0; --i) {
@@ -1084,7 +1094,7 @@ __device__ __forceinline__ void recompute_wave(msa::Eng& E, float* L, const floa
       if (par >= 0) L[w.rff + par * 6 + lane] += L[w.rff + i * 6 + lane];
     }
   }
-  wsync();
+  lds_order();
   // bias torques C_i = s_i . f_i; M~ = M + diag(armature)
   if (lane < nb) {
     const int i = lane;
@@ -1093,7 +1103,7 @@ __device__ __forceinline__ void recompute_wave(msa::Eng& E, float* L, const floa
     L[w.lz + i] = c;
     L[w.L + i * ND + i] += L[w.arm + i];
   }
-  wsync();
+  lds_order();
   // Gauss-Jordan elimination without pivoting (M~ is symmetric positive
   // definite), in registers: lane i < 16 holds row i; pivot p's row is read
   // from lane p with readlane (the pivot loop is unrolled, so every register
@@ -1157,14 +1167,14 @@ __device__ __forceinline__ void dynamics_bar_wave(msa::Eng& E, float* L) {
     for (int k = 0; k < nb; ++k) lz += L[w.Minv + k * ND + lane] * (h * L[w.vRb + k]);
     L[w.lz + lane] = lane < nb ? lz : 0.f;
   }
-  wsync();
+  lds_order();
   // M~bar -= lz z^T; drive^T
   for (int idx = lane; idx < ND * ND; idx += 64) {
     const int r = idx / ND, c = idx - ND * (idx / ND);
     if (r < nb && c < nb) L[w.Mb + idx] -= L[w.lz + r] * L[w.z + c];
   }
   if (lane < nb) E.drive_bar_one(lane, L[w.lz + lane]);
-  wsync();
+  lds_order();
   // CRBA^T, per body i: F_i = Ic_i s_i, Fbar_i = sum over the ancestors j of
   // c_ij s_j (c_ii = Mbar_ii, c_ij = Mbar_ij + Mbar_ji), Icbar_i = Fbar_i s_i^T
   if (lane < nb) {
@@ -1181,7 +1191,7 @@ __device__ __forceinline__ void dynamics_bar_wave(msa::Eng& E, float* L) {
     for (int r = 0; r < 6; ++r)
       for (int c = 0; c < 6; ++c) L[w.Icb + i * 36 + r * 6 + c] = Fb[r] * si[c];
   }
-  wsync();
+  lds_order();
   // sbar_j = sum over the descendants i of c_ij F_i + Ic_j^T Fbar_j; then
   // RNEA^T: fbar_i = -sum over the ancestors of s_k lz_k, sbar_i -= lz_i f_i
   if (lane < nb) {
@@ -1205,7 +1215,7 @@ __device__ __forceinline__ void dynamics_bar_wave(msa::Eng& E, float* L) {
     for (int t = 0; t < 6; ++t) sb[t] += Cb * L[w.rff + j * 6 + t];
     E.st6(w.sb + j * 6, sb);
   }
-  wsync();
+  lds_order();
   // Ibar_i = Icbar_i + Ibar_par (one lane per entry, down the tree)
   if (lane < 36) {
     for (int i = 0; i < nb; ++i) {
@@ -1213,7 +1223,7 @@ __device__ __forceinline__ void dynamics_bar_wave(msa::Eng& E, float* L) {
       L[w.Ib + i * 36 + lane] = L[w.Icb + i * 36 + lane] + (par >= 0 ? L[w.Ib + par * 36 + lane] : 0.f);
     }
   }
-  wsync();
+  lds_order();
   // body terms of f = I a + v x* (I v): Ibar, the own parts of abar and vbar
   if (lane < nb) {
     const int i = lane;
@@ -1238,7 +1248,7 @@ __device__ __forceinline__ void dynamics_bar_wave(msa::Eng& E, float* L) {
     float ov[6] = {omb.x + t6[0], omb.y + t6[1], omb.z + t6[2], nub.x + t6[3], nub.y + t6[4], nub.z + t6[5]};
     E.st6(w.tV + i * 6, ov);
   }
-  wsync();
+  lds_order();
   // abar_i = subtree sum of the own parts (one lane per component, up the
   // tree); then the a = a_par + v x vJ term's share of vbar_i
   if (lane < 6) {
@@ -1248,7 +1258,7 @@ __device__ __forceinline__ void dynamics_bar_wave(msa::Eng& E, float* L) {
       if (par >= 0) L[w.abar + par * 6 + lane] += L[w.abar + i * 6 + lane];
     }
   }
-  wsync();
+  lds_order();
   if (lane < nb) {
     const int i = lane;
     float ab[6];
@@ -1261,7 +1271,7 @@ __device__ __forceinline__ void dynamics_bar_wave(msa::Eng& E, float* L) {
     float o2[6] = {omb2.x, omb2.y, omb2.z, nub2.x, nub2.y, nub2.z};
     E.st6(w.tV2 + i * 6, o2);
   }
-  wsync();
+  lds_order();
   // vbar_i = subtree sum of both own parts (one lane per component, up the
   // tree); the joint velocity's adjoint
   if (lane < 6) {
@@ -1271,7 +1281,7 @@ __device__ __forceinline__ void dynamics_bar_wave(msa::Eng& E, float* L) {
       if (par >= 0) L[w.vbar + par * 6 + lane] += L[w.vbar + i * 6 + lane];
     }
   }
-  wsync();
+  lds_order();
   if (lane < nb) {
     const int i = lane;
     float vb[6];
@@ -1291,12 +1301,9 @@ __device__ __forceinline__ void dynamics_bar_wave(msa::Eng& E, float* L) {
     }
     L[gB + ND + i] += qdb;
   }
-  wsync();
-  // per body, door / drawer joint and free body
+  lds_order();
   if (lane < nb) E.body_bar_one(lane);
-  if (lane >= ND && lane < ND + E.sc.na) E.aux_dyn_bar_one(lane - ND);
-  for (int f = lane; f < E.sc.nf; f += 64) E.free_dyn_bar_one(s, f);
-  wsync();
+  lds_order();
 }
 
 // kinematics^T: joint k receives a_k . (Mo - o_k x F + Md) (revolute) or
@@ -1339,16 +1346,22 @@ __device__ __forceinline__ void eng_fresh(msa::Eng& E, int s, float* L0, int nc 
   E.cur_s = E.w.st;
 }
 
-// A substep's start state, end velocities and contact list from the record;
-// the contact counts
-__device__ __forceinline__ void load_substep(msa::Eng& E, float* L, const float* st0, const float* st1,
-                                             const float* cr, int& nc, int& nrob, int& nlim) {
+// The robot's part of a substep's start state and end velocities from the record
+__device__ __forceinline__ void load_robot(const msa::Eng& E, float* L, const float* st0, const float* st1) {
+  const int lane = lane_id();
+  const msa::WS& w = E.w;
+  if (lane < 2 * ND) L[w.st + lane] = st0[lane];
+  if (lane < ND) L[w.vR + lane] = st1[ND + lane];
+  lds_order();
+}
+// the free bodies' and joints' part, and the contact list
+__device__ __forceinline__ void load_free(const msa::Eng& E, float* L, const float* st0, const float* st1,
+                                          const float* cr) {
   using namespace msa;
   const int lane = lane_id();
   const WS& w = E.w;
-  const int fm = w.fmax, nf = E.sc.nf;
-  for (int i = lane; i < w.ss; i += 64) L[w.st + i] = st0[i];
-  if (lane < ND) L[w.vR + lane] = st1[ND + lane];
+  const int fm = w.fmax, nf = E.sc.nf, nc = E.nc, NL = E.nlim;
+  for (int i = 2 * ND + lane; i < w.ss; i += 64) L[w.st + i] = st0[i];
   if (lane < E.sc.na) L[w.vA + lane] = st1[32 + 16 * fm + 4 * lane + 1];
   for (int f = lane; f < nf; f += 64) {
     const float* x = st1 + 32 + 16 * f;
@@ -1356,11 +1369,6 @@ __device__ __forceinline__ void load_substep(msa::Eng& E, float* L, const float*
     L[w.vF + f * 6 + 3] = x[12]; L[w.vF + f * 6 + 4] = x[13]; L[w.vF + f * 6 + 5] = x[14];
   }
   // the substep's contacts as the forward kernel emitted them
-  const int NCf = __builtin_amdgcn_readfirstlane(__float_as_int(cr[0]));
-  const int NL = __builtin_amdgcn_readfirstlane(__float_as_int(cr[1]));
-  nrob = __builtin_amdgcn_readfirstlane(__float_as_int(cr[2]));
-  nc = NCf - NL;
-  nlim = NL;
   for (int ci = lane; ci < nc; ci += 64) {
     const float* c = cr + 4 + (size_t)(NL + ci) * CSTR;
     const int info = __float_as_int(c[0]);
@@ -1393,7 +1401,7 @@ __device__ __forceinline__ void load_substep(msa::Eng& E, float* L, const float*
     bs3(E.b, eo + C_N, n);
     bs3(E.b, eo + C_P, p);
   }
-  wsync();
+  lds_order();
 }
 
 // Schedule of the reverse sweeps.  As in the forward sweeps (limit rows, the
@@ -1480,31 +1488,38 @@ __device__ __forceinline__ Sched build_schedule(const msa::Eng& E, float* L) {
   return Sched{G, maxl};
 }
 
-// adjoint accumulators of a substep; integrate^T: lane per DoF, door / drawer
-// joint and free body
-__device__ __forceinline__ void integrate_wave(const msa::Eng& E, float* L) {
+// the robot's adjoint accumulators of a substep; integrate^T: lane per DoF
+__device__ __forceinline__ void integrate_robot(const msa::Eng& E, float* L) {
+  const int lane = lane_id();
+  const msa::WS& w = E.w;
+  zero_lds(L, w.gB, 2 * ND);
+  zero_lds(L, w.vRb, ND);
+  zero_lds(L, w.rJb, E.nrob * 3 * ND);
+  zero_lds(L, w.rwb, E.nrob * 3 * ND);
+  zero_lds(L, w.bacc, ND * 9);
+  zero_lds(L, w.Mb, ND * ND);
+  lds_order();
+  if (lane < ND) E.integrate_bar_dof(lane);
+  lds_order();
+}
+// the free bodies', joints' and contacts'; integrate^T: lane per body and joint
+__device__ __forceinline__ void integrate_free(const msa::Eng& E, float* L) {
   const int lane = lane_id();
   const msa::WS& w = E.w;
   const int fm = w.fmax;
-  zero_lds(L, w.gB, w.ss);
-  zero_lds(L, w.vRb, ND);
+  zero_lds(L, w.gB + 2 * ND, w.ss - 2 * ND);
   zero_lds(L, w.vAb, AMAX);
   zero_lds(L, w.vFb, fm * 6);
   zero_lds(L, w.limb, 2 * AMAX);
   zero_lds(L, w.llamb, 2 * AMAX);
   zero_lds(L, w.lamb, 3 * E.nc);
   zero_lds(L, w.conb, E.nc * msa::CB);
-  zero_lds(L, w.rJb, E.nrob * 3 * ND);
-  zero_lds(L, w.rwb, E.nrob * 3 * ND);
   zero_lds(L, w.fb, fm * msa::FB);
   zero_lds(L, w.xb, AMAX * msa::XB);
-  zero_lds(L, w.bacc, ND * 9);
-  zero_lds(L, w.Mb, ND * ND);
-  wsync();
-  if (lane < ND) E.integrate_bar_dof(lane);
-  if (lane >= ND && lane < ND + AMAX) E.integrate_bar_aux(lane - ND);
+  lds_order();
+  if (lane < AMAX) E.integrate_bar_aux(lane);
   for (int f = lane; f < E.sc.nf; f += 64) E.integrate_bar_free(w.st, f);
-  wsync();
+  lds_order();
 }
 
 // The reverse sweeps of everything that is not alone: per sweep the levels
@@ -1671,14 +1686,35 @@ __device__ __forceinline__ void finish_linked(msa::Eng& E, float* L, Sched sc) {
   }
   if (lane == 0)
     for (int li = 0; li < E.nlim; ++li) E.rows_bar_limit(li);
-  wsync();
+  lds_order();
 }
 
-__device__ void bwd_scene(int s, float* const L0) {
+// Scene s, by the workgroup's two wavefronts (wv).  Wavefront 0 runs the
+// robot's chain, wavefront 1 the free bodies'; per substep, last to first:
+//   0: state of the robot                       1: state, contact list, frames, rows of the
+//                                                  free bodies, schedule, integrate^T
+//   -- barrier --
+//   0: recompute (dynamics, M~^-1), robot rows, 1: sweeps, rows^T, contacts^T of the bodies
+//      integrate^T, sweeps, rows^T, contacts^T     only static targets touch
+//      of everything linked
+//   -- barrier --
+//   0: dynamics^T, kinematics^T                 1: dynamics^T and frames^T of the free bodies
+//                                                  and joints
+// so that up to the next barrier wavefront 1 already works on the substep before.
+// Everything either writes between two barriers (its part of the state and its
+// adjoints, its rows) the other leaves alone there.  The barriers lie outside
+// the branches on wv.
+// (One wavefront doing all in turn left the SIMDs idle most of the time, and LDS
+// holds only three scenes on a CU.  Forward and reverse of a control step of
+// 4096 uneven scenes: 4380 -> 3585 us, of 16 scenes over four steps: 1866 ->
+// 1633 us.)
+__device__ void bwd_scene(int s, int wv, float* const L0) {
   using namespace msa;
   const BwdArgs& a = args_fresh();
   const RecLayout RL = a.RL;
   const float* rec = a.rec + (size_t)s * RL.total;
+  // the phases' time as wavefront 0 sees it, its waits for wavefront 1 with
+  // the state's loads and with the sweeps
   const bool prof = a.cycles != nullptr;
   unsigned long long cyc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   unsigned long long tc = prof ? clock64() : 0;
@@ -1700,108 +1736,165 @@ __device__ void bwd_scene(int s, float* const L0) {
     const int lane = lane_id();
     const WS& w = E.w;
     const size_t S = (size_t)a.S;
-    zero_lds(L, w.gA, w.ss);
-    zero_lds(L, w.ub, ND);
-    wsync();
-    if (lane < ND) {
-      L[w.gA + lane] = a.gxo[16 * (size_t)s + lane];
-      L[w.gA + ND + lane] = a.gxo[16 * S + 16 * (size_t)s + lane];
+    if (wv == 0) {
+      zero_lds(L, w.ub, ND);
+      if (lane < ND) {
+        L[w.gA + lane] = a.gxo[16 * (size_t)s + lane];
+        L[w.gA + ND + lane] = a.gxo[16 * S + 16 * (size_t)s + lane];
+      }
+    } else {
+      zero_lds(L, w.gA + 2 * ND, w.ss - 2 * ND);
+      lds_order();
+      const float* gf = a.gxo + 32 * S + 16 * (size_t)D.f0;
+      for (int i = lane; i < D.nf * 16; i += 64) L[w.gA + 32 + i] = gf[i];
+      if (lane < D.na * 4)
+        L[w.gA + 32 + 16 * w.fmax + lane] = a.gxo[32 * S + 16 * (size_t)a.NF + 4 * (size_t)D.a0 + lane];
     }
-    const float* gf = a.gxo + 32 * S + 16 * (size_t)D.f0;
-    for (int i = lane; i < D.nf * 16; i += 64) L[w.gA + 32 + i] = gf[i];
-    if (lane < D.na * 4)
-      L[w.gA + 32 + 16 * w.fmax + lane] = a.gxo[32 * S + 16 * (size_t)a.NF + 4 * (size_t)D.a0 + lane];
-    wsync();
+    lds_order();
   }
   const int nsub = a.pr.nsub;
 #pragma unroll 1
   for (int si = nsub - 1; si >= 0; --si) {
-    int nc, nrob, nlim;
-    {
-      Eng E;
-      eng_fresh(E, s, L0);
-      load_substep(E, E.b.p, rec + (size_t)si * RL.ss, rec + (size_t)(si + 1) * RL.ss,
-                   rec + RL.con + (size_t)si * RL.cstride, nc, nrob, nlim);
-    }
-    phase(0);
-    // recompute: drive, kinematics, frames and dynamics (without the
-    // unconstrained velocities); M~^-1 and the contact rows over the lanes; the
-    // limit rows on one lane
-    {
-      Eng E;
-      eng_fresh(E, s, L0, nc, nrob, nlim);
-      recompute_wave(E, E.b.p, args_fresh().u + 16 * (size_t)s);
-      status |= E.status;
-    }
-    phase(1);
-    wsync();
-    {
-      Eng E;
-      eng_fresh(E, s, L0, nc, nrob, nlim);
-      solve_z_wave(E, E.b.p);
-      rows_wave(E, E.b.p);
-      if (lane_id() == 0) {
-        E.build_lims();
-        if (E.nlim != nlim) E.status |= MS_ST_RECORD;
-      }
-      status |= E.status;
-      wsync();
-    }
-    Sched sc;
-    {
-      Eng E;
-      eng_fresh(E, s, L0, nc, nrob, nlim);
-      sc = build_schedule(E, E.b.p);
-      sc.ng = __builtin_amdgcn_readfirstlane(sc.ng);
-      sc.maxl = __builtin_amdgcn_readfirstlane(sc.maxl);
-    }
-    phase(2);
-    {
-      Eng E;
-      eng_fresh(E, s, L0, nc, nrob, nlim);
-      integrate_wave(E, E.b.p);
-    }
-    phase(3);
-    // Gauss-Seidel sweeps in reverse
+    const float* cr = rec + RL.con + (size_t)si * RL.cstride;
     const float* tape_g = rec + RL.tape + (size_t)si * a.pr.K * RL.tsw;
-    {
+    const int nlim = __builtin_amdgcn_readfirstlane(__float_as_int(cr[1]));
+    const int nc = __builtin_amdgcn_readfirstlane(__float_as_int(cr[0])) - nlim;
+    const int nrob = __builtin_amdgcn_readfirstlane(__float_as_int(cr[2]));
+    const float *st0 = rec + (size_t)si * RL.ss, *st1 = st0 + RL.ss;
+    Sched sc{0, 0};
+    if (wv == 0) {
+      Eng E;
+      eng_fresh(E, s, L0, nc, nrob, nlim);
+      load_robot(E, E.b.p, st0, st1);
+    } else {
+      {
+        Eng E;
+        eng_fresh(E, s, L0, nc, nrob, nlim);
+        load_free(E, E.b.p, st0, st1, cr);
+        const int lane = lane_id();
+        if (lane >= ND && lane < ND + E.sc.na) E.aux_frame(E.w.st, lane - ND);
+        for (int f = lane; f < E.sc.nf; f += 64) E.free_frame(E.w.st, f);
+        lds_order();
+      }
+      {
+        Eng E;
+        eng_fresh(E, s, L0, nc, nrob, nlim);
+        rows_free(E, E.b.p);
+        // the limit rows on one lane
+        if (lane_id() == 0) {
+          E.build_lims();
+          if (E.nlim != nlim) E.status |= MS_ST_RECORD;
+        }
+        status |= E.status;
+        lds_order();
+      }
+      {
+        Eng E;
+        eng_fresh(E, s, L0, nc, nrob, nlim);
+        sc = build_schedule(E, E.b.p);
+        sc.ng = __builtin_amdgcn_readfirstlane(sc.ng);
+        sc.maxl = __builtin_amdgcn_readfirstlane(sc.maxl);
+        int* ctl = reinterpret_cast<int*>(E.b.p + E.w.ctl);
+        if (lane_id() == 0) {
+          ctl[0] = sc.ng;
+          ctl[1] = sc.maxl;
+        }
+      }
+      {
+        Eng E;
+        eng_fresh(E, s, L0, nc, nrob, nlim);
+        integrate_free(E, E.b.p);
+      }
+    }
+    both_sync();
+    phase(0);
+    if (wv == 0) {
+      // drive, kinematics and dynamics (without the unconstrained velocities),
+      // M~^-1, the robot's rows
+      {
+        Eng E;
+        eng_fresh(E, s, L0, nc, nrob, nlim);
+        recompute_wave(E, E.b.p, args_fresh().u + 16 * (size_t)s);
+        status |= E.status;
+      }
+      phase(1);
+      lds_order();
+      {
+        Eng E;
+        eng_fresh(E, s, L0, nc, nrob, nlim);
+        const int* ctl = reinterpret_cast<const int*>(E.b.p + E.w.ctl);
+        sc.ng = __builtin_amdgcn_readfirstlane(ctl[0]);
+        sc.maxl = __builtin_amdgcn_readfirstlane(ctl[1]);
+        solve_z_wave(E, E.b.p);
+        rows_robot(E, E.b.p);
+        status |= E.status;
+      }
+      phase(2);
+      {
+        Eng E;
+        eng_fresh(E, s, L0, nc, nrob, nlim);
+        integrate_robot(E, E.b.p);
+      }
+      phase(3);
+      // Gauss-Seidel sweeps in reverse
+      {
+        Eng E;
+        eng_fresh(E, s, L0, nc, nrob, nlim);
+        gs_linked_bar(E, E.b.p, sc, tape_g, RL.tsw);
+      }
+      phase(4);
+      {
+        Eng E;
+        eng_fresh(E, s, L0, nc, nrob, nlim);
+        finish_linked(E, E.b.p, sc);
+      }
+      phase(5);
+    } else {
       Eng E;
       eng_fresh(E, s, L0, nc, nrob, nlim);
       gs_alone_bar(E, E.b.p, lv_view(E.b.p, E.w), sc.ng, tape_g, RL.tsw);
     }
-    {
-      Eng E;
-      eng_fresh(E, s, L0, nc, nrob, nlim);
-      gs_linked_bar(E, E.b.p, sc, tape_g, RL.tsw);
-    }
+    both_sync();
     phase(4);
-    {
-      Eng E;
-      eng_fresh(E, s, L0, nc, nrob, nlim);
-      finish_linked(E, E.b.p, sc);
-    }
-    phase(5);
-    {
-      Eng E;
-      eng_fresh(E, s, L0, nc, nrob, nlim);
-      dynamics_bar_wave(E, E.b.p);
-    }
-    phase(6);
-    // frames^T per free body / joint; kinematics^T per joint
-    {
+    if (wv == 0) {
+      {
+        Eng E;
+        eng_fresh(E, s, L0, nc, nrob, nlim);
+        dynamics_bar_wave(E, E.b.p);
+      }
+      phase(6);
+      // kinematics^T per joint
+      {
+        Eng E;
+        eng_fresh(E, s, L0, nc, nrob, nlim);
+        float* L = E.b.p;
+        const WS& w = E.w;
+        const int lane = lane_id();
+        kin_bar_wave(E, L);
+        lds_order();
+        if (lane < 2 * ND) L[w.gA + lane] = L[w.gB + lane];
+        lds_order();
+      }
+      phase(7);
+    } else {
+      // dynamics^T and frames^T per free body / joint
       Eng E;
       eng_fresh(E, s, L0, nc, nrob, nlim);
       float* L = E.b.p;
       const WS& w = E.w;
       const int lane = lane_id();
-      for (int f = lane; f < E.sc.nf; f += 64) E.free_frame_bar(w.st, f);
-      if (lane >= ND && lane < ND + E.sc.na) E.aux_frame_bar(lane - ND);
-      kin_bar_wave(E, L);
-      wsync();
-      for (int i = lane; i < w.ss; i += 64) L[w.gA + i] = L[w.gB + i];
-      wsync();
+      if (lane >= ND && lane < ND + E.sc.na) {
+        E.aux_dyn_bar_one(lane - ND);
+        E.aux_frame_bar(lane - ND);
+      }
+      for (int f = lane; f < E.sc.nf; f += 64) {
+        E.free_dyn_bar_one(w.st, f);
+        E.free_frame_bar(w.st, f);
+      }
+      lds_order();
+      for (int i = 2 * ND + lane; i < w.ss; i += 64) L[w.gA + i] = L[w.gB + i];
+      lds_order();
     }
-    phase(7);
   }
   {
     Eng E;
@@ -1812,18 +1905,21 @@ __device__ void bwd_scene(int s, float* const L0) {
     const int lane = lane_id();
     const WS& w = E.w;
     const size_t S = (size_t)a.S;
-    if (lane < ND) {
-      a.gxi[16 * (size_t)s + lane] = L[w.gA + lane];
-      a.gxi[16 * S + 16 * (size_t)s + lane] = L[w.gA + ND + lane];
-      a.gu[16 * (size_t)s + lane] = L[w.ub + lane];
+    if (wv == 0) {
+      if (lane < ND) {
+        a.gxi[16 * (size_t)s + lane] = L[w.gA + lane];
+        a.gxi[16 * S + 16 * (size_t)s + lane] = L[w.gA + ND + lane];
+        a.gu[16 * (size_t)s + lane] = L[w.ub + lane];
+      }
+    } else {
+      float* gf = a.gxi + 32 * S + 16 * (size_t)D.f0;
+      for (int i = lane; i < D.nf * 16; i += 64) gf[i] = L[w.gA + 32 + i];
+      if (lane < D.na * 4)
+        a.gxi[32 * S + 16 * (size_t)a.NF + 4 * (size_t)D.a0 + lane] = L[w.gA + 32 + 16 * w.fmax + lane];
     }
-    float* gf = a.gxi + 32 * S + 16 * (size_t)D.f0;
-    for (int i = lane; i < D.nf * 16; i += 64) gf[i] = L[w.gA + 32 + i];
-    if (lane < D.na * 4)
-      a.gxi[32 * S + 16 * (size_t)a.NF + 4 * (size_t)D.a0 + lane] = L[w.gA + 32 + 16 * w.fmax + lane];
     // the status bits lane 0 met
-    if (lane == 0 && status) a.status[s] |= status;
-    if (prof && lane == 0)
+    if (lane == 0 && status) atomicOr(a.status + s, status);
+    if (prof && lane == 0 && wv == 0)
       for (int k = 0; k < 8; ++k) a.cycles[(size_t)s * 8 + k] = cyc[k];
   }
 }
@@ -1859,24 +1955,25 @@ __device__ __forceinline__ int wave_scan(int v) {
 
 // the LDS layout must hold the scene's lists (else the scene is flagged and
 // left out)
-__device__ void bwd_checked(const BwdArgs& a, int s, float* lds) {
+__device__ void bwd_checked(const BwdArgs& a, int s, int wv, float* lds) {
   if (!rec_fits(a.rec, a.RL, a.pr.nsub, s, a.w.ccap, a.w.rcap)) {
-    if (lane_id() == 0) a.status[s] |= MS_ST_RECORD;
+    if (threadIdx.x == 0) a.status[s] |= MS_ST_RECORD;
     return;
   }
-  bwd_scene(s, lds);
+  bwd_scene(s, wv, lds);
 }
 
-__global__ __launch_bounds__(64) void k_step_bwd_wave(BwdArgs a) {
+__global__ __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_step_bwd_wave(BwdArgs a) {
   extern __shared__ float lds[];
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   // mode 2 loops over the first *n_over positions; modes 0 and 1 take one
   // position each (one call site keeps the scene's code inlined)
   const bool loop = a.fit_mode == 2;
   const int end = loop ? *a.n_over : a.S;
   const int step = loop ? (int)gridDim.x : a.S;
   for (int pos = (a.fit_mode == 1 ? *a.n_over : 0) + (int)blockIdx.x; pos < end; pos += step) {
-    bwd_checked(a, __builtin_amdgcn_readfirstlane(a.order[pos]), lds);
-    wsync();
+    bwd_checked(a, __builtin_amdgcn_readfirstlane(a.order[pos]), wv, lds);
+    both_sync();
   }
 }
 
@@ -1944,7 +2041,7 @@ void launch_bwd_order(const float* rec, const RecLayout& RL, int S, int nsub, in
 }
 
 void launch_step_bwd_wave(const BwdArgs& a, size_t lds_bytes, int grid, hipStream_t st) {
-  hipLaunchKernelGGL(k_step_bwd_wave, dim3(grid), dim3(64), lds_bytes, st, a);
+  hipLaunchKernelGGL(k_step_bwd_wave, dim3(grid), dim3(BWD_THREADS), lds_bytes, st, a);
 }
 const void* step_bwd_wave_ptr() { return reinterpret_cast<const void*>(&k_step_bwd_wave); }
 

@@ -18,6 +18,7 @@ constexpr int SPH = 128;      // max robot collision spheres
 constexpr int WAVE = 64;
 constexpr int CTL_WORDS = 12;  // words the wavefronts of the forward step exchange in LDS
 constexpr int STEP_THREADS = 2 * WAVE;  // the forward step's workgroup: two wavefronts per scene
+constexpr int BWD_THREADS = 2 * WAVE;   // the wavefront adjoint's
 constexpr int AMAX = 4;       // max door / drawer joints per scene
 constexpr int PMAX = 8;       // max planes per scene
 constexpr int FMAXL = 58;     // max free bodies per scene (node ids 1 + AMAX + f < 63)
