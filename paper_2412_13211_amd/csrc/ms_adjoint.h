@@ -224,6 +224,8 @@ MSA_HD inline WS ws_layout(int fmax, int ntmax, int ccap, int rcap, int K, int n
   const int fm = w.fmax;
   int o = 0;
   auto take = [&](int n) { int r = o; o += n; return r; };
+  // the wavefront kernel reads some arrays with 8 and 16 byte loads
+  auto align = [&]() { if (wave) o = (o + 3) & ~3; };
   w.st = take((wave ? 1 : nsub + 1) * w.ss);
   w.gA = take(w.ss);
   w.gB = take(w.ss);
@@ -236,6 +238,7 @@ MSA_HD inline WS ws_layout(int fmax, int ntmax, int ccap, int rcap, int K, int n
   w.fR = take(fm * 9); w.fIw = take(fm * 9); w.fIi = take(fm * 9); w.fim = take(fm);
   w.xR = take(AMAX * 9); w.xbc = take(AMAX * 3); w.xa = take(AMAX * 3); w.xo = take(AMAX * 3);
   w.xM = take(AMAX); w.xC = take(AMAX); w.xty = take(AMAX);
+  align();
   w.tau = take(ND); w.arm = take(ND); w.L = take(ND * ND); w.z = take(ND);
   w.rv = take(ND * 6); w.ra = take(ND * 6); w.rfl = take(wave ? 0 : ND * 6); w.rff = take(ND * 6);
   w.vR = take(ND); w.vA = take(AMAX); w.vF = take(fm * 6);
@@ -256,6 +259,7 @@ MSA_HD inline WS ws_layout(int fmax, int ntmax, int ccap, int rcap, int K, int n
   const int rows_b = 2 * w.rcap * 3 * ND;
   const int live_b = rows_b + (wave ? 2 * w.trs : 0);
   const int dyn_b = ND * 6 + (wave ? 1 : 2) * ND * 36 + 8 * ND * 6;
+  align();
   const int kb = take(live_b > dyn_b ? live_b : dyn_b);
   w.rJb = kb; w.rwb = kb + w.rcap * 3 * ND;
   w.tring = wave ? kb + rows_b : 0;

@@ -848,100 +848,237 @@ __device__ __forceinline__ void rows_robot(msa::Eng& E, float* L) {
   lds_order();
 }
 
+// Lane (g, i) = (lane >> 4, lane & 15) of the sums over the robot's tree: body
+// i, and of its quantities the components g selects (two of a 6-vector, two
+// rows of a 6x6; the last 16 lanes repeat the third group's and store
+// nothing).  A sum over the ancestors or descendants of every body is then
+// one pass over the bodies k, whose terms all lanes read with broadcast loads
+// that do not wait for one another, each lane taking those its mask names.
+// (Running the recursions along the tree, a lane per component, made chains of
+// dependent LDS rounds with a parent's index from memory in each.  Per substep
+// of the 15-joint robot among 4096 uneven scenes: recompute 50 -> 27 k cycles,
+// dynamics^T 57 -> 17 k; forward and reverse of the batch 3585 -> 2930 us.)
+struct Tree {
+  int g, i, gc;
+  uint32_t am, dm;  // ancestors and descendants of body i, itself included (none past the robot's bodies)
+};
+__device__ __forceinline__ Tree tree_of(const msa::Eng& E) {
+  Tree T;
+  const int lane = lane_id();
+  T.g = lane >> 4;
+  T.i = lane & 15;
+  T.gc = T.g < 3 ? T.g : 2;
+  T.am = T.i < E.nb ? (uint32_t)E.sc.M->anc[T.i] : 0u;
+  T.dm = 0u;
+#pragma unroll
+  for (int k = 0; k < ND; ++k)
+    T.dm |= (((uint32_t)__builtin_amdgcn_readlane((int)T.am, k) >> T.i) & 1u) << k;
+  return T;
+}
+// Two components of the sum of the 6-vectors at off over the ancestors, root
+// first (added to r), or over the descendants, last first: along a chain the
+// order of the recursions, whose sums' rounding an ill-conditioned M~ amplifies.
+__device__ __forceinline__ float2 sum_anc(const float* L, long off, const Tree& T, int nb, float2 r) {
+  for (int k0 = 0; k0 < nb; k0 += 4) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int k = k0 + u;
+      const float2 v = *reinterpret_cast<const float2*>(L + off + k * 6 + 2 * T.gc);
+      const bool on = (T.am >> k) & 1u;
+      r.x += on ? v.x : 0.f;
+      r.y += on ? v.y : 0.f;
+    }
+  }
+  return r;
+}
+__device__ __forceinline__ float2 sum_desc(const float* L, long off, const Tree& T, int nb) {
+  float2 r = make_float2(0.f, 0.f);
+  for (int k0 = (nb - 1) & ~3; k0 >= 0; k0 -= 4) {
+#pragma unroll
+    for (int u = 3; u >= 0; --u) {
+      const int k = k0 + u;
+      const float2 v = *reinterpret_cast<const float2*>(L + off + k * 6 + 2 * T.gc);
+      const bool on = (T.dm >> k) & 1u;
+      r.x += on ? v.x : 0.f;
+      r.y += on ? v.y : 0.f;
+    }
+  }
+  return r;
+}
+__device__ __forceinline__ void st2(float* L, long off, const Tree& T, int nb, float2 v) {
+  if (T.g < 3 && T.i < nb) *reinterpret_cast<float2*>(L + off + T.i * 6 + 2 * T.gc) = v;
+}
+__device__ __forceinline__ float2 ld2(const float* L, long off, const Tree& T) {
+  return *reinterpret_cast<const float2*>(L + off + T.i * 6 + 2 * T.gc);
+}
+// rows 2 gc and 2 gc + 1 of body i's 6x6 matrix at off
+__device__ __forceinline__ void ld_rows(const float* L, long off, const Tree& T, float* R) {
+  const float4* q = reinterpret_cast<const float4*>(L + off + T.i * 36 + 12 * T.gc);
+#pragma unroll
+  for (int t = 0; t < 3; ++t) {
+    const float4 v = q[t];
+    R[4 * t] = v.x; R[4 * t + 1] = v.y; R[4 * t + 2] = v.z; R[4 * t + 3] = v.w;
+  }
+}
+__device__ __forceinline__ float2 rows_dot(const float* R, const float* v) {
+  float2 r = make_float2(0.f, 0.f);
+#pragma unroll
+  for (int t = 0; t < 6; ++t) {
+    r.x += R[t] * v[t];
+    r.y += R[6 + t] * v[t];
+  }
+  return r;
+}
+// components 2 gc and 2 gc + 1 of a 6-vector in registers (by value: selects
+// between array elements become an indexed load from scratch memory)
+__device__ __forceinline__ float2 pick2(float v0, float v1, float v2, float v3, float v4, float v5, const Tree& T) {
+  return make_float2(T.gc == 0 ? v0 : (T.gc == 1 ? v2 : v4), T.gc == 0 ? v1 : (T.gc == 1 ? v3 : v5));
+}
+// value of lane K of the lane's row of 16
+template <int K>
+__device__ __forceinline__ float row_bcast(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + K, 0xf, 0xf, false));
+}
+// row Q of 16 lanes in all four
+template <int Q>
+__device__ __forceinline__ float bcast_row(float v) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_int(v), __float_as_int(v), false, false);
+  const int y = a[Q & 1];
+  const auto b = __builtin_amdgcn_permlane32_swap(y, y, false, false);
+  return __int_as_float(b[Q >> 1]);
+}
+// Gauss-Jordan elimination without pivoting (M~ is symmetric positive
+// definite) in registers: lane (g, c) holds rows 4 g .. 4 g + 3 of column c,
+// the pivot row comes to all lanes by row swaps, a row's factor from its
+// lane p by a DPP broadcast.  True when a pivot of the robot's joints was not
+// positive.
+template <int P>
+__device__ __forceinline__ bool gj_step(float* e, int g, int c, int nb) {
+  constexpr int Q = P >> 2, R = P & 3;
+  const float prow = bcast_row<Q>(e[R]);
+  float piv = row_bcast<P>(prow);
+  bool degen = false;
+  if (P < nb && !(piv > 0.f)) {
+    degen = true;
+    piv = 1e-30f;
+  }
+  const float inv = 1.f / piv;
+  const float pn = prow * inv;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const float f = row_bcast<P>(e[r]);
+    const float x = c == P ? -f * inv : e[r] - f * pn;
+    e[r] = r == R && g == Q ? (c == P ? inv : pn) : x;
+  }
+  if constexpr (P + 1 < ND) return gj_step<P + 1>(e, g, c, nb) || degen;
+  else return degen;
+}
+
+// column j of the symmetric M~^-1 times a vector of which lane j of each row of
+// 16 holds entry j (0 past the robot's DoFs)
+template <int K>
+__device__ __forceinline__ float minv_dot(const float* Mj, float x, float acc = 0.f) {  // Mj: lane j's entries, in registers
+  acc = fmaf(Mj[K], row_bcast<K>(x), acc);
+  if constexpr (K + 1 < ND) return minv_dot<K + 1>(Mj, x, acc);
+  else return acc;
+}
+__device__ __forceinline__ float minv_times(const float* Minv_j, float x) {  // Minv_j: column j in LDS
+  float Mj[ND];
+#pragma unroll
+  for (int k = 0; k < ND; ++k) Mj[k] = Minv_j[k * ND];
+  return minv_dot<0>(Mj, x);
+}
 // adjoint of the robot rows (the robot owners' share; the engine's
 // rows_bar(false) does the rest).  With w = M~^-1 J^T and W += J . w:
 // Jbar += Wbar w + M~^-1 (wbar + Wbar J), M~bar -= M~^-1 (wbar + Wbar J) w^T;
-// Jbar then reaches the directions, the contact point and the joint axes
+// Jbar then reaches the directions, the contact point and the joint axes.
+// Four rows (contact, direction) at a time, lane j of a 16-lane group owns joint
+// j: its row of M~^-1, axis and accumulators stay in registers over the rows.
+// (In passes of their own over the rows, with the bodies' ancestors read from
+// memory for every row and joint, nine contacts took 21 k cycles, now 8 k.)
 __device__ __forceinline__ void robot_rows_bar_wave(msa::Eng& E, float* L) {
   using namespace msa;
   const int lane = lane_id();
   const WS& w = E.w;
   const DModel& M = *E.sc.M;
   const int nb = E.nb, nr = 3 * E.nrob;
-  // robot rows four at a time (lane j of a 16-lane group owns entry j):
-  // Jbar into rJb, alpha = M~^-1 (wbar + Wbar J) into rwb
-  const int g = lane >> 4, jj = lane & 15;
+  if (nr == 0) return;
+  const int g = lane >> 4, j = lane & 15;
+  auto anc_of = [&](int ci) { return (int)M.anc[M.sph_body[unpack_ids(L[w.con + ci * CR + C_ID]).oi]]; };
+  const int anc0 = lane < E.nrob ? anc_of(lane) : 0;
+  float Mj[ND];
+#pragma unroll
+  for (int k = 0; k < ND; ++k) Mj[k] = L[w.Minv + k * ND + j];
+  const bool rev = M.jtype[j] == 0;
+  V a{0.f, 0.f, 0.f}, o{0.f, 0.f, 0.f};  // (past the robot's joints the LDS holds anything)
+  if (j < nb) {
+    a = E.v3(w.ka + j * 3);
+    o = E.v3(w.ko + j * 3);
+  }
+  V X{0.f, 0.f, 0.f}, Y{0.f, 0.f, 0.f};  // adjoints of the joint's axis (before a x) and point
+#pragma unroll 1
   for (int r0 = 0; r0 < nr; r0 += 4) {
-    const int r = r0 + g;
-    const bool act = r < nr;
-    const int ci = r / 3, di = r - 3 * (r / 3);
-    const long rb = (long)r * ND + jj;
-    float Wb = 0.f;
-    if (act) {
-      Wb = L[w.conb + (long)ci * CB + B_W + di];
-      L[w.rwb + rb] += Wb * L[w.rJ + rb];
-    }
-    lds_order();
-    float s = 0.f;
-    if (act)
-      for (int k = 0; k < ND; ++k) s += L[w.Minv + k * ND + jj] * L[w.rwb + (long)r * ND + k];
-    lds_order();
-    if (act) {
-      L[w.rJb + rb] += Wb * L[w.rw + rb] + s;
-      L[w.rwb + rb] = s;
+    const bool act = r0 + g < nr;
+    const int r = act ? r0 + g : nr - 1, ci = r / 3, di = r - 3 * ci;
+    const float* e = L + w.con + ci * CR;
+    float* cb = L + w.conb + ci * CB;
+    const int rb = r * ND + j;
+    const float Wb = cb[B_W + di], wr = L[w.rw + rb], jb = L[w.rJb + rb];
+    const float xr = L[w.rwb + rb] + Wb * L[w.rJ + rb];
+    const V p{e[C_P], e[C_P + 1], e[C_P + 2]}, d = E.dir(w.con + (long)ci * CR, di);
+    int an = __shfl(anc0, ci & 63, 64);
+    if (ci >= 64) an = anc_of(ci);
+    const float s = minv_dot<0>(Mj, act ? xr : 0.f);
+    if (act) L[w.rwb + rb] = s;
+    const float Jb = act && j < nb && ((an >> j) & 1) ? jb + Wb * wr + s : 0.f;
+    const V ev = p - o;
+    const V c = rev ? cross(a, ev) : a, ar = rev ? a : V{0.f, 0.f, 0.f};
+    const V xd = rev ? cross(ev, d) : d;
+    X = X + xd * Jb;
+    Y = Y - cross(d, ar) * Jb;
+    const V db{sum16(c.x * Jb), sum16(c.y * Jb), sum16(c.z * Jb)};
+    const V pb = cross(d, V{sum16(ar.x * Jb), sum16(ar.y * Jb), sum16(ar.z * Jb)});
+    if (act && j == 0) {
+      cb[B_D + 3 * di] += db.x;
+      cb[B_D + 3 * di + 1] += db.y;
+      cb[B_D + 3 * di + 2] += db.z;
+      unsafeAtomicAdd(cb + B_P, pb.x);
+      unsafeAtomicAdd(cb + B_P + 1, pb.y);
+      unsafeAtomicAdd(cb + B_P + 2, pb.z);
     }
   }
   lds_order();
-  // M~bar: lane owns entries lane, lane + 64, ...
-  for (int idx = lane; idx < ND * ND; idx += 64) {
-    const int rr = idx / ND, cc = idx - ND * (idx / ND);
-    float s = 0.f;
-    for (int q = 0; q < nr; ++q) s += L[w.rwb + (long)q * ND + rr] * L[w.rw + (long)q * ND + cc];
-    L[w.Mb + idx] -= s;
+  // the joints' own body accumulators, from the four groups
+  auto all4 = [&](V v) {
+    v = v + V{__shfl_xor(v.x, 16, 64), __shfl_xor(v.y, 16, 64), __shfl_xor(v.z, 16, 64)};
+    return v + V{__shfl_xor(v.x, 32, 64), __shfl_xor(v.y, 32, 64), __shfl_xor(v.z, 32, 64)};
+  };
+  X = all4(X);
+  Y = all4(Y);
+  if (lane < nb) {
+    E.acc_dir(lane, a, X);
+    E.acc_point(lane, o, Y);
   }
-  // lane per robot contact: direction and contact-point adjoints
-  for (int ci = lane; ci < E.nrob; ci += 64) {
-    const long e = w.con + (long)ci * CR, cb = w.conb + (long)ci * CB;
-    const V p = E.v3(e + C_P);
-    const int anc = M.anc[M.sph_body[unpack_ids(L[e + C_ID]).oi]];
-    V pb{0.f, 0.f, 0.f};
-    for (int di = 0; di < 3; ++di) {
-      const V d = E.dir(e, di);
-      const long rjb = w.rJb + ((long)ci * 3 + di) * ND;
-      V db{0.f, 0.f, 0.f};
-      for (int j = 0; j < nb; ++j) {
-        const float Jb = L[rjb + j];
-        if (!((anc >> j) & 1) || Jb == 0.f) continue;
-        const V a = E.v3(w.ka + j * 3);
-        if (M.jtype[j] == 0) {
-          db = db + cross(a, p - E.v3(w.ko + j * 3)) * Jb;
-          pb = pb + cross(d, a) * Jb;
-        } else {
-          db = db + a * Jb;
-        }
-      }
-      E.a3(cb + B_D + di * 3, db);
-    }
-    E.a3(cb + B_P, pb);
+  // M~bar, rows 4 g .. 4 g + 3 of column j
+  float m[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int q = 0; q < nr; ++q) {
+    const float4 al = *reinterpret_cast<const float4*>(L + w.rwb + q * ND + 4 * g);
+    const float wq = L[w.rw + q * ND + j];
+    m[0] += al.x * wq;
+    m[1] += al.y * wq;
+    m[2] += al.z * wq;
+    m[3] += al.w * wq;
   }
-  // lane per joint: the joint's own body accumulators
-  for (int j = lane; j < nb; j += 64) {
-    const V a = E.v3(w.ka + j * 3), o = E.v3(w.ko + j * 3);
-    const bool rev = M.jtype[j] == 0;
-    for (int r = 0; r < nr; ++r) {
-      const int ci = r / 3, di = r - 3 * ci;
-      const long e = w.con + (long)ci * CR;
-      const float Jb = L[w.rJb + (long)r * ND + j];
-      if (!((M.anc[M.sph_body[unpack_ids(L[e + C_ID]).oi]] >> j) & 1) || Jb == 0.f) continue;
-      const V d = E.dir(e, di);
-      if (rev) {
-        const V ev = E.v3(e + C_P) - o;
-        E.acc_dir(j, a, cross(ev, d) * Jb);
-        E.acc_point(j, o, -(cross(d, a) * Jb));
-      } else {
-        E.acc_dir(j, a, d * Jb);
-      }
-    }
-  }
+#pragma unroll
+  for (int t = 0; t < 4; ++t) L[w.Mb + (4 * g + t) * ND + j] -= m[t];
   lds_order();
 }
 
 // Recompute of a substep's articulated quantities over the lanes: drive
-// (lane per DoF), body poses by pointer jumping (lane per body, four doubling rounds),
-// per-body quantities (lane per body); CRBA and RNEA with the tree
-// recursions run down or up the tree by one lane per matrix or vector
-// component, the per-body terms one lane per body; M~^-1 by Gauss-Jordan
-// elimination over the lanes.  The bias torques are left in w.lz.
+// (lane per DoF), body poses by pointer jumping (lane per body, four doubling
+// rounds), per-body quantities (lane per body); CRBA and RNEA as sums over
+// the tree; M~^-1.  The bias torques are left in w.lz.
 __device__ __forceinline__ void recompute_wave(msa::Eng& E, float* L, const float* u) {
   using namespace msa;
   const int lane = lane_id();
@@ -1017,137 +1154,143 @@ __device__ __forceinline__ void recompute_wave(msa::Eng& E, float* L, const floa
   lds_order();
   if (lane < nb) E.kin_body(lane);
   lds_order();
-  // composite inertias (one lane per entry, up the tree) and velocities
-  // v_i = v_par + s_i qd_i (one lane per component, down the tree)
-  for (int idx = lane; idx < nb * 36; idx += 64) L[w.kIc + idx] = L[w.kI + idx];
-  // M~: zero, identity past the robot's DoFs
-  for (int e = lane; e < ND * ND; e += 64) {
-    const int r = e >> 4, c = e & 15;
-    L[w.L + e] = (r >= nb || c >= nb) && r == c ? 1.f : 0.f;
+  const Tree T = tree_of(E);
+  // composite inertias (sum over the descendants) and velocities (over the
+  // ancestors, v_i = sum of s_k qd_k)
+  float Ic[12] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  for (int k0 = (nb - 1) & ~3; k0 >= 0; k0 -= 4) {
+#pragma unroll
+    for (int u = 3; u >= 0; --u) {
+      const int k = k0 + u;
+      const float4* q = reinterpret_cast<const float4*>(L + w.kI + k * 36 + 12 * T.gc);
+      const bool dn = (T.dm >> k) & 1u;
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        const float4 x = q[t];
+        Ic[4 * t] += dn ? x.x : 0.f;
+        Ic[4 * t + 1] += dn ? x.y : 0.f;
+        Ic[4 * t + 2] += dn ? x.z : 0.f;
+        Ic[4 * t + 3] += dn ? x.w : 0.f;
+      }
+    }
   }
-  lds_order();
-  if (lane < 36) {
-    for (int i = nb - 1; i > 0; --i) {
-      const int par = M.parent[i];
-      if (par >= 0) L[w.kIc + par * 36 + lane] += L[w.kIc + i * 36 + lane];
-    }
-  } else if (lane < 42) {
-    const int t = lane - 36;
-    for (int i = 0; i < nb; ++i) {
-      const int par = M.parent[i];
-      L[w.rv + i * 6 + t] = (par >= 0 ? L[w.rv + par * 6 + t] : 0.f) + L[w.ks + i * 6 + t] * L[s + ND + i];
+  float2 v2 = make_float2(0.f, 0.f);
+  for (int k0 = 0; k0 < nb; k0 += 4) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int k = k0 + u;
+      const float2 sk = *reinterpret_cast<const float2*>(L + w.ks + k * 6 + 2 * T.gc);
+      const float qd = L[s + ND + k];
+      const bool up = (T.am >> k) & 1u;
+      const float x = fmaf(sk.x, qd, v2.x), y = fmaf(sk.y, qd, v2.y);
+      v2.x = up ? x : v2.x;
+      v2.y = up ? y : v2.y;
     }
   }
+  st2(L, w.rv, T, nb, v2);
+  float si[6];
+#pragma unroll
+  for (int t = 0; t < 6; ++t) si[t] = L[w.ks + T.i * 6 + t];
+  if (T.g < 3 && T.i < nb) {
+    float4* q = reinterpret_cast<float4*>(L + w.kIc + T.i * 36 + 12 * T.gc);
+#pragma unroll
+    for (int t = 0; t < 3; ++t) q[t] = make_float4(Ic[4 * t], Ic[4 * t + 1], Ic[4 * t + 2], Ic[4 * t + 3]);
+  }
+  // F_i = Ic_i s_i; the terms v_i x (s_i qd_i) of the accelerations
+  st2(L, w.tF, T, nb, rows_dot(Ic, si));
   lds_order();
-  // mass matrix row / column i: M_ij = s_j . (Ic_i s_i), j an ancestor of i;
-  // the terms v_i x (s_i qd_i) (into ra, summed down the tree below)
-  if (lane < nb) {
-    const int i = lane;
-    float si[6], F[6];
-    E.ld6(w.ks + i * 6, si);
-    E.mul6(w.kIc + i * 36, si, F);
-    for (int j = i; j >= 0; j = M.parent[j]) {
-      float v = 0.f;
-      for (int t = 0; t < 6; ++t) v += L[w.ks + j * 6 + t] * F[t];
-      L[w.L + i * ND + j] = v;
-      L[w.L + j * ND + i] = v;
+  float v[6];
+  {
+    float vJ[6], t6[6];
+    const float qd = L[s + ND + T.i];
+#pragma unroll
+    for (int t = 0; t < 6; ++t) {
+      v[t] = L[w.rv + T.i * 6 + t];
+      vJ[t] = si[t] * qd;
     }
-    float v[6], vJ[6], t6[6];
-    E.ld6(w.rv + i * 6, v);
-    const float qd = L[s + ND + i];
-    for (int t = 0; t < 6; ++t) vJ[t] = si[t] * qd;
     Eng::crm6(v, vJ, t6);
-    E.st6(w.ra + i * 6, t6);
+    st2(L, w.ra, T, nb, pick2(t6[0], t6[1], t6[2], t6[3], t6[4], t6[5], T));
   }
   lds_order();
-  // accelerations a_i = a_par + v_i x (s_i qd_i), a_root's parent = -g
-  if (lane < 6) {
-    const int t = lane;
-    // the base acceleration's component t, formed arithmetically: a lane-
-    // dependent index into the parameters (or a select the compiler turns
-    // into one) would put the engine object in scratch memory
+  // accelerations a_i = -g + sum over the ancestors of v_k x (s_k qd_k)
+  float2 a2;
+  {
+    // formed arithmetically: a lane-dependent index into the parameters (or a
+    // select the compiler turns into one) would put the engine object in
+    // scratch memory
     const float g0 = E.pr.g[0], g1 = E.pr.g[1], g2 = E.pr.g[2];
-    const float base = -(g0 * (float)(t == 3) + g1 * (float)(t == 4) + g2 * (float)(t == 5));
-    for (int i = 0; i < nb; ++i) {
-      const int par = M.parent[i];
-      L[w.ra + i * 6 + t] += par >= 0 ? L[w.ra + par * 6 + t] : base;
+    a2.x = -(g1 * (float)(T.gc == 2));
+    a2.y = -(g0 * (float)(T.gc == 1) + g2 * (float)(T.gc == 2));
+    a2 = sum_anc(L, w.ra, T, nb, a2);
+  }
+  lds_order();
+  st2(L, w.ra, T, nb, a2);
+  // M~ (rows 4 g .. 4 g + 3, column i): M_ab = s_b . F_a for b an ancestor of
+  // a, the armature on the diagonal; identity past the robot's DoFs
+  float e[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int row = 4 * T.g + r;
+    const bool up = (T.am >> row) & 1u, dn = (T.dm >> row) & 1u;
+    const float2* sb = reinterpret_cast<const float2*>(L + w.ks + (up ? row : T.i) * 6);
+    const float2* Fa = reinterpret_cast<const float2*>(L + w.tF + (up ? T.i : row) * 6);
+    float m = 0.f;
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      m += sb[t].x * Fa[t].x;
+      m += sb[t].y * Fa[t].y;
     }
+    const float ar = L[w.arm + T.i];
+    e[r] = up || dn ? m + (row == T.i ? ar : 0.f) : (row == T.i ? 1.f : 0.f);
   }
   lds_order();
   // body forces f_i = I_i a_i + v_i x* (I_i v_i)
-  if (lane < nb) {
-    const int i = lane;
-    float v[6], acc[6], fl[6], hv[6], t6[6];
-    E.ld6(w.rv + i * 6, v);
-    E.ld6(w.ra + i * 6, acc);
-    E.mul6(w.kI + i * 36, acc, fl);
-    E.mul6(w.kI + i * 36, v, hv);
+  float2 f2;
+  {
+    float I[12], acc[6];
+    ld_rows(L, w.kI, T, I);
+#pragma unroll
+    for (int t = 0; t < 6; ++t) acc[t] = L[w.ra + T.i * 6 + t];
+    f2 = rows_dot(I, acc);
+    st2(L, w.tA, T, nb, rows_dot(I, v));
+  }
+  lds_order();
+  {
+    float hv[6], t6[6];
+#pragma unroll
+    for (int t = 0; t < 6; ++t) hv[t] = L[w.tA + T.i * 6 + t];
     Eng::crf6(v, hv, t6);
-    for (int t = 0; t < 6; ++t) fl[t] += t6[t];
-    E.st6(w.rff + i * 6, fl);
+    const float2 x = pick2(t6[0], t6[1], t6[2], t6[3], t6[4], t6[5], T);
+    st2(L, w.rff, T, nb, make_float2(f2.x + x.x, f2.y + x.y));
   }
   lds_order();
-  // subtree force sums (one lane per component, up the tree)
-  if (lane < 6) {
-    for (int i = nb - 1; i > 0; --i) {
-      const int par = M.parent[i];
-      if (par >= 0) L[w.rff + par * 6 + lane] += L[w.rff + i * 6 + lane];
-    }
+  // subtree force sums
+  f2 = sum_desc(L, w.rff, T, nb);
+  lds_order();
+  st2(L, w.rff, T, nb, f2);
+  if (gj_step<0>(e, T.g, T.i, nb) && lane == 0) E.status |= Eng::MS_DEGENERATE_BIT;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int row = 4 * T.g + r;
+    L[w.Minv + row * ND + T.i] = row < nb && T.i < nb ? e[r] : 0.f;
   }
   lds_order();
-  // bias torques C_i = s_i . f_i; M~ = M + diag(armature)
-  if (lane < nb) {
-    const int i = lane;
-    float c = 0.f;
-    for (int t = 0; t < 6; ++t) c += L[w.ks + i * 6 + t] * L[w.rff + i * 6 + t];
-    L[w.lz + i] = c;
-    L[w.L + i * ND + i] += L[w.arm + i];
-  }
-  lds_order();
-  // Gauss-Jordan elimination without pivoting (M~ is symmetric positive
-  // definite), in registers: lane i < 16 holds row i; pivot p's row is read
-  // from lane p with readlane (the pivot loop is unrolled, so every register
-  // index is a constant); rows and columns past the robot's degrees of
-  // freedom are identity and stay so
+  // bias torques C_i = s_i . f_i
   if (lane < ND) {
-    float a[ND];
+    float c = 0.f;
 #pragma unroll
-    for (int k = 0; k < ND; ++k) a[k] = L[w.L + lane * ND + k];
-    bool degen = false;
-#pragma unroll
-    for (int p = 0; p < ND; ++p) {
-      float prow[ND];
-#pragma unroll
-      for (int k = 0; k < ND; ++k) prow[k] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a[k]), p));
-      float piv = prow[p];
-      if (p < nb && !(piv > 0.f)) {
-        degen = true;
-        piv = 1e-30f;
-      }
-      const float inv = 1.f / piv;
-      const float f = a[p];
-      const bool own = lane == p;
-#pragma unroll
-      for (int k = 0; k < ND; ++k) {
-        if (k == p) a[k] = own ? inv : -f * inv;
-        else a[k] = own ? prow[k] * inv : a[k] - f * (prow[k] * inv);
-      }
-    }
-    if (degen && lane == 0) E.status |= Eng::MS_DEGENERATE_BIT;
-#pragma unroll
-    for (int k = 0; k < ND; ++k) L[w.Minv + lane * ND + k] = lane < nb && k < nb ? a[k] : 0.f;
+    for (int t = 0; t < 6; ++t) c += si[t] * L[w.rff + T.i * 6 + t];
+    L[w.lz + lane] = lane < nb ? c : 0.f;
   }
 }
 
 // z = M~^-1 (tau - C) from the explicit inverse (lane per DoF)
 __device__ __forceinline__ void solve_z_wave(const msa::Eng& E, float* L) {
-  const int lane = lane_id();
+  const int j = lane_id() & 15;
   const msa::WS& w = E.w;
-  if (lane < ND) {
-    float z = 0.f;
-    for (int k = 0; k < E.nb; ++k) z += L[w.Minv + k * ND + lane] * (L[w.tau + k] - L[w.lz + k]);
-    L[w.z + lane] = lane < E.nb ? z : 0.f;
-  }
+  const float x = j < E.nb ? L[w.tau + j] - L[w.lz + j] : 0.f;
+  const float z = minv_times(L + w.Minv + j, x);
+  if (lane_id() < ND) L[w.z + j] = j < E.nb ? z : 0.f;
 }
 
 // dynamics^T over the lanes (the same adjoint as the engine's dynamics_bar,
@@ -1156,144 +1299,194 @@ __device__ __forceinline__ void dynamics_bar_wave(msa::Eng& E, float* L) {
   using namespace msa;
   const int lane = lane_id();
   const WS& w = E.w;
-  const DModel& M = *E.sc.M;
   const int nb = E.nb;
   const float h = E.pr.h;
   const long s = w.st, gB = w.gB;
+  const Tree T = tree_of(E);
   // vR = qd + h z: qd gets vRbar; lz = M~^-1 h vRbar is tau's adjoint
-  if (lane < ND) {
-    L[gB + ND + lane] += L[w.vRb + lane];
-    float lz = 0.f;
-    for (int k = 0; k < nb; ++k) lz += L[w.Minv + k * ND + lane] * (h * L[w.vRb + k]);
-    L[w.lz + lane] = lane < nb ? lz : 0.f;
+  float lz;
+  {
+    const float x = L[w.vRb + T.i];
+    lz = minv_times(L + w.Minv + T.i, T.i < nb ? h * x : 0.f);
+    lz = T.i < nb ? lz : 0.f;
+    if (lane < ND) {
+      L[gB + ND + lane] += x;
+      L[w.lz + lane] = lz;
+    }
   }
   lds_order();
-  // M~bar -= lz z^T; drive^T
-  for (int idx = lane; idx < ND * ND; idx += 64) {
-    const int r = idx / ND, c = idx - ND * (idx / ND);
-    if (r < nb && c < nb) L[w.Mb + idx] -= L[w.lz + r] * L[w.z + c];
+  // M~bar -= lz z^T, rows 4 g .. 4 g + 3 of column i (the other triangle's
+  // entry likewise): c_ij = Mbar_ij + Mbar_ji (c_ii = Mbar_ii) in its place;
+  // drive^T
+  {
+    const float zi = L[w.z + T.i];
+    float c[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = 4 * T.g + r;
+      const float m = L[w.Mb + row * ND + T.i] - L[w.lz + row] * zi;
+      const float mt = L[w.Mb + T.i * ND + row] - lz * L[w.z + row];
+      c[r] = row == T.i ? m : m + mt;
+    }
+    lds_order();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) L[w.Mb + (4 * T.g + r) * ND + T.i] = c[r];
   }
-  if (lane < nb) E.drive_bar_one(lane, L[w.lz + lane]);
+  if (lane < nb) E.drive_bar_one(lane, lz);
   lds_order();
   // CRBA^T, per body i: F_i = Ic_i s_i, Fbar_i = sum over the ancestors j of
-  // c_ij s_j (c_ii = Mbar_ii, c_ij = Mbar_ij + Mbar_ji), Icbar_i = Fbar_i s_i^T
-  if (lane < nb) {
-    const int i = lane;
-    float si[6], F[6], Fb[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    E.ld6(w.ks + i * 6, si);
-    E.mul6(w.kIc + i * 36, si, F);
-    E.st6(w.tF + i * 6, F);
-    for (int j = i; j >= 0; j = M.parent[j]) {
-      const float c = j == i ? L[w.Mb + i * ND + i] : L[w.Mb + i * ND + j] + L[w.Mb + j * ND + i];
-      for (int t = 0; t < 6; ++t) Fb[t] += c * L[w.ks + j * 6 + t];
-    }
-    E.st6(w.tFb + i * 6, Fb);
-    for (int r = 0; r < 6; ++r)
-      for (int c = 0; c < 6; ++c) L[w.Icb + i * 36 + r * 6 + c] = Fb[r] * si[c];
-  }
-  lds_order();
-  // sbar_j = sum over the descendants i of c_ij F_i + Ic_j^T Fbar_j; then
-  // RNEA^T: fbar_i = -sum over the ancestors of s_k lz_k, sbar_i -= lz_i f_i
-  if (lane < nb) {
-    const int j = lane;
-    float sb[6], Fb[6];
-    E.ld6(w.tFb + j * 6, Fb);
-    E.mul6t(w.kIc + j * 36, Fb, sb);
-    for (int i = j; i < nb; ++i) {
-      if (!((M.anc[i] >> j) & 1)) continue;
-      const float c = j == i ? L[w.Mb + i * ND + i] : L[w.Mb + i * ND + j] + L[w.Mb + j * ND + i];
-      for (int t = 0; t < 6; ++t) sb[t] += c * L[w.tF + i * 6 + t];
-    }
-    const float Cb = -L[w.lz + j];
-    float fb[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int k = 0; k <= j; ++k)
-      if ((M.anc[j] >> k) & 1) {
-        const float ck = -L[w.lz + k];
-        for (int t = 0; t < 6; ++t) fb[t] += L[w.ks + k * 6 + t] * ck;
+  // c_ij s_j; RNEA^T: fbar_i = -sum over the ancestors of s_k lz_k
+  float si[6];
+#pragma unroll
+  for (int t = 0; t < 6; ++t) si[t] = L[w.ks + T.i * 6 + t];
+  {
+    float Ic[12];
+    ld_rows(L, w.kIc, T, Ic);
+    st2(L, w.tF, T, nb, rows_dot(Ic, si));
+    float2 Fb = make_float2(0.f, 0.f), fb = make_float2(0.f, 0.f);
+    for (int k0 = (nb - 1) & ~3; k0 >= 0; k0 -= 4) {
+#pragma unroll
+      for (int u = 3; u >= 0; --u) {
+        const int k = k0 + u;
+        const bool up = (T.am >> k) & 1u;
+        const float2 sk = *reinterpret_cast<const float2*>(L + w.ks + k * 6 + 2 * T.gc);
+        const float c = up ? L[w.Mb + k * ND + T.i] : 0.f, z = up ? L[w.lz + k] : 0.f;
+        const float sx = up ? sk.x : 0.f, sy = up ? sk.y : 0.f;
+        Fb.x += c * sx;
+        Fb.y += c * sy;
+        fb.x -= sx * z;
+        fb.y -= sy * z;
       }
-    E.st6(w.fbar + j * 6, fb);
-    for (int t = 0; t < 6; ++t) sb[t] += Cb * L[w.rff + j * 6 + t];
-    E.st6(w.sb + j * 6, sb);
-  }
-  lds_order();
-  // Ibar_i = Icbar_i + Ibar_par (one lane per entry, down the tree)
-  if (lane < 36) {
-    for (int i = 0; i < nb; ++i) {
-      const int par = M.parent[i];
-      L[w.Ib + i * 36 + lane] = L[w.Icb + i * 36 + lane] + (par >= 0 ? L[w.Ib + par * 36 + lane] : 0.f);
     }
+    st2(L, w.tFb, T, nb, Fb);
+    st2(L, w.fbar, T, nb, fb);
   }
   lds_order();
-  // body terms of f = I a + v x* (I v): Ibar, the own parts of abar and vbar
-  if (lane < nb) {
-    const int i = lane;
-    const long I = w.kI + i * 36;
-    float v[6], acc[6], fb[6], t6[6], hv[6];
-    E.ld6(w.rv + i * 6, v);
-    E.ld6(w.ra + i * 6, acc);
-    E.ld6(w.fbar + i * 6, fb);
-    for (int r = 0; r < 6; ++r)
-      for (int c = 0; c < 6; ++c) L[w.Ib + i * 36 + r * 6 + c] += fb[r] * acc[c];
-    E.mul6t(I, fb, t6);
-    E.st6(w.tA + i * 6, t6);
-    E.mul6(I, v, hv);
-    V om{v[0], v[1], v[2]}, nu{v[3], v[4], v[5]}, hn{hv[0], hv[1], hv[2]}, hf{hv[3], hv[4], hv[5]};
-    V fn{fb[0], fb[1], fb[2]}, ff{fb[3], fb[4], fb[5]};
-    V omb = cross(hn, fn) + cross(hf, ff), nub = cross(hf, fn);
-    V hnb = cross(fn, om), hfb = cross(fn, nu) + cross(ff, om);
-    float hb[6] = {hnb.x, hnb.y, hnb.z, hfb.x, hfb.y, hfb.z};
-    for (int r = 0; r < 6; ++r)
-      for (int c = 0; c < 6; ++c) L[w.Ib + i * 36 + r * 6 + c] += hb[r] * v[c];
-    E.mul6t(I, hb, t6);
-    float ov[6] = {omb.x + t6[0], omb.y + t6[1], omb.z + t6[2], nub.x + t6[3], nub.y + t6[4], nub.z + t6[5]};
-    E.st6(w.tV + i * 6, ov);
-  }
-  lds_order();
-  // abar_i = subtree sum of the own parts (one lane per component, up the
-  // tree); then the a = a_par + v x vJ term's share of vbar_i
-  if (lane < 6) {
-    for (int i = 0; i < nb; ++i) L[w.abar + i * 6 + lane] = L[w.tA + i * 6 + lane];
-    for (int i = nb - 1; i > 0; --i) {
-      const int par = M.parent[i];
-      if (par >= 0) L[w.abar + par * 6 + lane] += L[w.abar + i * 6 + lane];
+  // sbar_i = sum over the descendants k of c_ik F_k + Ic_i^T Fbar_i - lz_i f_i;
+  // the body terms of f = I a + v x* (I v): own parts of abar and vbar, and
+  // hbar of Ibar = ... + hbar v^T (kept where vbar comes later)
+  float v[6], acc[6];
+  {
+    float2 sb = make_float2(0.f, 0.f);
+    const long Ic = w.kIc + T.i * 36, I = w.kI + T.i * 36;
+    float Fb[6], fb[6], hv[6];
+#pragma unroll
+    for (int t = 0; t < 6; ++t) {
+      Fb[t] = L[w.tFb + T.i * 6 + t];
+      fb[t] = L[w.fbar + T.i * 6 + t];
+      v[t] = L[w.rv + T.i * 6 + t];
+      acc[t] = L[w.ra + T.i * 6 + t];
     }
-  }
-  lds_order();
-  if (lane < nb) {
-    const int i = lane;
-    float ab[6];
-    E.ld6(w.abar + i * 6, ab);
-    const float qd = L[s + ND + i];
-    const float* si = L + w.ks + i * 6;
-    V vJw{si[0] * qd, si[1] * qd, si[2] * qd}, vJv{si[3] * qd, si[4] * qd, si[5] * qd};
-    V aw{ab[0], ab[1], ab[2]}, av{ab[3], ab[4], ab[5]};
-    V omb2 = cross(vJw, aw) + cross(vJv, av), nub2 = cross(vJw, av);
-    float o2[6] = {omb2.x, omb2.y, omb2.z, nub2.x, nub2.y, nub2.z};
-    E.st6(w.tV2 + i * 6, o2);
-  }
-  lds_order();
-  // vbar_i = subtree sum of both own parts (one lane per component, up the
-  // tree); the joint velocity's adjoint
-  if (lane < 6) {
-    for (int i = 0; i < nb; ++i) L[w.vbar + i * 6 + lane] = L[w.tV + i * 6 + lane] + L[w.tV2 + i * 6 + lane];
-    for (int i = nb - 1; i > 0; --i) {
-      const int par = M.parent[i];
-      if (par >= 0) L[w.vbar + par * 6 + lane] += L[w.vbar + i * 6 + lane];
+    // columns 2 gc and 2 gc + 1 of Ic and I; I v from I's rows (I is symmetric)
+    float2 tA = make_float2(0.f, 0.f), hv2 = make_float2(0.f, 0.f);
+#pragma unroll
+    for (int t = 0; t < 6; ++t) {
+      const float2 cI = *reinterpret_cast<const float2*>(L + Ic + t * 6 + 2 * T.gc);
+      const float2 bI = *reinterpret_cast<const float2*>(L + I + t * 6 + 2 * T.gc);
+      sb.x += cI.x * Fb[t];
+      sb.y += cI.y * Fb[t];
+      tA.x += bI.x * fb[t];
+      tA.y += bI.y * fb[t];
+      hv2.x += bI.x * v[t];
+      hv2.y += bI.y * v[t];
     }
+    for (int k0 = 0; k0 < nb; k0 += 4) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k = k0 + u;
+        const bool dn = (T.dm >> k) & 1u;
+        const float2 F = *reinterpret_cast<const float2*>(L + w.tF + k * 6 + 2 * T.gc);
+        const float c = dn ? L[w.Mb + k * ND + T.i] : 0.f;
+        sb.x += c * (dn ? F.x : 0.f);
+        sb.y += c * (dn ? F.y : 0.f);
+      }
+    }
+    const float2 rf = ld2(L, w.rff, T);
+    sb.x -= lz * rf.x;
+    sb.y -= lz * rf.y;
+    st2(L, w.sb, T, nb, sb);
+    st2(L, w.tA, T, nb, tA);
+    st2(L, w.tV2, T, nb, hv2);
+    lds_order();
+#pragma unroll
+    for (int t = 0; t < 6; ++t) hv[t] = L[w.tV2 + T.i * 6 + t];
+    const V om{v[0], v[1], v[2]}, nu{v[3], v[4], v[5]}, hn{hv[0], hv[1], hv[2]}, hf{hv[3], hv[4], hv[5]};
+    const V fn{fb[0], fb[1], fb[2]}, ff{fb[3], fb[4], fb[5]};
+    const V omb = cross(hn, fn) + cross(hf, ff), nub = cross(hf, fn);
+    const V hnb = cross(fn, om), hfb = cross(fn, nu) + cross(ff, om);
+    const float hb[6] = {hnb.x, hnb.y, hnb.z, hfb.x, hfb.y, hfb.z};
+    float2 o2 = pick2(omb.x, omb.y, omb.z, nub.x, nub.y, nub.z, T);
+#pragma unroll
+    for (int t = 0; t < 6; ++t) {
+      const float2 bI = *reinterpret_cast<const float2*>(L + I + t * 6 + 2 * T.gc);
+      o2.x += bI.x * hb[t];
+      o2.y += bI.y * hb[t];
+    }
+    st2(L, w.tV, T, nb, o2);
+    st2(L, w.vbar, T, nb, pick2(hnb.x, hnb.y, hnb.z, hfb.x, hfb.y, hfb.z, T));
   }
+  lds_order();
+  // Ibar_i = sum over the ancestors of Fbar_k s_k^T + fbar_i a_i^T + hbar_i v_i^T
+  // (rows 2 gc and 2 gc + 1); abar_i = subtree sum of the own parts
+  const float2 ab2 = sum_desc(L, w.tA, T, nb);
+  {
+    float Ib[12] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int k0 = 0; k0 < nb; k0 += 4) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k = k0 + u;
+        const bool up = (T.am >> k) & 1u;
+        const float2 Fk = *reinterpret_cast<const float2*>(L + w.tFb + k * 6 + 2 * T.gc);
+        const float2* sk = reinterpret_cast<const float2*>(L + w.ks + k * 6);
+        const float fx = up ? Fk.x : 0.f, fy = up ? Fk.y : 0.f;
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+          const float2 q = sk[t];
+          const float qx = up ? q.x : 0.f, qy = up ? q.y : 0.f;
+          Ib[2 * t] += fx * qx;
+          Ib[2 * t + 1] += fx * qy;
+          Ib[6 + 2 * t] += fy * qx;
+          Ib[6 + 2 * t + 1] += fy * qy;
+        }
+      }
+    }
+    const float2 fb = ld2(L, w.fbar, T), hb = ld2(L, w.vbar, T);
+#pragma unroll
+    for (int t = 0; t < 6; ++t) {
+      Ib[t] += fb.x * acc[t] + hb.x * v[t];
+      Ib[6 + t] += fb.y * acc[t] + hb.y * v[t];
+    }
+    if (T.g < 3 && T.i < nb) {
+      float4* q = reinterpret_cast<float4*>(L + w.Ib + T.i * 36 + 12 * T.gc);
+#pragma unroll
+      for (int t = 0; t < 3; ++t) q[t] = make_float4(Ib[4 * t], Ib[4 * t + 1], Ib[4 * t + 2], Ib[4 * t + 3]);
+    }
+    st2(L, w.abar, T, nb, ab2);
+  }
+  lds_order();
+  // the a = a_par + v x vJ term's share of vbar_i
+  const float qd = L[s + ND + T.i];
+  float ab[6];
+  {
+#pragma unroll
+    for (int t = 0; t < 6; ++t) ab[t] = L[w.abar + T.i * 6 + t];
+    const V vJw{si[0] * qd, si[1] * qd, si[2] * qd}, vJv{si[3] * qd, si[4] * qd, si[5] * qd};
+    const V aw{ab[0], ab[1], ab[2]}, av{ab[3], ab[4], ab[5]};
+    const V omb2 = cross(vJw, aw) + cross(vJv, av), nub2 = cross(vJw, av);
+    const float2 t = ld2(L, w.tV, T), o2 = pick2(omb2.x, omb2.y, omb2.z, nub2.x, nub2.y, nub2.z, T);
+    st2(L, w.tV2, T, nb, make_float2(t.x + o2.x, t.y + o2.y));
+  }
+  lds_order();
+  // vbar_i = subtree sum of both own parts; the joint velocity's adjoint
+  st2(L, w.vbar, T, nb, sum_desc(L, w.tV2, T, nb));
   lds_order();
   if (lane < nb) {
     const int i = lane;
     float vb[6];
     E.ld6(w.vbar + i * 6, vb);
-    float v[6], ab[6], si[6];
-    E.ld6(w.rv + i * 6, v);
-    E.ld6(w.abar + i * 6, ab);
-    E.ld6(w.ks + i * 6, si);
     V om{v[0], v[1], v[2]}, nu{v[3], v[4], v[5]}, aw{ab[0], ab[1], ab[2]}, av{ab[3], ab[4], ab[5]};
     V vJwb = cross(aw, om) + cross(av, nu), vJvb = cross(av, om);
     float vJb[6] = {vJwb.x + vb[0], vJwb.y + vb[1], vJwb.z + vb[2], vJvb.x + vb[3], vJvb.y + vb[4], vJvb.z + vb[5]};
-    const float qd = L[s + ND + i];
     float qdb = 0.f;
     for (int t = 0; t < 6; ++t) {
       L[w.sb + i * 6 + t] += qd * vJb[t];
@@ -1307,21 +1500,30 @@ __device__ __forceinline__ void dynamics_bar_wave(msa::Eng& E, float* L) {
 }
 
 // kinematics^T: joint k receives a_k . (Mo - o_k x F + Md) (revolute) or
-// a_k . F (prismatic) with F, Mo, Md summed over the subtree of k
+// a_k . F (prismatic) with F, Mo, Md summed over the subtree of k (lane (g, i):
+// vector g of body i)
 __device__ __forceinline__ void kin_bar_wave(const msa::Eng& E, float* L) {
   using namespace msa;
-  const int lane = lane_id();
   const WS& w = E.w;
   const DModel& M = *E.sc.M;
-  if (lane < E.nb) {
-    const int i = lane;
-    V F{0.f, 0.f, 0.f}, Mo{0.f, 0.f, 0.f}, Md{0.f, 0.f, 0.f};
-    for (int k = i; k < E.nb; ++k)
-      if ((M.anc[k] >> i) & 1) {
-        F = F + E.v3(w.bacc + k * 9);
-        Mo = Mo + E.v3(w.bacc + k * 9 + 3);
-        Md = Md + E.v3(w.bacc + k * 9 + 6);
-      }
+  const int nb = E.nb;
+  const Tree T = tree_of(E);
+  V sum{0.f, 0.f, 0.f};
+  for (int k0 = 0; k0 < nb; k0 += 4) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int k = k0 + u;
+      const V x = E.v3(w.bacc + k * 9 + 3 * T.gc);
+      const bool dn = (T.dm >> k) & 1u;
+      sum = sum + V{dn ? x.x : 0.f, dn ? x.y : 0.f, dn ? x.z : 0.f};
+    }
+  }
+  auto from = [&](int g) {
+    return V{__shfl(sum.x, 16 * g + T.i, 64), __shfl(sum.y, 16 * g + T.i, 64), __shfl(sum.z, 16 * g + T.i, 64)};
+  };
+  const V F = from(0), Mo = from(1), Md = from(2);
+  if (lane_id() < nb) {
+    const int i = lane_id();
     const V a = E.v3(w.ka + i * 3);
     L[w.gB + i] += M.jtype[i] == 0 ? dot(a, Mo + Md - cross(E.v3(w.ko + i * 3), F)) : dot(a, F);
   }
