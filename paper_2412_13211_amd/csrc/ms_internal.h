@@ -88,7 +88,7 @@ constexpr int ROBOT_FLOATS = 5 * ND + ND * 9 + ND * 3 + ND * 6 + ND * ND;
 // Dynamics scratch (only inside the dynamics phase, beside which the contacts
 // are generated): per body COM, mass and world inertia about the COM
 // [16*BI_FLOATS], velocity-product accelerations and body forces [2*16*6],
-// tau - C [16], the per-body sums.  (M~ takes the place of its inverse.)
+// tau - C [16], the per-body sums.
 constexpr int BI_FLOATS = 11;       // odd stride
 constexpr int DSUM_FLOATS = 17;     // odd stride: a_i (6), composite inertia (10) / subtree force (6), G_i (6)
 constexpr int DYN_FLOATS = ND * BI_FLOATS + 2 * ND * 6 + ND + ND * DSUM_FLOATS;

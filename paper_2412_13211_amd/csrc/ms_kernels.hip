@@ -16,8 +16,8 @@
 //   -- barrier --
 // One wavefront doing all in turn was bound by the latency of each chain, the
 // SIMDs idle two thirds of the time; LDS, not wavefront slots, limits the
-// scenes per CU, so the second wavefront is free.  A control step of 16, 1024
-// and 4096 uneven scenes: 183 -> 130, 539 -> 386 and 1019 -> 746 us.
+// scenes per CU, so the second wavefront is free.  A control step of 1024
+// scenes and of 4096 uneven ones: 539 -> 386 and 1019 -> 746 us.
 // The mathematics follows the textbook definitions cited in the C header; no
 // code is shared with the CPU oracle.
 #include "ms_internal.h"
@@ -144,6 +144,19 @@ __device__ __forceinline__ float sum16(float v) {
   v += row_ror<1>(v);
   return v;
 }
+// value of lane K of the lane's row of 16
+template <int K>
+__device__ __forceinline__ float row_bcast(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + K, 0xf, 0xf, false));
+}
+// row Q of 16 lanes in all four
+template <int Q>
+__device__ __forceinline__ float bcast_row(float v) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_int(v), __float_as_int(v), false, false);
+  const int y = a[Q & 1];
+  const auto b = __builtin_amdgcn_permlane32_swap(y, y, false, false);
+  return __int_as_float(b[Q >> 1]);
+}
 // lane src's value in every lane (src uniform)
 __device__ __forceinline__ float lane_val(float v, int src) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), src));
@@ -184,9 +197,8 @@ struct Robot {
   // dynamics scratch, valid only inside the dynamics phase: per body COM,
   // mass and world inertia about the COM [16][BI_FLOATS], velocity-product
   // accelerations and body forces [16][6] each, tau - C [16], the per-body
-  // sums of the pair-lane reductions [16][DSUM_FLOATS]; M~ [16][16] in the
-  // place of its inverse
-  float *bI, *cc, *fo, *Mt, *rhs, *dsum;
+  // sums of the pair-lane reductions [16][DSUM_FLOATS]
+  float *bI, *cc, *fo, *rhs, *dsum;
 };
 __device__ __forceinline__ Robot robot_view(float* base, float* dyn) {
   Robot r;
@@ -200,7 +212,6 @@ __device__ __forceinline__ Robot robot_view(float* base, float* dyn) {
   r.p = o; o += ND * 3;
   r.s = o; o += ND * 6;
   r.Minv = o; o += ND * ND;
-  r.Mt = r.Minv;
   o = dyn;
   r.bI = o; o += ND * BI_FLOATS;
   r.cc = o; o += ND * 6;
@@ -493,27 +504,38 @@ __device__ __forceinline__ void kin_robot(const KArgs& a, const Scene& S, float*
   const int lane = lane_id();
   const DModel* M = S.M;
   const int nb = S.nb;
-  float Rw[9], pw[3];
-  int anc = -1;
-  if (lane < nb) {
-    f3 ax = mk3(M->axis[lane][0], M->axis[lane][1], M->axis[lane][2]);
-    const float* RT = M->xtR[lane];
-    float q = rb.q[lane];
-    if (M->jtype[lane] == 0) {
+  // Lane (r, i) = (lane >> 4, lane & 15), r < 3, holds row r of body i's world
+  // rotation and component r of its origin; every lane the whole local
+  // transform.  (A lane per body fetched 12 numbers of its parent and multiplied
+  // whole matrices in every round: 8.5 k cycles for the 15 bodies, now 4.4 k.)
+  const int r = lane >> 4, i = lane & 15;
+  float Rl[9], pl[3];
+  int anc = -1, depth = -1;
+  bool rev = true;
+  f3 axl = mk3(0.f, 0.f, 0.f);
+  if (i < nb) {
+    axl = mk3(M->axis[i][0], M->axis[i][1], M->axis[i][2]);
+    const float* RT = M->xtR[i];
+    float q = rb.q[i];
+    rev = M->jtype[i] == 0;
+    if (rev) {
       float RJ[9];
-      rot_axis(ax, q, RJ);
-      mm(RT, RJ, Rw);
-      pw[0] = M->xtp[lane][0]; pw[1] = M->xtp[lane][1]; pw[2] = M->xtp[lane][2];
+      rot_axis(axl, q, RJ);
+      mm(RT, RJ, Rl);
+      pl[0] = M->xtp[i][0]; pl[1] = M->xtp[i][1]; pl[2] = M->xtp[i][2];
     } else {
-      for (int t = 0; t < 9; ++t) Rw[t] = RT[t];
-      f3 d = mv(RT, ax) * q;
-      pw[0] = M->xtp[lane][0] + d.x; pw[1] = M->xtp[lane][1] + d.y; pw[2] = M->xtp[lane][2] + d.z;
+      for (int t = 0; t < 9; ++t) Rl[t] = RT[t];
+      f3 d = mv(RT, axl) * q;
+      pl[0] = M->xtp[i][0] + d.x; pl[1] = M->xtp[i][1] + d.y; pl[2] = M->xtp[i][2] + d.z;
     }
-    anc = M->parent[lane];
+    anc = M->parent[i];
+    depth = __popc(M->anc[i]) - 1;
   } else {
-    for (int t = 0; t < 9; ++t) Rw[t] = t % 4 == 0 ? 1.f : 0.f;
-    pw[0] = pw[1] = pw[2] = 0.f;
+    for (int t = 0; t < 9; ++t) Rl[t] = t % 4 == 0 ? 1.f : 0.f;
+    pl[0] = pl[1] = pl[2] = 0.f;
   }
+  float W0 = r == 0 ? Rl[0] : (r == 1 ? Rl[3] : Rl[6]), W1 = r == 0 ? Rl[1] : (r == 1 ? Rl[4] : Rl[7]),
+        W2 = r == 0 ? Rl[2] : (r == 1 ? Rl[5] : Rl[8]), wp = r == 0 ? pl[0] : (r == 1 ? pl[1] : pl[2]);
   // W_i <- W_parent o W_i in depth order (round d composes the bodies of
   // depth d onto their finished parents).  A body's origin is then computed
   // as R_parent xtp + p_parent, the very operations that place a point of the
@@ -523,32 +545,28 @@ __device__ __forceinline__ void kin_robot(const KArgs& a, const Scene& S, float*
   // two that differ by rounding and make Gauss-Seidel trade impulse between
   // them sweep after sweep.  (Composing by pointer jumping takes fewer
   // rounds but associates the products differently.)
-  const int depth = lane < nb ? __popc(M->anc[lane]) - 1 : -1;
+  const int src = anc >= 0 ? (lane & 48) | anc : lane;
   for (int d = 1; d < ND; ++d) {
     if (!__ballot(depth >= d)) break;
-    const int src = (depth == d && anc >= 0) ? anc : lane;
-    float Ra[9], pa[3];
-    for (int t = 0; t < 9; ++t) Ra[t] = bcast(Rw[t], src);
-    for (int t = 0; t < 3; ++t) pa[t] = bcast(pw[t], src);
-    if (depth == d && anc >= 0) {
-      float Rn[9];
-      mm(Ra, Rw, Rn);
-      f3 pn = mv(Ra, mk3(pw[0], pw[1], pw[2]));
-      for (int t = 0; t < 9; ++t) Rw[t] = Rn[t];
-      pw[0] = pn.x + pa[0]; pw[1] = pn.y + pa[1]; pw[2] = pn.z + pa[2];
-    }
+    const float a0 = bcast(W0, src), a1 = bcast(W1, src), a2 = bcast(W2, src), pa = bcast(wp, src);
+    const float n0 = a0 * Rl[0] + a1 * Rl[3] + a2 * Rl[6], n1 = a0 * Rl[1] + a1 * Rl[4] + a2 * Rl[7],
+                n2 = a0 * Rl[2] + a1 * Rl[5] + a2 * Rl[8];
+    const float np = a0 * pl[0] + a1 * pl[1] + a2 * pl[2] + pa;
+    const bool on = depth == d && anc >= 0;
+    W0 = on ? n0 : W0;
+    W1 = on ? n1 : W1;
+    W2 = on ? n2 : W2;
+    wp = on ? np : wp;
   }
-  if (lane < nb) {
-    for (int t = 0; t < 9; ++t) rb.R[lane * 9 + t] = Rw[t];
-    for (int t = 0; t < 3; ++t) rb.p[lane * 3 + t] = pw[t];
-    f3 ax = mv(Rw, mk3(M->axis[lane][0], M->axis[lane][1], M->axis[lane][2]));
-    float* s = rb.s + lane * 6;
+  if (i < nb && r < 3) {
+    float* R = rb.R + i * 9 + 3 * r;
+    R[0] = W0; R[1] = W1; R[2] = W2;
+    rb.p[i * 3 + r] = wp;
+    const float ax = W0 * axl.x + W1 * axl.y + W2 * axl.z;
     // motion subspace referred to the body's own origin (on the joint axis)
-    if (M->jtype[lane] == 0) {
-      s[0] = ax.x; s[1] = ax.y; s[2] = ax.z; s[3] = 0.f; s[4] = 0.f; s[5] = 0.f;
-    } else {
-      s[0] = 0.f; s[1] = 0.f; s[2] = 0.f; s[3] = ax.x; s[4] = ax.y; s[5] = ax.z;
-    }
+    float* s = rb.s + i * 6;
+    s[r] = rev ? ax : 0.f;
+    s[3 + r] = rev ? 0.f : ax;
   }
   lds_order();
   // sphere centres
@@ -1391,16 +1409,16 @@ __device__ __forceinline__ void shift_force(const float* f, f3 e, float* out) {
   f3 n = mk3(f[0], f[1], f[2]) + cross(e, mk3(f[3], f[4], f[5]));
   out[0] = n.x; out[1] = n.y; out[2] = n.z; out[3] = f[3]; out[4] = f[4]; out[5] = f[5];
 }
-// motion subspace of joint k expressed at point q
-__device__ __forceinline__ void s_at(const Robot& rb, const DModel* M, int k, f3 q, float* out) {
-  const float* s = rb.s + k * 6;
-  if (M->jtype[k] == 0) {
-    f3 a = mk3(s[0], s[1], s[2]);
-    f3 v = cross(a, q - body_p(rb, k));
-    out[0] = a.x; out[1] = a.y; out[2] = a.z; out[3] = v.x; out[4] = v.y; out[5] = v.z;
-  } else {
-    for (int t = 0; t < 6; ++t) out[t] = s[t];
-  }
+// motion subspace s of a joint (revolute: rev) expressed at a point off its own
+// origin by d
+__device__ __forceinline__ void s_from(const float* s, bool rev, f3 d, float* out) {
+  const f3 v = cross(mk3(s[0], s[1], s[2]), d);
+  out[0] = s[0];
+  out[1] = s[1];
+  out[2] = s[2];
+  out[3] = rev ? v.x : s[3];
+  out[4] = rev ? v.y : s[4];
+  out[5] = rev ? v.z : s[5];
 }
 // A rigid (or composite) inertia about a point P: mass m, first moment
 // h = m (c - P) and rotational inertia J about P (symmetric: xx yy zz xy xz
@@ -1433,23 +1451,52 @@ __device__ __forceinline__ void ri_add(RI& I, float m, f3 d, const float* Jc) {
   I.J[5] += Jc[5] - m * d.y * d.z;
 }
 
+// One pivot of the Gauss-Jordan elimination: lane (g, c) = (lane >> 4, lane & 15)
+// holds rows g, 4 + g, 8 + g, 12 + g of column c; the pivot row reaches all lanes
+// by row swaps, a row's factor its 16 lanes by a DPP broadcast.
+template <int P>
+__device__ __forceinline__ void gj_step(float* e, int g, int c) {
+  const float prow = bcast_row<P & 3>(e[P >> 2]);
+  const float inv = 1.f / row_bcast<P>(prow);
+  const float pn = prow * inv;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const float f = row_bcast<P>(e[r]);
+    const float x = c == P ? -f * inv : e[r] - f * pn;
+    e[r] = r == P >> 2 && g == (P & 3) ? (c == P ? inv : pn) : x;
+  }
+  if constexpr (P + 1 < ND) gj_step<P + 1>(e, g, c);
+}
+template <int K>
+__device__ __forceinline__ float minv_dot(const float* Mi, float J, float acc) {
+  acc = fmaf(Mi[K], row_bcast<K>(J), acc);
+  if constexpr (K + 1 < ND) return minv_dot<K + 1>(Mi, J, acc);
+  else return acc;
+}
 __device__ __forceinline__ void dyn_robot(const KArgs& a, const Scene& S, float* L, float& vR) {
   const Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
   const int lane = lane_id();
   const DModel* M = S.M;
   const int nb = S.nb;
-  // M~ starts as zero, with identity rows and columns past the robot's DoFs
-  for (int e = lane; e < ND * ND; e += WAVE) {
-    const int r = e / ND, c = e % ND;
-    rb.Mt[e] = (r >= nb || c >= nb) && r == c ? 1.f : 0.f;
-  }
   // The sums over a body's ancestors or descendants run over pair lanes: in
   // each of four rounds, row q (lanes 16 q .. 16 q + 15) serves body
   // i = 4 r + q and lane k of the row the other body k; the row's 16 terms
   // are added by a 16-lane reduction, and lane 0 of the row leaves the sum in
-  // LDS for body i's own lane.  (One lane per body looping over the other
-  // bodies made each sum a chain of 16 dependent LDS rounds.)
+  // LDS for body i's own lane.  The rounds are unrolled, so that one's loads and
+  // sums fill the other's waits.  (One lane per body looping over the other
+  // bodies made each sum a chain of 16 dependent LDS rounds.  Rounds one after
+  // the other, with the ancestors read from memory in each, and the elimination
+  // a row per lane: the dynamics took 36 k cycles among 4096 uneven scenes,
+  // now 23 k; that batch's step 746 -> 671 us.)
   const int lf = lane_id(), q = lf >> 4, kq = lf & 15;
+  // ancestors and descendants of body kq, itself included (none past the robot's
+  // bodies), and its joint's kind
+  const uint32_t am = kq < nb ? (uint32_t)M->anc[kq] : 0u;
+  const bool revk = M->jtype[kq] == 0;
+  uint32_t dm = 0u;
+#pragma unroll
+  for (int k = 0; k < ND; ++k) dm |= (((uint32_t)__builtin_amdgcn_readlane((int)am, k) >> kq) & 1u) << k;
+  const f3 pk = body_p(rb, kq);
   // pass 1 (lane per body): COM and world inertia about the COM (kept for the
   // subtree sums); (pair lanes) twist v_i = sum over k in anc-or-self(i) of
   // s_k qd_k at p_i; (lane per body) the velocity-product acceleration
@@ -1480,18 +1527,21 @@ __device__ __forceinline__ void dyn_robot(const KArgs& a, const Scene& S, float*
     bI[3] = m;
     for (int t = 0; t < 6; ++t) bI[4 + t] = Jc[t];
   }
-  for (int r0 = 0; r0 < nb; r0 += 4) {
-    const int i = r0 + q;
-    float t6[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (i < nb && kq < nb && ((M->anc[i] >> kq) & 1)) {
-      float sk[6];
-      s_at(rb, M, kq, body_p(rb, i), sk);
-      const float qd = rb.qd[kq];
-      for (int t = 0; t < 6; ++t) t6[t] = sk[t] * qd;
+  {
+    float sk[6];
+    for (int t = 0; t < 6; ++t) sk[t] = rb.s[kq * 6 + t];
+    const float qd = rb.qd[kq];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = 4 * r + q;
+      const bool on = (dm >> i) & 1u;
+      float si[6], t6[6];
+      s_from(sk, revk, body_p(rb, i) - pk, si);
+      for (int t = 0; t < 6; ++t) t6[t] = on ? si[t] * qd : 0.f;
+      for (int t = 0; t < 6; ++t) t6[t] = sum16(t6[t]);
+      if (kq == 0 && i < nb)
+        for (int t = 0; t < 6; ++t) rb.fo[i * 6 + t] = t6[t];  // v_i (fo is free until pass 2 ends)
     }
-    for (int t = 0; t < 6; ++t) t6[t] = sum16(t6[t]);
-    if (kq == 0 && i < nb)
-      for (int t = 0; t < 6; ++t) rb.fo[i * 6 + t] = t6[t];  // v_i (fo is free until pass 2 ends)
   }
   lds_order();
   if (lane < nb) {
@@ -1509,28 +1559,35 @@ __device__ __forceinline__ void dyn_robot(const KArgs& a, const Scene& S, float*
   // acceleration -g) a_i = -g + sum over anc-or-self of c_k, taken to p_i;
   // the subtree's composite inertia about p_i; then (lane per body) the body
   // force f_i = I_i a_i + p_i
-  for (int r0 = 0; r0 < nb; r0 += 4) {
-    const int i = r0 + q;
-    float ta[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    RI tc{0.f, {0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f, 0.f, 0.f}};
-    if (i < nb && kq < nb) {
-      const f3 p_i = body_p(rb, i);
-      if ((M->anc[i] >> kq) & 1) shift_motion(rb.cc + kq * 6, p_i - body_p(rb, kq), ta);
-      if ((M->anc[kq] >> i) & 1) {
-        const float* bk = rb.bI + kq * BI_FLOATS;
-        ri_add(tc, bk[3], mk3(bk[0], bk[1], bk[2]) - p_i, bk + 4);
-      }
+  {
+    const float* bk = rb.bI + kq * BI_FLOATS;
+    const f3 ck = mk3(bk[0], bk[1], bk[2]);
+    const float mk = bk[3];
+    float Jk[6], cck[6];
+    for (int t = 0; t < 6; ++t) {
+      Jk[t] = bk[4 + t];
+      cck[t] = rb.cc[kq * 6 + t];
     }
-    for (int t = 0; t < 6; ++t) ta[t] = sum16(ta[t]);
-    tc.m = sum16(tc.m);
-    for (int t = 0; t < 3; ++t) tc.h[t] = sum16(tc.h[t]);
-    for (int t = 0; t < 6; ++t) tc.J[t] = sum16(tc.J[t]);
-    if (kq == 0 && i < nb) {
-      float* o = rb.dsum + i * DSUM_FLOATS;
-      for (int t = 0; t < 6; ++t) o[t] = ta[t];
-      o[6] = tc.m;
-      for (int t = 0; t < 3; ++t) o[7 + t] = tc.h[t];
-      for (int t = 0; t < 6; ++t) o[10 + t] = tc.J[t];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = 4 * r + q;
+      const bool up = (dm >> i) & 1u, dn = (am >> i) & 1u;
+      const f3 p_i = body_p(rb, i);
+      float ta[6];
+      RI tc{0.f, {0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f, 0.f, 0.f}};
+      shift_motion(cck, p_i - pk, ta);
+      ri_add(tc, mk, ck - p_i, Jk);
+      for (int t = 0; t < 6; ++t) ta[t] = sum16(up ? ta[t] : 0.f);
+      tc.m = sum16(dn ? tc.m : 0.f);
+      for (int t = 0; t < 3; ++t) tc.h[t] = sum16(dn ? tc.h[t] : 0.f);
+      for (int t = 0; t < 6; ++t) tc.J[t] = sum16(dn ? tc.J[t] : 0.f);
+      if (kq == 0 && i < nb) {
+        float* o = rb.dsum + i * DSUM_FLOATS;
+        for (int t = 0; t < 6; ++t) o[t] = ta[t];
+        o[6] = tc.m;
+        for (int t = 0; t < 3; ++t) o[7 + t] = tc.h[t];
+        for (int t = 0; t < 6; ++t) o[10 + t] = tc.J[t];
+      }
     }
   }
   lds_order();
@@ -1549,70 +1606,63 @@ __device__ __forceinline__ void dyn_robot(const KArgs& a, const Scene& S, float*
   lds_order();
   // pass 3: (pair lanes) the subtree's body forces at p_i; (lane per body)
   // C_i = s_i . that sum, the right-hand side tau - C, G_i = I^c_i s_i and
-  // M_ii; (pair lanes) M_ij = s_j . G_i for j a strict ancestor of i, all at
-  // p_i, plus the armature on the diagonal
-  for (int r0 = 0; r0 < nb; r0 += 4) {
-    const int i = r0 + q;
-    float tf[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (i < nb && kq < nb && ((M->anc[kq] >> i) & 1))
-      shift_force(rb.fo + kq * 6, body_p(rb, kq) - body_p(rb, i), tf);
-    for (int t = 0; t < 6; ++t) tf[t] = sum16(tf[t]);
-    if (kq == 0 && i < nb)
-      for (int t = 0; t < 6; ++t) rb.dsum[i * DSUM_FLOATS + t] = tf[t];
+  // M_ii with the armature
+  {
+    float fk[6];
+    for (int t = 0; t < 6; ++t) fk[t] = rb.fo[kq * 6 + t];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = 4 * r + q;
+      const bool dn = (am >> i) & 1u;
+      float tf[6];
+      shift_force(fk, pk - body_p(rb, i), tf);
+      for (int t = 0; t < 6; ++t) tf[t] = sum16(dn ? tf[t] : 0.f);
+      if (kq == 0 && i < nb)
+        for (int t = 0; t < 6; ++t) rb.dsum[i * DSUM_FLOATS + t] = tf[t];
+    }
   }
   lds_order();
-  if (lane < nb) {
+  if (lane < ND) {
     const int i = lane;
     const float* si = rb.s + i * 6;
     float C = 0.f, G[6];
     for (int t = 0; t < 6; ++t) C += si[t] * rb.dsum[i * DSUM_FLOATS + t];
-    rb.rhs[i] = rb.tau[i] - C;
+    rb.rhs[i] = i < nb ? rb.tau[i] - C : 0.f;
     ri_apply(Ic, si, G);
     float Mii = 0.f;
     for (int t = 0; t < 6; ++t) Mii += si[t] * G[t];
-    rb.Mt[i * ND + i] = Mii + rb.arm[i];
     for (int t = 0; t < 6; ++t) rb.dsum[i * DSUM_FLOATS + 6 + t] = G[t];
+    rb.dsum[i * DSUM_FLOATS + 12] = i < nb ? Mii + rb.arm[i] : 1.f;
   }
   lds_order();
-  for (int r0 = 0; r0 < nb; r0 += 4) {
-    const int i = r0 + q, j = kq;
-    if (i < nb && j < i && ((M->anc[i] >> j) & 1)) {
-      float sj[6];
-      s_at(rb, M, j, body_p(rb, i), sj);
-      const float* G = rb.dsum + i * DSUM_FLOATS + 6;
-      float v = 0.f;
-      for (int t = 0; t < 6; ++t) v += sj[t] * G[t];
-      rb.Mt[i * ND + j] = v;
-      rb.Mt[j * ND + i] = v;
+  // M~, rows q, 4 + q, 8 + q, 12 + q of column kq: M_ij = s_j . G_i at p_i for j
+  // a strict ancestor of i (or the other way round); identity past the robot's
+  // DoFs.  Then M~^-1 by Gauss-Jordan elimination without pivoting (M~ is
+  // symmetric positive definite) in registers.  (With a row per lane and the
+  // pivot row by 16 readlanes most lanes idled.)
+  float e[4];
+  {
+    float sk[6], Gk[6];
+    for (int t = 0; t < 6; ++t) {
+      sk[t] = rb.s[kq * 6 + t];
+      Gk[t] = rb.dsum[kq * DSUM_FLOATS + 6 + t];
+    }
+    const float diag = rb.dsum[kq * DSUM_FLOATS + 12];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = 4 * r + q;
+      const bool up = (dm >> i) & 1u, dn = (am >> i) & 1u;  // kq an ancestor of i; i an ancestor of kq
+      const f3 p_i = body_p(rb, i);
+      const bool revi = __shfl(revk ? 1 : 0, i, WAVE) != 0;
+      // the ancestor's axis at the other body's origin
+      float sx[6], so[6], v = 0.f;
+      for (int t = 0; t < 6; ++t) sx[t] = up ? sk[t] : rb.s[i * 6 + t];
+      s_from(sx, up ? revk : revi, sel(up, p_i, pk) - sel(up, pk, p_i), so);
+      for (int t = 0; t < 6; ++t) v += so[t] * (up ? rb.dsum[i * DSUM_FLOATS + 6 + t] : Gk[t]);
+      e[r] = i == kq ? diag : (up || dn ? v : 0.f);
     }
   }
-  lds_order();
-  // M~^-1 by Gauss-Jordan elimination without pivoting (M~ is symmetric
-  // positive definite) in registers: lane r < 16 holds row r, the pivot row
-  // is read from its lane with readlane (the loops are unrolled, so every
-  // register index is a constant); the identity past the robot's DoFs stays
-  if (lane < ND) {
-    float e[ND];
-#pragma unroll
-    for (int k = 0; k < ND; ++k) e[k] = rb.Mt[lane * ND + k];
-#pragma unroll
-    for (int p = 0; p < ND; ++p) {
-      float prow[ND];
-#pragma unroll
-      for (int k = 0; k < ND; ++k) prow[k] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(e[k]), p));
-      const float inv = 1.f / prow[p];
-      const float f = e[p];
-      const bool own = lane == p;
-#pragma unroll
-      for (int k = 0; k < ND; ++k) {
-        if (k == p) e[k] = own ? inv : -f * inv;
-        else e[k] = own ? prow[k] * inv : e[k] - f * (prow[k] * inv);
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < ND; ++k) rb.Minv[lane * ND + k] = lane < nb && k < nb ? e[k] : 0.f;
-  }
-  lds_order();
+  gj_step<0>(e, q, kq);
   // M~^-1 is symmetric, but the elimination rounds its two triangles
   // differently.  The rows read it row-wise for W = J M~^-1 J^T and the sweeps
   // column-wise for w = M~^-1 J^T; with the two triangles averaged both see
@@ -1620,23 +1670,29 @@ __device__ __forceinline__ void dyn_robot(const KArgs& a, const Scene& S, float*
   // exactly the W its impulse was computed with (otherwise the mismatch
   // accumulates sweep after sweep on redundant contact sets, e.g. more robot
   // contacts than DoFs).
-  for (int e = lane; e < ND * ND; e += WAVE) {
-    const int i = e / ND, k = e % ND;
-    if (i < k) {
-      const float m = 0.5f * (rb.Minv[e] + rb.Minv[k * ND + i]);
-      rb.Minv[e] = m;
-      rb.Minv[k * ND + i] = m;
-    }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    e[r] = 4 * r + q < nb && kq < nb ? e[r] : 0.f;
+    rb.Minv[(4 * r + q) * ND + kq] = e[r];
+  }
+  lds_order();
+  {
+    float et[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) et[r] = rb.Minv[kq * ND + 4 * r + q];
+    lds_order();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) rb.Minv[(4 * r + q) * ND + kq] = 0.5f * (e[r] + et[r]);
   }
   lds_order();
   // unconstrained robot velocity qd + h M~^-1 (tau - C): joint j in lane j
   // of each 16-lane row (the four copies are equal)
   {
-    const int j = lane & 15;
-    float qdd = 0.f;
-    if (j < nb)
-      for (int k = 0; k < nb; ++k) qdd += rb.Minv[j * ND + k] * rb.rhs[k];
-    vR = rb.qd[j] + a.h * qdd;
+    float Mi[ND];
+#pragma unroll
+    for (int k = 0; k < ND; ++k) Mi[k] = rb.Minv[k * ND + kq];
+    const float qdd = minv_dot<0>(Mi, rb.rhs[kq], 0.f);
+    vR = rb.qd[kq] + a.h * qdd;
   }
   // aux joints: passive single-DoF bodies; the gravity torque about the axis
   float* Ax = L + a.L.aux;
@@ -1833,16 +1889,6 @@ __device__ __forceinline__ bool rows_free(const KArgs& a, float* L, int NC) {
 // (With J through LDS, the joint read anew for every row and the inverse
 // masses and the sweeps' blocks in passes of their own a row took 2.3 k
 // cycles.)
-template <int K>
-__device__ __forceinline__ float row_bcast(float v) {  // lane K of the lane's row of 16
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + K, 0xf, 0xf, false));
-}
-template <int K>
-__device__ __forceinline__ float minv_dot(const float* Mi, float J, float acc) {
-  acc = fmaf(Mi[K], row_bcast<K>(J), acc);
-  if constexpr (K + 1 < ND) return minv_dot<K + 1>(Mi, J, acc);
-  else return acc;
-}
 __device__ __forceinline__ bool rows_robot(const KArgs& a, const Scene& S, float* L, int NC, int NR, int NL) {
   const Robot rb = robot_view(L + a.L.robot, L + a.L.dyn);
   const int lane = lane_id();
