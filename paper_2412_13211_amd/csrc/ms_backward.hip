@@ -223,18 +223,42 @@ __device__ __forceinline__ float disk_bar(const TapeU& T, float& yb1, float& yb2
   return T.proj && T.lim > 0.f ? g : 0.f;
 }
 
+// A door / drawer joint as a contact's target: a body at the joint's origin that
+// only turns about the axis (wax) or moves along it (vax), with the joint's
+// velocity, its adjoint and its inverse inertia.
+struct XJoint {
+  msa::V o, vax, wax;
+  float im, v, vb;
+};
+__device__ __forceinline__ void xj_load(const msa::WS& w, const float* L, int x, XJoint& X) {
+  const msa::V a{L[w.xa + x * 3], L[w.xa + x * 3 + 1], L[w.xa + x * 3 + 2]};
+  const bool rev = L[w.xty + x] == 0.f;
+  const msa::V z{0.f, 0.f, 0.f};
+  X.o = msa::V{L[w.xo + x * 3], L[w.xo + x * 3 + 1], L[w.xo + x * 3 + 2]};
+  X.vax = rev ? z : a;
+  X.wax = rev ? a : z;
+  X.im = 1.f / L[w.xM + x];
+  X.v = L[w.vA + x];
+  X.vb = L[w.vAb + x];
+}
+__device__ __forceinline__ void xj_store(const msa::WS& w, float* L, int x, const XJoint& X) {
+  L[w.vA + x] = X.v;
+  L[w.vAb + x] = X.vb;
+}
+
 // Reverse of one contact row's update (friction pair, then normal) between the
-// free body A and a static target or (PAIR) the free body B, everything in
-// registers but the contact's records.  The contact's adjoint record collects,
+// free body A and a static target (KIND 0), the free body B (1) or the door /
+// drawer X (2), everything in registers but the contact's records.  The contact's adjoint record collects,
 // per direction, the linear part Lb of the direction's adjoint and the lever
 // part G (the adjoint of the lever row, owner minus target), from which
 // row_finish forms the direction and contact-point adjoints once: the levers
 // do not change over the sweeps, so an update adds 18 numbers instead of
 // forming cross products with each of its six row adjoints.
-template <bool PAIR>
+template <int KIND>
 __device__ __forceinline__ void row_bar(const msa::WS& w, float* L, int ci, const float* y, const float* q, float mu,
-                                        BSide& A, BSide& B) {
+                                        BSide& A, BSide& B, XJoint& X) {
   using namespace msa;
+  constexpr bool PAIR = KIND == 1, JOINT = KIND == 2;
   const float* e = L + w.con + ci * CR;
   float* cb = L + w.conb + ci * CB;
   float* lb = L + w.lamb + ci * 3;
@@ -255,6 +279,14 @@ __device__ __forceinline__ void row_bar(const msa::WS& w, float* L, int ci, cons
     dir_consts(B, rB, T2.D, T2B);
     xAB = A.x - B.x;
   }
+  float jN = 0.f, j1 = 0.f, j2 = 0.f;  // the joint's rows (target minus owner)
+  if (JOINT) {
+    const V rX = p - X.o;
+    jN = dot(N.D, X.vax) + dot(cross(rX, N.D), X.wax);
+    j1 = dot(T1.D, X.vax) + dot(cross(rX, T1.D), X.wax);
+    j2 = dot(T2.D, X.vax) + dot(cross(rX, T2.D), X.wax);
+    xAB = A.x - X.o;
+  }
   TapeU T;
   tape_update(y, q, mu, T);
   V Ld[3], G[3];
@@ -270,11 +302,11 @@ __device__ __forceinline__ void row_bar(const msa::WS& w, float* L, int ci, cons
     Ld[d] = Ld[d] - lin - cross(gB, xAB);
     G[d] = G[d] - gB;
     const V xc = cross(D, gB);
-    B.xb = B.xb + xc;
+    if (PAIR) B.xb = B.xb + xc;
     A.xb = A.xb - xc;
   };
   // adjoint of the impulse application of one direction (dl its impulse change)
-  auto apply_bar = [&](int d, const DirC& C, const DirC& CB_, float dl) -> float {
+  auto apply_bar = [&](int d, const DirC& C, const DirC& CB_, float jd, float dl) -> float {
     float dlb = bs_dlb(A, C);
     Ld[d] = vmadd(Ld[d], A.vb, A.im * dl);
     G[d] = vmadd(G[d], A.c, dl);
@@ -284,14 +316,19 @@ __device__ __forceinline__ void row_bar(const msa::WS& w, float* L, int ci, cons
       outer_add(B.II, B.wb * -dl, CB_.ang);
       target_bar(d, C.D, B.vb * (B.im * dl), B.c * dl);
     }
+    if (JOINT) {
+      dlb -= X.im * jd * X.vb;
+      target_bar(d, C.D, X.vax * (X.vb * X.im * dl), X.wax * (X.vb * X.im * dl));
+    }
     return dlb;
   };
-  auto rowvel = [&](const DirC& C, const DirC& CB_) -> float {
+  auto rowvel = [&](const DirC& C, const DirC& CB_, float jd) -> float {
     float r = bs_rowvel(A, C);
     if (PAIR) r -= bs_rowvel(B, CB_);
+    if (JOINT) r -= jd * X.v;
     return r;
   };
-  auto rowvel_bar = [&](int d, const DirC& C, const DirC& CB_, float rb) {
+  auto rowvel_bar = [&](int d, const DirC& C, const DirC& CB_, float jd, float rb) {
     Ld[d] = vmadd(Ld[d], A.v, rb);
     G[d] = vmadd(G[d], A.w, rb);
     A.vb = vmadd(A.vb, C.D, rb);
@@ -303,6 +340,10 @@ __device__ __forceinline__ void row_bar(const msa::WS& w, float* L, int ci, cons
       B.wb = vmadd(B.wb, CB_.ang, -rb);
       B.c = vmadd(B.c, CB_.b, -rb);
     }
+    if (JOINT) {
+      target_bar(d, C.D, X.vax * (X.v * rb), X.wax * (X.v * rb));
+      X.vb -= jd * rb;
+    }
   };
   // friction pair
   bs_apply(A, T2, -T.d2);
@@ -311,21 +352,23 @@ __device__ __forceinline__ void row_bar(const msa::WS& w, float* L, int ci, cons
     bs_apply(B, T2B, T.d2);
     bs_apply(B, T1B, T.d1);
   }
-  const float d1b = apply_bar(1, T1, T1B, T.d1), d2b = apply_bar(2, T2, T2B, T.d2);
+  if (JOINT) X.v += X.im * (j2 * T.d2 + j1 * T.d1);
+  const float d1b = apply_bar(1, T1, T1B, j1, T.d1), d2b = apply_bar(2, T2, T2B, j2, T.d2);
   float yb1 = lb1 + d1b, yb2 = lb2 + d2b;
   lb0 += mu * disk_bar(T, yb1, yb2);
-  const float r1 = rowvel(T1, T1B), r2 = rowvel(T2, T2B);
+  const float r1 = rowvel(T1, T1B, j1), r2 = rowvel(T2, T2B, j2);
   const float rb1 = -yb1 * iw1, rb2 = -yb2 * iw2;
-  rowvel_bar(1, T1, T1B, rb1);
-  rowvel_bar(2, T2, T2B, rb2);
+  rowvel_bar(1, T1, T1B, j1, rb1);
+  rowvel_bar(2, T2, T2B, j2, rb2);
   // normal
   bs_apply(A, N, -T.d0);
   if (PAIR) bs_apply(B, NB, T.d0);
-  const float dlb = apply_bar(0, N, NB, T.d0);
+  if (JOINT) X.v += X.im * jN * T.d0;
+  const float dlb = apply_bar(0, N, NB, jN, T.d0);
   const float yb = T.y0 > 0.f ? lb0 + dlb : 0.f;
-  const float r0 = rowvel(N, NB) + bias;
+  const float r0 = rowvel(N, NB, jN) + bias;
   const float rb0 = -yb * iw0;
-  rowvel_bar(0, N, NB, rb0);
+  rowvel_bar(0, N, NB, jN, rb0);
   lb[0] = yb - dlb;
   lb[1] = yb1 - d1b;
   lb[2] = yb2 - d2b;
@@ -357,8 +400,8 @@ __device__ __forceinline__ void add3_to(float* p, msa::V v) {
 // of its sides' geometry.  A free-body owner's are in registers (A.xb, A.II,
 // Rb); a moving target's are added to its record.  ROB: a robot contact (one
 // lane per contact, so lanes may share a target or a body; the joints' part
-// is robot_rows_bar_wave's).  The record holds row_bar's sums, or for a robot
-// contact or a door / drawer target the direction and point adjoints.
+// is robot_rows_bar_wave's).  The record holds row_bar's sums, of a robot
+// contact the direction and point adjoints.
 template <bool ROB>
 __device__ __forceinline__ void row_finish(const msa::Eng& E, float* L, int ci, BSide& A, float* Rb) {
   using namespace msa;
@@ -367,7 +410,7 @@ __device__ __forceinline__ void row_finish(const msa::Eng& E, float* L, int ci, 
   const float* cb = L + w.conb + ci * CB;
   const Ids id = unpack_ids(e[C_ID]);
   const V p{e[C_P], e[C_P + 1], e[C_P + 2]}, n{e[C_N], e[C_N + 1], e[C_N + 2]};
-  const bool direct = ROB || id.tk == 2;
+  constexpr bool direct = ROB;
   V db[3], pb{0.f, 0.f, 0.f};
 #pragma unroll
   for (int d = 0; d < 3; ++d) db[d] = V{cb[3 * d], cb[3 * d + 1], cb[3 * d + 2]};
@@ -525,6 +568,7 @@ __device__ __forceinline__ void gs_alone_bar(const msa::Eng& E, float* L, const 
     const int r0 = LV.gfirst[g], gn = LV.gfirst[g + 1] - r0, c0 = r0 - E.nlim;
     const int f = unpack_ids(L[w.con + c0 * CR + C_ID]).oi;
     BSide A, B;
+    XJoint X;
     bs_load(w, L, f, A);
     int k = gn - 1;
     const float* ty = tape + (size_t)(K - 1) * tsw + 3 * (r0 + k);
@@ -552,7 +596,7 @@ __device__ __forceinline__ void gs_alone_bar(const msa::Eng& E, float* L, const 
         yn[t] = tn[t];
         qn[t] = tq[t];
       }
-      row_bar<false>(w, L, ck, y, q, mu, A, B);
+      row_bar<0>(w, L, ck, y, q, mu, A, B, X);
 #pragma unroll
       for (int t = 0; t < 3; ++t) {
         y[t] = yn[t];
@@ -568,25 +612,54 @@ __device__ __forceinline__ void gs_alone_bar(const msa::Eng& E, float* L, const 
   }
 }
 
+// 3-vectors over the lanes of a quad: lane c < 3 of every four lanes holds
+// component c, lane 3 zero.  A cross product takes 6 instructions instead of
+// 6 per component, a product with the inverse inertia 3.
+template <int A, int B, int C, int D>
+__device__ __forceinline__ float qperm(float v) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(0, __float_as_int(v), A | B << 2 | C << 4 | D << 6, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float qcross(float a, float b) {
+  return qperm<1, 2, 0, 3>(a) * qperm<2, 0, 1, 3>(b) - qperm<2, 0, 1, 3>(a) * qperm<1, 2, 0, 3>(b);
+}
+__device__ __forceinline__ float qsum(float v) {
+  v += qperm<1, 0, 3, 2>(v);
+  return v + qperm<2, 3, 0, 1>(v);
+}
 // Reverse of the robot's rows of one sweep, last row first.  Lane j of each
 // 16-lane row carries the robot's joint j (velocity vr and its adjoint vrb,
 // kept in registers over all sweeps, the four copies equal), each 16-lane row
 // q forms one of the sums over the joints and keeps one of the accumulators:
 // friction part: w_1 . vbar, w_2 . vbar, J_1 . v, J_2 . v and the adjoints of
-// w_1, w_2, J_1, J_2; normal part: rows 0 and 1 for w_n and J_n.  The target
-// side (a free body or a door / drawer joint, none for furniture and planes)
-// is carried by every lane alike.
+// w_1, w_2, J_1, J_2; normal part: rows 0 and 1 for w_n and J_n.  A free-body
+// target is carried in quads: row q forms the target's share of the same sum
+// and accumulates one part of its direction's adjoints.  The contact's adjoint
+// record collects for it per direction what row_bar's does (linear part [9],
+// lever part [9]) and the angular velocity adjoints of its impulses
+// (w.rH [9]), for a door / drawer the row's adjoint (a scalar per direction);
+// rob_target_finish forms the direction, point, position and inertia adjoints
+// once after the sweeps.
+// (With the target's side in full in every lane a row against a free body took
+// about 3 k cycles, against a joint more.)
 struct RobB {
   float J0, J1, J2, w0, w1, w2;  // this lane's joint
   float iw0, iw1, iw2, bias, lb0, lb1, lb2;
   float y[3], q[3];
+  // a moving target: directions, lever, inverse inertia's row and mass, lever
+  // rows of the normal and of this row's friction direction (quads)
+  float D0, D1, D2, r, I0, I1, I2, im, angN, angF, bN;
+  float j0, j1, j2;  // a joint's rows
   msa::Ids id;
 };
+__device__ __forceinline__ float qsmv(const RobB& R, float a) {
+  return R.I0 * qperm<0, 0, 0, 0>(a) + R.I1 * qperm<1, 1, 1, 1>(a) + R.I2 * qperm<2, 2, 2, 2>(a);
+}
 __device__ __forceinline__ void rob_bar_load(const msa::Eng& E, const float* L, int rr, const float* ty,
                                              const float* tq, RobB& R) {
   using namespace msa;
   const WS& w = E.w;
-  const int j = lane_id() & 15;
+  const int lane = lane_id(), j = lane & 15;
   const float* e = L + w.con + rr * CR;
   const float* J = L + w.rJ + rr * 3 * ND + j;
   const float* W = L + w.rw + rr * 3 * ND + j;
@@ -606,6 +679,29 @@ __device__ __forceinline__ void rob_bar_load(const msa::Eng& E, const float* L, 
   id.tk = __builtin_amdgcn_readfirstlane(id.tk);
   id.ti = __builtin_amdgcn_readfirstlane(id.ti);
   R.id = id;
+  if (id.tk == 3) {
+    const int c = lane & 3, cc = c < 3 ? c : 0;
+    const float on = c < 3 ? 1.f : 0.f;
+    R.D0 = on * e[C_N + cc];
+    R.D1 = on * e[C_T1 + cc];
+    R.D2 = on * e[C_T2 + cc];
+    R.r = on * (e[C_P + cc] - L[w.st + 32 + 16 * id.ti + cc]);
+    const float* I = L + w.fIi + id.ti * 9 + 3 * cc;
+    R.I0 = on * I[0];
+    R.I1 = on * I[1];
+    R.I2 = on * I[2];
+    R.angN = qcross(R.r, R.D0);
+    R.angF = qcross(R.r, (lane >> 4) & 1 ? +R.D2 : +R.D1);
+    R.bN = qsmv(R, R.angN);
+    R.im = L[w.fim + id.ti];  // (last in both branches: one store, not two of selected fields)
+  } else if (id.tk == 2) {
+    const V a = E.v3(w.xa + id.ti * 3), rX = E.v3(w.con + rr * CR + C_P) - E.v3(w.xo + id.ti * 3);
+    const V col = L[w.xty + id.ti] == 0.f ? cross(a, rX) : a;
+    R.j0 = dot(E.v3(w.con + rr * CR + C_N), col);
+    R.j1 = dot(E.v3(w.con + rr * CR + C_T1), col);
+    R.j2 = dot(E.v3(w.con + rr * CR + C_T2), col);
+    R.im = 1.f / L[w.xM + id.ti];
+  }
 }
 __device__ __forceinline__ void rob_bar(const msa::Eng& E, float* L, int rr, const RobB& R, float& vr, float& vrb) {
   using namespace msa;
@@ -622,13 +718,16 @@ __device__ __forceinline__ void rob_bar(const msa::Eng& E, float* L, int rr, con
   float* cb = L + w.conb + rr * CB;
   const float Wb0 = cb[B_W], Wb1 = cb[B_W + 1], Wb2 = cb[B_W + 2], bb = cb[B_BIAS];
   vr += -(R.w2 * T.d2) - R.w1 * T.d1;
-  const float sw = odd ? R.w2 : R.w1, sj = odd ? R.J2 : R.J1;
-  const float xf = hi ? vr : vrb;
-  const float s4 = sum16((hi ? sj : sw) * xf);
-  float d1b = row_sum(s4, 0), d2b = row_sum(s4, 1), r1 = row_sum(s4, 2), r2 = row_sum(s4, 3), dlb, r0;
-  float rb0, rb1, rb2, yb1, yb2, yb, lb0 = R.lb0;
+  const float sw = odd ? +R.w2 : +R.w1, sj = odd ? +R.J2 : +R.J1;
+  const float xf = hi ? +vr : +vrb;
+  float s4 = sum16((hi ? sj : sw) * xf), s2;
+  float d1b, d2b, r1, r2, dlb, r0, rb0, rb1, rb2, yb1, yb2, yb, lb0 = R.lb0;
   // the scalars between the friction part's sums and its updates
   auto friction = [&]() {
+    d1b = row_sum(s4, 0);
+    d2b = row_sum(s4, 1);
+    r1 = row_sum(s4, 2);
+    r2 = row_sum(s4, 3);
     yb1 = R.lb1 + d1b;
     yb2 = R.lb2 + d2b;
     lb0 += mu * disk_bar(T, yb1, yb2);
@@ -636,111 +735,88 @@ __device__ __forceinline__ void rob_bar(const msa::Eng& E, float* L, int rr, con
     rb2 = -yb2 * R.iw2;
   };
   auto joints = [&]() {
-    *acc = a0 + (hi ? (odd ? rb2 : rb1) : (odd ? T.d2 : T.d1)) * xf;
+    *acc = a0 + (hi ? (odd ? +rb2 : +rb1) : (odd ? +T.d2 : +T.d1)) * xf;
     vrb += rb1 * R.J1 + rb2 * R.J2;
     vr -= R.w0 * T.d0;
-    const float xn = odd ? vr : vrb;
-    const float s2 = sum16((odd ? R.J0 : R.w0) * xn);
-    dlb = row_sum(s2, 0);
-    r0 = row_sum(s2, 1);
+    const float xn = odd ? +vr : +vrb;
+    s2 = sum16((odd ? +R.J0 : +R.w0) * xn);
   };
   auto normal = [&]() {
+    dlb = row_sum(s2, 0);
+    r0 = row_sum(s2, 1) + R.bias;
     yb = T.y0 > 0.f ? lb0 + dlb : 0.f;
-    r0 += R.bias;
     rb0 = -yb * R.iw0;
-    if (!hi) *acn = an0 + (odd ? rb0 : T.d0) * (odd ? vr : vrb);
+    if (!hi) *acn = an0 + (odd ? +rb0 : +T.d0) * (odd ? +vr : +vrb);
     vrb += rb0 * R.J0;
   };
   if (R.id.tk < 2) {
     friction();
     joints();
     normal();
-  } else {
-    const float* e = L + w.con + rr * CR;
-    const V p{e[C_P], e[C_P + 1], e[C_P + 2]}, D0{e[C_N], e[C_N + 1], e[C_N + 2]},
-        D1{e[C_T1], e[C_T1 + 1], e[C_T1 + 2]}, D2{e[C_T2], e[C_T2 + 1], e[C_T2 + 2]};
-    if (R.id.tk == 3) {
-      // the target's rows are -(D, (p - x) x D); its share of the direction
-      // and contact-point adjoints as in row_bar, with the levers applied here
-      BSide B;
-      bs_load(w, L, R.id.ti, B);
-      const V rB = p - B.x;
-      DirC N, T1, T2;
-      dir_consts(B, rB, D0, N);
-      dir_consts(B, rB, D1, T1);
-      dir_consts(B, rB, D2, T2);
-      V Ld0{0.f, 0.f, 0.f}, Ld1 = Ld0, Ld2 = Ld0, G0 = Ld0, G1 = Ld0, G2 = Ld0;
-      bs_apply(B, T2, T.d2);
-      bs_apply(B, T1, T.d1);
-      d1b -= bs_dlb(B, T1);
-      d2b -= bs_dlb(B, T2);
-      Ld1 = vmadd(Ld1, B.vb, B.im * T.d1);
-      Ld2 = vmadd(Ld2, B.vb, B.im * T.d2);
-      G1 = vmadd(G1, B.c, T.d1);
-      G2 = vmadd(G2, B.c, T.d2);
-      outer_add(B.II, B.wb * -T.d1, T1.ang);
-      outer_add(B.II, B.wb * -T.d2, T2.ang);
-      r1 -= bs_rowvel(B, T1);
-      r2 -= bs_rowvel(B, T2);
-      friction();
-      Ld1 = vmadd(Ld1, B.v, rb1);
-      Ld2 = vmadd(Ld2, B.v, rb2);
-      G1 = vmadd(G1, B.w, rb1);
-      G2 = vmadd(G2, B.w, rb2);
-      B.vb = vmadd(vmadd(B.vb, D1, -rb1), D2, -rb2);
-      B.wb = vmadd(vmadd(B.wb, T1.ang, -rb1), T2.ang, -rb2);
-      B.c = vmadd(vmadd(B.c, T1.b, -rb1), T2.b, -rb2);
-      joints();
-      bs_apply(B, N, T.d0);
-      dlb -= bs_dlb(B, N);
-      Ld0 = vmadd(Ld0, B.vb, B.im * T.d0);
-      G0 = vmadd(G0, B.c, T.d0);
-      outer_add(B.II, B.wb * -T.d0, N.ang);
-      r0 -= bs_rowvel(B, N);
-      normal();
-      Ld0 = vmadd(Ld0, B.v, rb0);
-      G0 = vmadd(G0, B.w, rb0);
-      B.vb = vmadd(B.vb, D0, -rb0);
-      B.wb = vmadd(B.wb, N.ang, -rb0);
-      const V pb = cross(D0, G0) + cross(D1, G1) + cross(D2, G2);
-      B.xb = B.xb + pb;
-      const V e0 = Ld0 + cross(G0, rB), e1 = Ld1 + cross(G1, rB), e2 = Ld2 + cross(G2, rB);
-      if (lane == 0) {
-        bs_store(w, L, R.id.ti, B);
-        cb[0] -= e0.x; cb[1] -= e0.y; cb[2] -= e0.z;
-        cb[3] -= e1.x; cb[4] -= e1.y; cb[5] -= e1.z;
-        cb[6] -= e2.x; cb[7] -= e2.y; cb[8] -= e2.z;
-        cb[B_P] -= pb.x; cb[B_P + 1] -= pb.y; cb[B_P + 2] -= pb.z;
-      }
-    } else {
-      // a door / drawer joint: J = -(d . col), col = a x (p - o) or a
-      Eng::XSide X;
-      Eng::RowAcc Q;
-      E.xs_load(X, R.id.ti);
-      Q.p = p;
-      Q.d[0] = D0; Q.d[1] = D1; Q.d[2] = D2;
-      Q.db[0] = Q.db[1] = Q.db[2] = Q.pb = V{0.f, 0.f, 0.f};
-      Eng::xs_apply(X, Q, 2, -T.d2);
-      Eng::xs_apply(X, Q, 1, -T.d1);
-      d1b += Eng::xs_apply_bar(X, Q, 1, T.d1);
-      d2b += Eng::xs_apply_bar(X, Q, 2, T.d2);
-      r1 += Eng::xs_rowvel(X, Q, 1);
-      r2 += Eng::xs_rowvel(X, Q, 2);
-      friction();
-      Eng::xs_rowvel_bar(X, Q, 1, rb1);
-      Eng::xs_rowvel_bar(X, Q, 2, rb2);
-      joints();
-      Eng::xs_apply(X, Q, 0, -T.d0);
-      dlb += Eng::xs_apply_bar(X, Q, 0, T.d0);
-      r0 += Eng::xs_rowvel(X, Q, 0);
-      normal();
-      Eng::xs_rowvel_bar(X, Q, 0, rb0);
-      if (lane == 0) {
-        E.xs_store(X);
-        for (int k = 0; k < 3; ++k) E.a3(w.conb + rr * CB + B_D + k * 3, Q.db[k]);
-        E.a3(w.conb + rr * CB + B_P, Q.pb);
+  } else if (R.id.tk == 3) {
+    // the target's rows are -(D, (p - x) x D)
+    const int c = lane & 3, cc = c < 3 ? c : 0;
+    const float on = c < 3 ? 1.f : 0.f;
+    float *pv = L + w.vF + R.id.ti * 6 + cc, *pb = L + w.vFb + R.id.ti * 6 + cc, *ph = L + w.rH + rr * 9 + cc;
+    float *pf = cb + (hi ? 9 : 0) + (odd ? 6 : 3) + cc, *pg = ph + (odd ? 6 : 3),
+          *pn = qq == 0 ? cb + cc : (qq == 2 ? cb + 9 + cc : ph);
+    float v = on * pv[0], om = on * pv[3], vb = on * pb[0], wb = on * pb[3];
+    const float af = *pf, ag = *pg, an = *pn;
+    float ci = qsmv(R, wb);
+    const float P = R.D1 * T.d1 + R.D2 * T.d2;
+    v += R.im * P;
+    om += qsmv(R, qcross(R.r, P));
+    const float X = R.im * vb;
+    s4 -= qsum((odd ? +R.D2 : +R.D1) * (hi ? +v : +X) + R.angF * (hi ? +om : +ci));
+    friction();
+    const float dk = odd ? +T.d2 : +T.d1, rk = odd ? +rb2 : +rb1;
+    const float nf = af + dk * (hi ? +ci : +X) + rk * (hi ? +om : +v), ng = ag + dk * wb;
+    const float Q = R.D1 * rb1 + R.D2 * rb2, rQ = qcross(R.r, Q);
+    vb -= Q;
+    wb -= rQ;
+    ci -= qsmv(R, rQ);
+    joints();
+    v += R.im * T.d0 * R.D0;
+    om += T.d0 * R.bN;
+    const float Xn = R.im * vb;
+    s2 -= qsum(R.D0 * (odd ? +v : +Xn) + R.angN * (odd ? +om : +ci));
+    normal();
+    const float nn = an + (qq == 0 ? T.d0 * Xn + rb0 * v : (qq == 2 ? T.d0 * ci + rb0 * om : T.d0 * wb));
+    vb -= R.D0 * rb0;
+    wb -= R.angN * rb0;
+    if (j < 3) {
+      *pf = nf;
+      if (!hi) *pg = ng;
+      if (qq < 3) *pn = nn;
+      if (qq == 0) {
+        pv[0] = v;
+        pv[3] = om;
+        pb[0] = vb;
+        pb[3] = wb;
       }
     }
+  } else {
+    // a door / drawer joint: J = -(d . col), col = a x (p - o) or a
+    float qv = L[w.vA + R.id.ti], qb = L[w.vAb + R.id.ti];
+    float* ps = cb + 12;
+    const float s0 = ps[0], s1 = ps[1], sd = ps[2];
+    qv += R.im * (R.j1 * T.d1 + R.j2 * T.d2);
+    s4 -= (odd ? +R.j2 : +R.j1) * (hi ? +qv : +R.im * qb);
+    friction();
+    const float n1 = s1 + R.im * qb * T.d1 + qv * rb1, n2 = sd + R.im * qb * T.d2 + qv * rb2;
+    qb -= R.j1 * rb1 + R.j2 * rb2;
+    joints();
+    qv += R.im * R.j0 * T.d0;
+    s2 -= R.j0 * (odd ? +qv : +R.im * qb);
+    normal();
+    const float n0 = s0 + R.im * qb * T.d0 + qv * rb0;
+    qb -= R.j0 * rb0;
+    // uniform values: every lane stores the same
+    ps[0] = n0;
+    ps[1] = n1;
+    ps[2] = n2;
+    L[w.vA + R.id.ti] = qv;
+    L[w.vAb + R.id.ti] = qb;
   }
   // uniform values: every lane stores the same
   float* lb = L + w.lamb + rr * 3;
@@ -752,6 +828,60 @@ __device__ __forceinline__ void rob_bar(const msa::Eng& E, float* L, int rr, con
   cb[B_W + 2] = Wb2 - rb2 * r2 * R.iw2;
   cb[B_BIAS] = bb + rb0;
 }
+// After the sweeps: the sums of a robot row's moving target (see above) into
+// the contact's direction and point adjoints and the target's position and
+// inertia adjoints; one lane per robot contact.
+__device__ __forceinline__ void rob_target_finish(const msa::Eng& E, float* L) {
+  using namespace msa;
+  const WS& w = E.w;
+  for (int rr = lane_id(); rr < E.nrob; rr += 64) {
+    const float* e = L + w.con + rr * CR;
+    float* cb = L + w.conb + rr * CB;
+    const Ids id = unpack_ids(e[C_ID]);
+    if (id.tk < 2) continue;
+    const V p{e[C_P], e[C_P + 1], e[C_P + 2]};
+    V db[3], pb{0.f, 0.f, 0.f};
+    if (id.tk == 3) {
+      const V r = p - V{L[w.st + 32 + 16 * id.ti], L[w.st + 32 + 16 * id.ti + 1], L[w.st + 32 + 16 * id.ti + 2]};
+      const float* h = L + w.rH + rr * 9;
+      float II[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        const int o = d == 0 ? C_N : (d == 1 ? C_T1 : C_T2);
+        const V D{e[o], e[o + 1], e[o + 2]}, G{cb[9 + 3 * d], cb[10 + 3 * d], cb[11 + 3 * d]};
+        db[d] = V{cb[3 * d], cb[3 * d + 1], cb[3 * d + 2]} + cross(G, r);
+        pb = pb + cross(D, G);
+        outer_add(II, V{-h[3 * d], -h[3 * d + 1], -h[3 * d + 2]}, cross(r, D));
+      }
+      float* fb = L + w.fb + id.ti * FB;
+      add3_to<true>(fb + F_XB, pb);
+#pragma unroll
+      for (int t = 0; t < 9; ++t) add_to<true>(fb + F_IIB + t, II[t]);
+    } else {
+      const V a = E.v3(w.xa + id.ti * 3);
+      const bool rev = L[w.xty + id.ti] == 0.f;
+      const V col = rev ? cross(a, p - E.v3(w.xo + id.ti * 3)) : a;
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        const int o = d == 0 ? C_N : (d == 1 ? C_T1 : C_T2);
+        const V D{e[o], e[o + 1], e[o + 2]};
+        const float S = cb[12 + d];
+        db[d] = col * S;
+        if (rev) pb = vmadd(pb, cross(D, a), S);
+      }
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      cb[3 * d] = -db[d].x;
+      cb[3 * d + 1] = -db[d].y;
+      cb[3 * d + 2] = -db[d].z;
+    }
+    cb[B_P] = -pb.x;
+    cb[B_P + 1] = -pb.y;
+    cb[B_P + 2] = -pb.z;
+  }
+  lds_order();
+}
 
 __device__ __forceinline__ void zero_lds(float* L, long off, int n) {
   for (int i = lane_id(); i < n; i += 64) L[off + i] = 0.f;
@@ -759,17 +889,13 @@ __device__ __forceinline__ void zero_lds(float* L, long off, int n) {
 
 // Contact rows (the same quantities as the engine's rows(), limit rows
 // excepted).  The sweeps read inverse effective masses (a row below 1e-12, or a
-// friction pair with either one below, is skipped: inverse 0), except where a
-// free body's target is a door / drawer (the engine's form).
+// friction pair with either one below, is skipped: inverse 0).
 __device__ __forceinline__ bool row_inverse(float* e) {
   using namespace msa;
   const bool ok0 = e[C_W] >= 1e-12f, ok1 = e[C_W + 1] >= 1e-12f, ok2 = e[C_W + 2] >= 1e-12f;
-  const Ids id = unpack_ids(e[C_ID]);
-  if (id.ok == 0 || id.tk != 2) {
-    e[C_W] = ok0 ? 1.f / e[C_W] : 0.f;
-    e[C_W + 1] = ok1 && ok2 ? 1.f / e[C_W + 1] : 0.f;
-    e[C_W + 2] = ok1 && ok2 ? 1.f / e[C_W + 2] : 0.f;
-  }
+  e[C_W] = ok0 ? 1.f / e[C_W] : 0.f;
+  e[C_W + 1] = ok1 && ok2 ? 1.f / e[C_W + 1] : 0.f;
+  e[C_W + 2] = ok1 && ok2 ? 1.f / e[C_W + 2] : 0.f;
   return ok0 && ok1 && ok2;
 }
 // One lane per contact: the tangents, bias and the free-body and door/drawer
@@ -1698,6 +1824,7 @@ __device__ __forceinline__ void integrate_robot(const msa::Eng& E, float* L) {
   zero_lds(L, w.vRb, ND);
   zero_lds(L, w.rJb, E.nrob * 3 * ND);
   zero_lds(L, w.rwb, E.nrob * 3 * ND);
+  zero_lds(L, w.rH, E.nrob * 9);
   zero_lds(L, w.bacc, ND * 9);
   zero_lds(L, w.Mb, ND * ND);
   lds_order();
@@ -1793,11 +1920,8 @@ __device__ __forceinline__ void gs_linked_bar(msa::Eng& E, float* L, Sched sc, c
         if ((first ? glv : LV.lvl[g]) != lv) continue;
         const int r0 = first ? gr0 : LV.gfirst[g], gn = first ? ggn : LV.gfirst[g + 1] - r0;
         const Ids id = unpack_ids(L[w.con + (r0 - NL) * CR + C_ID]);
-        if (id.tk == 2) {
-          E.contact_bar(it, r0 - NL);
-          continue;
-        }
         BSide A, B;
+        XJoint X;
         bs_load(w, L, id.oi, A);
         auto row = [&](int r, float* y, float* q) {
 #pragma unroll
@@ -1810,13 +1934,18 @@ __device__ __forceinline__ void gs_linked_bar(msa::Eng& E, float* L, Sched sc, c
         if (id.tk == 3) {
           bs_load(w, L, id.ti, B);
           row(r0, y, q);
-          row_bar<true>(w, L, r0 - NL, y, q, mu, A, B);
+          row_bar<1>(w, L, r0 - NL, y, q, mu, A, B, X);
           bs_store(w, L, id.ti, B);
+        } else if (id.tk == 2) {
+          xj_load(w, L, id.ti, X);
+          row(r0, y, q);
+          row_bar<2>(w, L, r0 - NL, y, q, mu, A, B, X);
+          xj_store(w, L, id.ti, X);
         } else {
 #pragma unroll 1
           for (int r = r0 + gn - 1; r >= r0; --r) {
             row(r, y, q);
-            row_bar<false>(w, L, r - NL, y, q, mu, A, B);
+            row_bar<0>(w, L, r - NL, y, q, mu, A, B, X);
           }
         }
         bs_store(w, L, id.oi, A);
@@ -1864,6 +1993,7 @@ __device__ __forceinline__ void finish_linked(msa::Eng& E, float* L, Sched sc) {
   const int lane = lane_id();
   const WS& w = E.w;
   const Lv LV = lv_view(L, w);
+  rob_target_finish(E, L);
   robot_rows_bar_wave(E, L);
   for (int rr = lane; rr < E.nrob; rr += 64) {
     BSide A;
