@@ -186,7 +186,7 @@ enum { X_RB = 0, X_BCB = 9, X_QB = 12, XB = 16 };
 // sweep schedule arrays (ints): a row's nodes (then a group's level), first
 // row of each group, groups touching each dynamic node
 MSA_HD inline int lv_rows(int ccap) { return 2 * AMAX + ccap; }
-MSA_HD inline int lv_ints(int ccap) { return 2 * lv_rows(ccap) + 1 + 64; }
+MSA_HD inline int lv_ints(int ccap) { return 2 * lv_rows(ccap) + 1 + 128; }
 
 struct WS {
   int wave;  // the wavefront kernel's LDS layout

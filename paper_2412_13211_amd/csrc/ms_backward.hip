@@ -64,7 +64,7 @@ __device__ __forceinline__ float bcast0(float v) { return __int_as_float(__built
 // rotation: a VALU operand modifier, no LDS crossbar)
 template <int N>
 __device__ __forceinline__ float row_ror(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, false));
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, true));
 }
 // sum within each 16-lane group, returned in every lane of the group
 __device__ __forceinline__ float sum16(float v) {
@@ -83,7 +83,7 @@ __device__ __forceinline__ float row_sum(float s16, int q) {
 
 // level-schedule views inside the LDS block
 struct Lv {
-  int *lvl, *gfirst, *last;
+  int *lvl, *gfirst, *last, *linked;
 };
 __device__ __forceinline__ Lv lv_view(float* L, const msa::WS& w) {
   Lv v;
@@ -91,7 +91,8 @@ __device__ __forceinline__ Lv lv_view(float* L, const msa::WS& w) {
   const int R = msa::lv_rows(w.ccap);
   v.lvl = p; p += R;
   v.gfirst = p; p += R + 1;
-  v.last = p;
+  v.last = p; p += 64;
+  v.linked = p;
   return v;
 }
 
@@ -223,6 +224,21 @@ __device__ __forceinline__ float disk_bar(const TapeU& T, float& yb1, float& yb2
   return T.proj && T.lim > 0.f ? g : 0.f;
 }
 
+// 3-vectors over the lanes of a quad: lane c < 3 of every four lanes holds
+// component c, lane 3 zero.  A cross product takes 6 instructions instead of
+// 6 per component, a product with the inverse inertia 3.
+template <int A, int B, int C, int D>
+__device__ __forceinline__ float qperm(float v) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(0, __float_as_int(v), A | B << 2 | C << 4 | D << 6, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float qcross(float a, float b) {
+  return qperm<1, 2, 0, 3>(a) * qperm<2, 0, 1, 3>(b) - qperm<2, 0, 1, 3>(a) * qperm<1, 2, 0, 3>(b);
+}
+__device__ __forceinline__ float qsum(float v) {
+  v += qperm<1, 0, 3, 2>(v);
+  return v + qperm<2, 3, 0, 1>(v);
+}
 // A door / drawer joint as a contact's target: a body at the joint's origin that
 // only turns about the axis (wax) or moves along it (vax), with the joint's
 // velocity, its adjoint and its inverse inertia.
@@ -247,8 +263,8 @@ __device__ __forceinline__ void xj_store(const msa::WS& w, float* L, int x, cons
 }
 
 // Reverse of one contact row's update (friction pair, then normal) between the
-// free body A and a static target (KIND 0), the free body B (1) or the door /
-// drawer X (2), everything in registers but the contact's records.  The contact's adjoint record collects,
+// free body A and the free body B (KIND 1) or the door / drawer X (2),
+// everything in registers but the contact's records.  The contact's adjoint record collects,
 // per direction, the linear part Lb of the direction's adjoint and the lever
 // part G (the adjoint of the lever row, owner minus target), from which
 // row_finish forms the direction and contact-point adjoints once: the levers
@@ -382,6 +398,135 @@ __device__ __forceinline__ void row_bar(const msa::WS& w, float* L, int ci, cons
   cb[B_W + 1] -= rb1 * r1 * iw1;
   cb[B_W + 2] -= rb2 * r2 * iw2;
   cb[B_BIAS] += rb0;
+}
+
+// The same between a free body and a static target with the body in a quad
+// (lane c < 3 component c, of matrices row c): most rows are of this kind, and
+// 4 lanes a body leave no scene with a chain longer than its bodies' rows.  (A
+// body per lane issued three times the instructions for the same chain: 2.2 k
+// cycles a row.)
+struct QBody {
+  float x, v, w, vb, wb, c, im, I0, I1, I2, II0, II1, II2;
+};
+__device__ __forceinline__ float qsmv(const QBody& B, float a) {
+  return B.I0 * qperm<0, 0, 0, 0>(a) + B.I1 * qperm<1, 1, 1, 1>(a) + B.I2 * qperm<2, 2, 2, 2>(a);
+}
+__device__ __forceinline__ void qb_load(const msa::WS& w, const float* L, int f, QBody& B) {
+  const int c = lane_id() & 3, cc = c < 3 ? c : 0;
+  const float on = c < 3 ? 1.f : 0.f;
+  const float *v = L + w.vF + f * 6 + cc, *vb = L + w.vFb + f * 6 + cc, *I = L + w.fIi + f * 9 + 3 * cc;
+  B.x = on * L[w.st + 32 + 16 * f + cc];
+  B.v = on * v[0];
+  B.w = on * v[3];
+  B.vb = on * vb[0];
+  B.wb = on * vb[3];
+  B.I0 = on * I[0];
+  B.I1 = on * I[1];
+  B.I2 = on * I[2];
+  B.im = L[w.fim + f];
+  B.c = qsmv(B, B.wb);
+  B.II0 = B.II1 = B.II2 = 0.f;
+}
+__device__ __forceinline__ void qb_store(const msa::WS& w, float* L, int f, const QBody& B) {
+  const int c = lane_id() & 3;
+  if (c == 3) return;
+  float *v = L + w.vF + f * 6 + c, *vb = L + w.vFb + f * 6 + c, *ib = L + w.fb + f * msa::FB + msa::F_IIB + 3 * c;
+  v[0] = B.v;
+  v[3] = B.w;
+  vb[0] = B.vb;
+  vb[3] = B.wb;
+  ib[0] += B.II0;
+  ib[1] += B.II1;
+  ib[2] += B.II2;
+}
+// a row's constants
+struct QRow {
+  float D0, D1, D2, p, iw0, iw1, iw2, bias;
+};
+__device__ __forceinline__ void qr_load(const float* e, QRow& R) {
+  using namespace msa;
+  const int c = lane_id() & 3, cc = c < 3 ? c : 0;
+  const float on = c < 3 ? 1.f : 0.f;
+  R.D0 = on * e[C_N + cc];
+  R.D1 = on * e[C_T1 + cc];
+  R.D2 = on * e[C_T2 + cc];
+  R.p = on * e[C_P + cc];
+  R.iw0 = e[C_W];
+  R.iw1 = e[C_W + 1];
+  R.iw2 = e[C_W + 2];
+  R.bias = e[C_BIAS];
+}
+// cb, lb: the contact's adjoint record and impulse adjoints
+__device__ __forceinline__ void row_quad(const QRow& R, float* cb, float* lb, const float* y, const float* q, float mu,
+                                         QBody& A) {
+  using namespace msa;
+  const int c = lane_id() & 3, cc = c < 3 ? c : 0;
+  float* cv = cb + cc;  // this component of the record's vectors
+  const float D0 = R.D0, D1 = R.D1, D2 = R.D2, r = R.p - A.x;
+  const float iw0 = R.iw0, iw1 = R.iw1, iw2 = R.iw2, bias = R.bias;
+  float lb0 = lb[0];
+  const float lb1 = lb[1], lb2 = lb[2];
+  float L0 = cv[0], L1 = cv[3], L2 = cv[6], G0 = cv[9], G1 = cv[12], G2 = cv[15];
+  const float Wb0 = cb[B_W], Wb1 = cb[B_W + 1], Wb2 = cb[B_W + 2], bb = cb[B_BIAS];
+  const float aN = qcross(r, D0), a1 = qcross(r, D1), a2 = qcross(r, D2);
+  const float bN = qsmv(A, aN);
+  TapeU T;
+  tape_update(y, q, mu, T);
+  auto inertia = [&](float s, float ang) {
+    A.II0 += s * qperm<0, 0, 0, 0>(ang);
+    A.II1 += s * qperm<1, 1, 1, 1>(ang);
+    A.II2 += s * qperm<2, 2, 2, 2>(ang);
+  };
+  // friction pair
+  const float P = D1 * T.d1 + D2 * T.d2;
+  A.v -= A.im * P;
+  A.w -= qsmv(A, a1 * T.d1 + a2 * T.d2);
+  const float X = A.im * A.vb;
+  const float d1b = qsum(D1 * X + a1 * A.c), d2b = qsum(D2 * X + a2 * A.c);
+  const float r1 = qsum(D1 * A.v + a1 * A.w), r2 = qsum(D2 * A.v + a2 * A.w);
+  inertia(A.wb * T.d1, a1);
+  inertia(A.wb * T.d2, a2);
+  float yb1 = lb1 + d1b, yb2 = lb2 + d2b;
+  lb0 += mu * disk_bar(T, yb1, yb2);
+  const float rb1 = -yb1 * iw1, rb2 = -yb2 * iw2;
+  L1 += X * T.d1 + A.v * rb1;
+  L2 += X * T.d2 + A.v * rb2;
+  G1 += A.c * T.d1 + A.w * rb1;
+  G2 += A.c * T.d2 + A.w * rb2;
+  const float Q = a1 * rb1 + a2 * rb2;
+  A.vb += D1 * rb1 + D2 * rb2;
+  A.wb += Q;
+  A.c += qsmv(A, Q);
+  // normal
+  A.v -= A.im * T.d0 * D0;
+  A.w -= T.d0 * bN;
+  const float Xn = A.im * A.vb;
+  const float dlb = qsum(D0 * Xn + aN * A.c), r0 = qsum(D0 * A.v + aN * A.w) + bias;
+  inertia(A.wb * T.d0, aN);
+  const float yb = T.y0 > 0.f ? lb0 + dlb : 0.f;
+  const float rb0 = -yb * iw0;
+  L0 += Xn * T.d0 + A.v * rb0;
+  G0 += A.c * T.d0 + A.w * rb0;
+  A.vb += D0 * rb0;
+  A.wb += aN * rb0;
+  A.c += bN * rb0;
+  if (c < 3) {
+    cv[0] = L0;
+    cv[3] = L1;
+    cv[6] = L2;
+    cv[9] = G0;
+    cv[12] = G1;
+    cv[15] = G2;
+  }
+  // equal in the quad's lanes
+  lb[0] = yb - dlb;
+  lb[1] = yb1 - d1b;
+  lb[2] = yb2 - d2b;
+  // W's adjoint: yb r / W^2
+  cb[B_W] = Wb0 - rb0 * r0 * iw0;
+  cb[B_W + 1] = Wb1 - rb1 * r1 * iw1;
+  cb[B_W + 2] = Wb2 - rb2 * r2 * iw2;
+  cb[B_BIAS] = bb + rb0;
 }
 
 // add to a value that other lanes (SHARED) may add to in the same instruction
@@ -553,23 +698,33 @@ __device__ __forceinline__ void finish_end(const msa::WS& w, float* L, int f, co
 }
 
 // The reverse sweeps of the bodies that only static targets touch (groups of
-// level 0), then their rows^T and contacts^T: one lane per body, the body in
+// level 0), then their rows^T and contacts^T: one quad per body, the body in
 // registers over all sweeps.  Every lane reads its rows' tape values straight
-// from the record, a row ahead.
+// from the record, a row ahead.  The contacts^T take a contact per lane, the
+// quad's sums over them go to the body.
 __device__ __forceinline__ void gs_alone_bar(const msa::Eng& E, float* L, const Lv& LV, int G, const float* tape,
                                              int tsw) {
   using namespace msa;
   const WS& w = E.w;
   const int K = E.pr.K;
   const float mu = E.pr.mu;
+  // these groups (at most one per free body) in a row, in the schedule's scratch
+  int na = 0;
+  for (int base = 0; base < G; base += 64) {
+    const int g = base + lane_id();
+    const bool alone = g < G && LV.lvl[g] == 0;
+    const uint64_t mk = __ballot(alone);
+    if (alone) LV.last[na + __popcll(mk & ((1ull << lane_id()) - 1ull))] = g;
+    na += __popcll(mk);
+  }
+  lds_order();
 #pragma unroll 1
-  for (int g = lane_id(); g < G; g += 64) {
-    if (LV.lvl[g] != 0) continue;
+  for (int i0 = lane_id() >> 2; i0 < na; i0 += 16) {
+    const int g = LV.last[i0];
     const int r0 = LV.gfirst[g], gn = LV.gfirst[g + 1] - r0, c0 = r0 - E.nlim;
     const int f = unpack_ids(L[w.con + c0 * CR + C_ID]).oi;
-    BSide A, B;
-    XJoint X;
-    bs_load(w, L, f, A);
+    QBody A;
+    qb_load(w, L, f, A);
     int k = gn - 1;
     const float* ty = tape + (size_t)(K - 1) * tsw + 3 * (r0 + k);
     float y[3], q[3];
@@ -580,14 +735,28 @@ __device__ __forceinline__ void gs_alone_bar(const msa::Eng& E, float* L, const 
     }
     const int n = K * gn;
     int it = K - 1;
+    const float* e0 = L + w.con + c0 * CR;
+    const float* e = e0 + k * CR;
+    float *cb0 = L + w.conb + c0 * CB, *cb = cb0 + k * CB, *lb0 = L + w.lamb + c0 * 3, *lb = lb0 + k * 3;
+    const int wrap = gn - 1;
+    QRow R;
+    qr_load(e, R);
 #pragma unroll 1
     for (int i = 0; i < n; ++i) {
-      const int ck = c0 + k;
+      float *cr = cb, *lr = lb;
       // the next row: the one before it in this sweep, or the last of the sweep before
+      e -= CR;
+      cb -= CB;
+      lb -= 3;
       if (--k < 0) {
-        k = gn - 1;
+        k = wrap;
         --it;
+        e = e0 + wrap * CR;
+        cb = cb0 + wrap * CB;
+        lb = lb0 + wrap * 3;
       }
+      QRow Rn;
+      qr_load(e, Rn);
       float yn[3], qn[3];
       const float* tn = tape + (size_t)(it > 0 ? it : 0) * tsw + 3 * (r0 + k);
       const float* tq = tape + (size_t)(it > 0 ? it - 1 : 0) * tsw + 3 * (r0 + k);
@@ -596,37 +765,31 @@ __device__ __forceinline__ void gs_alone_bar(const msa::Eng& E, float* L, const 
         yn[t] = tn[t];
         qn[t] = tq[t];
       }
-      row_bar<0>(w, L, ck, y, q, mu, A, B, X);
+      row_quad(R, cr, lr, y, q, mu, A);
 #pragma unroll
       for (int t = 0; t < 3; ++t) {
         y[t] = yn[t];
         q[t] = it > 0 ? qn[t] : 0.f;
       }
+      R = Rn;
     }
-    bs_store(w, L, f, A);
+    qb_store(w, L, f, A);
+    lds_order();
+    BSide S;
     float Rb[9];
-    finish_begin(w, L, f, A, Rb);
+    finish_begin(w, L, f, S, Rb);
 #pragma unroll 1
-    for (int c = c0; c < c0 + gn; ++c) row_finish<false>(E, L, c, A, Rb);
-    finish_end(w, L, f, A, Rb);
+    for (int c = c0 + (lane_id() & 3); c < c0 + gn; c += 4) row_finish<false>(E, L, c, S, Rb);
+    S.xb = msa::V{qsum(S.xb.x), qsum(S.xb.y), qsum(S.xb.z)};
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+      S.II[t] = qsum(S.II[t]);
+      Rb[t] = qsum(Rb[t]);
+    }
+    if ((lane_id() & 3) == 0) finish_end(w, L, f, S, Rb);
   }
 }
 
-// 3-vectors over the lanes of a quad: lane c < 3 of every four lanes holds
-// component c, lane 3 zero.  A cross product takes 6 instructions instead of
-// 6 per component, a product with the inverse inertia 3.
-template <int A, int B, int C, int D>
-__device__ __forceinline__ float qperm(float v) {
-  return __int_as_float(
-      __builtin_amdgcn_update_dpp(0, __float_as_int(v), A | B << 2 | C << 4 | D << 6, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float qcross(float a, float b) {
-  return qperm<1, 2, 0, 3>(a) * qperm<2, 0, 1, 3>(b) - qperm<2, 0, 1, 3>(a) * qperm<1, 2, 0, 3>(b);
-}
-__device__ __forceinline__ float qsum(float v) {
-  v += qperm<1, 0, 3, 2>(v);
-  return v + qperm<2, 3, 0, 1>(v);
-}
 // Reverse of the robot's rows of one sweep, last row first.  Lane j of each
 // 16-lane row carries the robot's joint j (velocity vr and its adjoint vrb,
 // kept in registers over all sweeps, the four copies equal), each 16-lane row
@@ -1063,7 +1226,7 @@ __device__ __forceinline__ float2 pick2(float v0, float v1, float v2, float v3, 
 // value of lane K of the lane's row of 16
 template <int K>
 __device__ __forceinline__ float row_bcast(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + K, 0xf, 0xf, false));
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + K, 0xf, 0xf, true));
 }
 // row Q of 16 lanes in all four
 template <int Q>
@@ -1897,9 +2060,34 @@ __device__ __forceinline__ void gs_linked_bar(msa::Eng& E, float* L, Sched sc, c
   if (K > 0) stage(K - 1);
   if (K > 1) stage(K - 2);
   if (K > 2) fetch(K - 3);
-  // the lane's group (of the first 64): level, first row, rows
-  const int glv = lane < sc.ng ? LV.lvl[lane] : 0;
-  const int gr0 = lane < sc.ng ? LV.gfirst[lane] : 0, ggn = lane < sc.ng ? LV.gfirst[lane + 1] - gr0 : 0;
+  // Groups against static targets by quads, the others by lanes.  The former in a
+  // row when they are at most 64 (quad k of chunk h: the (16 h + k)-th), their
+  // levels in the quad's registers; else looked up among all groups.  The level
+  // of the lane's group of the first 64 (0: by quads, or alone).
+  auto by_quad = [&](int g) { return unpack_ids(L[w.con + (LV.gfirst[g] - NL) * CR + C_ID]).tk < 2; };
+  const int qd = lane >> 2;
+  int nq = 0, glv = 0;
+  for (int base = 0; base < sc.ng; base += 64) {
+    const int g = base + lane;
+    const int l = g < sc.ng ? LV.lvl[g] : 0;
+    const bool quad = l > 0 && by_quad(g);
+    if (base == 0) glv = quad ? 0 : l;
+    const uint64_t mk = __ballot(quad);
+    const int at = nq + __popcll(mk & ((1ull << lane) - 1ull));
+    if (quad && at < 64) LV.linked[at] = g;
+    nq += __popcll(mk);
+  }
+  lds_order();
+  const bool listed = nq <= 64;
+  if (!listed) nq = sc.ng;
+  uint64_t qlv = 0ull;
+  if (listed) {
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+      const int i = 16 * h + qd;
+      qlv |= (uint64_t)(i < nq ? LV.lvl[LV.linked[i]] : 0) << (16 * h);
+    }
+  }
   float vr = L[w.vR + (lane & 15)], vrb = L[w.vRb + (lane & 15)];
   lds_order();
   const float mu = E.pr.mu;
@@ -1912,41 +2100,69 @@ __device__ __forceinline__ void gs_linked_bar(msa::Eng& E, float* L, Sched sc, c
     lds_order();
     const float* ty = L + w.tring + (it & 1) * w.trs;
     const float* tq = it > 0 ? L + w.tring + ((it - 1) & 1) * w.trs : nullptr;
+    auto row = [&](int r, float* y, float* q) {
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        y[t] = ty[3 * r + t];
+        q[t] = tq ? tq[3 * r + t] : 0.f;
+      }
+    };
 #pragma unroll 1
     for (int lv = sc.maxl; lv >= 1; --lv) {
 #pragma unroll 1
+      for (int i = qd, h = 0; i < nq; i += 16, h += 16) {
+        const int l = listed ? (int)(qlv >> h) & 0xffff : LV.lvl[i];
+        if (l != lv) continue;
+        const int g = listed ? LV.linked[i] : i;
+        if (!listed && !by_quad(g)) continue;
+        const int r0 = LV.gfirst[g], gn = LV.gfirst[g + 1] - r0;
+        const int f = unpack_ids(L[w.con + (r0 - NL) * CR + C_ID]).oi;
+        QBody A;
+        qb_load(w, L, f, A);
+        int r = r0 + gn - 1;
+        const float* e = L + w.con + (r - NL) * CR;
+        float *cb = L + w.conb + (r - NL) * CB, *lb = L + w.lamb + (r - NL) * 3;
+        QRow R;
+        float y[3], q[3];
+        qr_load(e, R);
+        row(r, y, q);
+#pragma unroll 1
+        for (;; cb -= CB, lb -= 3) {
+          r = r > r0 ? r - 1 : r0 - 1;
+          e -= r >= r0 ? CR : 0;
+          QRow Rn;
+          float yn[3], qn[3];
+          qr_load(e, Rn);
+          row(r >= r0 ? r : r0, yn, qn);
+          row_quad(R, cb, lb, y, q, mu, A);
+          if (r < r0) break;
+          R = Rn;
+#pragma unroll
+          for (int t = 0; t < 3; ++t) {
+            y[t] = yn[t];
+            q[t] = qn[t];
+          }
+        }
+        qb_store(w, L, f, A);
+      }
+#pragma unroll 1
       for (int g = lane; g < sc.ng; g += 64) {
-        const bool first = g == lane;
-        if ((first ? glv : LV.lvl[g]) != lv) continue;
-        const int r0 = first ? gr0 : LV.gfirst[g], gn = first ? ggn : LV.gfirst[g + 1] - r0;
-        const Ids id = unpack_ids(L[w.con + (r0 - NL) * CR + C_ID]);
+        if (g == lane ? glv != lv : LV.lvl[g] != lv || by_quad(g)) continue;
+        const int r = LV.gfirst[g];
+        const Ids id = unpack_ids(L[w.con + (r - NL) * CR + C_ID]);
         BSide A, B;
         XJoint X;
         bs_load(w, L, id.oi, A);
-        auto row = [&](int r, float* y, float* q) {
-#pragma unroll
-          for (int t = 0; t < 3; ++t) {
-            y[t] = ty[3 * r + t];
-            q[t] = tq ? tq[3 * r + t] : 0.f;
-          }
-        };
         float y[3], q[3];
+        row(r, y, q);
         if (id.tk == 3) {
           bs_load(w, L, id.ti, B);
-          row(r0, y, q);
-          row_bar<1>(w, L, r0 - NL, y, q, mu, A, B, X);
+          row_bar<1>(w, L, r - NL, y, q, mu, A, B, X);
           bs_store(w, L, id.ti, B);
-        } else if (id.tk == 2) {
-          xj_load(w, L, id.ti, X);
-          row(r0, y, q);
-          row_bar<2>(w, L, r0 - NL, y, q, mu, A, B, X);
-          xj_store(w, L, id.ti, X);
         } else {
-#pragma unroll 1
-          for (int r = r0 + gn - 1; r >= r0; --r) {
-            row(r, y, q);
-            row_bar<0>(w, L, r - NL, y, q, mu, A, B, X);
-          }
+          xj_load(w, L, id.ti, X);
+          row_bar<2>(w, L, r - NL, y, q, mu, A, B, X);
+          xj_store(w, L, id.ti, X);
         }
         bs_store(w, L, id.oi, A);
       }

@@ -134,7 +134,7 @@ __device__ __forceinline__ int bcasti(int v, int src) { return __shfl(v, src, WA
 // rotation: a VALU operand modifier, no LDS crossbar)
 template <int N>
 __device__ __forceinline__ float row_ror(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, false));
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, true));
 }
 // sum over aligned groups of 16 lanes (result in every lane of the group)
 __device__ __forceinline__ float sum16(float v) {
@@ -147,7 +147,7 @@ __device__ __forceinline__ float sum16(float v) {
 // value of lane K of the lane's row of 16
 template <int K>
 __device__ __forceinline__ float row_bcast(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + K, 0xf, 0xf, false));
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + K, 0xf, 0xf, true));
 }
 // row Q of 16 lanes in all four
 template <int Q>
