@@ -232,7 +232,16 @@ MSA_HD inline WS ws_layout(int fmax, int ntmax, int ccap, int rcap, int K, int n
   w.gB = take(w.ss);
   w.ub = take(ND);
   w.tape = take(wave ? 0 : K * 3 * (2 * AMAX + ccap));
-  w.kR = take(ND * 9); w.kp = take(ND * 3); w.ka = take(ND * 3); w.ko = take(ND * 3); w.kc = take(ND * 3);
+  w.kR = take(ND * 9); w.kp = take(ND * 3);
+  // the wavefront kernel's bodies' poses and drive terms are dead before the
+  // reverse sweeps: the robot rows' rH lies there
+  if (wave) {
+    w.tau = take(ND);
+    w.arm = take(ND);
+    w.rH = w.kR;
+    if (w.rcap * 9 > o - w.kR) o = (w.kR + w.rcap * 9 + 3) & ~3;
+  }
+  w.ka = take(ND * 3); w.ko = take(ND * 3); w.kc = take(ND * 3);
   w.kIcw = take(ND * 6); w.ks = take(ND * 6); w.kI = take(ND * 36); w.kIc = take(ND * 36);
   w.sph = take(wave ? 0 : SPH * 3);  // sphere centres: only the lane kernel's contact search reads them
   w.tl = take(wave ? 0 : (ND + 1) * (w.ntmax + 1));
@@ -240,7 +249,12 @@ MSA_HD inline WS ws_layout(int fmax, int ntmax, int ccap, int rcap, int K, int n
   w.xR = take(AMAX * 9); w.xbc = take(AMAX * 3); w.xa = take(AMAX * 3); w.xo = take(AMAX * 3);
   w.xM = take(AMAX); w.xC = take(AMAX); w.xty = take(AMAX);
   align();
-  w.tau = take(ND); w.arm = take(ND); w.L = take(ND * ND); w.z = take(ND);
+  if (!wave) {
+    w.tau = take(ND);
+    w.arm = take(ND);
+    w.rH = 0;
+  }
+  w.L = take(ND * ND); w.z = take(ND);
   w.rv = take(ND * 6); w.ra = take(ND * 6); w.rfl = take(wave ? 0 : ND * 6); w.rff = take(ND * 6);
   w.vR = take(ND); w.vA = take(AMAX); w.vF = take(fm * 6);
   // impulses: working storage of the lane kernel's forward sweeps (the
@@ -271,7 +285,6 @@ MSA_HD inline WS ws_layout(int fmax, int ntmax, int ccap, int rcap, int K, int n
   w.fb = take(fm * FB); w.xb = take(AMAX * XB);
   w.Mb = take(ND * ND);
   w.bacc = take(ND * 9);
-  w.rH = take(wave ? w.rcap * 9 : 0);
   w.ctl = take(wave ? 2 : 0);
   w.lv = take(wave ? lv_ints(ccap) : 0);
   w.Minv = w.L;  // the elimination runs in registers and replaces M~
