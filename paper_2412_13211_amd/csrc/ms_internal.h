@@ -113,7 +113,8 @@ __host__ __device__ inline LdsLayout make_layout(int fmax, int smax, int ccap, i
   // words the two wavefronts exchange: CTL_*
   L.ctl = o;   o += CTL_WORDS;
   L.robot = o; o += lds_align4(ROBOT_FLOATS);
-  L.sph = o;   o += nsph * 4;   // world sphere centres and radii of the robot
+  // world sphere centres and radii of the robot, then each sphere's body and flags
+  L.sph = o;   o += lds_align4(nsph * 5);
   L.fr = o;    o += lds_align4((fmax + 1) * FREE_FLOATS);  // + a zero record (static side)
   L.aux = o;   o += AMAX * AUX_FLOATS;
   L.stat = o;  o += lds_align4(L.smax * 6);
@@ -121,13 +122,13 @@ __host__ __device__ inline LdsLayout make_layout(int fmax, int smax, int ccap, i
   L.own = o;   o += lds_align4((L.owners + 1) / 2);        // uint16 owner table
   L.con = o;   o += lds_align4(ccap * CON_FLOATS);
   // robot contact rows.  Before the rows phase builds them, the culling masks
-  // (per robot or free body and 64-target chunk, 64 bits) with the bodies'
-  // bounding spheres (4 floats each) lie there, the robot's then the free
-  // bodies', and after them the dynamics scratch.
+  // (per robot or free body and 64-target chunk, 64 bits) lie there, the robot's
+  // then the free bodies' with their bounding spheres (4 floats each), and
+  // after them the dynamics scratch.
   L.rows = o;
   L.nch = (L.ntmax + WAVE - 1) / WAVE;
   L.cmask = o;
-  L.fmask = o + lds_align4(ND * L.nch * 2) + ND * 4;
+  L.fmask = o + lds_align4(ND * L.nch * 2);
   L.dyn = L.fmask + lds_align4(fmax * L.nch * 2) + fmax * 4;
   {
     const int rw = lds_align4(rcap * ROW_FLOATS), mk = lds_align4(L.dyn - o + DYN_FLOATS);

@@ -136,6 +136,13 @@ template <int N>
 __device__ __forceinline__ float row_ror(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, true));
 }
+// minimum over aligned groups of 16 lanes
+__device__ __forceinline__ float row_min(float v) {
+  v = fminf(v, row_ror<8>(v));
+  v = fminf(v, row_ror<4>(v));
+  v = fminf(v, row_ror<2>(v));
+  return fminf(v, row_ror<1>(v));
+}
 // sum over aligned groups of 16 lanes (result in every lane of the group)
 __device__ __forceinline__ float sum16(float v) {
   v += row_ror<8>(v);
@@ -576,6 +583,7 @@ __device__ __forceinline__ void kin_robot(const KArgs& a, const Scene& S, float*
     float4 sp = M->sph[k];
     f3 c = mv(rb.R + b * 9, mk3(sp.x, sp.y, sp.z)) + mk3(rb.p[b * 3], rb.p[b * 3 + 1], rb.p[b * 3 + 2]);
     SW[k * 4 + 0] = c.x; SW[k * 4 + 1] = c.y; SW[k * 4 + 2] = c.z; SW[k * 4 + 3] = sp.w;
+    SW[4 * S.nsph + k] = __int_as_float(b | (int)M->sph_flags[k] << 8);
   }
   lds_order();
 }
@@ -654,7 +662,7 @@ struct ConCtx {
   const DModel* M;
   float* C;
   int cc;
-  const float* SW;
+  const float *SW, *SI;
   const float* F;
   int fm;
   const float* A;
@@ -683,8 +691,9 @@ __device__ __forceinline__ void owner_geom(const ConCtx& X, int o, f3& c, float&
   if (o < X.nsph) {
     c = mk3(X.SW[o * 4], X.SW[o * 4 + 1], X.SW[o * 4 + 2]);
     r = X.SW[o * 4 + 3];
-    oflags = X.M->sph_flags[o];
-    oidx = X.M->sph_body[o];
+    const int info = __float_as_int(X.SI[o]);  // body | flags << 8
+    oflags = info >> 8;
+    oidx = info & 0xff;
     okind = 0;
   } else {
     int ow = X.own[o - X.nsph];
@@ -948,18 +957,20 @@ __device__ __forceinline__ int select_bit(uint64_t m, int k) {
   return pos;
 }
 
-// Exact tests of bodies' owners against their culled candidates (body b:
-// mem(b) owners from owner index obase(b); candidates: the set bits of its
+// Exact tests of bodies' owners against their culled candidates (lane b holds of
+// body b: mem owners from owner index obase; candidates: the set bits of its
 // masks, bit j of chunk ch standing for target tgt(ch, j)), packed into full
 // chunks: consecutive bodies are grouped while the group's pairs fit one
 // chunk; a body with more than a chunk of pairs runs alone over several.
 // Pairs are enumerated (body, owner, candidate) in increasing order, so the
 // contacts come out in canonical order.  A lane finds its body by comparing
 // its pair index with the members' first pairs, and its candidate as the
-// set bit of that rank in the body's masks.
-template <class Mem, class Obase, class Tgt>
+// set bit of that rank in the body's masks.  (The grouping takes the bodies'
+// numbers from their lanes: read from memory one body after the other they
+// made it half of the phase.)
+template <class Tgt>
 __device__ __forceinline__ void exact_grouped(const ConCtx& X, int rcap, int nbod, const uint32_t* msk, int nch,
-                                              Mem mem, Obase obase, Tgt tgt, EmitState& E) {
+                                              int mem, int obase, Tgt tgt, EmitState& E) {
   const int lane = lane_id();
   auto mask_of = [&](int b, int ch) -> uint64_t {
     return (uint64_t)msk[(b * nch + ch) * 2] | ((uint64_t)msk[(b * nch + ch) * 2 + 1] << 32);
@@ -968,31 +979,28 @@ __device__ __forceinline__ void exact_grouped(const ConCtx& X, int rcap, int nbo
   int bcnt = 0;
   if (lane < nbod)
     for (int ch = 0; ch < nch; ++ch) bcnt += __popcll(mask_of(lane, ch));
-  int b = 0;
-  while (b < nbod) {
+  const int bpair = lane < nbod ? mem * bcnt : 0;
+  uint64_t todo = __ballot(bpair > 0);
+  while (todo) {
     // lane gi: group member gi's first pair, candidates, owner base, body
     int ng = 0, pairs = 0;
     int gP = 0, gC = 1, gO = 0, gB = 0;
-    while (b < nbod) {
-      const int cnt = __builtin_amdgcn_readlane(bcnt, b);
-      const int m = mem(b);
-      if (cnt == 0 || m == 0) {
-        ++b;
-        continue;
-      }
-      if (ng > 0 && pairs + m * cnt > WAVE) break;
+    while (todo) {
+      const int b = __ffsll((long long)todo) - 1;
+      const int np = __builtin_amdgcn_readlane(bpair, b);
+      if (ng > 0 && pairs + np > WAVE) break;
+      const int cnt = __builtin_amdgcn_readlane(bcnt, b), ob = __builtin_amdgcn_readlane(obase, b);
       if (lane == ng) {
         gP = pairs;
         gC = cnt;
-        gO = obase(b);
+        gO = ob;
         gB = b;
       }
-      pairs += m * cnt;
+      pairs += np;
       ++ng;
-      ++b;
+      todo &= todo - 1ull;
       if (pairs > WAVE) break;
     }
-    if (ng == 0) break;
     for (int base = 0; base < pairs; base += WAVE) {
       const int idx = base + lane;
       int gi = 0;
@@ -1026,6 +1034,7 @@ __device__ __forceinline__ void con_ctx(const KArgs& a, const Scene& S, float* L
   X.C = L + Y.con;
   X.cc = Y.ccap;
   X.SW = L + Y.sph;
+  X.SI = X.SW + 4 * S.nsph;
   X.F = L + Y.fr;
   X.fm = Y.fmax;
   X.A = L + Y.aux;
@@ -1053,19 +1062,23 @@ __device__ __forceinline__ int cull_robot(const KArgs& a, const Scene& S, float*
   const float slack = margin + 1e-3f;
   uint16_t* listA = reinterpret_cast<uint16_t*>(L + Y.cand);
   const DModel* M = S.M;
-  // axis-aligned box around the robot's body bounding spheres
-  f3 lo = mk3(1e30f, 1e30f, 1e30f), hi = mk3(-1e30f, -1e30f, -1e30f);
-  if (lane < S.nb && M->sph_count[lane] > 0) {
-    float4 bs = M->bsph[lane];
-    f3 c = mv(rb.R + lane * 9, mk3(bs.x, bs.y, bs.z)) + body_p(rb, lane);
-    lo = mk3(c.x - bs.w, c.y - bs.w, c.z - bs.w);
-    hi = mk3(c.x + bs.w, c.y + bs.w, c.z + bs.w);
+  // lane b: body b's bounding sphere (radius -1: a body without spheres); the
+  // axis-aligned box around them (the bodies are in the first 16 lanes)
+  f3 sc = mk3(0.f, 0.f, 0.f), lo = mk3(1e30f, 1e30f, 1e30f), hi = mk3(-1e30f, -1e30f, -1e30f);
+  float sr = -1.f;
+  if (lane < S.nb) {
+    const float4 bs = M->bsph[lane];
+    sc = mv(rb.R + lane * 9, mk3(bs.x, bs.y, bs.z)) + body_p(rb, lane);
+    if (M->sph_count[lane] > 0) {
+      sr = bs.w;
+      lo = mk3(sc.x - bs.w, sc.y - bs.w, sc.z - bs.w);
+      hi = mk3(sc.x + bs.w, sc.y + bs.w, sc.z + bs.w);
+    }
   }
-  for (int off = 32; off > 0; off >>= 1) {
-    lo.x = fminf(lo.x, __shfl_xor(lo.x, off, WAVE)); lo.y = fminf(lo.y, __shfl_xor(lo.y, off, WAVE));
-    lo.z = fminf(lo.z, __shfl_xor(lo.z, off, WAVE)); hi.x = fmaxf(hi.x, __shfl_xor(hi.x, off, WAVE));
-    hi.y = fmaxf(hi.y, __shfl_xor(hi.y, off, WAVE)); hi.z = fmaxf(hi.z, __shfl_xor(hi.z, off, WAVE));
-  }
+  lo = mk3(row_min(lo.x), row_min(lo.y), row_min(lo.z));
+  hi = mk3(-row_min(-hi.x), -row_min(-hi.y), -row_min(-hi.z));
+  lo = mk3(lane_val(lo.x, 0), lane_val(lo.y, 0), lane_val(lo.z, 0));
+  hi = mk3(lane_val(hi.x, 0), lane_val(hi.y, 0), lane_val(hi.z, 0));
   f3 bc = (lo + hi) * 0.5f, he = (hi - lo) * 0.5f;
   // the robot's candidate targets in increasing order; the furniture
   // boxes of four chunks are loaded together
@@ -1098,31 +1111,27 @@ __device__ __forceinline__ int cull_robot(const KArgs& a, const Scene& S, float*
   }
   // the robot bodies' bounding spheres against the robot's candidates,
   // transposed as for the free bodies below: lanes over a chunk of the
-  // candidates, a loop over the bodies, one ballot per (body, chunk)
+  // candidates, a loop over the bodies (their spheres by readlane), one ballot
+  // per (body, chunk), kept by the body's lane
   uint32_t* msk = reinterpret_cast<uint32_t*>(L + Y.cmask);
   const int ncA = (nra + WAVE - 1) / WAVE;
-  // the bodies' bounding spheres (centre, radius; a body without spheres
-  // radius -1) where every lane reads them with one broadcast load
-  float4* rbd = reinterpret_cast<float4*>(L + Y.cmask + lds_align4(ND * Y.nch * 2));
-  if (lane < S.nb) {
-    float4 bs = M->bsph[lane];
-    const f3 c = mv(rb.R + lane * 9, mk3(bs.x, bs.y, bs.z)) + body_p(rb, lane);
-    rbd[lane] = make_float4(c.x, c.y, c.z, M->sph_count[lane] > 0 ? bs.w : -1.f);
-  }
   lds_order();
   for (int ch = 0; ch < ncA; ++ch) {
     const int i = ch * WAVE + lane;
     TBound B;
     target_bound(X, i < nra ? (int)listA[i] : -1, B);
+    uint64_t mym = 0;
 #pragma unroll 4
     for (int b = 0; b < S.nb; ++b) {
-      const float4 bd = rbd[b];
-      const bool m = bd.w >= 0.f && B.valid && bound_near(B, mk3(bd.x, bd.y, bd.z), bd.w, slack);
+      const float R = lane_val(sr, b);
+      const bool m =
+          R >= 0.f && B.valid && bound_near(B, mk3(lane_val(sc.x, b), lane_val(sc.y, b), lane_val(sc.z, b)), R, slack);
       const uint64_t mk = __ballot(m);
-      if (lane == 0) {
-        msk[(b * ncA + ch) * 2] = (uint32_t)mk;
-        msk[(b * ncA + ch) * 2 + 1] = (uint32_t)(mk >> 32);
-      }
+      mym = lane == b ? mk : mym;
+    }
+    if (lane < S.nb) {
+      msk[(lane * ncA + ch) * 2] = (uint32_t)mym;
+      msk[(lane * ncA + ch) * 2 + 1] = (uint32_t)(mym >> 32);
     }
   }
   lds_order();
@@ -1369,12 +1378,11 @@ __device__ __forceinline__ void emit_contacts(const KArgs& a, const Scene& S, fl
     const DModel* M = S.M;
     if (S.nsph > 0)
       exact_grouped(
-          X, a.rcap, S.nb, reinterpret_cast<const uint32_t*>(L + Y.cmask), ncA, [&](int b) { return M->sph_count[b]; },
-          [&](int b) { return M->sph_first[b]; }, [&](int ch, int j) { return (int)listA[ch * WAVE + j]; }, E);
+          X, a.rcap, S.nb, reinterpret_cast<const uint32_t*>(L + Y.cmask), ncA, lane < S.nb ? (int)M->sph_count[lane] : 0,
+          lane < S.nb ? (int)M->sph_first[lane] : 0, [&](int ch, int j) { return (int)listA[ch * WAVE + j]; }, E);
     exact_grouped(
-        X, a.rcap, S.nf, reinterpret_cast<const uint32_t*>(L + Y.fmask), (NT + WAVE - 1) / WAVE,
-        [&](int f) { return __builtin_amdgcn_readlane(fmem, f); },
-        [&](int f) { return __builtin_amdgcn_readlane(fob, f); }, [&](int ch, int j) { return ch * WAVE + j; }, E);
+        X, a.rcap, S.nf, reinterpret_cast<const uint32_t*>(L + Y.fmask), (NT + WAVE - 1) / WAVE, fmem, fob,
+        [&](int ch, int j) { return ch * WAVE + j; }, E);
   }
   uint64_t ks = E.ks;
   for (int off = 32; off > 0; off >>= 1) ks += __shfl_xor(ks, off, WAVE);
@@ -2999,8 +3007,8 @@ __global__ __launch_bounds__(WAVE) void k_spawn_check(KArgs a, uint8_t* collide)
     const DModel* M = S.M;
     EmitState E{0, 0, false, false, 0ull};
     exact_grouped(
-        X, a.rcap, S.nb, reinterpret_cast<const uint32_t*>(L + a.L.cmask), ncA, [&](int b) { return M->sph_count[b]; },
-        [&](int b) { return M->sph_first[b]; }, [&](int ch, int j) { return (int)listA[ch * WAVE + j]; }, E);
+        X, a.rcap, S.nb, reinterpret_cast<const uint32_t*>(L + a.L.cmask), ncA, lane < S.nb ? (int)M->sph_count[lane] : 0,
+        lane < S.nb ? (int)M->sph_first[lane] : 0, [&](int ch, int j) { return (int)listA[ch * WAVE + j]; }, E);
     hit = E.n > 0 || E.over || E.rover;
   } else {
     const int NT = X.NT, total = S.nsph * NT;
