@@ -928,11 +928,13 @@ __device__ __forceinline__ void target_bound(const ConCtx& X, int t, TBound& B) 
 // conservative: may sphere (c, R) come within `slack` of the bound?  Sphere-
 // to-box distances are compared squared (slack covers the rounding).
 __device__ __forceinline__ bool bound_near(const TBound& B, f3 c, float R, float slack) {
-  if (B.isplane) return dot(B.ctr, c) - B.pd - R < slack;
+  // (both forms in every lane: the lanes of a chunk hold planes and boxes)
+  const bool pl = dot(B.ctr, c) - B.pd - R < slack;
   const f3 q = mk3(fmaxf(fabsf(c.x - B.ctr.x) - B.half.x, 0.f), fmaxf(fabsf(c.y - B.ctr.y) - B.half.y, 0.f),
                    fmaxf(fabsf(c.z - B.ctr.z) - B.half.z, 0.f));
   const float lim = R + B.rt + slack;
-  return dot(q, q) < lim * lim;
+  const bool bx = dot(q, q) < lim * lim;
+  return (B.isplane & pl) | (!B.isplane & bx);
 }
 
 // position of the k-th (from 0) set bit of m (k < popcount(m))
