@@ -140,10 +140,32 @@ KArgs make_args(const ms_batch* b, const void* x_in, const float* u, void* x_out
 
 size_t lds_bytes_of(const KArgs& a) { return (size_t)a.L.total * sizeof(float); }
 
-int persistent_grid(const ms_batch* b, size_t lds) {
+// Plain steps with four wavefronts per SIMD instead of three (eight scenes on a
+// CU instead of six, at 128 registers with a few spilled): where the LDS block
+// lets more than six scenes onto a CU and the batch fills the CUs twice over at
+// six.  Measured three / four per SIMD, us: 4096 room scenes 557 / 503, 4096
+// pushing scenes 767 / 669, 4096 arms 335 / 298, 8192 scenes with doors
+// 1121 / 1041; below the line 2048 room scenes 394 / 404, 2048 scenes with doors
+// 785 / 809, 1024 room scenes 404 / 407.
+bool fwd_dense(const ms_batch* b, size_t lds, bool plain) {
+  return plain && size_t{163840} / (lds + 1024) > 6 && b->cnt.S > 12 * b->n_cu;
+}
+
+// Workgroups of the forward kernel per CU at an LDS size (the occupancy
+// query, capped by the measured LDS rule of bwd_per_cu)
+int fwd_per_cu(const ms_batch* b, size_t lds, bool plain) {
+  int n = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, step_kernel_ptr(fwd_dense(b, lds, plain)), STEP_THREADS, lds) !=
+      hipSuccess)
+    n = 0;
+  return std::min(n, (int)(size_t{163840} / (lds + 1024)));
+}
+
+int persistent_grid(const ms_batch* b, size_t lds, bool dense) {
   if (b->sched.grid > 0) return b->sched.grid;
   int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, step_kernel_ptr(), STEP_THREADS, lds) != hipSuccess || per_cu <= 0)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, step_kernel_ptr(dense), STEP_THREADS, lds) != hipSuccess ||
+      per_cu <= 0)
     per_cu = 1;
   return std::min(b->cnt.S, per_cu * b->n_cu);
 }
@@ -185,14 +207,6 @@ void set_step_order(ms_batch* b, KArgs& a, hipStream_t st, int fit_c) {
   a.order = ord;
 }
 
-// Workgroups of the forward kernel per CU at an LDS size (the occupancy
-// query, capped by the measured LDS rule of bwd_per_cu)
-int fwd_per_cu(size_t lds) {
-  int n = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, step_kernel_ptr(), STEP_THREADS, lds) != hipSuccess) n = 0;
-  return std::min(n, (int)(size_t{163840} / (lds + 1024)));
-}
-
 // rc < 0: the batch's robot contact cap
 LdsLayout fwd_layout(const ms_batch* b, int cc, int stage, int force, int rc = -1) {
   const Counts& c = b->cnt;
@@ -213,11 +227,11 @@ int fwd_split_cap(ms_batch* b, int stage, int force) {
   v = 0;
   const int cap = b->desc.contact_cap;
   const size_t full = (size_t)fwd_layout(b, cap, stage, force).total * sizeof(float);
-  const int occ = fwd_per_cu(full);
+  const int occ = fwd_per_cu(b, full, false);
   if (occ <= 0) return v;
   int best = occ;
   for (int k = cap - 1; k >= std::max((3 * cap) / 4, 1); --k) {
-    const int o = fwd_per_cu((size_t)fwd_layout(b, k, stage, force, fwd_split_rcap(b)).total * sizeof(float));
+    const int o = fwd_per_cu(b, (size_t)fwd_layout(b, k, stage, force, fwd_split_rcap(b)).total * sizeof(float), false);
     if (o > best) {
       best = o;
       v = k;
@@ -242,8 +256,10 @@ ms_status launch_fused(ms_batch* b, KArgs& a, size_t lds, hipStream_t st) {
                      : 0;
   set_step_order(b, a, st, fc);
   HIP_TRY(hipGetLastError());
+  const bool plain = !a.rec && !force;
   if (fc <= 0) {
-    launch_step(a, a.persistent ? persistent_grid(b, lds) : b->cnt.S, lds, st);
+    a.dense = fwd_dense(b, lds, plain);
+    launch_step(a, a.persistent ? persistent_grid(b, lds, a.dense) : b->cnt.S, lds, st);
     HIP_TRY(hipGetLastError());
     return MS_OK;
   }
@@ -254,12 +270,13 @@ ms_status launch_fused(ms_batch* b, KArgs& a, size_t lds, hipStream_t st) {
   small.rcap = std::min(a.rcap, small.L.rcap);  // a scene with more robot contacts gives up (status 8) and is retried
   rt.fit_mode = 3;
   const size_t lds_s = lds_bytes_of(small);
+  small.dense = fwd_dense(b, lds_s, plain);
   HIP_TRY(hipEventRecord(b->ev_fork, st));
   HIP_TRY(hipStreamWaitEvent(b->bwd_stream, b->ev_fork, 0));
   launch_step(big, std::min(b->cnt.S, b->n_cu), lds, st);
   HIP_TRY(hipGetLastError());
   launch_delay(1500, b->bwd_stream);
-  launch_step(small, persistent_grid(b, lds_s), lds_s, b->bwd_stream);
+  launch_step(small, persistent_grid(b, lds_s, small.dense), lds_s, b->bwd_stream);
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipEventRecord(b->ev_join, b->bwd_stream));
   HIP_TRY(hipStreamWaitEvent(st, b->ev_join, 0));
@@ -292,7 +309,7 @@ ms_status enqueue_step(ms_batch* b, const void* x_in, const float* u, void* x_ou
     int grid = b->cnt.S;
     if (ak.persistent) {
       if (k > 0) launch_reset_queue(ak.queue, st);
-      grid = persistent_grid(b, lds);
+      grid = persistent_grid(b, lds, false);
     }
     launch_step(ak, grid, lds, st);
     HIP_TRY(hipGetLastError());
@@ -454,7 +471,8 @@ ms_status ms_create_batch(const ms_batch_desc* d, const ms_scene_desc* sc, void*
     return fail(MS_E_HIP, "stream / event creation failed");
   }
   // allow the kernels the whole LDS of a workgroup
-  (void)hipFuncSetAttribute(step_kernel_ptr(), hipFuncAttributeMaxDynamicSharedMemorySize, (int)b->max_lds);
+  for (bool dense : {false, true})
+    (void)hipFuncSetAttribute(step_kernel_ptr(dense), hipFuncAttributeMaxDynamicSharedMemorySize, (int)b->max_lds);
   (void)hipFuncSetAttribute(step_rec_kernel_ptr(), hipFuncAttributeMaxDynamicSharedMemorySize, (int)b->max_lds);
   (void)hipFuncSetAttribute(step_frc_kernel_ptr(), hipFuncAttributeMaxDynamicSharedMemorySize, (int)b->max_lds);
   (void)hipFuncSetAttribute(spawn_check_kernel_ptr(), hipFuncAttributeMaxDynamicSharedMemorySize, (int)b->max_lds);
@@ -676,7 +694,8 @@ ms_status ms_step_noalloc(ms_batch* b, const void* x_in, const float* u, void* x
     launch_reset_queue(queue, st);   // the counter keeps the last call's value
     HIP_TRY(hipGetLastError());
   }
-  launch_step(a, a.persistent ? persistent_grid(b, lds) : b->cnt.S, lds, st);
+  a.dense = fwd_dense(b, lds, b->frc_robot == nullptr && b->grip == nullptr);
+  launch_step(a, a.persistent ? persistent_grid(b, lds, a.dense) : b->cnt.S, lds, st);
   HIP_TRY(hipGetLastError());
   return MS_OK;
 }
@@ -1164,7 +1183,7 @@ ms_status ms_autotune(ms_batch* b, const void* x, const float* u, void* tmp, int
         // the full layout's occupancy, then the smaller layout's at each cap
         splits = occupancy_steps(b->desc.contact_cap, [&](int k) {
           const int rc = k == b->desc.contact_cap ? -1 : fwd_split_rcap(b);
-          return fwd_per_cu((size_t)fwd_layout(b, k, si, force, rc).total * sizeof(float));
+          return fwd_per_cu(b, (size_t)fwd_layout(b, k, si, force, rc).total * sizeof(float), !force);
         }, (3 * b->desc.contact_cap) / 4);
         if (splits.empty()) continue;   // no smaller layout: the same as one launch
       }
@@ -1173,7 +1192,7 @@ ms_status ms_autotune(ms_batch* b, const void* x, const float* u, void* tmp, int
         if (form & P) {
           const size_t lds = fs > 0 ? (size_t)fwd_layout(b, fs, si, force, fwd_split_rcap(b)).total * sizeof(float)
                                     : full;
-          const int per_cu = fwd_per_cu(lds);
+          const int per_cu = fwd_per_cu(b, lds, !force);
           if (per_cu > 1 && b->n_cu * (per_cu - 1) < b->cnt.S) grids.push_back(b->n_cu * (per_cu - 1));
         }
         for (int g : grids) cands.push_back({fl, g, fs});

@@ -209,6 +209,7 @@ struct KArgs {
   int persistent, stage_static, cull;
   float h, mu, beta, margin;
   float g[3];
+  int dense;  // plain steps: the instantiation with four wavefronts per SIMD (ms_api.hip, fwd_dense)
   LdsLayout L;
   float* rec;              // record of the control step for the adjoint, or null
   RecLayout RL;
@@ -234,7 +235,7 @@ void launch_actions_bwd(const DModel* models, const DScene* scenes, const float*
                         const float* gtgt, float* ga, float* gx, int S, hipStream_t st);
 void launch_masked_copy(float* dst, const float* src, const uint8_t* mask, int S, int NF, int NA,
                         const int* free_off, const int* aux_off, hipStream_t st);
-const void* step_kernel_ptr();
+const void* step_kernel_ptr(bool dense);
 const void* step_rec_kernel_ptr();
 const void* step_frc_kernel_ptr();
 const void* spawn_check_kernel_ptr();

@@ -2289,6 +2289,7 @@ struct Group {
   RowC R;
   BodyReg A, B;
 };
+template <bool DENSE>
 __device__ __forceinline__ void pgs_linked(const KArgs& a, float* L, int NC, int NL, int NR, Levels lv_, float& vR,
                                            float* tape) {
 #pragma clang fp contract(off)
@@ -2313,10 +2314,9 @@ __device__ __forceinline__ void pgs_linked(const KArgs& a, float* L, int NC, int
   // other side, and the first row's and the bodies' constants (a scene with
   // more groups than lanes loads them again for each 64)
   Group G;
+  auto grp_level = [&](int base) { G.lv = base + lane < NG ? (int)lvl[base + lane] : 0; };
   auto grp_load = [&](int base) {
     const int g = base + lane;
-    G.lv = g < NG ? (int)lvl[g] : 0;
-    if (G.lv == 0) return;
     G.c0 = gfirst[g];
     G.gn = (int)gfirst[g + 1] - G.c0;
     const float* c = C + G.c0 * CSTR;
@@ -2330,7 +2330,8 @@ __device__ __forceinline__ void pgs_linked(const KArgs& a, float* L, int NC, int
     body_consts(F + G.fa * FSTR, G.A);
     body_consts(F + G.fb * FSTR, G.B);
   };
-  grp_load(0);
+  grp_level(0);
+  if (!DENSE && G.lv != 0) grp_load(0);
   const int rblk = lane < NR ? rob_block(Y, NC, NR, lane) : -1;
   // robot rows with a block (a prefix of them: blocks are given out in order)
   const int NB = __popcll(__ballot(rblk >= 0));
@@ -2511,8 +2512,9 @@ __device__ __forceinline__ void pgs_linked(const KArgs& a, float* L, int NC, int
     for (int lv = 1; lv <= maxl; ++lv) {
 #pragma unroll 1
       for (int base = 0; base < NG; base += WAVE) {
-        if (NG > WAVE) grp_load(base);
+        if (NG > WAVE) grp_level(base);
         if (G.lv != lv) continue;
+        if (DENSE || NG > WAVE) grp_load(base);
         float* c = C + G.c0 * CSTR;
         float* fa = F + G.fa * FSTR;
         Lam l = lam_load(c);
@@ -2718,13 +2720,15 @@ __device__ __forceinline__ void scene_view(const KArgs& a, int s, Scene& S) {
 
 // MODE 0: the plain step; 1: also the record of the control step for the
 // adjoint; 2: also the contact-force outputs.  Separate instantiations, so
-// the plain step keeps its register allocation.
+// the plain step keeps its register allocation.  DENSE: the plain step at 128
+// registers, for batches that fill the CUs with more scenes (the sweeps then
+// load a lane's group again at its level instead of keeping it).
 //
 // wv: the wavefront (0: the robot's part, 1: the free bodies').  Every barrier
 // is outside the branches on wv, and the substep loop ends alike in both
 // wavefronts (the counts and the status they test come from LDS words read
 // after a barrier).  Returns the next queue position.
-template <int MODE>
+template <int MODE, bool DENSE>
 __device__ __forceinline__ int run_scene(int s, int wv, float* const L0) {
   const KArgs& a = args_fresh();
   float* const L = lds_fresh(L0);
@@ -2845,7 +2849,7 @@ __device__ __forceinline__ int run_scene(int s, int wv, float* const L0) {
         MS_PHASE(3)
         lv.ng = uniform(ctl[CTL_NG]);
         lv.maxl = uniform(ctl[CTL_MAXL]);
-        pgs_linked(args_fresh(), lds_fresh(L0), NC, NL, NR, lv, vR, tape);
+        pgs_linked<DENSE>(args_fresh(), lds_fresh(L0), NC, NL, NR, lv, vR, tape);
         if (MODE == 2) phase_forces(args_fresh(), S, lds_fresh(L0), NL, NR, frc, ks == a.n_sub_total - 1);
         integrate_robot(args_fresh(), S, lds_fresh(L0), vR);
         kin_aux(args_fresh(), S, lds_fresh(L0));
@@ -2943,7 +2947,7 @@ __device__ __forceinline__ int run_scene(int s, int wv, float* const L0) {
   return next;
 }
 
-template <int MODE>
+template <int MODE, bool DENSE = false>
 __device__ __forceinline__ void step_body(const KArgs& a, float* lds) {
   // one call site: the persistent form pulls positions from its work counter
   // (wavefront 0, for both), the plain form takes its block index once
@@ -2958,7 +2962,7 @@ __device__ __forceinline__ void step_body(const KArgs& a, float* lds) {
     pos = base + uniform(ctl[CTL_POS]);
   }
   while (pos < end) {
-    pos = base + run_scene<MODE>(uniform(a.fit_mode == 3 ? a.retry[1 + pos] : a.order[pos]), wv, lds);
+    pos = base + run_scene<MODE, DENSE>(uniform(a.fit_mode == 3 ? a.retry[1 + pos] : a.order[pos]), wv, lds);
     if (!a.persistent) break;
   }
 }
@@ -2966,6 +2970,10 @@ __device__ __forceinline__ void step_body(const KArgs& a, float* lds) {
 __global__ __launch_bounds__(STEP_THREADS) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_step(KArgs a) {
   extern __shared__ float lds[];
   step_body<0>(a, lds);
+}
+__global__ __launch_bounds__(STEP_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_step_dense(KArgs a) {
+  extern __shared__ float lds[];
+  step_body<0, true>(a, lds);
 }
 __global__ __launch_bounds__(STEP_THREADS) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_step_rec(KArgs a) {
   extern __shared__ float lds[];
@@ -3140,6 +3148,7 @@ __global__ void k_masked_copy(float* dst, const float* src, const uint8_t* mask,
 void launch_step(const KArgs& a, int grid, size_t lds_bytes, hipStream_t st) {
   if (a.rec) hipLaunchKernelGGL(k_step_rec, dim3(grid), dim3(STEP_THREADS), lds_bytes, st, a);
   else if (a.frc_robot || a.grip) hipLaunchKernelGGL(k_step_frc, dim3(grid), dim3(STEP_THREADS), lds_bytes, st, a);
+  else if (a.dense) hipLaunchKernelGGL(k_step_dense, dim3(grid), dim3(STEP_THREADS), lds_bytes, st, a);
   else hipLaunchKernelGGL(k_step, dim3(grid), dim3(STEP_THREADS), lds_bytes, st, a);
 }
 void launch_reset_queue(int* q, hipStream_t st) { hipLaunchKernelGGL(k_reset_queue, dim3(1), dim3(64), 0, st, q); }
@@ -3224,7 +3233,9 @@ void launch_masked_copy(float* dst, const float* src, const uint8_t* mask, int S
   if (S <= 0) return;
   hipLaunchKernelGGL(k_masked_copy, dim3(S), dim3(64), 0, st, dst, src, mask, S, NF, NA, free_off, aux_off);
 }
-const void* step_kernel_ptr() { return reinterpret_cast<const void*>(&k_step); }
+const void* step_kernel_ptr(bool dense) {
+  return dense ? reinterpret_cast<const void*>(&k_step_dense) : reinterpret_cast<const void*>(&k_step);
+}
 const void* step_rec_kernel_ptr() { return reinterpret_cast<const void*>(&k_step_rec); }
 const void* step_frc_kernel_ptr() { return reinterpret_cast<const void*>(&k_step_frc); }
 const void* spawn_check_kernel_ptr() { return reinterpret_cast<const void*>(&k_spawn_check); }

@@ -143,3 +143,53 @@ def test_gradient_robot_rows(depth):
     st["aux"][:, 0] += rng.uniform(1e-4, 1e-3, b.n_aux)
     b.state0[:] = sg.join_state(st["q"], st["qd"], st["free"], st["aux"])
     _check_gradient(_ms(), b)
+
+
+@pytest.mark.parametrize("cfg,n", [(1, 2), (2, 3), (5, 5)])
+def test_large_batches_step_like_small_ones(cfg, n):
+    """Batches past the line of the instantiation with more scenes per CU: the
+    same scenes many times over give bit for bit the small batch's results."""
+    ms = _ms()
+    small = sg.make(cfg, n)
+    reps = (12 * torch.cuda.get_device_properties(0).multi_processor_count) // n + 1
+    rows = np.tile(np.arange(n), reps)
+    b = _repeat(small, rows)
+    out = {}
+    for name, batch in (("small", small), ("large", b)):
+        mb = ms.MsBatch(batch)
+        mb.set_schedule(ms.MS_SCHED_PERSISTENT | ms.MS_SCHED_CULL | ms.MS_SCHED_STAGE_STATIC)
+        x = torch.as_tensor(batch.state0).cuda()
+        u = torch.as_tensor(np.ascontiguousarray(small.controls(0)[rows] if name == "large" else small.controls(0))).cuda()
+        y = mb.step(mb.step(x, u), u).cpu().numpy()
+        out[name] = sg.split_state(y, batch.n_scenes, batch.n_free, batch.n_aux)
+    nf, na = small.n_free, small.n_aux
+    want = out["small"]
+    got = out["large"]
+    for k in ("q", "qd", "free", "aux"):
+        w = np.ascontiguousarray(np.concatenate([want[k]] * reps)).view(np.uint32)
+        assert np.array_equal(np.ascontiguousarray(got[k]).view(np.uint32), w), k
+
+
+def _repeat(b, rows):
+    """The scenes `rows` of a batch, one after the other."""
+    import dataclasses
+
+    def gather(off):
+        off = np.asarray(off, np.int64)
+        n = off[rows + 1] - off[rows]
+        new = np.zeros(len(rows) + 1, np.int64)
+        np.cumsum(n, out=new[1:])
+        return new.astype(np.int32), np.repeat(off[rows] - new[:-1], n) + np.arange(new[-1])
+    S = len(rows)
+    st = sg.split_state(b.state0, b.n_scenes, b.n_free, b.n_aux)
+    fo, fi = gather(b.free_off)
+    so, si = gather(b.static_off)
+    po, pi = gather(b.plane_off)
+    ao, ai = gather(b.aux_off)
+    kw = {k: getattr(b, k)[fi] for k in ("free_type", "free_size", "free_mass", "free_inertia")}
+    kw.update({k: getattr(b, k)[ai] for k in ("aux_type", "aux_rot", "aux_pos", "aux_axis", "aux_box", "aux_mass",
+                                              "aux_inertia", "aux_limit")})
+    return dataclasses.replace(
+        b, n_scenes=S, scene_model=b.scene_model[rows], scene_hold=b.scene_hold[rows], free_off=fo, static_off=so,
+        plane_off=po, aux_off=ao, static_box=b.static_box[si], plane=b.plane[pi],
+        state0=sg.join_state(st["q"][rows], st["qd"][rows], st["free"][fi], st["aux"][ai]), **kw)
