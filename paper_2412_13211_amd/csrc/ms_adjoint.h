@@ -200,7 +200,7 @@ struct WS {
   int vRb, vAb, vFb, lamb, llamb, limb, conb, rJb, rwb, fb, xb;
   int Mb, sb, Ib, Icb, fbar, abar, vbar, bacc;
   int rH;    // angular velocity adjoints of the impulses on the robot rows' free-body targets (wavefront kernel only)
-  int ctl;   // the schedule's group and level counts, from one wavefront to the other (wavefront kernel only)
+  int ctl;   // the schedule's group and level counts, from one wavefront to the other, and a spare word (wavefront kernel only)
   int lv;    // level schedule (wavefront kernel only)
   int tring;  // two sweeps of the tape staged from the record (wavefront kernel only)
   int trs;    // floats per staged sweep
@@ -285,7 +285,7 @@ MSA_HD inline WS ws_layout(int fmax, int ntmax, int ccap, int rcap, int K, int n
   w.fb = take(fm * FB); w.xb = take(AMAX * XB);
   w.Mb = take(ND * ND);
   w.bacc = take(ND * 9);
-  w.ctl = take(wave ? 2 : 0);
+  w.ctl = take(wave ? 3 : 0);
   w.lv = take(wave ? lv_ints(ccap) : 0);
   w.Minv = w.L;  // the elimination runs in registers and replaces M~
   w.lz = take(wave ? ND : 0);

@@ -809,16 +809,47 @@ struct RobB {
   float J0, J1, J2, w0, w1, w2;  // this lane's joint
   float iw0, iw1, iw2, bias, lb0, lb1, lb2;
   float y[3], q[3];
-  // a moving target: directions, lever, inverse inertia's row and mass, lever
-  // rows of the normal and of this row's friction direction (quads)
-  float D0, D1, D2, r, I0, I1, I2, im, angN, angF, bN;
-  float j0, j1, j2;  // a joint's rows
-  msa::Ids id;
+  // a moving target: directions, contact point (quads); a joint's rows
+  float D0, D1, D2, p;
+  float j0, j1, j2, im;
+  int tk, ti;
 };
-__device__ __forceinline__ float qsmv(const RobB& R, float a) {
+// the free body the robot's rows act on, in quads: state, inverse inertia's row
+// and mass; kept from row to row while the target stays (-1: none)
+struct RobT {
+  int ti;
+  float x, v, w, vb, wb, c, I0, I1, I2, im;
+};
+__device__ __forceinline__ float qsmv(const RobT& R, float a) {
   return R.I0 * qperm<0, 0, 0, 0>(a) + R.I1 * qperm<1, 1, 1, 1>(a) + R.I2 * qperm<2, 2, 2, 2>(a);
 }
-__device__ __forceinline__ void rob_bar_load(const msa::Eng& E, const float* L, int rr, const float* ty,
+__device__ __forceinline__ void rt_store(const msa::WS& w, float* L, const RobT& B) {
+  const int lane = lane_id();
+  if (B.ti < 0 || lane > 2) return;
+  float *pv = L + w.vF + B.ti * 6 + lane, *pb = L + w.vFb + B.ti * 6 + lane;
+  pv[0] = B.v;
+  pv[3] = B.w;
+  pb[0] = B.vb;
+  pb[3] = B.wb;
+}
+__device__ __forceinline__ void rt_load(const msa::WS& w, const float* L, int ti, RobT& B) {
+  const int c = lane_id() & 3, cc = c < 3 ? c : 0;
+  const float on = c < 3 ? 1.f : 0.f;
+  const float *pv = L + w.vF + ti * 6 + cc, *pb = L + w.vFb + ti * 6 + cc, *I = L + w.fIi + ti * 9 + 3 * cc;
+  B.ti = ti;
+  B.x = on * L[w.st + 32 + 16 * ti + cc];
+  B.v = on * pv[0];
+  B.w = on * pv[3];
+  B.vb = on * pb[0];
+  B.wb = on * pb[3];
+  B.I0 = on * I[0];
+  B.I1 = on * I[1];
+  B.I2 = on * I[2];
+  B.im = L[w.fim + ti];
+  B.c = qsmv(B, B.wb);
+}
+// ids: lane rr holds robot row rr's owner and target
+__device__ __forceinline__ void rob_bar_load(const msa::Eng& E, const float* L, int rr, float ids, const float* ty,
                                              const float* tq, RobB& R) {
   using namespace msa;
   const WS& w = E.w;
@@ -838,26 +869,17 @@ __device__ __forceinline__ void rob_bar_load(const msa::Eng& E, const float* L, 
     R.y[t] = ty[o + t];
     R.q[t] = tq ? tq[o + t] : 0.f;
   }
-  Ids id = unpack_ids(e[C_ID]);
-  id.tk = __builtin_amdgcn_readfirstlane(id.tk);
-  id.ti = __builtin_amdgcn_readfirstlane(id.ti);
-  R.id = id;
-  if (id.tk == 3) {
-    const int c = lane & 3, cc = c < 3 ? c : 0;
-    const float on = c < 3 ? 1.f : 0.f;
-    R.D0 = on * e[C_N + cc];
-    R.D1 = on * e[C_T1 + cc];
-    R.D2 = on * e[C_T2 + cc];
-    R.r = on * (e[C_P + cc] - L[w.st + 32 + 16 * id.ti + cc]);
-    const float* I = L + w.fIi + id.ti * 9 + 3 * cc;
-    R.I0 = on * I[0];
-    R.I1 = on * I[1];
-    R.I2 = on * I[2];
-    R.angN = qcross(R.r, R.D0);
-    R.angF = qcross(R.r, (lane >> 4) & 1 ? +R.D2 : +R.D1);
-    R.bN = qsmv(R, R.angN);
-    R.im = L[w.fim + id.ti];  // (last in both branches: one store, not two of selected fields)
-  } else if (id.tk == 2) {
+  const Ids id = unpack_ids(rr < 64 ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ids), rr))
+                                    : __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(e[C_ID]))));
+  R.tk = id.tk;
+  R.ti = id.ti;
+  // (plain loads, so that nothing waits for them here)
+  const int c = lane & 3, cc = c < 3 ? c : 0;
+  R.D0 = e[C_N + cc];
+  R.D1 = e[C_T1 + cc];
+  R.D2 = e[C_T2 + cc];
+  R.p = e[C_P + cc];
+  if (id.tk == 2) {
     const V a = E.v3(w.xa + id.ti * 3), rX = E.v3(w.con + rr * CR + C_P) - E.v3(w.xo + id.ti * 3);
     const V col = L[w.xty + id.ti] == 0.f ? cross(a, rX) : a;
     R.j0 = dot(E.v3(w.con + rr * CR + C_N), col);
@@ -866,7 +888,8 @@ __device__ __forceinline__ void rob_bar_load(const msa::Eng& E, const float* L, 
     R.im = 1.f / L[w.xM + id.ti];
   }
 }
-__device__ __forceinline__ void rob_bar(const msa::Eng& E, float* L, int rr, const RobB& R, float& vr, float& vrb) {
+__device__ __forceinline__ void rob_bar(const msa::Eng& E, float* L, int rr, const RobB& R, RobT& B, float& vr,
+                                        float& vrb) {
   using namespace msa;
   const WS& w = E.w;
   const int lane = lane_id(), j = lane & 15, qq = lane >> 4;
@@ -912,55 +935,59 @@ __device__ __forceinline__ void rob_bar(const msa::Eng& E, float* L, int rr, con
     if (!hi) *acn = an0 + (odd ? +rb0 : +T.d0) * (odd ? +vr : +vrb);
     vrb += rb0 * R.J0;
   };
-  if (R.id.tk < 2) {
+  if (R.tk < 2) {
     friction();
     joints();
     normal();
-  } else if (R.id.tk == 3) {
+  } else if (R.tk == 3) {
     // the target's rows are -(D, (p - x) x D)
+    if (R.ti != B.ti) {
+      rt_store(w, L, B);
+      rt_load(w, L, R.ti, B);
+    }
     const int c = lane & 3, cc = c < 3 ? c : 0;
     const float on = c < 3 ? 1.f : 0.f;
-    float *pv = L + w.vF + R.id.ti * 6 + cc, *pb = L + w.vFb + R.id.ti * 6 + cc, *ph = L + w.rH + rr * 9 + cc;
+    // the accumulators of this 16-lane row (lanes that keep none: a spare word)
+    float *ph = L + w.rH + rr * 9 + cc, *spare = L + w.ctl + 2;
     float *pf = cb + (hi ? 9 : 0) + (odd ? 6 : 3) + cc, *pg = ph + (odd ? 6 : 3),
           *pn = qq == 0 ? cb + cc : (qq == 2 ? cb + 9 + cc : ph);
-    float v = on * pv[0], om = on * pv[3], vb = on * pb[0], wb = on * pb[3];
     const float af = *pf, ag = *pg, an = *pn;
-    float ci = qsmv(R, wb);
-    const float P = R.D1 * T.d1 + R.D2 * T.d2;
-    v += R.im * P;
-    om += qsmv(R, qcross(R.r, P));
-    const float X = R.im * vb;
-    s4 -= qsum((odd ? +R.D2 : +R.D1) * (hi ? +v : +X) + R.angF * (hi ? +om : +ci));
+    const float D0 = on * R.D0, D1 = on * R.D1, D2 = on * R.D2, r = on * R.p - B.x;
+    const float Df = odd ? +D2 : +D1;
+    const float angF = qcross(r, Df), angN = qcross(r, D0);
+    const float P = D1 * T.d1 + D2 * T.d2;
+    B.v += B.im * P;
+    B.w += qsmv(B, qcross(r, P));
+    const float X = B.im * B.vb, c0 = B.c;
+    const float tv = hi ? +B.v : +X, tw = hi ? +B.w : +c0;
+    s4 -= qsum(Df * tv + angF * tw);
     friction();
     const float dk = odd ? +T.d2 : +T.d1, rk = odd ? +rb2 : +rb1;
-    const float nf = af + dk * (hi ? +ci : +X) + rk * (hi ? +om : +v), ng = ag + dk * wb;
-    const float Q = R.D1 * rb1 + R.D2 * rb2, rQ = qcross(R.r, Q);
-    vb -= Q;
-    wb -= rQ;
-    ci -= qsmv(R, rQ);
+    const float nf = af + dk * (hi ? +c0 : +X) + rk * (hi ? +B.w : +B.v), ng = ag + dk * B.wb;
+    const float Q = D1 * rb1 + D2 * rb2, rQ = qcross(r, Q);
+    B.vb -= Q;
+    B.wb -= rQ;
+    B.c -= qsmv(B, rQ);
     joints();
-    v += R.im * T.d0 * R.D0;
-    om += T.d0 * R.bN;
-    const float Xn = R.im * vb;
-    s2 -= qsum(R.D0 * (odd ? +v : +Xn) + R.angN * (odd ? +om : +ci));
+    const float bN = qsmv(B, angN);
+    B.v += B.im * T.d0 * D0;
+    B.w += T.d0 * bN;
+    const float Xn = B.im * B.vb;
+    s2 -= qsum(D0 * (odd ? +B.v : +Xn) + angN * (odd ? +B.w : +B.c));
     normal();
-    const float nn = an + (qq == 0 ? T.d0 * Xn + rb0 * v : (qq == 2 ? T.d0 * ci + rb0 * om : T.d0 * wb));
-    vb -= R.D0 * rb0;
-    wb -= R.angN * rb0;
-    if (j < 3) {
-      *pf = nf;
-      if (!hi) *pg = ng;
-      if (qq < 3) *pn = nn;
-      if (qq == 0) {
-        pv[0] = v;
-        pv[3] = om;
-        pb[0] = vb;
-        pb[3] = wb;
-      }
-    }
+    const float nn = an + (qq == 0 ? T.d0 * Xn + rb0 * B.v : (qq == 2 ? T.d0 * B.c + rb0 * B.w : T.d0 * B.wb));
+    B.vb -= D0 * rb0;
+    B.wb -= angN * rb0;
+    B.c -= bN * rb0;
+    pf = j < 3 ? pf : spare;
+    pg = j < 3 && !hi ? pg : spare;
+    pn = j < 3 && qq < 3 ? pn : spare;
+    *pf = nf;
+    *pg = ng;
+    *pn = nn;
   } else {
     // a door / drawer joint: J = -(d . col), col = a x (p - o) or a
-    float qv = L[w.vA + R.id.ti], qb = L[w.vAb + R.id.ti];
+    float qv = L[w.vA + R.ti], qb = L[w.vAb + R.ti];
     float* ps = cb + 12;
     const float s0 = ps[0], s1 = ps[1], sd = ps[2];
     qv += R.im * (R.j1 * T.d1 + R.j2 * T.d2);
@@ -978,8 +1005,8 @@ __device__ __forceinline__ void rob_bar(const msa::Eng& E, float* L, int rr, con
     ps[0] = n0;
     ps[1] = n1;
     ps[2] = n2;
-    L[w.vA + R.id.ti] = qv;
-    L[w.vAb + R.id.ti] = qb;
+    L[w.vA + R.ti] = qv;
+    L[w.vAb + R.ti] = qb;
   }
   // uniform values: every lane stores the same
   float* lb = L + w.lamb + rr * 3;
@@ -2089,6 +2116,7 @@ __device__ __forceinline__ void gs_linked_bar(msa::Eng& E, float* L, Sched sc, c
     }
   }
   float vr = L[w.vR + (lane & 15)], vrb = L[w.vRb + (lane & 15)];
+  const float rids = lane < NR ? L[w.con + lane * CR + C_ID] : 0.f;
   lds_order();
   const float mu = E.pr.mu;
 #pragma unroll 1
@@ -2171,17 +2199,22 @@ __device__ __forceinline__ void gs_linked_bar(msa::Eng& E, float* L, Sched sc, c
     if (NR > 0) {
       // two rows at a time, the next one's data loaded a row ahead
       RobB R0, R1;
-      rob_bar_load(E, L, NR - 1, ty, tq, R0);
+      RobT B;
+      B.ti = -1;
+      B.x = B.v = B.w = B.vb = B.wb = B.c = B.I0 = B.I1 = B.I2 = B.im = 0.f;
+      rob_bar_load(E, L, NR - 1, rids, ty, tq, R0);
 #pragma unroll 1
       for (int rr = NR - 1; rr >= 0; rr -= 2) {
-        rob_bar_load(E, L, rr > 0 ? rr - 1 : 0, ty, tq, R1);
-        rob_bar(E, L, rr, R0, vr, vrb);
+        rob_bar_load(E, L, rr > 0 ? rr - 1 : 0, rids, ty, tq, R1);
+        rob_bar(E, L, rr, R0, B, vr, vrb);
         lds_order();
         if (rr == 0) break;
-        rob_bar_load(E, L, rr > 1 ? rr - 2 : 0, ty, tq, R0);
-        rob_bar(E, L, rr - 1, R1, vr, vrb);
+        rob_bar_load(E, L, rr > 1 ? rr - 2 : 0, rids, ty, tq, R0);
+        rob_bar(E, L, rr - 1, R1, B, vr, vrb);
         lds_order();
       }
+      rt_store(w, L, B);
+      lds_order();
     }
     // limit rows: the first row of a joint runs its second one first
     if (lane < NL) {
