@@ -2281,7 +2281,6 @@ struct RobRow {
   f3 D;
   float iw, wt, bias, l;
   f3 n, t1, t2, p;
-  BodyReg B;  // a free-body target's constants
 };
 // a lane's group of free-body rows
 struct Group {
@@ -2336,8 +2335,7 @@ __device__ __forceinline__ void pgs_linked(const KArgs& a, float* L, int NC, int
   // robot rows with a block (a prefix of them: blocks are given out in order)
   const int NB = __popcll(__ballot(rblk >= 0));
   const int dd = dr < 3 ? dr : 2;  // this lane's direction (the last 16 lanes repeat the third)
-  // row rr (which has a block): every load unconditional, a target that is no
-  // free body reads the zero record
+  // row rr (which has a block): every load unconditional
   auto rob_load = [&](int rr, RobRow& Q) {
     const float* b = L + __builtin_amdgcn_readlane(rblk, rr);
     Q.sB = __builtin_amdgcn_readlane(rsB, rr);
@@ -2357,7 +2355,6 @@ __device__ __forceinline__ void pgs_linked(const KArgs& a, float* L, int NC, int
     Q.t1 = mk3(a1.x, a1.y, a1.z);
     Q.t2 = mk3(a2.x, a2.y, a2.z);
     Q.p = mk3(ap.x, ap.y, ap.z);
-    body_consts(F + (side_kind(Q.sB) == K_FREE ? side_idx(Q.sB) : Y.fmax) * FSTR, Q.B);
   };
   // Row rr from the approach velocity sv of each lane's direction: the normal
   // (first 16 lanes), then the friction pair, which sees the velocity after
@@ -2379,29 +2376,38 @@ __device__ __forceinline__ void pgs_linked(const KArgs& a, float* L, int NC, int
     if (tr && j == 0 && dr < 3) tr[dr] = dr == 0 ? y0 : y;
     return dr == 0 ? nl0 : y * sc;
   };
+  // the free body the robot's rows act on, kept in registers while consecutive
+  // rows have the same target (-1: none)
+  int tf = -1;
+  BodyReg TB;
+  auto target_store = [&]() {
+    if (tf >= 0) body_store(F + tf * FSTR, TB);
+    tf = -1;
+  };
   // row rr from Q; the row after it is loaded into N
   auto rob_step = [&](int rr, float* tsweep, RobRow& Q, RobRow& N) {
 #pragma clang fp contract(off)
     float* lam = L + __builtin_amdgcn_readlane(rblk, rr) + RB_DIR + 8 * dd + RB_LAM;
     float* tr = tsweep ? tsweep + (NL + rr) * 3 : nullptr;
     const int kB = side_kind(Q.sB), xi = side_idx(Q.sB);
-    float* f = F + (kB == K_FREE ? xi : Y.fmax) * FSTR;
-    f3 bv = mk3(f[F_V], f[F_V + 1], f[F_V + 2]), bw = mk3(f[F_W], f[F_W + 1], f[F_W + 2]);
+    if (kB == K_FREE && xi != tf) {
+      target_store();
+      tf = xi;
+      body_load(F + xi * FSTR, TB);
+    }
     rob_load(rr + 1 < NB ? rr + 1 : 0, N);
     float sv = sum16(Q.Jd * vR), ln, dl, dl1, dl2;
     if (kB == K_STATIC) {
       ln = rob_solve(Q, sv, tr, dl, dl1, dl2);
     } else if (kB == K_FREE) {
-      const f3 rB = Q.p - Q.B.x;
-      sv = sv - dot_f(Q.D, bv + cross_f(bw, rB));
+      const f3 rB = Q.p - TB.x;
+      sv = sv - dot_f(Q.D, TB.v + cross_f(TB.w, rB));
       ln = rob_solve(Q, sv, tr, dl, dl1, dl2);
-      // the target receives -P (every lane stores the same values)
+      // the target receives -P (the same values in every lane)
       const f3 P = madd(madd(Q.t1 * dl1, Q.n, dl), Q.t2, dl2);
       const f3 q = mk3(fmaf(rB.z, P.y, -(rB.y * P.z)), fmaf(rB.x, P.z, -(rB.z * P.x)), fmaf(rB.y, P.x, -(rB.x * P.y)));
-      bv = madd(bv, P, -Q.B.im);
-      bw = bw + body_iinv(Q.B, q);
-      f[F_V] = bv.x; f[F_V + 1] = bv.y; f[F_V + 2] = bv.z;
-      f[F_W] = bw.x; f[F_W + 1] = bw.y; f[F_W + 2] = bw.z;
+      TB.v = madd(TB.v, P, -TB.im);
+      TB.w = TB.w + body_iinv(TB, q);
     } else {
       const f3 col = aux_col_f(A, xi, Q.p);
       const float qv = A[A_V * AMAX + xi], imx = A[A_IM * AMAX + xi];
@@ -2443,13 +2449,14 @@ __device__ __forceinline__ void pgs_linked(const KArgs& a, float* L, int NC, int
       }
     }
     float* f = F + (kB == K_FREE ? xi : Y.fmax) * FSTR;
-    body_load(f, Q.B);
-    const f3 rB = Q.p - Q.B.x;
+    BodyReg B;
+    body_load(f, B);
+    const f3 rB = Q.p - B.x;
     float sv = sum16(row[dd * ND + j] * vR), dl, dl1, dl2;
     f3 col = mk3(0.f, 0.f, 0.f);
     float qv = 0.f;
     if (kB == K_FREE) {
-      sv = sv - dot_f(Q.D, Q.B.v + cross_f(Q.B.w, rB));
+      sv = sv - dot_f(Q.D, B.v + cross_f(B.w, rB));
     } else if (kB == K_AUX) {
       col = aux_col_f(A, xi, Q.p);
       qv = A[A_V * AMAX + xi];
@@ -2458,10 +2465,10 @@ __device__ __forceinline__ void pgs_linked(const KArgs& a, float* L, int NC, int
     c[C_LAM + dd] = rob_solve(Q, sv, tr, dl, dl1, dl2);
     const f3 P = madd(madd(Q.t1 * dl1, Q.n, dl), Q.t2, dl2);
     if (kB == K_FREE) {
-      Q.B.v = madd(Q.B.v, P, -Q.B.im);
-      Q.B.w = Q.B.w + body_iinv(Q.B, mk3(fmaf(rB.z, P.y, -(rB.y * P.z)), fmaf(rB.x, P.z, -(rB.z * P.x)),
+      B.v = madd(B.v, P, -B.im);
+      B.w = B.w + body_iinv(B, mk3(fmaf(rB.z, P.y, -(rB.y * P.z)), fmaf(rB.x, P.z, -(rB.z * P.x)),
                                          fmaf(rB.y, P.x, -(rB.x * P.y))));
-      body_store(f, Q.B);
+      body_store(f, B);
     } else if (kB == K_AUX) {
       A[A_V * AMAX + xi] =
           fmaf(A[A_IM * AMAX + xi], fmaf(-col.z, P.z, fmaf(col.y, -P.y, -(col.x * P.x))), qv);
@@ -2505,6 +2512,8 @@ __device__ __forceinline__ void pgs_linked(const KArgs& a, float* L, int NC, int
       if (rr + 1 < NB) rob_step(rr + 1, tsweep, Q1, Q0);
       else Q0 = Q1;
     }
+    target_store();
+    lds_order();
 #pragma unroll 1
     for (int rr = NB; rr < NR; ++rr) rob_step_far(rr, tsweep);
     // the other groups, level by level
