@@ -525,7 +525,10 @@ ms_status ms_debug_contacts(const ms_batch* b, uint32_t* out_host);
 /* Per-phase shader-clock cycles of the last ms_step, summed over its
  * substeps (synchronises): uint64 [S][8] for the phases drive+kinematics,
  * contacts, dynamics, rows, level schedule, Gauss-Seidel, integration, and
- * load/store.  Enabled by ms_enable_phase_profile (adds clock reads). */
+ * load/store, as the robot's wavefront of a scene sees them: the bounds of the
+ * contact phase under contacts, and its waits for the free bodies' wavefront
+ * (contact list and schedule; the end of a substep) under level schedule and
+ * integration.  Enabled by ms_enable_phase_profile (adds clock reads). */
 ms_status ms_enable_phase_profile(ms_batch* b, int32_t on);
 ms_status ms_phase_cycles(const ms_batch* b, unsigned long long* out_host);
 

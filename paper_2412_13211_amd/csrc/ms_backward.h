@@ -2,7 +2,7 @@
 // of one control step; the arithmetic is in ms_adjoint.h.
 //
 // Two kernels compute it:
-//   k_step_bwd_wave  one wavefront per scene.  It reads the record of the
+//   k_step_bwd_wave  two wavefronts per scene.  It reads the record of the
 //                    control step that the forward kernel writes in record
 //                    mode (substep states, contact lists, pre-projection
 //                    values of the Gauss-Seidel updates), keeps the scene's

@@ -75,7 +75,6 @@ __device__ __forceinline__ float sum16(float v) {
   return v;
 }
 // sum over lanes 0..15 (other lanes pass 0), returned in every lane
-__device__ __forceinline__ float sum16_b(float v) { return bcast0(sum16(v)); }
 // the sum of 16-lane row q (q = 0..3), read by every lane
 __device__ __forceinline__ float row_sum(float s16, int q) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(s16), 16 * q));

@@ -3,7 +3,7 @@
 // The scene description is packed once into one device buffer ("params"):
 //   [DModel x M][DScene x S][DFree x NF][static boxes 6 floats x NS]
 //   [planes float4 x NP][DAux x NA][scene order int x S]
-// Every scene is processed by one 64-lane wavefront (one workgroup); all of
+// Every scene is processed by one workgroup of two 64-lane wavefronts; all of
 // a scene's working data lives in that workgroup's LDS for the whole control
 // step, so HBM traffic is the state in/out, the controls and the scene
 // description.

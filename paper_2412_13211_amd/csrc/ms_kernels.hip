@@ -664,7 +664,6 @@ struct ConCtx {
   int cc;
   const float *SW, *SI;
   const float* F;
-  int fm;
   const float* A;
   const float* Pl;
   const uint16_t* own;
@@ -700,7 +699,6 @@ __device__ __forceinline__ void owner_geom(const ConCtx& X, int o, f3& c, float&
     of = ow >> 3;
     ovk = ow & 7;
     const float* F = X.F;
-    const int fm = X.fm;
     f3 x = mk3(F[(of) * FSTR + F_X + 0], F[(of) * FSTR + F_X + 1], F[(of) * FSTR + F_X + 2]);
     oidx = of;
     if (F[(of) * FSTR + F_TYPE] == 0.f) {
@@ -732,7 +730,6 @@ __device__ __forceinline__ bool eval_pair(const ConCtx& X, int o, int t, PairOut
   int tkey = 0, bside = 0;
   bool allowed = true;
   const float* F = X.F;
-  const int fm = X.fm;
   const float* A = X.A;
   if (t < X.np) {
     allowed = !(t == 0 && okind == 0 && (oflags & 1));
@@ -852,7 +849,6 @@ __device__ __forceinline__ float dist_point_box(f3 y, f3 e) {
 // conservative test of an axis-aligned box (centre bc, half extents he) against target t
 __device__ __forceinline__ bool box_near_target(const ConCtx& X, f3 bc, f3 he, int t, float slack) {
   const float* F = X.F;
-  const int fm = X.fm;
   const float* A = X.A;
   if (t < X.np) {
     f3 pn = mk3(X.Pl[t * 4], X.Pl[t * 4 + 1], X.Pl[t * 4 + 2]);
@@ -1038,7 +1034,6 @@ __device__ __forceinline__ void con_ctx(const KArgs& a, const Scene& S, float* L
   X.SW = L + Y.sph;
   X.SI = X.SW + 4 * S.nsph;
   X.F = L + Y.fr;
-  X.fm = Y.fmax;
   X.A = L + Y.aux;
   X.Pl = L + Y.plane;
   X.own = reinterpret_cast<const uint16_t*>(L + Y.own);
