@@ -367,6 +367,22 @@ void choose_bwd_split(const ms_batch* b, int& cc, int& rc) {
   }
 }
 
+// The wavefront adjoint's layout for the most contacts that the LDS block
+// holds beside the batch's robot contacts, or, when that is less than half
+// the batch's contacts, beside 8; total 0 when nothing fits.
+msa::WS bwd_ws_fitting(const ms_batch* b) {
+  const ms_batch_desc* d = &b->desc;
+  const int rfull = std::max(d->robot_contact_cap, 1);
+  for (int few = 0; few < 2; ++few)
+    for (int k = d->contact_cap; k >= std::max(few ? 1 : d->contact_cap / 2, 1); --k) {
+      const msa::WS w = bwd_ws_wave(d, b->cnt, k, few ? std::min(rfull, 8) : rfull);
+      if ((size_t)w.total * sizeof(float) <= b->max_lds) return w;
+    }
+  msa::WS none;
+  std::memset(&none, 0, sizeof none);
+  return none;
+}
+
 // record of a control step written by the forward kernel for the wavefront adjoint kernel
 RecLayout bwd_rec(const ms_batch_desc* d, const Counts& c) {
   return rec_layout(std::max(c.fmax, 1), d->contact_cap, d->pgs_iters, d->n_substeps);
@@ -877,7 +893,40 @@ static ms_status step_backward_impl(ms_batch* b, const void* x_in, const float* 
                   d->pgs_iters, step_mode(b), d->contact_cap, std::max(d->robot_contact_cap, 1), d->n_substeps};
   const msa::WS ww = bwd_ws_wave(d, c);
   const size_t lds = (size_t)ww.total * sizeof(float);
-  if ((b->sched.flags & MS_SCHED_BWD_REFERENCE) || lds > b->max_lds) {
+  // caps past the LDS block: the largest layout that fits it, and the lane
+  // kernel for the scenes whose lists overflow that
+  msa::WS wfit = ww;
+  const bool reference = (b->sched.flags & MS_SCHED_BWD_REFERENCE) != 0;
+  if (!reference && lds > b->max_lds) wfit = bwd_ws_fitting(b);
+  if (reference || wfit.total <= 0) {
+    if (!b->tape) return fail(MS_E_STATE, "ms_step_backward: the batch was created without a tape buffer");
+    a.w = bwd_ws(d, c);
+    launch_step_bwd(a, st);
+  } else if (lds > b->max_lds) {
+    if (!b->tape) return fail(MS_E_STATE, "ms_step_backward: the batch was created without a tape buffer");
+    const float* rec = given_rec;
+    if (!rec) {
+      float* tr = reinterpret_cast<float*>(b->tape);
+      ms_status rs = enqueue_record(b, x_in, ut, tr, st);
+      if (rs != MS_OK) return rs;
+      rec = tr;
+    }
+    BwdArgs wv = a;
+    wv.rec = rec;
+    wv.RL = bwd_rec(d, c);
+    wv.w = wfit;
+    int* bord = reinterpret_cast<int*>(b->scratch + b->sl.bwd_order);
+    int* nover = reinterpret_cast<int*>(b->scratch + b->sl.bwd_nover);
+    launch_bwd_order(rec, wv.RL, c.S, d->n_substeps, wfit.ccap, wfit.rcap,
+                     reinterpret_cast<int*>(b->scratch + b->sl.bwd_slot), bord, nover, st);
+    HIP_TRY(hipGetLastError());
+    wv.order = bord;
+    wv.n_over = nover;
+    wv.fit_mode = 1;
+    launch_step_bwd_wave(wv, (size_t)wfit.total * sizeof(float), c.S, st);
+    HIP_TRY(hipGetLastError());
+    a.order = bord;  // (after the record in the tape buffer has been read)
+    a.n_over = nover;
     a.w = bwd_ws(d, c);
     launch_step_bwd(a, st);
   } else {

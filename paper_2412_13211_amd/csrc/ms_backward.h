@@ -43,7 +43,7 @@ struct BwdArgs {
   // order (those whose contact lists fit the smaller layout), slot by slot;
   // 2 the first *n_over, a fixed grid looping over them
   int fit_mode;
-  const int* n_over;
+  const int* n_over;      // (lane kernel: null, or only the first *n_over scenes of the order)
 };
 
 inline int bwd_stride(int S) { return (S + 63) & ~63; }

@@ -8,7 +8,7 @@ namespace msk {
 // similar size; workspace interleaved across the lanes)
 __global__ __launch_bounds__(64) void k_step_bwd(BwdArgs a) {
   const int slot = blockIdx.x * 64 + threadIdx.x;
-  if (slot >= a.S) return;
+  if (slot >= (a.n_over ? *a.n_over : a.S)) return;
   const int s = a.order[slot];
   const DScene& D = a.scenes[s];
   msa::Eng E;

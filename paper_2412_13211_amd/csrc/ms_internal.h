@@ -109,43 +109,53 @@ __host__ __device__ inline LdsLayout make_layout(int fmax, int smax, int ccap, i
   L.rcap = rcap;
   L.owners = fmax * 8;
   L.ntmax = PMAX + smax + AMAX + fmax;
-  int o = 0;
-  // words the two wavefronts exchange: CTL_*
-  L.ctl = o;   o += CTL_WORDS;
-  L.robot = o; o += lds_align4(ROBOT_FLOATS);
-  // world sphere centres and radii of the robot, then each sphere's body and flags
-  L.sph = o;   o += lds_align4(nsph * 5);
-  L.fr = o;    o += lds_align4((fmax + 1) * FREE_FLOATS);  // + a zero record (static side)
-  L.aux = o;   o += AMAX * AUX_FLOATS;
-  L.stat = o;  o += lds_align4(L.smax * 6);
-  L.plane = o; o += PMAX * 4;
-  L.own = o;   o += lds_align4((L.owners + 1) / 2);        // uint16 owner table
-  L.con = o;   o += lds_align4(ccap * CON_FLOATS);
-  // robot contact rows.  Before the rows phase builds them, the culling masks
-  // (per robot or free body and 64-target chunk, 64 bits) lie there, the robot's
-  // then the free bodies' with their bounding spheres (4 floats each), and
-  // after them the dynamics scratch.
-  L.rows = o;
-  L.nch = (L.ntmax + WAVE - 1) / WAVE;
-  L.cmask = o;
-  L.fmask = o + lds_align4(ND * L.nch * 2);
-  L.dyn = L.fmask + lds_align4(fmax * L.nch * 2) + fmax * 4;
-  {
-    const int rw = lds_align4(rcap * ROW_FLOATS), mk = lds_align4(L.dyn - o + DYN_FLOATS);
-    o += rw > mk ? rw : mk;
+  // (a block past the 160 KiB of a workgroup: the dynamics scratch moves into the
+  // contact list and the robot's masks into the schedule; the dynamics then run
+  // before the contact list is written instead of beside it)
+  for (int serial = 0; serial < 2; ++serial) {
+    int o = 0;
+    // words the two wavefronts exchange: CTL_*
+    L.ctl = o;   o += CTL_WORDS;
+    L.robot = o; o += lds_align4(ROBOT_FLOATS);
+    // world sphere centres and radii of the robot, then each sphere's body and flags
+    L.sph = o;   o += lds_align4(nsph * 5);
+    L.fr = o;    o += lds_align4((fmax + 1) * FREE_FLOATS);  // + a zero record (static side)
+    L.aux = o;   o += AMAX * AUX_FLOATS;
+    L.stat = o;  o += lds_align4(L.smax * 6);
+    L.plane = o; o += PMAX * 4;
+    L.own = o;   o += lds_align4((L.owners + 1) / 2);        // uint16 owner table
+    L.con = o;   o += lds_align4(ccap * CON_FLOATS);
+    // robot contact rows.  Before the rows phase builds them, the culling masks
+    // (per robot or free body and 64-target chunk, 64 bits) lie there, the robot's
+    // then the free bodies' with their bounding spheres (4 floats each), and
+    // after them the dynamics scratch.
+    L.rows = o;
+    L.nch = (L.ntmax + WAVE - 1) / WAVE;
+    const int sched = lds_align4((4 * ccap + 5 + 1) / 2), rmask = lds_align4(ND * L.nch * 2);
+    const bool in_sched = serial && rmask <= sched;
+    L.cmask = o;
+    L.fmask = o + (in_sched ? 0 : rmask);
+    L.dyn = L.fmask + lds_align4(fmax * L.nch * 2) + fmax * 4;
+    {
+      const int rw = lds_align4(rcap * ROW_FLOATS), mk = lds_align4(L.dyn - o + (serial ? 0 : DYN_FLOATS));
+      o += rw > mk ? rw : mk;
+    }
+    if (serial) L.dyn = L.con;
+    if (in_sched) L.cmask = o;
+    // sweep schedule: each group's previous groups [ccap + 2] twice, its level
+    // [ccap] and first row [ccap + 1] (uint16)
+    L.lvl = o;   o += sched;
+    // two uint16 candidate lists; after the contact phase the level schedule's
+    // per-node group masks (64-bit, per node and 64-group chunk) and the mask
+    // of the robot's nodes
+    {
+      const int masks = (1 + AMAX + fmax) * ((ccap + WAVE - 1) / WAVE) * 2 + 2;
+      L.cand = o;  o += lds_align4(L.ntmax > masks ? L.ntmax : masks);
+    }
+    L.frc = o;   o += force ? lds_align4(fmax * FRC_FLOATS) : 0;  // force-output accumulators
+    L.total = o;
+    if (o * 4 <= 163840 || ccap * CON_FLOATS < DYN_FLOATS) break;
   }
-  // sweep schedule: each group's previous groups [ccap + 2] twice, its level
-  // [ccap] and first row [ccap + 1] (uint16)
-  L.lvl = o;   o += lds_align4((4 * ccap + 5 + 1) / 2);
-  // two uint16 candidate lists; after the contact phase the level schedule's
-  // per-node group masks (64-bit, per node and 64-group chunk) and the mask
-  // of the robot's nodes
-  {
-    const int masks = (1 + AMAX + fmax) * ((ccap + WAVE - 1) / WAVE) * 2 + 2;
-    L.cand = o;  o += lds_align4(L.ntmax > masks ? L.ntmax : masks);
-  }
-  L.frc = o;   o += force ? lds_align4(fmax * FRC_FLOATS) : 0;  // force-output accumulators
-  L.total = o;
   return L;
 }
 

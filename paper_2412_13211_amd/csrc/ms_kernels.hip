@@ -2806,14 +2806,18 @@ __device__ __forceinline__ int run_scene(int s, int wv, float* const L0) {
       kin_free(args_fresh(), S, lds_fresh(L0));
       if (cull) cull_free(args_fresh(), S, lds_fresh(L0), fmem, fob);
     }
-    both_sync();
+    // the dynamics beside the contact list, or (scratch in its place) before it
+    const bool serial = args_fresh().L.dyn == args_fresh().L.con;
+    if (!serial) both_sync();
     MS_PHASE(1)
     // the robot's dynamics; the contact list, its schedule and rows
     Levels lv{0, 0, 0ull};
     if (wv == 0) {
       dyn_robot(args_fresh(), S, lds_fresh(L0), vR);
       MS_PHASE(2)
-    } else {
+    }
+    if (serial) both_sync();
+    if (wv != 0) {
       Contacts cn;
       emit_contacts(args_fresh(), S, lds_fresh(L0), cull ? uniform(ctl[CTL_NCA]) : 0, fmem, fob, cn);
       keysum = cn.keysum;

@@ -193,3 +193,35 @@ def _repeat(b, rows):
         b, n_scenes=S, scene_model=b.scene_model[rows], scene_hold=b.scene_hold[rows], free_off=fo, static_off=so,
         plane_off=po, aux_off=ao, static_box=b.static_box[si], plane=b.plane[pi],
         state0=sg.join_state(st["q"][rows], st["qd"][rows], st["free"][fi], st["aux"][ai]), **kw)
+
+
+@pytest.mark.parametrize("ccap,rcap", [(700, 24), (700, 200), (None, 1)])
+def test_caps_past_the_adjoint_block(ccap, rcap):
+    """Contact caps whose adjoint workspace is past the LDS block (None: the
+    largest cap the forward step takes, where its dynamics scratch lies in the
+    contact list's place): the same step and gradient bit for bit as with caps
+    that fit."""
+    ms = _ms()
+    b = sg.make(2, 6)
+    x = torch.as_tensor(b.state0).cuda()
+    u = torch.as_tensor(b.controls(0)).cuda()
+    g = torch.as_tensor(np.random.default_rng(3).normal(size=b.state0.size).astype(np.float32)).cuda()
+    if ccap is None:
+        for ccap in range(2100, 1500, -1):
+            try:
+                ms.MsBatch(b, contact_cap=ccap, robot_contact_cap=rcap).step(x, u)
+                break
+            except ms.MsError:
+                pass
+        print(f"[largest caps] {ccap} contacts, {rcap} of the robot", flush=True)
+        assert ccap > 1800
+    got = []
+    for cc, rc in ((64, rcap if rcap < 24 else 24), (ccap, rcap)):
+        mb = ms.MsBatch(b, contact_cap=cc, robot_contact_cap=rc, backward=True)
+        y = mb.step(x, u)
+        gx, gu = mb.step_backward(x, u, g)
+        torch.cuda.synchronize()
+        assert not np.any(mb.status())
+        got.append([t.cpu().numpy() for t in (y, gx, gu)])
+    for a, c in zip(*got):
+        assert np.array_equal(a.view(np.uint32), c.view(np.uint32))
