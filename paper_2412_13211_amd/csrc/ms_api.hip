@@ -489,6 +489,7 @@ ms_status ms_create_batch(const ms_batch_desc* d, const ms_scene_desc* sc, void*
   // allow the kernels the whole LDS of a workgroup
   for (bool dense : {false, true})
     (void)hipFuncSetAttribute(step_kernel_ptr(dense), hipFuncAttributeMaxDynamicSharedMemorySize, (int)b->max_lds);
+  set_step_tight_lds(b->max_lds);
   (void)hipFuncSetAttribute(step_rec_kernel_ptr(), hipFuncAttributeMaxDynamicSharedMemorySize, (int)b->max_lds);
   (void)hipFuncSetAttribute(step_frc_kernel_ptr(), hipFuncAttributeMaxDynamicSharedMemorySize, (int)b->max_lds);
   (void)hipFuncSetAttribute(spawn_check_kernel_ptr(), hipFuncAttributeMaxDynamicSharedMemorySize, (int)b->max_lds);

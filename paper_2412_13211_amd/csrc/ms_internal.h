@@ -109,7 +109,7 @@ __host__ __device__ inline LdsLayout make_layout(int fmax, int smax, int ccap, i
   L.rcap = rcap;
   L.owners = fmax * 8;
   L.ntmax = PMAX + smax + AMAX + fmax;
-  // (a block past the 160 KiB of a workgroup: the dynamics scratch moves into the
+  // (a block past the 160 KiB of a workgroup, k_step_tight: the dynamics scratch moves into the
   // contact list and the robot's masks into the schedule; the dynamics then run
   // before the contact list is written instead of beside it)
   for (int serial = 0; serial < 2; ++serial) {
@@ -246,6 +246,7 @@ void launch_actions_bwd(const DModel* models, const DScene* scenes, const float*
 void launch_masked_copy(float* dst, const float* src, const uint8_t* mask, int S, int NF, int NA,
                         const int* free_off, const int* aux_off, hipStream_t st);
 const void* step_kernel_ptr(bool dense);
+void set_step_tight_lds(size_t bytes);  // the forms for LDS blocks near the limit
 const void* step_rec_kernel_ptr();
 const void* step_frc_kernel_ptr();
 const void* spawn_check_kernel_ptr();

@@ -2726,13 +2726,16 @@ __device__ __forceinline__ void scene_view(const KArgs& a, int s, Scene& S) {
 // adjoint; 2: also the contact-force outputs.  Separate instantiations, so
 // the plain step keeps its register allocation.  DENSE: the plain step at 128
 // registers, for batches that fill the CUs with more scenes (the sweeps then
-// load a lane's group again at its level instead of keeping it).
+// load a lane's group again at its level instead of keeping it).  TIGHT: for LDS
+// blocks that only fit with the dynamics scratch in the contact list's place
+// (make_layout); a form of its own, because the choice inside the loop cost the
+// others 2 %.
 //
 // wv: the wavefront (0: the robot's part, 1: the free bodies').  Every barrier
 // is outside the branches on wv, and the substep loop ends alike in both
 // wavefronts (the counts and the status they test come from LDS words read
 // after a barrier).  Returns the next queue position.
-template <int MODE, bool DENSE>
+template <int MODE, bool DENSE, bool TIGHT>
 __device__ __forceinline__ int run_scene(int s, int wv, float* const L0) {
   const KArgs& a = args_fresh();
   float* const L = lds_fresh(L0);
@@ -2806,18 +2809,16 @@ __device__ __forceinline__ int run_scene(int s, int wv, float* const L0) {
       kin_free(args_fresh(), S, lds_fresh(L0));
       if (cull) cull_free(args_fresh(), S, lds_fresh(L0), fmem, fob);
     }
-    // the dynamics beside the contact list, or (scratch in its place) before it
-    const bool serial = args_fresh().L.dyn == args_fresh().L.con;
-    if (!serial) both_sync();
+    // (dynamics scratch in the contact list's place: the dynamics before it)
+    if (TIGHT && wv == 0) dyn_robot(args_fresh(), S, lds_fresh(L0), vR);
+    both_sync();
     MS_PHASE(1)
     // the robot's dynamics; the contact list, its schedule and rows
     Levels lv{0, 0, 0ull};
     if (wv == 0) {
-      dyn_robot(args_fresh(), S, lds_fresh(L0), vR);
+      if (!TIGHT) dyn_robot(args_fresh(), S, lds_fresh(L0), vR);
       MS_PHASE(2)
-    }
-    if (serial) both_sync();
-    if (wv != 0) {
+    } else {
       Contacts cn;
       emit_contacts(args_fresh(), S, lds_fresh(L0), cull ? uniform(ctl[CTL_NCA]) : 0, fmem, fob, cn);
       keysum = cn.keysum;
@@ -2955,7 +2956,7 @@ __device__ __forceinline__ int run_scene(int s, int wv, float* const L0) {
   return next;
 }
 
-template <int MODE, bool DENSE = false>
+template <int MODE, bool DENSE = false, bool TIGHT = false>
 __device__ __forceinline__ void step_body(const KArgs& a, float* lds) {
   // one call site: the persistent form pulls positions from its work counter
   // (wavefront 0, for both), the plain form takes its block index once
@@ -2970,7 +2971,7 @@ __device__ __forceinline__ void step_body(const KArgs& a, float* lds) {
     pos = base + uniform(ctl[CTL_POS]);
   }
   while (pos < end) {
-    pos = base + run_scene<MODE, DENSE>(uniform(a.fit_mode == 3 ? a.retry[1 + pos] : a.order[pos]), wv, lds);
+    pos = base + run_scene<MODE, DENSE, TIGHT>(uniform(a.fit_mode == 3 ? a.retry[1 + pos] : a.order[pos]), wv, lds);
     if (!a.persistent) break;
   }
 }
@@ -2990,6 +2991,20 @@ __global__ __launch_bounds__(STEP_THREADS) __attribute__((amdgpu_waves_per_eu(3,
 __global__ __launch_bounds__(STEP_THREADS) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_step_frc(KArgs a) {
   extern __shared__ float lds[];
   step_body<2>(a, lds);
+}
+
+// LDS blocks near the limit (one workgroup per CU)
+__global__ __launch_bounds__(STEP_THREADS) void k_step_tight(KArgs a) {
+  extern __shared__ float lds[];
+  step_body<0, false, true>(a, lds);
+}
+__global__ __launch_bounds__(STEP_THREADS) void k_step_rec_tight(KArgs a) {
+  extern __shared__ float lds[];
+  step_body<1, false, true>(a, lds);
+}
+__global__ __launch_bounds__(STEP_THREADS) void k_step_frc_tight(KArgs a) {
+  extern __shared__ float lds[];
+  step_body<2, false, true>(a, lds);
 }
 
 __global__ void k_reset_queue(int* q) {
@@ -3154,10 +3169,11 @@ __global__ void k_masked_copy(float* dst, const float* src, const uint8_t* mask,
 }
 
 void launch_step(const KArgs& a, int grid, size_t lds_bytes, hipStream_t st) {
-  if (a.rec) hipLaunchKernelGGL(k_step_rec, dim3(grid), dim3(STEP_THREADS), lds_bytes, st, a);
-  else if (a.frc_robot || a.grip) hipLaunchKernelGGL(k_step_frc, dim3(grid), dim3(STEP_THREADS), lds_bytes, st, a);
-  else if (a.dense) hipLaunchKernelGGL(k_step_dense, dim3(grid), dim3(STEP_THREADS), lds_bytes, st, a);
-  else hipLaunchKernelGGL(k_step, dim3(grid), dim3(STEP_THREADS), lds_bytes, st, a);
+  const bool tight = a.L.dyn == a.L.con, frc = a.frc_robot || a.grip;
+  void (*k)(KArgs) = a.rec ? (tight ? k_step_rec_tight : k_step_rec)
+                           : (frc ? (tight ? k_step_frc_tight : k_step_frc)
+                                  : (tight ? k_step_tight : (a.dense ? k_step_dense : k_step)));
+  hipLaunchKernelGGL(k, dim3(grid), dim3(STEP_THREADS), lds_bytes, st, a);
 }
 void launch_reset_queue(int* q, hipStream_t st) { hipLaunchKernelGGL(k_reset_queue, dim3(1), dim3(64), 0, st, q); }
 
@@ -3240,6 +3256,11 @@ void launch_masked_copy(float* dst, const float* src, const uint8_t* mask, int S
                         const int* free_off, const int* aux_off, hipStream_t st) {
   if (S <= 0) return;
   hipLaunchKernelGGL(k_masked_copy, dim3(S), dim3(64), 0, st, dst, src, mask, S, NF, NA, free_off, aux_off);
+}
+void set_step_tight_lds(size_t bytes) {
+  for (const void* k : {reinterpret_cast<const void*>(&k_step_tight), reinterpret_cast<const void*>(&k_step_rec_tight),
+                        reinterpret_cast<const void*>(&k_step_frc_tight)})
+    (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 const void* step_kernel_ptr(bool dense) {
   return dense ? reinterpret_cast<const void*>(&k_step_dense) : reinterpret_cast<const void*>(&k_step);

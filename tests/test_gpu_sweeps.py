@@ -225,3 +225,33 @@ def test_caps_past_the_adjoint_block(ccap, rcap):
         got.append([t.cpu().numpy() for t in (y, gx, gu)])
     for a, c in zip(*got):
         assert np.array_equal(a.view(np.uint32), c.view(np.uint32))
+
+
+def test_force_outputs_at_the_largest_cap():
+    """The contact-force step in an LDS block near the limit (dynamics before the
+    contact list): states and forces as with a small cap, bit for bit, into the
+    steps where the robots push bodies."""
+    ms = _ms()
+    b = sg.make(2, 32)
+    got = []
+    for cc in (64, *range(2100, 1900, -1)):
+        x = torch.as_tensor(b.state0).cuda()
+        try:
+            mb = ms.MsBatch(b, contact_cap=cc, robot_contact_cap=16)
+            fr, fb = mb.enable_forces()
+            out = []
+            for t in range(7):
+                x = mb.step(x, torch.as_tensor(b.controls_for(t)).cuda())
+                torch.cuda.synchronize()
+                assert not np.any(mb.status())
+                out.append([v.cpu().numpy() for v in (x, fr, fb)])
+        except ms.MsError:
+            continue
+        got.append(out)
+        if len(got) == 2:
+            break
+    print(f"[largest cap with forces] {cc}", flush=True)
+    assert len(got) == 2 and np.any(got[0][-1][2])
+    for step in zip(*got):
+        for a, c in zip(*step):
+            assert np.array_equal(a.view(np.uint32), c.view(np.uint32))
