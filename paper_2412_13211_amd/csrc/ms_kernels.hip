@@ -933,6 +933,39 @@ __device__ __forceinline__ bool bound_near(const TBound& B, f3 c, float R, float
   return (B.isplane & pl) | (!B.isplane & bx);
 }
 
+// Whether the bounds' slack covers a frame, a rotated target or a body: the
+// bounds take frames as rigid, plane normals as unit vectors and half extents as
+// positive, and their slack of 1e-3 covers the rounding of coordinates below
+// BOUND_FAR (an ulp there is 6e-5) and, of a frame within 2e-5 of rigid, levers
+// below BOUND_LEVER.
+constexpr float BOUND_FAR = 512.f, BOUND_LEVER = 16.f;
+__device__ __forceinline__ bool within(f3 v, float lim) {
+  return fabsf(v.x) < lim && fabsf(v.y) < lim && fabsf(v.z) < lim;
+}
+__device__ __forceinline__ bool extents(f3 e, float lim) { return fminf(fminf(e.x, e.y), e.z) >= 0.f && within(e, lim); }
+__device__ __forceinline__ bool rigid(const float* R) {
+  const f3 a = mk3(R[0], R[1], R[2]), b = mk3(R[3], R[4], R[5]), c = mk3(R[6], R[7], R[8]);
+  return within(mk3(dot(a, a) - 1.f, dot(b, b) - 1.f, dot(c, c) - 1.f), 2e-5f) &&
+         within(mk3(dot(a, b), dot(a, c), dot(b, c)), 2e-5f);
+}
+__device__ __forceinline__ bool bound_holds(const ConCtx& X, int t) {
+  const float* F = X.F;
+  const float* A = X.A;
+  if (t < X.np) {
+    const f3 n = mk3(X.Pl[t * 4], X.Pl[t * 4 + 1], X.Pl[t * 4 + 2]);
+    return fabsf(dot(n, n) - 1.f) < 2e-5f && fabsf(X.Pl[t * 4 + 3]) < BOUND_FAR;
+  }
+  const bool aux = t < X.np + X.ns + X.na;
+  const int i = aux ? t - X.np - X.ns : t - X.np - X.ns - X.na;
+  float R[9];
+  for (int k = 0; k < 9; ++k) R[k] = aux ? A[(A_R + k) * AMAX + i] : F[i * FSTR + F_R + k];
+  if (aux)
+    return rigid(R) && within(mk3(A[(A_BC + 0) * AMAX + i], A[(A_BC + 1) * AMAX + i], A[(A_BC + 2) * AMAX + i]), BOUND_FAR) &&
+           extents(mk3(A[(A_BH + 0) * AMAX + i], A[(A_BH + 1) * AMAX + i], A[(A_BH + 2) * AMAX + i]), BOUND_LEVER);
+  return (F[i * FSTR + F_TYPE] != 0.f || rigid(R)) && within(mk3(F[i * FSTR + F_X], F[i * FSTR + F_X + 1], F[i * FSTR + F_X + 2]), BOUND_FAR) &&
+         extents(mk3(F[i * FSTR + F_H], F[i * FSTR + F_H + 1], F[i * FSTR + F_H + 2]), BOUND_LEVER);
+}
+
 // position of the k-th (from 0) set bit of m (k < popcount(m))
 __device__ __forceinline__ int select_bit(uint64_t m, int k) {
   int pos = 0;
@@ -1048,7 +1081,9 @@ __device__ __forceinline__ void con_ctx(const KArgs& a, const Scene& S, float* L
 //
 // The robot's part: the targets near the robot into listA, per robot body the
 // mask of those near its bounding sphere.  Returns the number of 64-target
-// chunks of listA.
+// chunks of listA; CHECK: -1 when the scene holds a body or target whose bound
+// does not cover what the pair test may accept (bound_holds).
+template <bool CHECK = false>
 __device__ __forceinline__ int cull_robot(const KArgs& a, const Scene& S, float* L, float margin) {
   const int lane = lane_id();
   const LdsLayout& Y = a.L;
@@ -1063,10 +1098,14 @@ __device__ __forceinline__ int cull_robot(const KArgs& a, const Scene& S, float*
   // axis-aligned box around them (the bodies are in the first 16 lanes)
   f3 sc = mk3(0.f, 0.f, 0.f), lo = mk3(1e30f, 1e30f, 1e30f), hi = mk3(-1e30f, -1e30f, -1e30f);
   float sr = -1.f;
+  bool held = true;
   if (lane < S.nb) {
     const float4 bs = M->bsph[lane];
     sc = mv(rb.R + lane * 9, mk3(bs.x, bs.y, bs.z)) + body_p(rb, lane);
     if (M->sph_count[lane] > 0) {
+      if (CHECK)
+        held = rigid(rb.R + lane * 9) && within(body_p(rb, lane), BOUND_FAR) &&
+               within(mk3(bs.x, bs.y, bs.z), BOUND_LEVER) && bs.w < BOUND_LEVER;
       sr = bs.w;
       lo = mk3(sc.x - bs.w, sc.y - bs.w, sc.z - bs.w);
       hi = mk3(sc.x + bs.w, sc.y + bs.w, sc.z + bs.w);
@@ -1095,7 +1134,12 @@ __device__ __forceinline__ int cull_robot(const KArgs& a, const Scene& S, float*
       const int t = base + u * WAVE + lane;
       bool m = false;
       if (t < NT) {
-        if (t >= S.np && t < S.np + S.ns)
+        const bool furniture = t >= S.np && t < S.np + S.ns;
+        if (CHECK)
+          held = held && (furniture ? within(mk3(bx[u][0], bx[u][1], bx[u][2]), BOUND_FAR) &&
+                                          extents(mk3(bx[u][3], bx[u][4], bx[u][5]), BOUND_FAR)
+                                    : bound_holds(X, t));
+        if (furniture)
           m = fabsf(bc.x - bx[u][0]) < he.x + bx[u][3] + slack && fabsf(bc.y - bx[u][1]) < he.y + bx[u][4] + slack &&
               fabsf(bc.z - bx[u][2]) < he.z + bx[u][5] + slack;
         else
@@ -1106,6 +1150,7 @@ __device__ __forceinline__ int cull_robot(const KArgs& a, const Scene& S, float*
       nra += __popcll(mk);
     }
   }
+  if (CHECK && __ballot(!held)) return -1;
   // the robot bodies' bounding spheres against the robot's candidates,
   // transposed as for the free bodies below: lanes over a chunk of the
   // candidates, a loop over the bodies (their spheres by readlane), one ballot
@@ -3013,9 +3058,11 @@ __global__ void k_reset_queue(int* q) {
 
 // Spawn check of a reset: collide[s] = 1 where a robot sphere penetrates
 // (phi < 0) another body: the step's culling and pair test of the robot with a
-// zero margin, one wavefront per scene.  Without culling every (robot sphere,
-// target) pair is tested: 4 to 11 thousand pairs in a furnished room where
-// the culling leaves a few hundred (4096 scenes: 174 -> 49 us).
+// zero margin, one wavefront per scene.  Every (robot sphere, target) pair is
+// tested, 4 to 11 thousand in a furnished room where the culling leaves a few
+// hundred, without culling and in a scene whose bounds do not cover what the
+// pair test may accept (bound_holds): the state is the caller's, its
+// quaternions and distances are anything.
 __global__ __launch_bounds__(WAVE) void k_spawn_check(KArgs a, uint8_t* collide) {
   extern __shared__ float lds[];
   const int s = blockIdx.x;
@@ -3034,8 +3081,8 @@ __global__ __launch_bounds__(WAVE) void k_spawn_check(KArgs a, uint8_t* collide)
   X.margin = 0.f;
   X.hash = false;
   bool hit = false;
-  if (a.cull && S.nsph > 0) {
-    const int ncA = cull_robot(a, S, L, 0.f);
+  const int ncA = a.cull && S.nsph > 0 ? cull_robot<true>(a, S, L, 0.f) : -1;
+  if (ncA >= 0) {
     const uint16_t* listA = reinterpret_cast<const uint16_t*>(L + a.L.cand);
     const DModel* M = S.M;
     EmitState E{0, 0, false, false, 0ull};
