@@ -76,7 +76,7 @@ struct DAux {
 
 // Offsets (in floats) of the regions of one scene's LDS block.
 struct LdsLayout {
-  int fmax, smax, ccap, rcap, owners, ntmax;
+  int fmax, smax, ccap, rcap, owners, ntmax, tight;
   int ctl, robot, sph, fr, aux, stat, plane, own, con, rows, dyn, cmask, fmask, nch, lvl, cand, frc, total;
 };
 
@@ -109,11 +109,14 @@ __host__ __device__ inline LdsLayout make_layout(int fmax, int smax, int ccap, i
   L.rcap = rcap;
   L.owners = fmax * 8;
   L.ntmax = PMAX + smax + AMAX + fmax;
-  // (a block past the 160 KiB of a workgroup, k_step_tight: the dynamics scratch moves into the
-  // contact list and the robot's masks into the schedule; the dynamics then run
-  // before the contact list is written instead of beside it)
-  for (int serial = 0; serial < 2; ++serial) {
+  // A block past the 160 KiB of a workgroup shares more (tight; the forms
+  // k_step_tight ...): the dynamics run before the culling with their scratch in
+  // the place of the contact list and the robot rows, and the free bodies are
+  // culled after the robot's exact tests, with their masks in the robot's place
+  // (or the robot's in the schedule's, where they fit).
+  for (int tight = 0; tight < 2; ++tight) {
     int o = 0;
+    L.tight = tight;
     // words the two wavefronts exchange: CTL_*
     L.ctl = o;   o += CTL_WORDS;
     L.robot = o; o += lds_align4(ROBOT_FLOATS);
@@ -131,30 +134,31 @@ __host__ __device__ inline LdsLayout make_layout(int fmax, int smax, int ccap, i
     // after them the dynamics scratch.
     L.rows = o;
     L.nch = (L.ntmax + WAVE - 1) / WAVE;
-    const int sched = lds_align4((4 * ccap + 5 + 1) / 2), rmask = lds_align4(ND * L.nch * 2);
-    const bool in_sched = serial && rmask <= sched;
+    const int sched = lds_align4((4 * ccap + 5 + 1) / 2);
+    const int rmask = lds_align4(ND * L.nch * 2), fmask = lds_align4(fmax * L.nch * 2) + fmax * 4;
+    const int rw = lds_align4(rcap * ROW_FLOATS);
+    const bool in_sched = tight && rmask <= sched;
     L.cmask = o;
-    L.fmask = o + (in_sched ? 0 : rmask);
-    L.dyn = L.fmask + lds_align4(fmax * L.nch * 2) + fmax * 4;
-    {
-      const int rw = lds_align4(rcap * ROW_FLOATS), mk = lds_align4(L.dyn - o + (serial ? 0 : DYN_FLOATS));
-      o += rw > mk ? rw : mk;
-    }
-    if (serial) L.dyn = L.con;
+    L.fmask = tight ? o : o + rmask;
+    L.dyn = tight ? L.con : L.fmask + fmask;
+    int mk = rmask + fmask + lds_align4(DYN_FLOATS);
+    if (tight) mk = in_sched || fmask > rmask ? fmask : rmask;
+    o += rw > mk ? rw : mk;
+    if (tight && o < L.con + lds_align4(DYN_FLOATS)) o = L.con + lds_align4(DYN_FLOATS);
     if (in_sched) L.cmask = o;
     // sweep schedule: each group's previous groups [ccap + 2] twice, its level
     // [ccap] and first row [ccap + 1] (uint16)
     L.lvl = o;   o += sched;
-    // two uint16 candidate lists; after the contact phase the level schedule's
-    // per-node group masks (64-bit, per node and 64-group chunk) and the mask
-    // of the robot's nodes
+    // the robot's candidate targets (uint16); after the contact phase the level
+    // schedule's per-node group masks (64-bit, per node and 64-group chunk) and
+    // the mask of the robot's nodes
     {
-      const int masks = (1 + AMAX + fmax) * ((ccap + WAVE - 1) / WAVE) * 2 + 2;
-      L.cand = o;  o += lds_align4(L.ntmax > masks ? L.ntmax : masks);
+      const int masks = (1 + AMAX + fmax) * ((ccap + WAVE - 1) / WAVE) * 2 + 2, list = (L.ntmax + 1) / 2;
+      L.cand = o;  o += lds_align4(list > masks ? list : masks);
     }
     L.frc = o;   o += force ? lds_align4(fmax * FRC_FLOATS) : 0;  // force-output accumulators
     L.total = o;
-    if (o * 4 <= 163840 || ccap * CON_FLOATS < DYN_FLOATS) break;
+    if (o * 4 <= 163840) break;
   }
   return L;
 }

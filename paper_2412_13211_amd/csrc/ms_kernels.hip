@@ -1369,7 +1369,9 @@ struct Contacts {
 };
 // The contact list: joint-limit rows, then the exact tests of the robot's and
 // the free bodies' candidates in canonical order (ncA: chunks of the robot's
-// candidate list).
+// candidate list).  TIGHT: the free bodies are culled in between, their masks
+// in the place of the robot's.
+template <bool TIGHT>
 __device__ __forceinline__ void emit_contacts(const KArgs& a, const Scene& S, float* L, int ncA, int fmem, int fob,
                                               Contacts& out) {
   const int lane = lane_id();
@@ -1422,6 +1424,7 @@ __device__ __forceinline__ void emit_contacts(const KArgs& a, const Scene& S, fl
       exact_grouped(
           X, a.rcap, S.nb, reinterpret_cast<const uint32_t*>(L + Y.cmask), ncA, lane < S.nb ? (int)M->sph_count[lane] : 0,
           lane < S.nb ? (int)M->sph_first[lane] : 0, [&](int ch, int j) { return (int)listA[ch * WAVE + j]; }, E);
+    if (TIGHT) cull_free(a, S, L, fmem, fob);
     exact_grouped(
         X, a.rcap, S.nf, reinterpret_cast<const uint32_t*>(L + Y.fmask), (NT + WAVE - 1) / WAVE, fmem, fob,
         [&](int ch, int j) { return ch * WAVE + j; }, E);
@@ -2772,9 +2775,9 @@ __device__ __forceinline__ void scene_view(const KArgs& a, int s, Scene& S) {
 // the plain step keeps its register allocation.  DENSE: the plain step at 128
 // registers, for batches that fill the CUs with more scenes (the sweeps then
 // load a lane's group again at its level instead of keeping it).  TIGHT: for LDS
-// blocks that only fit with the dynamics scratch in the contact list's place
-// (make_layout); a form of its own, because the choice inside the loop cost the
-// others 2 %.
+// blocks that only fit with the dynamics scratch and the culling masks in the
+// contact list's and the rows' place (make_layout); a form of its own, because
+// the choice inside the loop cost the others 2 %.
 //
 // wv: the wavefront (0: the robot's part, 1: the free bodies').  Every barrier
 // is outside the branches on wv, and the substep loop ends alike in both
@@ -2845,6 +2848,8 @@ __device__ __forceinline__ int run_scene(int s, int wv, float* const L0) {
       phase_drive(args_fresh(), S, lds_fresh(L0));
       kin_robot(args_fresh(), S, lds_fresh(L0));
       MS_PHASE(0)
+      // (the dynamics scratch in the place of the contact list and the masks: before either)
+      if (TIGHT) dyn_robot(args_fresh(), S, lds_fresh(L0), vR);
       if (cull && S.nsph > 0) {
         const int ncA = cull_robot(args_fresh(), S, lds_fresh(L0), args_fresh().margin);
         if (lane_id() == 0) ctl[CTL_NCA] = ncA;
@@ -2852,10 +2857,8 @@ __device__ __forceinline__ int run_scene(int s, int wv, float* const L0) {
     } else {
       if (rec) rec_free(args_fresh(), S, lds_fresh(L0), rec + ks * a.RL.ss);
       kin_free(args_fresh(), S, lds_fresh(L0));
-      if (cull) cull_free(args_fresh(), S, lds_fresh(L0), fmem, fob);
+      if (!TIGHT && cull) cull_free(args_fresh(), S, lds_fresh(L0), fmem, fob);
     }
-    // (dynamics scratch in the contact list's place: the dynamics before it)
-    if (TIGHT && wv == 0) dyn_robot(args_fresh(), S, lds_fresh(L0), vR);
     both_sync();
     MS_PHASE(1)
     // the robot's dynamics; the contact list, its schedule and rows
@@ -2865,7 +2868,7 @@ __device__ __forceinline__ int run_scene(int s, int wv, float* const L0) {
       MS_PHASE(2)
     } else {
       Contacts cn;
-      emit_contacts(args_fresh(), S, lds_fresh(L0), cull ? uniform(ctl[CTL_NCA]) : 0, fmem, fob, cn);
+      emit_contacts<TIGHT>(args_fresh(), S, lds_fresh(L0), cull ? uniform(ctl[CTL_NCA]) : 0, fmem, fob, cn);
       keysum = cn.keysum;
       const bool over = a.fit_mode == 1 && cn.status;
       if (!over) {
@@ -3216,7 +3219,7 @@ __global__ void k_masked_copy(float* dst, const float* src, const uint8_t* mask,
 }
 
 void launch_step(const KArgs& a, int grid, size_t lds_bytes, hipStream_t st) {
-  const bool tight = a.L.dyn == a.L.con, frc = a.frc_robot || a.grip;
+  const bool tight = a.L.tight != 0, frc = a.frc_robot || a.grip;
   void (*k)(KArgs) = a.rec ? (tight ? k_step_rec_tight : k_step_rec)
                            : (frc ? (tight ? k_step_frc_tight : k_step_frc)
                                   : (tight ? k_step_tight : (a.dense ? k_step_dense : k_step)));
