@@ -174,10 +174,11 @@ MSA_HD inline Ids unpack_ids(float f) {
   const int v = __builtin_bit_cast(int, f);
   return Ids{v & 3, (v >> 7) & 255, (v >> 2) & 7, (v >> 5) & 3, (v >> 15) & 0xffff};
 }
-// contact adjoint record: direction adjoints (n, t1, t2), contact point, W,
-// bias.  (The wavefront kernel keeps nine lever adjoints from B_P on while it
-// reverses the sweeps of a free body's contacts.)
-enum { B_D = 0, B_P = 9, B_W = 18, B_BIAS = 21, CB = 22 };
+// contact adjoint record: direction adjoints (n, t1, t2), contact point, W, bias
+enum { B_D = 0, B_P = 9, B_W = 12, B_BIAS = 15, CB = 16 };
+// the wavefront kernel's: nine lever adjoints from the contact point's place on
+// while it reverses the sweeps of a free body's contacts
+enum { CW_D = 0, CW_P = 9, CW_W = 18, CW_BIAS = 21, CW = 22 };
 // free-body adjoint record
 enum { F_XB = 0, F_RB = 3, F_IIB = 12, F_IWB = 21, FB = 30 };
 // door / drawer adjoint record
@@ -265,7 +266,7 @@ MSA_HD inline WS ws_layout(int fmax, int ntmax, int ccap, int rcap, int K, int n
   w.rJ = take(w.rcap * 3 * ND); w.rw = take(w.rcap * 3 * ND);
   w.vRb = take(ND); w.vAb = take(AMAX); w.vFb = take(fm * 6);
   w.lamb = take(3 * ccap); w.llamb = take(2 * AMAX); w.limb = take(2 * AMAX);
-  w.conb = take(ccap * CB);
+  w.conb = take(ccap * (wave ? CW : CB));
   // the robot rows' adjoints (and in the wavefront kernel the staged tape)
   // are dead once rows^T is done; the dynamics^T scratch (written before it
   // is read) shares their space.  The wavefront kernel forms Ibar in place

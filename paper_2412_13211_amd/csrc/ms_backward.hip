@@ -275,7 +275,7 @@ __device__ __forceinline__ void row_bar(const msa::WS& w, float* L, int ci, cons
   using namespace msa;
   constexpr bool PAIR = KIND == 1, JOINT = KIND == 2;
   const float* e = L + w.con + ci * CR;
-  float* cb = L + w.conb + ci * CB;
+  float* cb = L + w.conb + ci * CW;
   float* lb = L + w.lamb + ci * 3;
   const V p{e[C_P], e[C_P + 1], e[C_P + 2]};
   const float iw0 = e[C_W], iw1 = e[C_W + 1], iw2 = e[C_W + 2], bias = e[C_BIAS];
@@ -393,10 +393,10 @@ __device__ __forceinline__ void row_bar(const msa::WS& w, float* L, int ci, cons
     cb[9 + 3 * d] = G[d].x; cb[10 + 3 * d] = G[d].y; cb[11 + 3 * d] = G[d].z;
   }
   // W's adjoint: yb r / W^2
-  cb[B_W] -= rb0 * r0 * iw0;
-  cb[B_W + 1] -= rb1 * r1 * iw1;
-  cb[B_W + 2] -= rb2 * r2 * iw2;
-  cb[B_BIAS] += rb0;
+  cb[CW_W] -= rb0 * r0 * iw0;
+  cb[CW_W + 1] -= rb1 * r1 * iw1;
+  cb[CW_W + 2] -= rb2 * r2 * iw2;
+  cb[CW_BIAS] += rb0;
 }
 
 // The same between a free body and a static target with the body in a quad
@@ -466,7 +466,7 @@ __device__ __forceinline__ void row_quad(const QRow& R, float* cb, float* lb, co
   float lb0 = lb[0];
   const float lb1 = lb[1], lb2 = lb[2];
   float L0 = cv[0], L1 = cv[3], L2 = cv[6], G0 = cv[9], G1 = cv[12], G2 = cv[15];
-  const float Wb0 = cb[B_W], Wb1 = cb[B_W + 1], Wb2 = cb[B_W + 2], bb = cb[B_BIAS];
+  const float Wb0 = cb[CW_W], Wb1 = cb[CW_W + 1], Wb2 = cb[CW_W + 2], bb = cb[CW_BIAS];
   const float aN = qcross(r, D0), a1 = qcross(r, D1), a2 = qcross(r, D2);
   const float bN = qsmv(A, aN);
   TapeU T;
@@ -522,10 +522,10 @@ __device__ __forceinline__ void row_quad(const QRow& R, float* cb, float* lb, co
   lb[1] = yb1 - d1b;
   lb[2] = yb2 - d2b;
   // W's adjoint: yb r / W^2
-  cb[B_W] = Wb0 - rb0 * r0 * iw0;
-  cb[B_W + 1] = Wb1 - rb1 * r1 * iw1;
-  cb[B_W + 2] = Wb2 - rb2 * r2 * iw2;
-  cb[B_BIAS] = bb + rb0;
+  cb[CW_W] = Wb0 - rb0 * r0 * iw0;
+  cb[CW_W + 1] = Wb1 - rb1 * r1 * iw1;
+  cb[CW_W + 2] = Wb2 - rb2 * r2 * iw2;
+  cb[CW_BIAS] = bb + rb0;
 }
 
 // add to a value that other lanes (SHARED) may add to in the same instruction
@@ -551,14 +551,14 @@ __device__ __forceinline__ void row_finish(const msa::Eng& E, float* L, int ci, 
   using namespace msa;
   const WS& w = E.w;
   const float* e = L + w.con + ci * CR;
-  const float* cb = L + w.conb + ci * CB;
+  const float* cb = L + w.conb + ci * CW;
   const Ids id = unpack_ids(e[C_ID]);
   const V p{e[C_P], e[C_P + 1], e[C_P + 2]}, n{e[C_N], e[C_N + 1], e[C_N + 2]};
   constexpr bool direct = ROB;
   V db[3], pb{0.f, 0.f, 0.f};
 #pragma unroll
   for (int d = 0; d < 3; ++d) db[d] = V{cb[3 * d], cb[3 * d + 1], cb[3 * d + 2]};
-  if (direct) pb = V{cb[B_P], cb[B_P + 1], cb[B_P + 2]};
+  if (direct) pb = V{cb[CW_P], cb[CW_P + 1], cb[CW_P + 2]};
   auto dirv = [&](int d) -> V {
     const int o = d == 0 ? C_N : (d == 1 ? C_T1 : C_T2);
     return V{e[o], e[o + 1], e[o + 2]};
@@ -569,7 +569,7 @@ __device__ __forceinline__ void row_finish(const msa::Eng& E, float* L, int ci, 
     for (int d = 0; d < 3; ++d) {
       DirC C;
       dir_consts(A, rA, dirv(d), C);
-      const float Wb = cb[B_W + d];
+      const float Wb = cb[CW_W + d];
       // W += D . D / m + ang . I^-1 ang
       V G = C.b * (2.f * Wb);
       if (!direct) G = G + V{cb[9 + 3 * d], cb[10 + 3 * d], cb[11 + 3 * d]};
@@ -591,7 +591,7 @@ __device__ __forceinline__ void row_finish(const msa::Eng& E, float* L, int ci, 
     for (int d = 0; d < 3; ++d) {
       DirC T;
       dir_consts(B, rB, dirv(d), T);
-      const float Wb = cb[B_W + d];
+      const float Wb = cb[CW_W + d];
       const V g = T.b * (2.f * Wb);
       outer_add(B.II, T.ang * Wb, T.ang);
       db[d] = vmadd(db[d], T.D, 2.f * Wb * B.im) + cross(g, rB);
@@ -607,7 +607,7 @@ __device__ __forceinline__ void row_finish(const msa::Eng& E, float* L, int ci, 
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       const V D = dirv(d);
-      const float Jb = cb[B_W + d] * 2.f * dot(D, col) / L[w.xM + id.ti];  // -J's adjoint
+      const float Jb = cb[CW_W + d] * 2.f * dot(D, col) / L[w.xM + id.ti];  // -J's adjoint
       db[d] = vmadd(db[d], col, Jb);
       if (rev) pb = vmadd(pb, cross(D, a), Jb);
     }
@@ -615,7 +615,7 @@ __device__ __forceinline__ void row_finish(const msa::Eng& E, float* L, int ci, 
   // contacts^T: p = c - r n, the basis, and the gap's geometry
   const float r = e[C_R], phi = e[C_PHI];
   const V c = p + n * r;
-  const float phib = cb[B_BIAS] * (phi >= 0.f ? 1.f / E.pr.h : E.pr.beta / E.pr.h);
+  const float phib = cb[CW_BIAS] * (phi >= 0.f ? 1.f / E.pr.h : E.pr.beta / E.pr.h);
   float nbv[3] = {0.f, 0.f, 0.f};
   onb_bar(n, db[1], db[2], nbv);
   const V nb3 = db[0] + V{nbv[0], nbv[1], nbv[2]} - pb * r;
@@ -736,7 +736,7 @@ __device__ __forceinline__ void gs_alone_bar(const msa::Eng& E, float* L, const 
     int it = K - 1;
     const float* e0 = L + w.con + c0 * CR;
     const float* e = e0 + k * CR;
-    float *cb0 = L + w.conb + c0 * CB, *cb = cb0 + k * CB, *lb0 = L + w.lamb + c0 * 3, *lb = lb0 + k * 3;
+    float *cb0 = L + w.conb + c0 * CW, *cb = cb0 + k * CW, *lb0 = L + w.lamb + c0 * 3, *lb = lb0 + k * 3;
     const int wrap = gn - 1;
     QRow R;
     qr_load(e, R);
@@ -745,13 +745,13 @@ __device__ __forceinline__ void gs_alone_bar(const msa::Eng& E, float* L, const 
       float *cr = cb, *lr = lb;
       // the next row: the one before it in this sweep, or the last of the sweep before
       e -= CR;
-      cb -= CB;
+      cb -= CW;
       lb -= 3;
       if (--k < 0) {
         k = wrap;
         --it;
         e = e0 + wrap * CR;
-        cb = cb0 + wrap * CB;
+        cb = cb0 + wrap * CW;
         lb = lb0 + wrap * 3;
       }
       QRow Rn;
@@ -900,8 +900,8 @@ __device__ __forceinline__ void rob_bar(const msa::Eng& E, float* L, int rr, con
   float* acc = L + (hi ? w.rJb : w.rwb) + (rr * 3 + 1 + (odd ? 1 : 0)) * ND + j;
   float* acn = L + (odd ? w.rJb : w.rwb) + rr * 3 * ND + j;
   const float a0 = *acc, an0 = *acn;
-  float* cb = L + w.conb + rr * CB;
-  const float Wb0 = cb[B_W], Wb1 = cb[B_W + 1], Wb2 = cb[B_W + 2], bb = cb[B_BIAS];
+  float* cb = L + w.conb + rr * CW;
+  const float Wb0 = cb[CW_W], Wb1 = cb[CW_W + 1], Wb2 = cb[CW_W + 2], bb = cb[CW_BIAS];
   vr += -(R.w2 * T.d2) - R.w1 * T.d1;
   const float sw = odd ? +R.w2 : +R.w1, sj = odd ? +R.J2 : +R.J1;
   const float xf = hi ? +vr : +vrb;
@@ -1012,10 +1012,10 @@ __device__ __forceinline__ void rob_bar(const msa::Eng& E, float* L, int rr, con
   lb[0] = yb - dlb;
   lb[1] = yb1 - d1b;
   lb[2] = yb2 - d2b;
-  cb[B_W] = Wb0 - rb0 * r0 * R.iw0;
-  cb[B_W + 1] = Wb1 - rb1 * r1 * R.iw1;
-  cb[B_W + 2] = Wb2 - rb2 * r2 * R.iw2;
-  cb[B_BIAS] = bb + rb0;
+  cb[CW_W] = Wb0 - rb0 * r0 * R.iw0;
+  cb[CW_W + 1] = Wb1 - rb1 * r1 * R.iw1;
+  cb[CW_W + 2] = Wb2 - rb2 * r2 * R.iw2;
+  cb[CW_BIAS] = bb + rb0;
 }
 // After the sweeps: the sums of a robot row's moving target (see above) into
 // the contact's direction and point adjoints and the target's position and
@@ -1025,7 +1025,7 @@ __device__ __forceinline__ void rob_target_finish(const msa::Eng& E, float* L) {
   const WS& w = E.w;
   for (int rr = lane_id(); rr < E.nrob; rr += 64) {
     const float* e = L + w.con + rr * CR;
-    float* cb = L + w.conb + rr * CB;
+    float* cb = L + w.conb + rr * CW;
     const Ids id = unpack_ids(e[C_ID]);
     if (id.tk < 2) continue;
     const V p{e[C_P], e[C_P + 1], e[C_P + 2]};
@@ -1065,9 +1065,9 @@ __device__ __forceinline__ void rob_target_finish(const msa::Eng& E, float* L) {
       cb[3 * d + 1] = -db[d].y;
       cb[3 * d + 2] = -db[d].z;
     }
-    cb[B_P] = -pb.x;
-    cb[B_P + 1] = -pb.y;
-    cb[B_P + 2] = -pb.z;
+    cb[CW_P] = -pb.x;
+    cb[CW_P + 1] = -pb.y;
+    cb[CW_P + 2] = -pb.z;
   }
   lds_order();
 }
@@ -1336,9 +1336,9 @@ __device__ __forceinline__ void robot_rows_bar_wave(msa::Eng& E, float* L) {
     const bool act = r0 + g < nr;
     const int r = act ? r0 + g : nr - 1, ci = r / 3, di = r - 3 * ci;
     const float* e = L + w.con + ci * CR;
-    float* cb = L + w.conb + ci * CB;
+    float* cb = L + w.conb + ci * CW;
     const int rb = r * ND + j;
-    const float Wb = cb[B_W + di], wr = L[w.rw + rb], jb = L[w.rJb + rb];
+    const float Wb = cb[CW_W + di], wr = L[w.rw + rb], jb = L[w.rJb + rb];
     const float xr = L[w.rwb + rb] + Wb * L[w.rJ + rb];
     const V p{e[C_P], e[C_P + 1], e[C_P + 2]}, d = E.dir(w.con + (long)ci * CR, di);
     int an = __shfl(anc0, ci & 63, 64);
@@ -1354,12 +1354,12 @@ __device__ __forceinline__ void robot_rows_bar_wave(msa::Eng& E, float* L) {
     const V db{sum16(c.x * Jb), sum16(c.y * Jb), sum16(c.z * Jb)};
     const V pb = cross(d, V{sum16(ar.x * Jb), sum16(ar.y * Jb), sum16(ar.z * Jb)});
     if (act && j == 0) {
-      cb[B_D + 3 * di] += db.x;
-      cb[B_D + 3 * di + 1] += db.y;
-      cb[B_D + 3 * di + 2] += db.z;
-      unsafeAtomicAdd(cb + B_P, pb.x);
-      unsafeAtomicAdd(cb + B_P + 1, pb.y);
-      unsafeAtomicAdd(cb + B_P + 2, pb.z);
+      cb[CW_D + 3 * di] += db.x;
+      cb[CW_D + 3 * di + 1] += db.y;
+      cb[CW_D + 3 * di + 2] += db.z;
+      unsafeAtomicAdd(cb + CW_P, pb.x);
+      unsafeAtomicAdd(cb + CW_P + 1, pb.y);
+      unsafeAtomicAdd(cb + CW_P + 2, pb.z);
     }
   }
   lds_order();
@@ -2031,7 +2031,7 @@ __device__ __forceinline__ void integrate_free(const msa::Eng& E, float* L) {
   zero_lds(L, w.limb, 2 * AMAX);
   zero_lds(L, w.llamb, 2 * AMAX);
   zero_lds(L, w.lamb, 3 * E.nc);
-  zero_lds(L, w.conb, E.nc * msa::CB);
+  zero_lds(L, w.conb, E.nc * msa::CW);
   zero_lds(L, w.fb, fm * msa::FB);
   zero_lds(L, w.xb, AMAX * msa::XB);
   lds_order();
@@ -2148,13 +2148,13 @@ __device__ __forceinline__ void gs_linked_bar(msa::Eng& E, float* L, Sched sc, c
         qb_load(w, L, f, A);
         int r = r0 + gn - 1;
         const float* e = L + w.con + (r - NL) * CR;
-        float *cb = L + w.conb + (r - NL) * CB, *lb = L + w.lamb + (r - NL) * 3;
+        float *cb = L + w.conb + (r - NL) * CW, *lb = L + w.lamb + (r - NL) * 3;
         QRow R;
         float y[3], q[3];
         qr_load(e, R);
         row(r, y, q);
 #pragma unroll 1
-        for (;; cb -= CB, lb -= 3) {
+        for (;; cb -= CW, lb -= 3) {
           r = r > r0 ? r - 1 : r0 - 1;
           e -= r >= r0 ? CR : 0;
           QRow Rn;

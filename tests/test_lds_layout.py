@@ -96,6 +96,18 @@ def test_blocks_over_the_range():
         tried += 1
 
 
+@pytest.mark.parametrize("cfg,tape", [(1, 6879744), (2, 8242176), (3, 16018944), (5, 8605696)])
+def test_tape_holds_no_more_than_the_lane_adjoint_needs(cfg, tape):
+    """The tape buffer of 70 scenes, a lane of the reference adjoint each (in
+    wavefronts of 64): its contact adjoint record takes 16 floats."""
+    b = sg.make(cfg, 70)
+    d = ms.make_desc(b)
+    sd, keep = ms.make_scene_desc(b)
+    sz = ms.Sizes()
+    assert ms.lib().ms_query_sizes(C.byref(d), C.byref(sd), C.byref(sz)) == 0
+    assert sz.tape <= tape
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("boxes,staged", [(600, True), (4000, True), (9000, False), (22000, False)])
 @pytest.mark.parametrize("force", [False, True])
