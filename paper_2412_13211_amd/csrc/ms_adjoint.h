@@ -191,6 +191,7 @@ MSA_HD inline int lv_ints(int ccap) { return 2 * lv_rows(ccap) + 1 + 128; }
 
 struct WS {
   int wave;  // the wavefront kernel's LDS layout
+  int tight;  // its form for blocks near the limit
   int fmax, ntmax, ccap, rcap, K, nsub, ss;
   int st, gA, gB, ub, tape;
   int kR, kp, ka, ko, kc, kIcw, ks, kI, kIc, sph, tl;
@@ -212,10 +213,13 @@ struct WS {
 };
 
 // wave = true: the layout of the wavefront kernel's LDS block (one state
-// record, the tape and candidate lists elsewhere, plus the level schedule)
-MSA_HD inline WS ws_layout(int fmax, int ntmax, int ccap, int rcap, int K, int nsub, bool wave = false) {
+// record, the tape and candidate lists elsewhere, plus the level schedule).
+// tight: no sweeps of the tape staged in it, and the composite inertias, which
+// dynamics^T then forms again, in the space of the robot rows' rH.
+MSA_HD inline WS ws_layout_form(int fmax, int ntmax, int ccap, int rcap, int K, int nsub, bool wave, bool tight) {
   WS w;
   w.wave = wave ? 1 : 0;
+  w.tight = tight ? 1 : 0;
   w.fmax = fmax < 1 ? 1 : fmax;
   w.ntmax = ntmax < 1 ? 1 : ntmax;
   w.ccap = ccap;
@@ -239,11 +243,13 @@ MSA_HD inline WS ws_layout(int fmax, int ntmax, int ccap, int rcap, int K, int n
   if (wave) {
     w.tau = take(ND);
     w.arm = take(ND);
+    if (tight) w.kIc = take(ND * 36);
     w.rH = w.kR;
     if (w.rcap * 9 > o - w.kR) o = (w.kR + w.rcap * 9 + 3) & ~3;
   }
   w.ka = take(ND * 3); w.ko = take(ND * 3); w.kc = take(ND * 3);
-  w.kIcw = take(ND * 6); w.ks = take(ND * 6); w.kI = take(ND * 36); w.kIc = take(ND * 36);
+  w.kIcw = take(ND * 6); w.ks = take(ND * 6); w.kI = take(ND * 36);
+  if (!tight) w.kIc = take(ND * 36);
   w.sph = take(wave ? 0 : SPH * 3);  // sphere centres: only the lane kernel's contact search reads them
   w.tl = take(wave ? 0 : (ND + 1) * (w.ntmax + 1));
   w.fR = take(fm * 9); w.fIw = take(fm * 9); w.fIi = take(fm * 9); w.fim = take(fm);
@@ -273,7 +279,7 @@ MSA_HD inline WS ws_layout(int fmax, int ntmax, int ccap, int rcap, int K, int n
   // of Icbar.
   w.trs = 3 * (2 * AMAX + ccap);
   const int rows_b = 2 * w.rcap * 3 * ND;
-  const int live_b = rows_b + (wave ? 2 * w.trs : 0);
+  const int live_b = rows_b + (wave && !tight ? 2 * w.trs : 0);
   const int dyn_b = ND * 6 + (wave ? 1 : 2) * ND * 36 + 8 * ND * 6;
   align();
   const int kb = take(live_b > dyn_b ? live_b : dyn_b);
@@ -292,6 +298,11 @@ MSA_HD inline WS ws_layout(int fmax, int ntmax, int ccap, int rcap, int K, int n
   w.lz = take(wave ? ND : 0);
   w.total = o;
   return w;
+}
+MSA_HD inline WS ws_layout(int fmax, int ntmax, int ccap, int rcap, int K, int nsub, bool wave = false) {
+  const WS w = ws_layout_form(fmax, ntmax, ccap, rcap, K, nsub, wave, false);
+  if (!wave || w.total * 4 <= 163840) return w;
+  return ws_layout_form(fmax, ntmax, ccap, rcap, K, nsub, wave, true);
 }
 
 // ------------------------------------------------------------ small kernels of the step

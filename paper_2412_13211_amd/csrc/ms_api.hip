@@ -339,7 +339,7 @@ msa::WS bwd_ws_wave(const ms_batch_desc* d, const Counts& c, int cc = -1, int rc
 // within the CU's 160 KiB, which stays below every measured threshold.
 int bwd_per_cu(size_t lds) {
   int n = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, step_bwd_wave_ptr(), BWD_THREADS, lds) != hipSuccess) n = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, step_bwd_wave_ptr(false), BWD_THREADS, lds) != hipSuccess) n = 0;
   const int by_size = (int)(size_t{163840} / (lds + 1024));
   return std::min(n, by_size);
 }
@@ -493,7 +493,8 @@ ms_status ms_create_batch(const ms_batch_desc* d, const ms_scene_desc* sc, void*
   (void)hipFuncSetAttribute(step_rec_kernel_ptr(), hipFuncAttributeMaxDynamicSharedMemorySize, (int)b->max_lds);
   (void)hipFuncSetAttribute(step_frc_kernel_ptr(), hipFuncAttributeMaxDynamicSharedMemorySize, (int)b->max_lds);
   (void)hipFuncSetAttribute(spawn_check_kernel_ptr(), hipFuncAttributeMaxDynamicSharedMemorySize, (int)b->max_lds);
-  (void)hipFuncSetAttribute(step_bwd_wave_ptr(), hipFuncAttributeMaxDynamicSharedMemorySize, (int)b->max_lds);
+  for (bool tight : {false, true})
+    (void)hipFuncSetAttribute(step_bwd_wave_ptr(tight), hipFuncAttributeMaxDynamicSharedMemorySize, (int)b->max_lds);
   choose_bwd_split(b, b->split_c, b->split_r);
   // status starts at zero; the first step's scene times (which order the
   // step) decrease along the static order

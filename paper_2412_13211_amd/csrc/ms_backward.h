@@ -57,7 +57,7 @@ void launch_delay(long long ticks, hipStream_t st);
 // slot: [S] ints of scratch
 void launch_bwd_order(const float* rec, const RecLayout& RL, int S, int nsub, int fit_c, int fit_r, int* slot,
                       int* order, int* n_over, hipStream_t st);
-const void* step_bwd_wave_ptr();
+const void* step_bwd_wave_ptr(bool tight);
 
 // status bit set when the record and the recomputed joint-limit rows disagree
 constexpr uint32_t MS_ST_RECORD = 16u;

@@ -1190,6 +1190,35 @@ __device__ __forceinline__ Tree tree_of(const msa::Eng& E) {
     T.dm |= (((uint32_t)__builtin_amdgcn_readlane((int)T.am, k) >> T.i) & 1u) << k;
   return T;
 }
+// Composite inertia of body i (the sum over the descendants), rows 2 gc and
+// 2 gc + 1
+__device__ __forceinline__ void composite_rows(const float* L, const msa::WS& w, const Tree& T, int nb, float* Ic) {
+#pragma unroll
+  for (int t = 0; t < 12; ++t) Ic[t] = 0.f;
+  for (int k0 = (nb - 1) & ~3; k0 >= 0; k0 -= 4) {
+#pragma unroll
+    for (int u = 3; u >= 0; --u) {
+      const int k = k0 + u;
+      const float4* q = reinterpret_cast<const float4*>(L + w.kI + k * 36 + 12 * T.gc);
+      const bool dn = (T.dm >> k) & 1u;
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        const float4 x = q[t];
+        Ic[4 * t] += dn ? x.x : 0.f;
+        Ic[4 * t + 1] += dn ? x.y : 0.f;
+        Ic[4 * t + 2] += dn ? x.z : 0.f;
+        Ic[4 * t + 3] += dn ? x.w : 0.f;
+      }
+    }
+  }
+}
+__device__ __forceinline__ void composite_store(float* L, const msa::WS& w, const Tree& T, int nb, const float* Ic) {
+  if (T.g < 3 && T.i < nb) {
+    float4* q = reinterpret_cast<float4*>(L + w.kIc + T.i * 36 + 12 * T.gc);
+#pragma unroll
+    for (int t = 0; t < 3; ++t) q[t] = make_float4(Ic[4 * t], Ic[4 * t + 1], Ic[4 * t + 2], Ic[4 * t + 3]);
+  }
+}
 // Two components of the sum of the 6-vectors at off over the ancestors, root
 // first (added to r), or over the descendants, last first: along a chain the
 // order of the recursions, whose sums' rounding an ill-conditioned M~ amplifies.
@@ -1394,6 +1423,7 @@ __device__ __forceinline__ void robot_rows_bar_wave(msa::Eng& E, float* L) {
 // (lane per DoF), body poses by pointer jumping (lane per body, four doubling
 // rounds), per-body quantities (lane per body); CRBA and RNEA as sums over
 // the tree; M~^-1.  The bias torques are left in w.lz.
+template <bool TIGHT>
 __device__ __forceinline__ void recompute_wave(msa::Eng& E, float* L, const float* u) {
   using namespace msa;
   const int lane = lane_id();
@@ -1472,23 +1502,8 @@ __device__ __forceinline__ void recompute_wave(msa::Eng& E, float* L, const floa
   const Tree T = tree_of(E);
   // composite inertias (sum over the descendants) and velocities (over the
   // ancestors, v_i = sum of s_k qd_k)
-  float Ic[12] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  for (int k0 = (nb - 1) & ~3; k0 >= 0; k0 -= 4) {
-#pragma unroll
-    for (int u = 3; u >= 0; --u) {
-      const int k = k0 + u;
-      const float4* q = reinterpret_cast<const float4*>(L + w.kI + k * 36 + 12 * T.gc);
-      const bool dn = (T.dm >> k) & 1u;
-#pragma unroll
-      for (int t = 0; t < 3; ++t) {
-        const float4 x = q[t];
-        Ic[4 * t] += dn ? x.x : 0.f;
-        Ic[4 * t + 1] += dn ? x.y : 0.f;
-        Ic[4 * t + 2] += dn ? x.z : 0.f;
-        Ic[4 * t + 3] += dn ? x.w : 0.f;
-      }
-    }
-  }
+  float Ic[12];
+  composite_rows(L, w, T, nb, Ic);
   float2 v2 = make_float2(0.f, 0.f);
   for (int k0 = 0; k0 < nb; k0 += 4) {
 #pragma unroll
@@ -1506,11 +1521,7 @@ __device__ __forceinline__ void recompute_wave(msa::Eng& E, float* L, const floa
   float si[6];
 #pragma unroll
   for (int t = 0; t < 6; ++t) si[t] = L[w.ks + T.i * 6 + t];
-  if (T.g < 3 && T.i < nb) {
-    float4* q = reinterpret_cast<float4*>(L + w.kIc + T.i * 36 + 12 * T.gc);
-#pragma unroll
-    for (int t = 0; t < 3; ++t) q[t] = make_float4(Ic[4 * t], Ic[4 * t + 1], Ic[4 * t + 2], Ic[4 * t + 3]);
-  }
+  if (!TIGHT) composite_store(L, w, T, nb, Ic);
   // F_i = Ic_i s_i; the terms v_i x (s_i qd_i) of the accelerations
   st2(L, w.tF, T, nb, rows_dot(Ic, si));
   lds_order();
@@ -1610,6 +1621,7 @@ __device__ __forceinline__ void solve_z_wave(const msa::Eng& E, float* L) {
 
 // dynamics^T over the lanes (the same adjoint as the engine's dynamics_bar,
 // with its recursions written as ancestor / descendant sums)
+template <bool TIGHT>
 __device__ __forceinline__ void dynamics_bar_wave(msa::Eng& E, float* L) {
   using namespace msa;
   const int lane = lane_id();
@@ -1656,7 +1668,12 @@ __device__ __forceinline__ void dynamics_bar_wave(msa::Eng& E, float* L) {
   for (int t = 0; t < 6; ++t) si[t] = L[w.ks + T.i * 6 + t];
   {
     float Ic[12];
-    ld_rows(L, w.kIc, T, Ic);
+    if (TIGHT) {
+      composite_rows(L, w, T, nb, Ic);
+      composite_store(L, w, T, nb, Ic);
+    } else {
+      ld_rows(L, w.kIc, T, Ic);
+    }
     st2(L, w.tF, T, nb, rows_dot(Ic, si));
     float2 Fb = make_float2(0.f, 0.f), fb = make_float2(0.f, 0.f);
     for (int k0 = (nb - 1) & ~3; k0 >= 0; k0 -= 4) {
@@ -2042,7 +2059,9 @@ __device__ __forceinline__ void integrate_free(const msa::Eng& E, float* L) {
 
 // The reverse sweeps of everything that is not alone: per sweep the levels
 // last to first (one lane per group), the robot's rows last to first, the
-// joint-limit rows; the tape two sweeps at a time in an LDS ring.
+// joint-limit rows; the tape two sweeps at a time in an LDS ring (TIGHT: straight
+// from the record).
+template <bool TIGHT>
 __device__ __forceinline__ void gs_linked_bar(msa::Eng& E, float* L, Sched sc, const float* tape_g, int tsw) {
   using namespace msa;
   const int lane = lane_id();
@@ -2050,9 +2069,9 @@ __device__ __forceinline__ void gs_linked_bar(msa::Eng& E, float* L, Sched sc, c
   const Lv LV = lv_view(L, w);
   const int K = E.pr.K, NR = E.nrob, NL = E.nlim;
   if (sc.maxl == 0 && NR == 0 && NL == 0) return;
-  E.tb = Buf{L + w.tring, 1};
-  E.tsw = w.trs;
-  E.tmask = 1;
+  E.tb = Buf{TIGHT ? const_cast<float*>(tape_g) : L + w.tring, 1};
+  E.tsw = TIGHT ? tsw : w.trs;
+  E.tmask = TIGHT ? -1 : 1;
   const int R3 = 3 * (NL + E.nc);
   // the tape of this substep's sweeps (sweep it in slot it & 1); the reverse
   // sweep it reads sweeps it and it - 1
@@ -2083,9 +2102,11 @@ __device__ __forceinline__ void gs_linked_bar(msa::Eng& E, float* L, Sched sc, c
     const float* src = tape_g + (size_t)it * tsw;
     for (int i = lane + 64 * TPF; i < R3; i += 64) dst[i] = src[i];
   };
-  if (K > 0) stage(K - 1);
-  if (K > 1) stage(K - 2);
-  if (K > 2) fetch(K - 3);
+  if (!TIGHT) {
+    if (K > 0) stage(K - 1);
+    if (K > 1) stage(K - 2);
+    if (K > 2) fetch(K - 3);
+  }
   // Groups against static targets by quads, the others by lanes.  The former in a
   // row when they are at most 64 (quad k of chunk h: the (16 h + k)-th), their
   // levels in the quad's registers; else looked up among all groups.  The level
@@ -2120,13 +2141,13 @@ __device__ __forceinline__ void gs_linked_bar(msa::Eng& E, float* L, Sched sc, c
   const float mu = E.pr.mu;
 #pragma unroll 1
   for (int it = K - 1; it >= 0; --it) {
-    if (it >= 1 && it <= K - 2) {
+    if (!TIGHT && it >= 1 && it <= K - 2) {
       put(it - 1);
       if (it >= 2) fetch(it - 2);
     }
     lds_order();
-    const float* ty = L + w.tring + (it & 1) * w.trs;
-    const float* tq = it > 0 ? L + w.tring + ((it - 1) & 1) * w.trs : nullptr;
+    const float* ty = TIGHT ? tape_g + (size_t)it * tsw : L + w.tring + (it & 1) * w.trs;
+    const float* tq = it == 0 ? nullptr : (TIGHT ? ty - tsw : L + w.tring + ((it - 1) & 1) * w.trs);
     auto row = [&](int r, float* y, float* q) {
 #pragma unroll
       for (int t = 0; t < 3; ++t) {
@@ -2288,6 +2309,7 @@ __device__ __forceinline__ void finish_linked(msa::Eng& E, float* L, Sched sc) {
 // holds only three scenes on a CU.  Forward and reverse of a control step of
 // 4096 uneven scenes: 4380 -> 3585 us, of 16 scenes over four steps: 1866 ->
 // 1633 us.)
+template <bool TIGHT>
 __device__ void bwd_scene(int s, int wv, float* const L0) {
   using namespace msa;
   const BwdArgs& a = args_fresh();
@@ -2394,7 +2416,7 @@ __device__ void bwd_scene(int s, int wv, float* const L0) {
       {
         Eng E;
         eng_fresh(E, s, L0, nc, nrob, nlim);
-        recompute_wave(E, E.b.p, args_fresh().u + 16 * (size_t)s);
+        recompute_wave<TIGHT>(E, E.b.p, args_fresh().u + 16 * (size_t)s);
         status |= E.status;
       }
       phase(1);
@@ -2420,7 +2442,7 @@ __device__ void bwd_scene(int s, int wv, float* const L0) {
       {
         Eng E;
         eng_fresh(E, s, L0, nc, nrob, nlim);
-        gs_linked_bar(E, E.b.p, sc, tape_g, RL.tsw);
+        gs_linked_bar<TIGHT>(E, E.b.p, sc, tape_g, RL.tsw);
       }
       phase(4);
       {
@@ -2440,7 +2462,7 @@ __device__ void bwd_scene(int s, int wv, float* const L0) {
       {
         Eng E;
         eng_fresh(E, s, L0, nc, nrob, nlim);
-        dynamics_bar_wave(E, E.b.p);
+        dynamics_bar_wave<TIGHT>(E, E.b.p);
       }
       phase(6);
       // kinematics^T per joint
@@ -2535,16 +2557,17 @@ __device__ __forceinline__ int wave_scan(int v) {
 
 // the LDS layout must hold the scene's lists (else the scene is flagged and
 // left out)
+template <bool TIGHT>
 __device__ void bwd_checked(const BwdArgs& a, int s, int wv, float* lds) {
   if (!rec_fits(a.rec, a.RL, a.pr.nsub, s, a.w.ccap, a.w.rcap)) {
     if (threadIdx.x == 0) a.status[s] |= MS_ST_RECORD;
     return;
   }
-  bwd_scene(s, wv, lds);
+  bwd_scene<TIGHT>(s, wv, lds);
 }
 
-__global__ __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_step_bwd_wave(BwdArgs a) {
-  extern __shared__ float lds[];
+template <bool TIGHT>
+__device__ __forceinline__ void bwd_body(const BwdArgs& a, float* lds) {
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   // mode 2 loops over the first *n_over positions; modes 0 and 1 take one
   // position each (one call site keeps the scene's code inlined)
@@ -2552,9 +2575,18 @@ __global__ __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
   const int end = loop ? *a.n_over : a.S;
   const int step = loop ? (int)gridDim.x : a.S;
   for (int pos = (a.fit_mode == 1 ? *a.n_over : 0) + (int)blockIdx.x; pos < end; pos += step) {
-    bwd_checked(a, __builtin_amdgcn_readfirstlane(a.order[pos]), wv, lds);
+    bwd_checked<TIGHT>(a, __builtin_amdgcn_readfirstlane(a.order[pos]), wv, lds);
     both_sync();
   }
+}
+__global__ __launch_bounds__(BWD_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_step_bwd_wave(BwdArgs a) {
+  extern __shared__ float lds[];
+  bwd_body<false>(a, lds);
+}
+// LDS blocks near the limit (one workgroup per CU); results are bit for bit the same
+__global__ __launch_bounds__(BWD_THREADS) void k_step_bwd_wave_tight(BwdArgs a) {
+  extern __shared__ float lds[];
+  bwd_body<true>(a, lds);
 }
 
 // sort slot of each scene: group * NKEY + (NKEY - 1 - key), the cost key
@@ -2621,8 +2653,11 @@ void launch_bwd_order(const float* rec, const RecLayout& RL, int S, int nsub, in
 }
 
 void launch_step_bwd_wave(const BwdArgs& a, size_t lds_bytes, int grid, hipStream_t st) {
-  hipLaunchKernelGGL(k_step_bwd_wave, dim3(grid), dim3(BWD_THREADS), lds_bytes, st, a);
+  hipLaunchKernelGGL(a.w.tight ? k_step_bwd_wave_tight : k_step_bwd_wave, dim3(grid), dim3(BWD_THREADS), lds_bytes, st,
+                     a);
 }
-const void* step_bwd_wave_ptr() { return reinterpret_cast<const void*>(&k_step_bwd_wave); }
+const void* step_bwd_wave_ptr(bool tight) {
+  return tight ? reinterpret_cast<const void*>(&k_step_bwd_wave_tight) : reinterpret_cast<const void*>(&k_step_bwd_wave);
+}
 
 }  // namespace msk

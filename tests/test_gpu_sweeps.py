@@ -255,3 +255,44 @@ def test_force_outputs_at_the_largest_cap():
     for step in zip(*got):
         for a, c in zip(*step):
             assert np.array_equal(a.view(np.uint32), c.view(np.uint32))
+
+
+def _moving(depth, n=6):
+    """_crowded with moving robots, objects, doors and drawers."""
+    b = _crowded(depth, n)
+    st = sg.split_state(b.state0, n, b.n_free, b.n_aux)
+    rng = np.random.default_rng(4)
+    st["qd"][:, :15] = rng.normal(0.0, 0.1, st["qd"][:, :15].shape)
+    st["free"][:, 2] -= rng.uniform(0.0, 2e-4, b.n_free)
+    st["free"][:, 8:11] = rng.normal(0.0, 0.02, (b.n_free, 3))
+    st["free"][:, 12:15] = rng.normal(0.0, 0.05, (b.n_free, 3))
+    st["aux"][:, 0] += rng.uniform(1e-4, 1e-3, b.n_aux)
+    b.state0[:] = sg.join_state(st["q"], st["qd"], st["free"], st["aux"])
+    return b
+
+
+@pytest.mark.parametrize("depth,ccap,rcap", [(0.1, 658, 24), (0.1, 627, 32), (0.1, 376, 96), (0.1, 153, 153),
+                                             (0.25, 282, 120)])
+def test_reverse_from_a_record_without_a_tape_buffer(depth, ccap, rcap):
+    """The largest contact caps whose adjoint block held one wavefront's arrays: a
+    kept record is reversed without a tape buffer, bit for bit as with small
+    caps."""
+    ms = _ms()
+    b = _moving(depth)
+    x, u = torch.as_tensor(b.state0).cuda(), torch.as_tensor(b.controls(0)).cuda()
+    g = torch.as_tensor(np.random.default_rng(3).normal(size=b.state0.size).astype(np.float32)).cuda()
+    got = []
+    for cc, rc in ((120, 80), (ccap, rcap)):
+        mb = ms.MsBatch(b, contact_cap=cc, robot_contact_cap=rc)
+        mb.enable_debug(True)
+        mb.step(x, u)
+        robot = mb.debug_contacts()[..., 1].max()
+        assert (robot > 64) == (depth == 0.25) and robot >= 20
+        rec = mb.new_record()
+        y = mb.step_record(x, u, rec)
+        gx, gu = mb.step_backward_recorded(x, u, rec, g)
+        torch.cuda.synchronize()
+        assert not np.any(mb.status() & (ms.MS_ST_OVERFLOW | ms.MS_ST_ROBOT_OVERFLOW | ms.MS_ST_NONFINITE))
+        got.append([t.cpu().numpy() for t in (y, gx, gu)])
+    for a, c in zip(*got):
+        assert np.array_equal(a.view(np.uint32), c.view(np.uint32))
