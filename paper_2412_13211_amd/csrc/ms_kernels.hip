@@ -948,22 +948,30 @@ __device__ __forceinline__ bool rigid(const float* R) {
   return within(mk3(dot(a, a) - 1.f, dot(b, b) - 1.f, dot(c, c) - 1.f), 2e-5f) &&
          within(mk3(dot(a, b), dot(a, c), dot(b, c)), 2e-5f);
 }
-__device__ __forceinline__ bool bound_holds(const ConCtx& X, int t) {
-  const float* F = X.F;
-  const float* A = X.A;
-  if (t < X.np) {
-    const f3 n = mk3(X.Pl[t * 4], X.Pl[t * 4 + 1], X.Pl[t * 4 + 2]);
-    return fabsf(dot(n, n) - 1.f) < 2e-5f && fabsf(X.Pl[t * 4 + 3]) < BOUND_FAR;
+// planes, doors / drawers and free bodies, one of each per lane
+__device__ __forceinline__ bool bounds_hold(const ConCtx& X) {
+  const int i = lane_id();
+  bool ok = true;
+  if (i < X.np) {
+    const f3 n = mk3(X.Pl[i * 4], X.Pl[i * 4 + 1], X.Pl[i * 4 + 2]);
+    ok = fabsf(dot(n, n) - 1.f) < 2e-5f && fabsf(X.Pl[i * 4 + 3]) < BOUND_FAR;
   }
-  const bool aux = t < X.np + X.ns + X.na;
-  const int i = aux ? t - X.np - X.ns : t - X.np - X.ns - X.na;
-  float R[9];
-  for (int k = 0; k < 9; ++k) R[k] = aux ? A[(A_R + k) * AMAX + i] : F[i * FSTR + F_R + k];
-  if (aux)
-    return rigid(R) && within(mk3(A[(A_BC + 0) * AMAX + i], A[(A_BC + 1) * AMAX + i], A[(A_BC + 2) * AMAX + i]), BOUND_FAR) &&
-           extents(mk3(A[(A_BH + 0) * AMAX + i], A[(A_BH + 1) * AMAX + i], A[(A_BH + 2) * AMAX + i]), BOUND_LEVER);
-  return (F[i * FSTR + F_TYPE] != 0.f || rigid(R)) && within(mk3(F[i * FSTR + F_X], F[i * FSTR + F_X + 1], F[i * FSTR + F_X + 2]), BOUND_FAR) &&
-         extents(mk3(F[i * FSTR + F_H], F[i * FSTR + F_H + 1], F[i * FSTR + F_H + 2]), BOUND_LEVER);
+  if (i < X.na) {
+    const float* A = X.A;
+    float R[9];
+    for (int k = 0; k < 9; ++k) R[k] = A[(A_R + k) * AMAX + i];
+    ok = ok && rigid(R) &&
+         within(mk3(A[(A_BC + 0) * AMAX + i], A[(A_BC + 1) * AMAX + i], A[(A_BC + 2) * AMAX + i]), BOUND_FAR) &&
+         extents(mk3(A[(A_BH + 0) * AMAX + i], A[(A_BH + 1) * AMAX + i], A[(A_BH + 2) * AMAX + i]), BOUND_LEVER);
+  }
+  if (i < X.nf) {
+    // (R of a quaternion q differs from a rotation by |q|^2 - 1)
+    const float* f = X.F + i * FSTR;
+    const float nq = f[F_Q] * f[F_Q] + f[F_Q + 1] * f[F_Q + 1] + f[F_Q + 2] * f[F_Q + 2] + f[F_Q + 3] * f[F_Q + 3];
+    ok = ok && (f[F_TYPE] != 0.f || fabsf(nq - 1.f) < 5e-6f) && within(mk3(f[F_X], f[F_X + 1], f[F_X + 2]), BOUND_FAR) &&
+         extents(mk3(f[F_H], f[F_H + 1], f[F_H + 2]), BOUND_LEVER);
+  }
+  return ok;
 }
 
 // position of the k-th (from 0) set bit of m (k < popcount(m))
@@ -1082,7 +1090,7 @@ __device__ __forceinline__ void con_ctx(const KArgs& a, const Scene& S, float* L
 // The robot's part: the targets near the robot into listA, per robot body the
 // mask of those near its bounding sphere.  Returns the number of 64-target
 // chunks of listA; CHECK: -1 when the scene holds a body or target whose bound
-// does not cover what the pair test may accept (bound_holds).
+// does not cover what the pair test may accept (bounds_hold).
 template <bool CHECK = false>
 __device__ __forceinline__ int cull_robot(const KArgs& a, const Scene& S, float* L, float margin) {
   const int lane = lane_id();
@@ -1098,13 +1106,14 @@ __device__ __forceinline__ int cull_robot(const KArgs& a, const Scene& S, float*
   // axis-aligned box around them (the bodies are in the first 16 lanes)
   f3 sc = mk3(0.f, 0.f, 0.f), lo = mk3(1e30f, 1e30f, 1e30f), hi = mk3(-1e30f, -1e30f, -1e30f);
   float sr = -1.f;
-  bool held = true;
+  bool held = !CHECK || bounds_hold(X);
+  float far = 0.f, least = 0.f;  // of the furniture: largest coordinate and half extent, least half extent
   if (lane < S.nb) {
     const float4 bs = M->bsph[lane];
     sc = mv(rb.R + lane * 9, mk3(bs.x, bs.y, bs.z)) + body_p(rb, lane);
     if (M->sph_count[lane] > 0) {
       if (CHECK)
-        held = rigid(rb.R + lane * 9) && within(body_p(rb, lane), BOUND_FAR) &&
+        held = held && rigid(rb.R + lane * 9) && within(body_p(rb, lane), BOUND_FAR) &&
                within(mk3(bs.x, bs.y, bs.z), BOUND_LEVER) && bs.w < BOUND_LEVER;
       sr = bs.w;
       lo = mk3(sc.x - bs.w, sc.y - bs.w, sc.z - bs.w);
@@ -1128,6 +1137,14 @@ __device__ __forceinline__ int cull_robot(const KArgs& a, const Scene& S, float*
 #pragma unroll
         for (int e = 0; e < 6; ++e) bx[u][e] = X.St[si * 6 + e];
       }
+      if (CHECK) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          far = fmaxf(far, fmaxf(fmaxf(fabsf(bx[u][0]), fabsf(bx[u][1])), fabsf(bx[u][2])));
+          far = fmaxf(far, fmaxf(fmaxf(bx[u][3], bx[u][4]), bx[u][5]));
+          least = fminf(least, fminf(fminf(bx[u][3], bx[u][4]), bx[u][5]));
+        }
+      }
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -1135,10 +1152,6 @@ __device__ __forceinline__ int cull_robot(const KArgs& a, const Scene& S, float*
       bool m = false;
       if (t < NT) {
         const bool furniture = t >= S.np && t < S.np + S.ns;
-        if (CHECK)
-          held = held && (furniture ? within(mk3(bx[u][0], bx[u][1], bx[u][2]), BOUND_FAR) &&
-                                          extents(mk3(bx[u][3], bx[u][4], bx[u][5]), BOUND_FAR)
-                                    : bound_holds(X, t));
         if (furniture)
           m = fabsf(bc.x - bx[u][0]) < he.x + bx[u][3] + slack && fabsf(bc.y - bx[u][1]) < he.y + bx[u][4] + slack &&
               fabsf(bc.z - bx[u][2]) < he.z + bx[u][5] + slack;
@@ -1150,7 +1163,7 @@ __device__ __forceinline__ int cull_robot(const KArgs& a, const Scene& S, float*
       nra += __popcll(mk);
     }
   }
-  if (CHECK && __ballot(!held)) return -1;
+  if (CHECK && __ballot(!held || !(far < BOUND_FAR && least >= 0.f))) return -1;
   // the robot bodies' bounding spheres against the robot's candidates,
   // transposed as for the free bodies below: lanes over a chunk of the
   // candidates, a loop over the bodies (their spheres by readlane), one ballot
@@ -3064,7 +3077,7 @@ __global__ void k_reset_queue(int* q) {
 // zero margin, one wavefront per scene.  Every (robot sphere, target) pair is
 // tested, 4 to 11 thousand in a furnished room where the culling leaves a few
 // hundred, without culling and in a scene whose bounds do not cover what the
-// pair test may accept (bound_holds): the state is the caller's, its
+// pair test may accept (bounds_hold): the state is the caller's, its
 // quaternions and distances are anything.
 __global__ __launch_bounds__(WAVE) void k_spawn_check(KArgs a, uint8_t* collide) {
   extern __shared__ float lds[];
