@@ -106,10 +106,11 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z) {
 }
 // the lane index, opaque to the optimizer: address arithmetic on it stays
 // in the phase that asks for it instead of being hoisted out of the scene
-// and substep loops into registers that live (or spill) across the whole step
+// and substep loops into registers that live (or spill) across the whole step.
+// Counted anew each time, so that not even the thread's index stays in one.
 __device__ __forceinline__ int lane_id() {
-  int l = threadIdx.x & (WAVE - 1);
-  asm volatile("" : "+v"(l));
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
   return l;
 }
 // the same for the kernel's arguments and the LDS block: a phase reads what it
@@ -2042,6 +2043,11 @@ __device__ __forceinline__ bool rows_robot(const KArgs& a, const Scene& S, float
 // previous group on each of its nodes, and the levels are the longest-path
 // depths of that DAG, relaxed over the lanes until no level changes (as many
 // rounds as the deepest chain).
+//   - More groups than lanes are then sorted by level (the groups in order and
+//     the levels' ends take the place of the previous groups), so that a sweep
+//     goes through them once, 64 at a time.  (With 56 touching boxes, 480
+//     contacts, looking for each level's groups among all of them was half of a
+//     sweep.)
 __device__ __forceinline__ void row_nodes(int inf, int& na, int& nbn) {
   na = node_of(inf & 0xffff);
   nbn = node_of((inf >> 16) & 0xffff);
@@ -2167,8 +2173,39 @@ __device__ __forceinline__ Levels phase_levels(const KArgs& a, float* L, int NC,
     lds_order();
   }
   for (int off = 32; off > 0; off >>= 1) maxl = max(maxl, __shfl_xor(maxl, off, WAVE));
+  maxl = uniform(maxl);
   lds_order();
-  return Levels{uniform(NG), uniform(maxl), uniform64(linked)};
+  if (NG > WAVE) {
+    // counting sort; the counters are the halves of 32-bit words (at most
+    // 4096 groups, so none carries into the other)
+    uint32_t* cnt = reinterpret_cast<uint32_t*>(pvA);
+    for (int e = lane; e < (maxl + 2) / 2; e += WAVE) cnt[e] = 0u;
+    lds_order();
+    for (int g = lane; g < NG; g += WAVE) {
+      const int lv = lvl[g];
+      if (lv > 0) atomicAdd(cnt + (lv >> 1), 1u << (16 * (lv & 1)));
+    }
+    lds_order();
+    int base = 0;
+    for (int l0 = 0; l0 <= maxl; l0 += WAVE) {
+      const int l = l0 + lane, c = l <= maxl ? (int)pvA[l] : 0;
+      int inc = c;
+      for (int off = 1; off < WAVE; off <<= 1) {
+        const int v = __shfl_up(inc, off, WAVE);
+        if (lane >= off) inc += v;
+      }
+      if (l <= maxl) pvA[l] = (uint16_t)(base + inc - c);
+      base += __builtin_amdgcn_readlane(inc, WAVE - 1);
+    }
+    lds_order();
+    // (a level's start becomes its end)
+    for (int g = lane; g < NG; g += WAVE) {
+      const int lv = lvl[g];
+      if (lv > 0) pvB[(atomicAdd(cnt + (lv >> 1), 1u << (16 * (lv & 1))) >> (16 * (lv & 1))) & 0xffffu] = (uint16_t)g;
+    }
+    lds_order();
+  }
+  return Levels{uniform(NG), maxl, uniform64(linked)};
 }
 
 // Scale of a friction pair with squared length nn onto the disk of radius
@@ -2344,7 +2381,8 @@ struct Group {
   RowC R;
   BodyReg A, B;
 };
-template <bool DENSE>
+// DENSE: nothing of a group kept over the sweeps.  MANY: more groups than lanes.
+template <bool DENSE, bool MANY>
 __device__ __forceinline__ void pgs_linked(const KArgs& a, float* L, int NC, int NL, int NR, Levels lv_, float& vR,
                                            float* tape) {
 #pragma clang fp contract(off)
@@ -2366,12 +2404,14 @@ __device__ __forceinline__ void pgs_linked(const KArgs& a, float* L, int NC, int
   // lane rr: the target side of robot row rr
   const int rsB = lane < NR ? (__float_as_int(C[(NL + lane) * CSTR + C_INFO]) >> 16) & 0xffff : 0;
   // the lane's group: level (0: alone, or none), first row, rows, body, the
-  // other side, and the first row's and the bodies' constants (a scene with
-  // more groups than lanes loads them again for each 64)
+  // other side, and the first row's and the bodies' constants.  MANY: 64 groups
+  // at a time in the order of their levels, each loaded at its level.
+  constexpr bool KEEP = !DENSE && !MANY;
+  const uint16_t* sorted = reinterpret_cast<const uint16_t*>(L + Y.lvl) + Y.ccap + 2;
+  const int NS = MANY ? uniform((sorted - (Y.ccap + 2))[maxl]) : 0;  // the groups that are not alone
+  int gbase = 0, glast = 0, gi = lane;  // first of the 64, level of the last, this lane's
   Group G;
-  auto grp_level = [&](int base) { G.lv = base + lane < NG ? (int)lvl[base + lane] : 0; };
-  auto grp_load = [&](int base) {
-    const int g = base + lane;
+  auto grp_load = [&](int g) {
     G.c0 = gfirst[g];
     G.gn = (int)gfirst[g + 1] - G.c0;
     const float* c = C + G.c0 * CSTR;
@@ -2385,8 +2425,14 @@ __device__ __forceinline__ void pgs_linked(const KArgs& a, float* L, int NC, int
     body_consts(F + G.fa * FSTR, G.A);
     body_consts(F + G.fb * FSTR, G.B);
   };
-  grp_level(0);
-  if (!DENSE && G.lv != 0) grp_load(0);
+  auto grp_chunk = [&](int base) {
+    gbase = base;
+    gi = sorted[min(base + lane, NS - 1)];
+    G.lv = base + lane < NS ? (int)lvl[gi] : 0;
+    glast = base + WAVE < NS ? __builtin_amdgcn_readlane(G.lv, WAVE - 1) : maxl + 1;
+  };
+  if (!MANY) G.lv = lane < NG ? (int)lvl[lane] : 0;
+  if (KEEP && G.lv != 0) grp_load(lane);
   const int rblk = lane < NR ? rob_block(Y, NC, NR, lane) : -1;
   // robot rows with a block (a prefix of them: blocks are given out in order)
   const int NB = __popcll(__ballot(rblk >= 0));
@@ -2573,13 +2619,14 @@ __device__ __forceinline__ void pgs_linked(const KArgs& a, float* L, int NC, int
 #pragma unroll 1
     for (int rr = NB; rr < NR; ++rr) rob_step_far(rr, tsweep);
     // the other groups, level by level
+    if (MANY && maxl > 0) grp_chunk(0);
 #pragma unroll 1
     for (int lv = 1; lv <= maxl; ++lv) {
 #pragma unroll 1
-      for (int base = 0; base < NG; base += WAVE) {
-        if (NG > WAVE) grp_level(base);
+      for (bool more = false; !more || (MANY && glast <= lv); more = true) {
+        if (MANY && more) grp_chunk(gbase + WAVE);  // (the level goes on past these 64)
         if (G.lv != lv) continue;
-        if (DENSE || NG > WAVE) grp_load(base);
+        if (!KEEP) grp_load(gi);
         float* c = C + G.c0 * CSTR;
         float* fa = F + G.fa * FSTR;
         Lam l = lam_load(c);
@@ -2919,7 +2966,8 @@ __device__ __forceinline__ int run_scene(int s, int wv, float* const L0) {
         MS_PHASE(3)
         lv.ng = uniform(ctl[CTL_NG]);
         lv.maxl = uniform(ctl[CTL_MAXL]);
-        pgs_linked<DENSE>(args_fresh(), lds_fresh(L0), NC, NL, NR, lv, vR, tape);
+        if (lv.ng > WAVE) pgs_linked<DENSE, true>(args_fresh(), lds_fresh(L0), NC, NL, NR, lv, vR, tape);
+        else pgs_linked<DENSE, false>(args_fresh(), lds_fresh(L0), NC, NL, NR, lv, vR, tape);
         if (MODE == 2) phase_forces(args_fresh(), S, lds_fresh(L0), NL, NR, frc, ks == a.n_sub_total - 1);
         integrate_robot(args_fresh(), S, lds_fresh(L0), vR);
         kin_aux(args_fresh(), S, lds_fresh(L0));

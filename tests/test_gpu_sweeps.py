@@ -296,3 +296,88 @@ def test_reverse_from_a_record_without_a_tape_buffer(depth, ccap, rcap):
         got.append([t.cpu().numpy() for t in (y, gx, gu)])
     for a, c in zip(*got):
         assert np.array_equal(a.view(np.uint32), c.view(np.uint32))
+
+
+def _sphere_chains(counts, lone, pgs_iters=10, n_sub=2):
+    """Per entry of `counts` a scene with a row of that many touching spheres on the
+    floor (n floor groups, n - 1 pairs), and `lone` spheres apart."""
+    scenes = []
+    for s, n in enumerate(counts):
+        rng = np.random.default_rng(s)
+        at = [(i * 0.101, 0.0) for i in range(n)] + [(i * 0.3, 1.0) for i in range(lone)]
+        scenes.append(dict(free=[sg.sphere_object(0.05, float(rng.uniform(0.1, 1.0)),
+                                                  (x, y, 0.05 + float(rng.uniform(-2e-4, 2e-4))),
+                                                  vel=tuple(rng.normal(0, 0.05, 3)), angvel=tuple(rng.normal(0, 0.2, 3)))
+                                 for x, y in at], planes=[(0.0, 0.0, 1.0, 0.0)]))
+    return sg.custom_batch([sg.empty_model()], scenes, h=0.002, n_sub=n_sub, pgs_iters=pgs_iters, contact_cap=160)
+
+
+def _boxes(nx, ny, nz, seed=0):
+    """Touching boxes on the floor, stacked: rows of a body broken by its neighbours'."""
+    rng = np.random.default_rng(seed)
+    out = []
+    for k in range(nz):
+        for j in range(ny):
+            for i in range(nx):
+                out.append(sg.box_object((0.05, 0.05, 0.05), 0.5, (i * 0.1001, j * 0.1001, 0.05 + 0.1 * k - float(rng.uniform(0, 2e-4))),
+                                         vel=tuple(rng.normal(0, 0.02, 3)), angvel=tuple(rng.normal(0, 0.05, 3))))
+    return dict(free=out, planes=[(0.0, 0.0, 1.0, 0.0)])
+
+
+@pytest.mark.parametrize("counts,lone", [((31, 32, 33), 0), ((31, 32, 33), 1), ((32, 33, 34), 24), ((3, 57, 58), 0)])
+def test_group_counts_about_the_lanes(counts, lone):
+    """2 n - 1 + lone groups, about 64 and more: the repository's one-step parity bars."""
+    ms = _ms()
+    b = _sphere_chains(counts, lone)
+    o = oracle.Oracle(b)
+    x, u = b.state0.astype(np.float64), np.zeros((len(counts), 16))
+    mb = ms.MsBatch(b)
+    mb.enable_debug(True)
+    xg = mb.step(torch.as_tensor(b.state0).cuda(), torch.as_tensor(u.astype(np.float32)).cuda()).cpu().numpy()
+    xo, d = o.step(x, u, debug=True)
+    assert d["n_contacts"][:, 0].tolist() == [2 * n - 1 + lone for n in counts]
+    assert same_contacts(d, mb.debug_contacts()).all()
+    pe, ve = errors(o, b, xo, xg.astype(np.float64))
+    ps, vs = fp32_sensitivity(o, b, x, u)
+    pf, vf = errors(o, b, xo, o.step_f32(x, u))
+    assert pe.max() <= max(1e-5, 10 * ps.max(), 4 * pf.max()), pe
+    assert ve.max() <= max(1e-4, 10 * vs.max(), 4 * vf.max()), ve
+
+
+@pytest.mark.parametrize("what", ["boxes", "spheres"])
+def test_forms_agree_on_many_groups(what):
+    """Scenes with few and with hundreds of groups: the plain step, the one for
+    large batches, the recording one and the ones for LDS blocks near the limit
+    give the same bits."""
+    ms = _ms()
+    if what == "boxes":
+        scenes, cap = [_boxes(1, 1, 2), _boxes(2, 2, 1), _boxes(1, 1, 12), _boxes(5, 5, 1), _boxes(3, 3, 2),
+                       _boxes(4, 2, 3)], 720
+        small = sg.custom_batch([sg.empty_model()], scenes, h=0.005, n_sub=2, pgs_iters=10, contact_cap=cap)
+    else:
+        small, cap = _sphere_chains((3, 28, 34), 2), 80
+    n = small.n_scenes
+    reps = (12 * torch.cuda.get_device_properties(0).multi_processor_count) // n + 1
+    large = _repeat(small, np.tile(np.arange(n), reps))
+    got = {}
+    for name, b, c in (("plain", small, cap), ("large", large, cap), ("tight", small, 1500)):
+        mb = ms.MsBatch(b, contact_cap=c, robot_contact_cap=1)
+        if what == "spheres" and name == "large":
+            assert 163840 // (mb.sizes.lds + 1024) > 6
+        x = torch.as_tensor(b.state0).cuda()
+        u = torch.zeros((b.n_scenes, 16), device="cuda")
+        mb.enable_debug(name == "plain")
+        y = mb.step(mb.step(x, u), u)
+        torch.cuda.synchronize()
+        assert not np.any(mb.status())
+        if name == "plain":
+            nc = mb.debug_contacts()[..., 0]
+            assert nc.max() > 64 and nc.min() < 64
+        z = mb.step_record(mb.step(x, u), u, mb.new_record()) if name != "large" else y
+        for v in (y, z):
+            st = sg.split_state(v.cpu().numpy(), b.n_scenes, b.n_free, b.n_aux)["free"]
+            got.setdefault(name, []).append(np.ascontiguousarray(st).view(np.uint32))
+    want = got["plain"][0]
+    for name, vs in got.items():
+        for v in vs:
+            assert np.array_equal(v, np.concatenate([want] * reps) if name == "large" else want), name
