@@ -82,14 +82,25 @@ __device__ __forceinline__ float row_sum(float s16, int q) {
 
 // level-schedule views inside the LDS block
 struct Lv {
-  int *lvl, *gfirst, *last, *linked;
+  int* pack;         // a row's nodes, while the schedule is built
+  uint16_t* lvl;     // then in their place each group's level
+  uint16_t* lend;    // and, of more groups than lanes, each level's end in sorted
+  uint16_t* gfirst;  // first row of each group
+  uint16_t* sorted;  // groups by level (SORT_QUAD: against static targets, first within a level)
+  int *last, *linked;
 };
+constexpr int SORT_QUAD = 0x8000;
 __device__ __forceinline__ Lv lv_view(float* L, const msa::WS& w) {
   Lv v;
   int* p = reinterpret_cast<int*>(L + w.lv);
   const int R = msa::lv_rows(w.ccap);
-  v.lvl = p; p += R;
-  v.gfirst = p; p += R + 1;
+  v.pack = p;
+  v.lvl = reinterpret_cast<uint16_t*>(p);
+  v.lend = v.lvl + ((R + 1) & ~1);
+  p += R;
+  v.gfirst = reinterpret_cast<uint16_t*>(p);
+  v.sorted = v.gfirst + R + 1;
+  p += R + 1;
   v.last = p; p += 64;
   v.linked = p;
   return v;
@@ -1944,7 +1955,7 @@ __device__ __forceinline__ void load_free(const msa::Eng& E, float* L, const flo
 // share), run backwards.  Each row's nodes packed per lane; the groups' first
 // rows; how many groups touch each node (LDS atomics); one pass over the
 // groups that are not alone with the last level of node j in lane j's register
-// (read with readlane).
+// (read with readlane).  More groups than lanes are then sorted by level.
 struct Sched {
   int ng, maxl;
 };
@@ -1958,7 +1969,7 @@ __device__ __forceinline__ Sched build_schedule(const msa::Eng& E, float* L) {
     int n1, n2;
     row_nodes(E, r, n1, n2);
     const Ids id = E.ids(E.w.con + (long)(r - E.nlim) * CR);
-    LV.lvl[r] = n1 | ((n2 + 1) << 8) | (id.tk < 2 ? 1 << 17 : 0);
+    LV.pack[r] = n1 | ((n2 + 1) << 8) | (id.tk < 2 ? 1 << 17 : 0);
   }
   lds_order();
   int G = 0;
@@ -1966,22 +1977,22 @@ __device__ __forceinline__ Sched build_schedule(const msa::Eng& E, float* L) {
     const int r = base + lane;
     bool st = false;
     if (r < R) {
-      const int pk = LV.lvl[r];
+      const int pk = LV.pack[r];
       st = true;
       if (r > r0 && (pk >> 17) & 1) {
-        const int pp = LV.lvl[r - 1];
+        const int pp = LV.pack[r - 1];
         st = !(((pp >> 17) & 1) && (pp & 0xff) == (pk & 0xff));
       }
     }
     const uint64_t mk = __ballot(st);
-    if (st) LV.gfirst[G + __popcll(mk & ((1ull << lane) - 1ull))] = r;
+    if (st) LV.gfirst[G + __popcll(mk & ((1ull << lane) - 1ull))] = (uint16_t)r;
     G += __popcll(mk);
   }
-  if (lane == 0) LV.gfirst[G] = R;
+  if (lane == 0) LV.gfirst[G] = (uint16_t)R;
   lds_order();
   // groups per node; a robot contact's target counts as touched by another
   for (int g = lane; g < G; g += 64) {
-    const int pk = LV.lvl[LV.gfirst[g]], n2 = ((pk >> 8) & 0xff) - 1;
+    const int pk = LV.pack[LV.gfirst[g]], n2 = ((pk >> 8) & 0xff) - 1;
     atomicAdd(&LV.last[pk & 0xff], 1);
     if (n2 >= 0) atomicAdd(&LV.last[n2], 1);
   }
@@ -1994,7 +2005,7 @@ __device__ __forceinline__ Sched build_schedule(const msa::Eng& E, float* L) {
   int last = 0, maxl = 0;
   for (int base = 0; base < G; base += 64) {
     const bool in = base + lane < G;
-    const int pkv = in ? LV.lvl[LV.gfirst[base + lane]] : 0;
+    const int pkv = in ? LV.pack[LV.gfirst[base + lane]] : 0;
     const bool alone = in && ((pkv >> 17) & 1) && LV.last[pkv & 0xff] == 1;
     int mine = 0;
     uint64_t todo = __ballot(in && !alone);
@@ -2014,10 +2025,48 @@ __device__ __forceinline__ Sched build_schedule(const msa::Eng& E, float* L) {
       maxl = lv > maxl ? lv : maxl;
     }
     lds_order();
-    // group g's first row is at index >= g, so the packs still to be read
-    // (groups past this chunk) are not overwritten
-    if (in) LV.lvl[base + lane] = mine;
+    // group g's first row is at index >= g, and a level is half a pack, so the
+    // packs still to be read (groups past this chunk) are not overwritten
+    if (in) LV.lvl[base + lane] = (uint16_t)mine;
     lds_order();
+  }
+  if (G > 64) {
+    // counting sort by level, within a level the groups against static targets
+    // first; the counters are the halves of 32-bit words (at most 4096 groups,
+    // so none carries into the other)
+    maxl = __builtin_amdgcn_readfirstlane(maxl);
+    uint32_t* cnt = reinterpret_cast<uint32_t*>(LV.lend);
+    for (int e = lane; e < (maxl + 2) / 2; e += 64) cnt[e] = 0u;
+    lds_order();
+    for (int g = lane; g < G; g += 64) {
+      const int lv = LV.lvl[g];
+      if (lv > 0) atomicAdd(cnt + (lv >> 1), 1u << (16 * (lv & 1)));
+    }
+    lds_order();
+    int base = 0;
+    for (int l0 = 0; l0 <= maxl; l0 += 64) {
+      const int l = l0 + lane, c = l <= maxl ? (int)LV.lend[l] : 0;
+      int inc = c;
+      for (int off = 1; off < 64; off <<= 1) {
+        const int v = __shfl_up(inc, off, 64);
+        if (lane >= off) inc += v;
+      }
+      if (l <= maxl) LV.lend[l] = (uint16_t)(base + inc - c);
+      base += __builtin_amdgcn_readlane(inc, 63);
+    }
+    lds_order();
+    // (a level's start becomes its end)
+    for (int pass = 0; pass < 2; ++pass) {
+      for (int g = lane; g < G; g += 64) {
+        const int lv = LV.lvl[g];
+        const bool quad = E.ids(E.w.con + (long)(LV.gfirst[g] - E.nlim) * CR).tk < 2;
+        if (lv > 0 && quad == (pass == 0)) {
+          const uint32_t at = atomicAdd(cnt + (lv >> 1), 1u << (16 * (lv & 1))) >> (16 * (lv & 1));
+          LV.sorted[at & 0xffffu] = (uint16_t)(g | (quad ? SORT_QUAD : 0));
+        }
+      }
+      lds_order();
+    }
   }
   return Sched{G, maxl};
 }
@@ -2060,8 +2109,10 @@ __device__ __forceinline__ void integrate_free(const msa::Eng& E, float* L) {
 // The reverse sweeps of everything that is not alone: per sweep the levels
 // last to first (one lane per group), the robot's rows last to first, the
 // joint-limit rows; the tape two sweeps at a time in an LDS ring (TIGHT: straight
-// from the record).
-template <bool TIGHT>
+// from the record).  MANY: more groups than lanes, taken 64 at a time in the order
+// of their levels.  (Looking for each level's groups among all of them took most
+// of a sweep: 56 touching boxes, 480 contacts, 88 M cycles a step.)
+template <bool TIGHT, bool MANY>
 __device__ __forceinline__ void gs_linked_bar(msa::Eng& E, float* L, Sched sc, const float* tape_g, int tsw) {
   using namespace msa;
   const int lane = lane_id();
@@ -2108,33 +2159,34 @@ __device__ __forceinline__ void gs_linked_bar(msa::Eng& E, float* L, Sched sc, c
     if (K > 2) fetch(K - 3);
   }
   // Groups against static targets by quads, the others by lanes.  The former in a
-  // row when they are at most 64 (quad k of chunk h: the (16 h + k)-th), their
-  // levels in the quad's registers; else looked up among all groups.  The level
-  // of the lane's group of the first 64 (0: by quads, or alone).
-  auto by_quad = [&](int g) { return unpack_ids(L[w.con + (LV.gfirst[g] - NL) * CR + C_ID]).tk < 2; };
+  // row (quad k of chunk h: the (16 h + k)-th), their levels in the quad's
+  // registers.  The level of the lane's group (0: by quads, or alone).
   const int qd = lane >> 2;
   int nq = 0, glv = 0;
-  for (int base = 0; base < sc.ng; base += 64) {
-    const int g = base + lane;
-    const int l = g < sc.ng ? LV.lvl[g] : 0;
-    const bool quad = l > 0 && by_quad(g);
-    if (base == 0) glv = quad ? 0 : l;
-    const uint64_t mk = __ballot(quad);
-    const int at = nq + __popcll(mk & ((1ull << lane) - 1ull));
-    if (quad && at < 64) LV.linked[at] = g;
-    nq += __popcll(mk);
-  }
-  lds_order();
-  const bool listed = nq <= 64;
-  if (!listed) nq = sc.ng;
   uint64_t qlv = 0ull;
-  if (listed) {
+  if (!MANY) {
+    const int l = lane < sc.ng ? (int)LV.lvl[lane] : 0;
+    const bool quad = l > 0 && unpack_ids(L[w.con + (LV.gfirst[lane] - NL) * CR + C_ID]).tk < 2;
+    glv = quad ? 0 : l;
+    const uint64_t mk = __ballot(quad);
+    if (quad) LV.linked[__popcll(mk & ((1ull << lane) - 1ull))] = lane;
+    nq = __popcll(mk);
+    lds_order();
 #pragma unroll
     for (int h = 0; h < 4; ++h) {
       const int i = 16 * h + qd;
-      qlv |= (uint64_t)(i < nq ? LV.lvl[LV.linked[i]] : 0) << (16 * h);
+      qlv |= (uint64_t)(i < nq ? (int)LV.lvl[LV.linked[i]] : 0) << (16 * h);
     }
   }
+  // MANY: the 64 groups at cbase: this lane's entry and level, the first's level
+  const int NS = MANY && sc.maxl > 0 ? __builtin_amdgcn_readfirstlane((int)LV.lend[sc.maxl]) : 0;
+  int cbase = 0, cent = 0, clow = 0;
+  auto chunk = [&](int base) {
+    cbase = base;
+    cent = base + lane < NS ? (int)LV.sorted[base + lane] : 0;
+    glv = base + lane < NS ? (int)LV.lvl[cent & ~SORT_QUAD] : 0;
+    clow = base > 0 ? __builtin_amdgcn_readfirstlane(glv) : 0;
+  };
   float vr = L[w.vR + (lane & 15)], vrb = L[w.vRb + (lane & 15)];
   const float rids = lane < NR ? L[w.con + lane * CR + C_ID] : 0.f;
   lds_order();
@@ -2155,64 +2207,72 @@ __device__ __forceinline__ void gs_linked_bar(msa::Eng& E, float* L, Sched sc, c
         q[t] = tq ? tq[3 * r + t] : 0.f;
       }
     };
+    if (MANY && NS > 0) chunk((NS - 1) & ~63);
 #pragma unroll 1
     for (int lv = sc.maxl; lv >= 1; --lv) {
 #pragma unroll 1
-      for (int i = qd, h = 0; i < nq; i += 16, h += 16) {
-        const int l = listed ? (int)(qlv >> h) & 0xffff : LV.lvl[i];
-        if (l != lv) continue;
-        const int g = listed ? LV.linked[i] : i;
-        if (!listed && !by_quad(g)) continue;
-        const int r0 = LV.gfirst[g], gn = LV.gfirst[g + 1] - r0;
-        const int f = unpack_ids(L[w.con + (r0 - NL) * CR + C_ID]).oi;
-        QBody A;
-        qb_load(w, L, f, A);
-        int r = r0 + gn - 1;
-        const float* e = L + w.con + (r - NL) * CR;
-        float *cb = L + w.conb + (r - NL) * CW, *lb = L + w.lamb + (r - NL) * 3;
-        QRow R;
-        float y[3], q[3];
-        qr_load(e, R);
-        row(r, y, q);
+      for (bool more = false; !more || (MANY && clow >= lv); more = true) {
+        if (MANY && more) chunk(cbase - 64);  // (the level goes on before these 64)
+        int qoff = 0;
+        if (MANY) {
+          const uint64_t mk = __ballot(glv == lv && (cent & SORT_QUAD));
+          nq = __popcll(mk);
+          qoff = __ffsll((long long)mk) - 1;
+        }
 #pragma unroll 1
-        for (;; cb -= CW, lb -= 3) {
-          r = r > r0 ? r - 1 : r0 - 1;
-          e -= r >= r0 ? CR : 0;
-          QRow Rn;
-          float yn[3], qn[3];
-          qr_load(e, Rn);
-          row(r >= r0 ? r : r0, yn, qn);
-          row_quad(R, cb, lb, y, q, mu, A);
-          if (r < r0) break;
-          R = Rn;
+        for (int i = qd, h = 0; i < nq; i += 16, h += 16) {
+          if (!MANY && ((int)(qlv >> h) & 0xffff) != lv) continue;
+          const int g = MANY ? (int)LV.sorted[cbase + qoff + i] & ~SORT_QUAD : LV.linked[i];
+          const int r0 = LV.gfirst[g], gn = LV.gfirst[g + 1] - r0;
+          const int f = unpack_ids(L[w.con + (r0 - NL) * CR + C_ID]).oi;
+          QBody A;
+          qb_load(w, L, f, A);
+          int r = r0 + gn - 1;
+          const float* e = L + w.con + (r - NL) * CR;
+          float *cb = L + w.conb + (r - NL) * CW, *lb = L + w.lamb + (r - NL) * 3;
+          QRow R;
+          float y[3], q[3];
+          qr_load(e, R);
+          row(r, y, q);
+#pragma unroll 1
+          for (;; cb -= CW, lb -= 3) {
+            r = r > r0 ? r - 1 : r0 - 1;
+            e -= r >= r0 ? CR : 0;
+            QRow Rn;
+            float yn[3], qn[3];
+            qr_load(e, Rn);
+            row(r >= r0 ? r : r0, yn, qn);
+            row_quad(R, cb, lb, y, q, mu, A);
+            if (r < r0) break;
+            R = Rn;
 #pragma unroll
-          for (int t = 0; t < 3; ++t) {
-            y[t] = yn[t];
-            q[t] = qn[t];
+            for (int t = 0; t < 3; ++t) {
+              y[t] = yn[t];
+              q[t] = qn[t];
+            }
           }
+          qb_store(w, L, f, A);
         }
-        qb_store(w, L, f, A);
-      }
-#pragma unroll 1
-      for (int g = lane; g < sc.ng; g += 64) {
-        if (g == lane ? glv != lv : LV.lvl[g] != lv || by_quad(g)) continue;
-        const int r = LV.gfirst[g];
-        const Ids id = unpack_ids(L[w.con + (r - NL) * CR + C_ID]);
-        BSide A, B;
-        XJoint X;
-        bs_load(w, L, id.oi, A);
-        float y[3], q[3];
-        row(r, y, q);
-        if (id.tk == 3) {
-          bs_load(w, L, id.ti, B);
-          row_bar<1>(w, L, r - NL, y, q, mu, A, B, X);
-          bs_store(w, L, id.ti, B);
-        } else {
-          xj_load(w, L, id.ti, X);
-          row_bar<2>(w, L, r - NL, y, q, mu, A, B, X);
-          xj_store(w, L, id.ti, X);
+        if (glv == lv && !(MANY && (cent & SORT_QUAD))) {
+          const int g = MANY ? cent : lane;
+          const int r = LV.gfirst[g];
+          const Ids id = unpack_ids(L[w.con + (r - NL) * CR + C_ID]);
+          BSide A, B;
+          XJoint X;
+          bs_load(w, L, id.oi, A);
+          float y[3], q[3];
+          row(r, y, q);
+          if (id.tk == 3) {
+            bs_load(w, L, id.ti, B);
+            row_bar<1>(w, L, r - NL, y, q, mu, A, B, X);
+            bs_store(w, L, id.ti, B);
+          } else {
+            xj_load(w, L, id.ti, X);
+            row_bar<2>(w, L, r - NL, y, q, mu, A, B, X);
+            xj_store(w, L, id.ti, X);
+          }
+          bs_store(w, L, id.oi, A);
         }
-        bs_store(w, L, id.oi, A);
       }
       lds_order();
     }
@@ -2269,11 +2329,26 @@ __device__ __forceinline__ void finish_linked(msa::Eng& E, float* L, Sched sc) {
     row_finish<true>(E, L, rr, A, nullptr);
   }
   lds_order();
+  // 64 groups at a time, in the order of their levels where there are more
+  const bool many = sc.ng > 64;
+  const int NS = !many ? sc.ng : (sc.maxl > 0 ? __builtin_amdgcn_readfirstlane((int)LV.lend[sc.maxl]) : 0);
+  int base = 0, g = 0, glv = 0, last = 0;
+  auto chunk = [&]() {
+    const bool in = base + lane < NS;
+    g = !in ? 0 : (many ? (int)LV.sorted[base + lane] & ~SORT_QUAD : lane);
+    glv = in ? (int)LV.lvl[g] : 0;
+    last = many && base + 64 < NS ? __builtin_amdgcn_readlane(glv, 63) : sc.maxl + 1;
+  };
+  chunk();
 #pragma unroll 1
   for (int lv = 1; lv <= sc.maxl; ++lv) {
 #pragma unroll 1
-    for (int g = lane; g < sc.ng; g += 64) {
-      if (LV.lvl[g] != lv) continue;
+    for (bool more = false; !more || last <= lv; more = true) {
+      if (more) {
+        base += 64;
+        chunk();
+      }
+      if (glv != lv) continue;
       const int c0 = LV.gfirst[g] - E.nlim, c1 = LV.gfirst[g + 1] - E.nlim;
       const int f = unpack_ids(L[w.con + c0 * CR + C_ID]).oi;
       BSide A;
@@ -2442,7 +2517,8 @@ __device__ void bwd_scene(int s, int wv, float* const L0) {
       {
         Eng E;
         eng_fresh(E, s, L0, nc, nrob, nlim);
-        gs_linked_bar<TIGHT>(E, E.b.p, sc, tape_g, RL.tsw);
+        if (sc.ng > 64) gs_linked_bar<TIGHT, true>(E, E.b.p, sc, tape_g, RL.tsw);
+        else gs_linked_bar<TIGHT, false>(E, E.b.p, sc, tape_g, RL.tsw);
       }
       phase(4);
       {

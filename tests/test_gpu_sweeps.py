@@ -381,3 +381,65 @@ def test_forms_agree_on_many_groups(what):
     for name, vs in got.items():
         for v in vs:
             assert np.array_equal(v, np.concatenate([want] * reps) if name == "large" else want), name
+
+
+@pytest.mark.parametrize("counts,lone", [((31, 32, 33), 1), ((32, 33), 24), ((57, 58), 0)])
+def test_gradient_group_counts_about_the_lanes(counts, lone):
+    _check_gradient(_ms(), _sphere_chains(counts, lone))
+
+
+def _arm_beside(n, cap=160):
+    """An arm leaning onto the floor and onto the first of n touching spheres."""
+    rng = np.random.default_rng(7)
+    q = np.zeros(16)
+    q[:7] = rng.normal(0.0, 0.05, 7)
+    q[1] = 1.8
+    free = [sg.sphere_object(0.05, float(rng.uniform(0.1, 1.0)), (1.1, 0.101 * i, 0.05 + float(rng.uniform(-2e-4, 2e-4))),
+                             vel=tuple(rng.normal(0, 0.05, 3)), angvel=tuple(rng.normal(0, 0.2, 3))) for i in range(n)]
+    scene = dict(q=q, qd=np.concatenate([rng.normal(0.0, 0.2, 7), np.zeros(9)]), free=free,
+                 planes=[(0.0, 0.0, 1.0, 0.0)])
+    return sg.custom_batch([sg.arm7_model(np.random.default_rng(1))], [scene], h=0.002, n_sub=2, pgs_iters=10,
+                           contact_cap=cap)
+
+
+@pytest.mark.parametrize("n", [20, 40])
+def test_gradient_many_groups_beside_a_robot(n):
+    """Robot rows beside few and many groups: the gradient against the oracle's, and
+    the same bits from the form for LDS blocks near the limit."""
+    ms = _ms()
+    b = _arm_beside(n)
+    _check_gradient(ms, b)
+    g = np.random.default_rng(2).normal(size=b.state0.size)
+    robot, got = [], []
+    for cap in (160, 570):
+        mb = ms.MsBatch(b, contact_cap=cap, backward=True)
+        mb.enable_debug(True)
+        mb.step(torch.as_tensor(b.state0).cuda(), torch.zeros((1, 16), device="cuda"))
+        robot.append(mb.debug_contacts()[..., 1].max())
+        got.append(_vjp(mb, b, g))
+    assert min(robot) > 0
+    assert all(np.array_equal(p, q) for p, q in zip(*got))
+
+
+def test_gradient_of_piles():
+    """Hundreds of groups of boxes against the reference adjoint, which takes the
+    rows one after the other, and the same bits from a small block and from one
+    near the limit.  (The last pile, at rest on redundant contacts, has no gradient
+    to compare: its sweeps sit on kinks, and float64 gives another one.)"""
+    ms = _ms()
+    scenes = [_boxes(1, 1, 2), _boxes(1, 1, 14), _boxes(4, 2, 1), _boxes(3, 2, 2)]
+    b = sg.custom_batch([sg.empty_model()], scenes, h=0.005, n_sub=2, pgs_iters=10, contact_cap=360)
+    g = np.random.default_rng(2).normal(size=b.state0.size)
+    got = []
+    for cap, flags in ((360, 0), (720, 0), (360, ms.MS_SCHED_BWD_REFERENCE)):
+        mb = ms.MsBatch(b, contact_cap=cap, robot_contact_cap=1, backward=True)
+        mb.set_schedule(ms.MS_SCHED_CULL | ms.MS_SCHED_STAGE_STATIC | flags)
+        mb.enable_debug(True)
+        mb.step(torch.as_tensor(b.state0).cuda(), torch.zeros((b.n_scenes, 16), device="cuda"))
+        assert not np.any(mb.status()) and mb.debug_contacts()[..., 0].max() > 100
+        got.append(_vjp(mb, b, g))
+    assert all(np.array_equal(p, q) for p, q in zip(*got[:2]))
+    mine, ref = (scene_vectors(b, *v) for v in (got[0], got[2]))
+    err = [np.linalg.norm(p - q) / np.linalg.norm(q) for p, q in zip(mine[:3], ref)]
+    print(f"[piles] rel err {np.array2string(np.array(err), precision=2)}", flush=True)
+    assert max(err) <= GRAD_TOL, err
