@@ -59,6 +59,9 @@ struct ms_batch {
   // split adjoint launches: contact caps of the smaller LDS layout (0: no
   // split), the stream of the full-size launch and the fork / join events
   int split_c, split_r;
+  // the wavefront adjoint's layout: the batch's caps', or, past the LDS block,
+  // the largest that fits it (total 0: none)
+  msa::WS bwd_fit;
   // the forward's smaller layout: contact cap per (furniture staging, force
   // outputs), -1 until computed, 0 for none; a forced cap (>= 0) or -1
   int fsplit[2][2];
@@ -367,11 +370,14 @@ void choose_bwd_split(const ms_batch* b, int& cc, int& rc) {
   }
 }
 
-// The wavefront adjoint's layout for the most contacts that the LDS block
-// holds beside the batch's robot contacts, or, when that is less than half
-// the batch's contacts, beside 8; total 0 when nothing fits.
+// The wavefront adjoint's layout: the batch's caps', or, past the LDS block,
+// the one for the most contacts that it holds beside the batch's robot
+// contacts, or, when that is less than half the batch's contacts, beside 8;
+// total 0 when nothing fits.
 msa::WS bwd_ws_fitting(const ms_batch* b) {
   const ms_batch_desc* d = &b->desc;
+  const msa::WS full = bwd_ws_wave(d, b->cnt);
+  if ((size_t)full.total * sizeof(float) <= b->max_lds) return full;
   const int rfull = std::max(d->robot_contact_cap, 1);
   for (int few = 0; few < 2; ++few)
     for (int k = d->contact_cap; k >= std::max(few ? 1 : d->contact_cap / 2, 1); --k) {
@@ -495,6 +501,7 @@ ms_status ms_create_batch(const ms_batch_desc* d, const ms_scene_desc* sc, void*
   (void)hipFuncSetAttribute(spawn_check_kernel_ptr(), hipFuncAttributeMaxDynamicSharedMemorySize, (int)b->max_lds);
   for (bool tight : {false, true})
     (void)hipFuncSetAttribute(step_bwd_wave_ptr(tight), hipFuncAttributeMaxDynamicSharedMemorySize, (int)b->max_lds);
+  b->bwd_fit = bwd_ws_fitting(b);
   choose_bwd_split(b, b->split_c, b->split_r);
   // status starts at zero; the first step's scene times (which order the
   // step) decrease along the static order
@@ -897,9 +904,8 @@ static ms_status step_backward_impl(ms_batch* b, const void* x_in, const float* 
   const size_t lds = (size_t)ww.total * sizeof(float);
   // caps past the LDS block: the largest layout that fits it, and the lane
   // kernel for the scenes whose lists overflow that
-  msa::WS wfit = ww;
+  const msa::WS& wfit = b->bwd_fit;
   const bool reference = (b->sched.flags & MS_SCHED_BWD_REFERENCE) != 0;
-  if (!reference && lds > b->max_lds) wfit = bwd_ws_fitting(b);
   if (reference || wfit.total <= 0) {
     if (!b->tape) return fail(MS_E_STATE, "ms_step_backward: the batch was created without a tape buffer");
     a.w = bwd_ws(d, c);

@@ -443,3 +443,43 @@ def test_gradient_of_piles():
     err = [np.linalg.norm(p - q) / np.linalg.norm(q) for p, q in zip(mine[:3], ref)]
     print(f"[piles] rel err {np.array2string(np.array(err), precision=2)}", flush=True)
     assert max(err) <= GRAD_TOL, err
+
+
+@pytest.mark.parametrize("kept", [False, True])
+@pytest.mark.parametrize("depth,ccap,rcap", [(0.15, 900, 200), (0.25, 1200, 120)])
+def test_caps_past_the_adjoint_block_in_a_mixed_batch(depth, ccap, rcap, kept):
+    """Caps past the adjoint's LDS block, in a batch where some scenes' robot contacts
+    fit the layout that runs in LDS (eight of them) and others' do not: those go to
+    the lane kernel, from a kept record and from one it makes itself in the buffer
+    that then is the lane kernel's workspace."""
+    ms = _ms()
+    few = _moving(depth)
+    rows = np.tile(np.arange(6), 12)
+    b = _repeat(few, rows)
+    x = torch.as_tensor(b.state0).cuda()
+    u = torch.as_tensor(np.ascontiguousarray(few.controls(0)[rows])).cuda()
+    g = torch.as_tensor(np.random.default_rng(3).normal(size=b.state0.size).astype(np.float32)).cuda()
+
+    def grads(cc, rc, flags=0):
+        mb = ms.MsBatch(b, contact_cap=cc, robot_contact_cap=rc, backward=True)
+        mb.set_schedule(ms.MS_SCHED_CULL | flags)
+        mb.enable_debug(True)
+        mb.step(x, u)
+        robot = mb.debug_contacts()[..., 1].max(1)
+        if kept and not flags:
+            rec = mb.new_record()
+            mb.step_record(x, u, rec)
+            gx, gu = mb.step_backward_recorded(x, u, rec, g)
+        else:
+            gx, gu = mb.step_backward(x, u, g)
+        torch.cuda.synchronize()
+        assert not np.any(mb.status() & (ms.MS_ST_OVERFLOW | ms.MS_ST_ROBOT_OVERFLOW))
+        return robot, scene_vectors(b, gx.cpu().numpy().astype(np.float64), gu.cpu().numpy().astype(np.float64))
+
+    robot, mixed = grads(ccap, rcap)
+    assert np.sum(robot > 8) >= 20 and np.sum((robot <= 8) & (robot > 0)) >= 10
+    _, wave = grads(220, 100)      # every scene in LDS
+    _, lane = grads(220, 100, ms.MS_SCHED_BWD_REFERENCE)
+    for s in range(b.n_scenes):
+        want = lane[s] if robot[s] > 8 else wave[s]
+        assert np.array_equal(mixed[s], want), (s, robot[s])
