@@ -483,3 +483,72 @@ def test_caps_past_the_adjoint_block_in_a_mixed_batch(depth, ccap, rcap, kept):
     for s in range(b.n_scenes):
         want = lane[s] if robot[s] > 8 else wave[s]
         assert np.array_equal(mixed[s], want), (s, robot[s])
+
+
+@pytest.mark.parametrize("depth", [0.25, 0.35])
+def test_robot_rows_past_the_lanes(depth):
+    """More robot rows than lanes, with room for their data and without."""
+    ms = _ms()
+    b = _crowded(depth)
+    wide = _run(ms, b, 640, 300)
+    nc, nr = int(wide[3][..., 0].max()), int(wide[3][..., 1].max())
+    assert nr > 64
+    tight = _run(ms, b, nc + 4, nr)
+    # the tight layout has room for the data of a few rows only: past the
+    # contact list fewer floats than one block, past the Jacobian rows none
+    # (their block is the larger one), and the spheres' centres
+    assert 4 * 17 < 76 and 48 * nr > 1600 and 5 * int(b.model_nsph.max()) // 76 < 10
+    assert not np.any(tight[4] & (ms.MS_ST_OVERFLOW | ms.MS_ST_ROBOT_OVERFLOW))
+    for a, c in zip(wide[:3], tight[:3]):
+        assert np.array_equal(a.view(np.uint32), c.view(np.uint32))
+
+
+@pytest.mark.parametrize("depth,tight", [(0.1, False), (0.15, False), (0.15, True)])
+def test_large_batches_with_robot_contacts_step_like_small_ones(depth, tight):
+    """The instantiation with more scenes per CU on scenes whose robots push
+    furniture, doors, drawers and objects, with room for the robot rows' data and
+    without."""
+    ms = _ms()
+    small = _moving(depth)
+    n = small.n_scenes
+    u = small.controls(0)
+    mb = ms.MsBatch(small)
+    mb.enable_debug(True)
+    x = torch.as_tensor(small.state0).cuda()
+    for _ in range(2):
+        x = mb.step(x, torch.as_tensor(u).cuda())
+        torch.cuda.synchronize()
+        assert not np.any(mb.status())
+    want = sg.split_state(x.cpu().numpy(), n, small.n_free, small.n_aux)
+    mb.step(torch.as_tensor(small.state0).cuda(), torch.as_tensor(u).cuda())
+    d = mb.debug_contacts()
+    nc, nr = int(d[..., 0].max()), int(d[..., 1].max())
+    assert np.sum(d[..., 1].max(1) > 8) >= 2 and nr > (24 if depth > 0.1 else 16)
+    caps = dict(contact_cap=nc + 8, robot_contact_cap=nr) if tight else {}
+    reps = (12 * torch.cuda.get_device_properties(0).multi_processor_count) // n + 1
+    rows = np.tile(np.arange(n), reps)
+    large = _repeat(small, rows)
+    for flags in (0, ms.MS_SCHED_PERSISTENT):
+        mb = ms.MsBatch(large, **caps)
+        assert 163840 // (mb.sizes.lds + 1024) > 6
+        mb.set_schedule(flags | ms.MS_SCHED_CULL | ms.MS_SCHED_STAGE_STATIC)
+        x, ul = torch.as_tensor(large.state0).cuda(), torch.as_tensor(np.ascontiguousarray(u[rows])).cuda()
+        x = mb.step(mb.step(x, ul), ul)
+        got = sg.split_state(x.cpu().numpy(), large.n_scenes, large.n_free, large.n_aux)
+        assert not np.any(mb.status())
+        for k in ("q", "qd", "free", "aux"):
+            w = np.ascontiguousarray(np.concatenate([want[k]] * reps)).view(np.uint32)
+            assert np.array_equal(np.ascontiguousarray(got[k]).view(np.uint32), w), k
+
+
+def test_gradient_robot_rows_past_the_lanes():
+    """More robot rows than lanes in reverse, against the oracle's gradient on its
+    smooth components."""
+    import dataclasses
+    b = dataclasses.replace(_moving(0.25), contact_cap=120, robot_contact_cap=80)
+    ms = _ms()
+    mb = ms.MsBatch(b)
+    mb.enable_debug(True)
+    mb.step(torch.as_tensor(b.state0).cuda(), torch.as_tensor(b.controls(0)).cuda())
+    assert mb.debug_contacts()[..., 1].max() > 64
+    _check_gradient(ms, b)
