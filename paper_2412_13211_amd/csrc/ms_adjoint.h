@@ -1563,51 +1563,6 @@ struct Eng {
     S.vb = S.vb + lin * rb;
     S.wb = S.wb + ang * rb;
   }
-  // a door / drawer target in registers: J = -(d . (a x (p - o))) (revolute)
-  // or -(d . a) (prismatic), v += (J / M) dl; the arithmetic of the aux
-  // branches of apply / apply_bar / rowvel / rowvel_bar / aux_J_bar, with the
-  // direction and point adjoints accumulated in the RowAcc
-  struct XSide {
-    int x, type;
-    V a, o;
-    float M, v, vb;
-  };
-  MSA_HD void xs_load(XSide& X, int x) const {
-    X.x = x;
-    X.type = (int)at(w.xty + x);
-    X.a = v3(w.xa + x * 3);
-    X.o = v3(w.xo + x * 3);
-    X.M = at(w.xM + x);
-    X.v = at(w.vA + x);
-    X.vb = at(w.vAb + x);
-  }
-  MSA_HD void xs_store(const XSide& X) const {
-    at(w.vA + X.x) = X.v;
-    at(w.vAb + X.x) = X.vb;
-  }
-  MSA_HD static float xs_J(const XSide& X, const RowAcc& A, int di) {
-    return X.type == 0 ? -dot(A.d[di], cross(X.a, A.p - X.o)) : -dot(A.d[di], X.a);
-  }
-  MSA_HD static void xs_J_bar(const XSide& X, RowAcc& A, int di, float Jb) {
-    if (X.type == 0) {
-      A.db[di] = A.db[di] - cross(X.a, A.p - X.o) * Jb;
-      A.pb = A.pb - cross(A.d[di], X.a) * Jb;
-    } else {
-      A.db[di] = A.db[di] - X.a * Jb;
-    }
-  }
-  MSA_HD static void xs_apply(XSide& X, const RowAcc& A, int di, float dl) { X.v += (xs_J(X, A, di) / X.M) * dl; }
-  MSA_HD static float xs_apply_bar(XSide& X, RowAcc& A, int di, float dl) {
-    const float J = xs_J(X, A, di);
-    xs_J_bar(X, A, di, X.vb * dl / X.M);
-    return (J / X.M) * X.vb;
-  }
-  MSA_HD static float xs_rowvel(const XSide& X, const RowAcc& A, int di) { return xs_J(X, A, di) * X.v; }
-  MSA_HD static void xs_rowvel_bar(XSide& X, RowAcc& A, int di, float rb) {
-    const float J = xs_J(X, A, di);
-    xs_J_bar(X, A, di, rb * X.v);
-    X.vb += rb * J;
-  }
   MSA_HD void contact_bar_reg(int it, int ci, int oi, int tk, int ti) const {
     const bool two = tk == 3;
     FSide A, B;
@@ -1616,14 +1571,6 @@ struct Eng {
     contact_bar_core(it, ci, A, B, two);
     fs_store(A);
     if (two) fs_store(B);
-  }
-  // reverse of a run of rows ci0 .. ci0 + n - 1 between one free body and
-  // static targets, last row first, with the body's side in registers
-  MSA_HD void contact_group_bar(int it, int ci0, int n) const {
-    FSide A, B;
-    fs_load(A, ids(w.con + (long)ci0 * CR).oi, 1.f);
-    for (int ci = ci0 + n - 1; ci >= ci0; --ci) contact_bar_core(it, ci, A, B, false);
-    fs_store(A);
   }
   // the register form's arithmetic between the sides' load and store
   MSA_HD void contact_bar_core(int it, int ci, FSide& A, FSide& B, bool two) const {
@@ -1813,15 +1760,14 @@ struct Eng {
     pb = pb + rrb;
     a3(w.fb + f * FB + F_XB, -rrb);
   }
-  // robot_side = false: the robot owners' rows are reversed elsewhere (the
-  // wavefront kernel spreads them over lanes); M~bar must be zeroed before
-  MSA_HD void rows_bar(bool robot_side = true) {
-    for (int ci = 0; ci < nc; ++ci) rows_bar_one(ci, robot_side);
+  // (M~bar must be zeroed before)
+  MSA_HD void rows_bar() {
+    for (int ci = 0; ci < nc; ++ci) rows_bar_one(ci);
     for (int li = 0; li < nlim; ++li) rows_bar_limit(li);
   }
   // rows^T of contact ci (touches the contact's own adjoint record and its
   // sides' accumulators)
-  MSA_HD void rows_bar_one(int ci, bool robot_side) const {
+  MSA_HD void rows_bar_one(int ci) const {
     const DModel& M = *sc.M;
     {
       long e = w.con + (long)ci * CR, cb = w.conb + (long)ci * CB;
@@ -1833,9 +1779,7 @@ struct Eng {
         V d = dir(e, di);
         V db{0.f, 0.f, 0.f};
         float Wb = at(cb + B_W + di);
-        if (ok == 0 && !robot_side) {
-          // nothing: this side is handled by the caller
-        } else if (ok == 0) {
+        if (ok == 0) {
           long rj = w.rJ + ((long)ci * 3 + di) * ND, rwv = w.rw + ((long)ci * 3 + di) * ND;
           long rjb = w.rJb + ((long)ci * 3 + di) * ND, rwb = w.rwb + ((long)ci * 3 + di) * ND;
           float Jb[ND], al[ND];

@@ -335,11 +335,12 @@ msa::WS bwd_ws_wave(const ms_batch_desc* d, const Counts& c, int cc = -1, int rc
 }
 
 // Workgroups of the wavefront adjoint per CU at an LDS size.  Near the
-// thresholds gfx950 fits fewer single-wave workgroups than the occupancy
-// query reports (timed: three fit at 53760 B but not at 53768 B, five at
-// 32000 B but not at 32064 B, while the query allows 54528 B and 32768 B);
-// n workgroups are counted as fitting only when n (size + 1 KiB) stays
-// within the CU's 160 KiB, which stays below every measured threshold.
+// thresholds gfx950 fits fewer workgroups than the occupancy query reports: LDS
+// is given out in pieces of 1280 B (timed with workgroups of one and of two
+// wavefronts alike: three fit at 53760 B but not at 53776 B, five at 32000 B but
+// not at 32016 B, while the query allows 54528 B and 32768 B).  n workgroups are
+// counted as fitting only when n (size + 1 KiB) stays within the CU's 160 KiB,
+// which stays below every measured threshold.
 int bwd_per_cu(size_t lds) {
   int n = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, step_bwd_wave_ptr(false), BWD_THREADS, lds) != hipSuccess) n = 0;

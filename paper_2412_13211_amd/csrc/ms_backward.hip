@@ -59,7 +59,6 @@ __device__ __forceinline__ void both_sync() { __syncthreads(); }
 // write sees it; only the compiler must not move memory accesses across (no
 // wait for outstanding accesses, unlike the barrier).
 __device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
-__device__ __forceinline__ float bcast0(float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0)); }
 // value of the lane N places along within its row of 16 lanes (DPP row
 // rotation: a VALU operand modifier, no LDS crossbar)
 template <int N>
@@ -74,7 +73,6 @@ __device__ __forceinline__ float sum16(float v) {
   v += row_ror<1>(v);
   return v;
 }
-// sum over lanes 0..15 (other lanes pass 0), returned in every lane
 // the sum of 16-lane row q (q = 0..3), read by every lane
 __device__ __forceinline__ float row_sum(float s16, int q) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(s16), 16 * q));
@@ -106,18 +104,11 @@ __device__ __forceinline__ Lv lv_view(float* L, const msa::WS& w) {
   return v;
 }
 
-// dynamic node of a row (robot 0, door/drawer 1 + x, free body 1 + AMAX + f; -1 none)
-__device__ __forceinline__ void row_nodes(const msa::Eng& E, int r, int& na, int& nbn) {
-  if (r < E.nlim) {
-    na = 1 + (int)E.at(E.w.lim + r * 4);
-    nbn = -1;
-    return;
-  }
-  long e = E.w.con + (long)(r - E.nlim) * msa::CR;
-  const msa::Ids id = E.ids(e);
-  const int ok = id.ok, oi = id.oi, tk = id.tk, ti = id.ti;
-  na = ok == 0 ? 0 : 1 + AMAX + oi;
-  nbn = tk == 2 ? 1 + ti : (tk == 3 ? 1 + AMAX + ti : -1);
+// dynamic nodes of a free body's row (door/drawer 1 + x, free body 1 + AMAX + f;
+// -1 none)
+__device__ __forceinline__ void row_nodes(const msa::Ids& id, int& na, int& nbn) {
+  na = 1 + AMAX + id.oi;
+  nbn = id.tk == 2 ? 1 + id.ti : (id.tk == 3 ? 1 + AMAX + id.ti : -1);
 }
 
 // ------------------------------------------------------------ Gauss-Seidel^T
@@ -189,9 +180,8 @@ __device__ __forceinline__ void outer_add(float* M, msa::V a, msa::V b) {
   M[6] += a.z * b.x; M[7] += a.z * b.y; M[8] += a.z * b.z;
 }
 // the primitives of a side with row (sgn D, sgn ang): s folds the sign into
-// the scalar.  bs_apply: v += M^-1 J^T dl.  bs_apply_bar: its adjoint; returns
-// dlbar, adds to the direction's linear part Lb and its lever part G.
-// bs_rowvel: J . v.  bs_rowvel_bar: its adjoint for rbar.
+// the scalar.  bs_apply: v += M^-1 J^T dl.  bs_dlb: dl's adjoint in it.
+// bs_rowvel: J . v.
 __device__ __forceinline__ void bs_apply(BSide& B, const DirC& C, float s) {
   B.v = vmadd(B.v, C.D, B.im * s);
   B.w = vmadd(B.w, C.b, s);
@@ -565,11 +555,10 @@ __device__ __forceinline__ void row_finish(const msa::Eng& E, float* L, int ci, 
   const float* cb = L + w.conb + ci * CW;
   const Ids id = unpack_ids(e[C_ID]);
   const V p{e[C_P], e[C_P + 1], e[C_P + 2]}, n{e[C_N], e[C_N + 1], e[C_N + 2]};
-  constexpr bool direct = ROB;
   V db[3], pb{0.f, 0.f, 0.f};
 #pragma unroll
   for (int d = 0; d < 3; ++d) db[d] = V{cb[3 * d], cb[3 * d + 1], cb[3 * d + 2]};
-  if (direct) pb = V{cb[CW_P], cb[CW_P + 1], cb[CW_P + 2]};
+  if (ROB) pb = V{cb[CW_P], cb[CW_P + 1], cb[CW_P + 2]};
   auto dirv = [&](int d) -> V {
     const int o = d == 0 ? C_N : (d == 1 ? C_T1 : C_T2);
     return V{e[o], e[o + 1], e[o + 2]};
@@ -582,8 +571,7 @@ __device__ __forceinline__ void row_finish(const msa::Eng& E, float* L, int ci, 
       dir_consts(A, rA, dirv(d), C);
       const float Wb = cb[CW_W + d];
       // W += D . D / m + ang . I^-1 ang
-      V G = C.b * (2.f * Wb);
-      if (!direct) G = G + V{cb[9 + 3 * d], cb[10 + 3 * d], cb[11 + 3 * d]};
+      const V G = C.b * (2.f * Wb) + V{cb[9 + 3 * d], cb[10 + 3 * d], cb[11 + 3 * d]};
       db[d] = vmadd(db[d], C.D, 2.f * Wb * A.im) + cross(G, rA);
       outer_add(A.II, C.ang * Wb, C.ang);
       const V pc = cross(C.D, G);
@@ -1182,8 +1170,8 @@ __device__ __forceinline__ void rows_robot(msa::Eng& E, float* L) {
 // that do not wait for one another, each lane taking those its mask names.
 // (Running the recursions along the tree, a lane per component, made chains of
 // dependent LDS rounds with a parent's index from memory in each.  Per substep
-// of the 15-joint robot among 4096 uneven scenes: recompute 50 -> 27 k cycles,
-// dynamics^T 57 -> 17 k; forward and reverse of the batch 3585 -> 2930 us.)
+// of the 15-joint robot among 4096 uneven scenes: recompute 43 k cycles, now
+// 28 k; dynamics^T 54 k, now 18 k.)
 struct Tree {
   int g, i, gc;
   uint32_t am, dm;  // ancestors and descendants of body i, itself included (none past the robot's bodies)
@@ -1343,8 +1331,8 @@ __device__ __forceinline__ float minv_times(const float* Minv_j, float x) {  // 
   for (int k = 0; k < ND; ++k) Mj[k] = Minv_j[k * ND];
   return minv_dot<0>(Mj, x);
 }
-// adjoint of the robot rows (the robot owners' share; the engine's
-// rows_bar(false) does the rest).  With w = M~^-1 J^T and W += J . w:
+// adjoint of the robot rows (the robot owners' share; row_finish does the
+// rest).  With w = M~^-1 J^T and W += J . w:
 // Jbar += Wbar w + M~^-1 (wbar + Wbar J), M~bar -= M~^-1 (wbar + Wbar J) w^T;
 // Jbar then reaches the directions, the contact point and the joint axes.
 // Four rows (contact, direction) at a time, lane j of a 16-lane group owns joint
@@ -1967,8 +1955,8 @@ __device__ __forceinline__ Sched build_schedule(const msa::Eng& E, float* L) {
   LV.last[lane] = 0;
   for (int r = r0 + lane; r < R; r += 64) {
     int n1, n2;
-    row_nodes(E, r, n1, n2);
     const Ids id = E.ids(E.w.con + (long)(r - E.nlim) * CR);
+    row_nodes(id, n1, n2);
     LV.pack[r] = n1 | ((n2 + 1) << 8) | (id.tk < 2 ? 1 << 17 : 0);
   }
   lds_order();
@@ -2381,9 +2369,9 @@ __device__ __forceinline__ void finish_linked(msa::Eng& E, float* L, Sched sc) {
 // adjoints, its rows) the other leaves alone there.  The barriers lie outside
 // the branches on wv.
 // (One wavefront doing all in turn left the SIMDs idle most of the time, and LDS
-// holds only three scenes on a CU.  Forward and reverse of a control step of
-// 4096 uneven scenes: 4380 -> 3585 us, of 16 scenes over four steps: 1866 ->
-// 1633 us.)
+// holds only three scenes on a CU.  The split alone took forward and reverse of a
+// control step of 4096 uneven scenes from 4380 to 3585 us, of 16 arms over four
+// steps from 1866 to 1633.)
 template <bool TIGHT>
 __device__ void bwd_scene(int s, int wv, float* const L0) {
   using namespace msa;

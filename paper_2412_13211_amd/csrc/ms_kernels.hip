@@ -16,8 +16,8 @@
 //   -- barrier --
 // One wavefront doing all in turn was bound by the latency of each chain, the
 // SIMDs idle two thirds of the time; LDS, not wavefront slots, limits the
-// scenes per CU, so the second wavefront is free.  A control step of 1024
-// scenes and of 4096 uneven ones: 539 -> 386 and 1019 -> 746 us.
+// scenes per CU, so the second wavefront is free.  The split alone took a control
+// step of 1024 room scenes from 539 to 408 us, of 4096 uneven ones from 1019 to 774.
 // The mathematics follows the textbook definitions cited in the C header; no
 // code is shared with the CPU oracle.
 #include "ms_internal.h"
@@ -515,7 +515,8 @@ __device__ __forceinline__ void kin_robot(const KArgs& a, const Scene& S, float*
   // Lane (r, i) = (lane >> 4, lane & 15), r < 3, holds row r of body i's world
   // rotation and component r of its origin; every lane the whole local
   // transform.  (A lane per body fetched 12 numbers of its parent and multiplied
-  // whole matrices in every round: 8.5 k cycles for the 15 bodies, now 4.4 k.)
+  // whole matrices in every round: drive and frames of the 15 bodies 11 k cycles
+  // among 4096 uneven scenes, now 8 k.)
   const int r = lane >> 4, i = lane & 15;
   float Rl[9], pl[3];
   int anc = -1, depth = -1;
@@ -1553,8 +1554,8 @@ __device__ __forceinline__ void dyn_robot(const KArgs& a, const Scene& S, float*
   // sums fill the other's waits.  (One lane per body looping over the other
   // bodies made each sum a chain of 16 dependent LDS rounds.  Rounds one after
   // the other, with the ancestors read from memory in each, and the elimination
-  // a row per lane: the dynamics took 36 k cycles among 4096 uneven scenes,
-  // now 23 k; that batch's step 746 -> 671 us.)
+  // a row per lane: the dynamics took 32 k cycles among 4096 uneven scenes,
+  // now 22 k.)
   const int lf = lane_id(), q = lf >> 4, kq = lf & 15;
   // ancestors and descendants of body kq, itself included (none past the robot's
   // bodies), and its joint's kind
